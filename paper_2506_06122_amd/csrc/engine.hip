@@ -40,7 +40,7 @@ static void alloc_weights(rollout_ctx& c) {
     }
     if (!c.simple) {
       // MoE: the experts' matrices are stacked, [E * Fe][hidden] and [E * hidden][Fe]; Fe is a
-      // multiple of 16, so the stacked gate/up column tiles still alternate inside every expert
+      // multiple of 16, so no gate/up column tile crosses from one expert to the next
       const size_t f = moe ? (size_t)m.n_experts * m.expert_ffn_dim : (size_t)m.ffn_dim;
       if (moe) L.router_p.alloc((size_t)m.n_experts * d * 2);
       L.wqkv_p.alloc((size_t)c.qkv_dim * d * 2);
@@ -92,7 +92,7 @@ void engine_load_tensor(rollout_ctx& c, int layer, int which, const void* src) {
   if (which == ROLLOUT_W_FINAL_NORM) return load_gain(c, c.final_norm, src);
   if (which == ROLLOUT_W_LM_HEAD) {
     if (c.simple) return load_matrix(c, c.lm_head, 0, src, (size_t)m.vocab * d);
-    return launch_pack_weight(src, c.lm_head_p.p, m.vocab, (int)d, 0, 1, c.stream);
+    return launch_pack_weight(src, c.lm_head_p.p, m.vocab, (int)d, 0, -1, c.stream);
   }
   (void)model_level;
   LayerWeights& L = c.layers[layer];
@@ -110,15 +110,15 @@ void engine_load_tensor(rollout_ctx& c, int layer, int which, const void* src) {
     const int down_rows = moe ? m.n_experts * (int)d : (int)d;
     const int down_k = moe ? m.expert_ffn_dim : m.ffn_dim;
     switch (which) {
-      case ROLLOUT_W_WQ: return launch_pack_weight(src, L.wqkv_p.p, c.q_dim, (int)d, 0, 1, c.stream);
-      case ROLLOUT_W_WK: return launch_pack_weight(src, L.wqkv_p.p, c.kv_dim, (int)d, c.q_dim / 16, 1, c.stream);
+      case ROLLOUT_W_WQ: return launch_pack_weight(src, L.wqkv_p.p, c.q_dim, (int)d, 0, -1, c.stream);
+      case ROLLOUT_W_WK: return launch_pack_weight(src, L.wqkv_p.p, c.kv_dim, (int)d, c.q_dim / 16, -1, c.stream);
       case ROLLOUT_W_WV:
-        return launch_pack_weight(src, L.wqkv_p.p, c.kv_dim, (int)d, (c.q_dim + c.kv_dim) / 16, 1, c.stream);
-      case ROLLOUT_W_WO: return launch_pack_weight(src, L.wo_p.p, (int)d, c.q_dim, 0, 1, c.stream);
-      case ROLLOUT_W_GATE: return launch_pack_weight(src, L.w_gate_up_p.p, f, (int)d, 0, 2, c.stream);
-      case ROLLOUT_W_UP: return launch_pack_weight(src, L.w_gate_up_p.p, f, (int)d, 1, 2, c.stream);
-      case ROLLOUT_W_DOWN: return launch_pack_weight(src, L.w_down_p.p, down_rows, down_k, 0, 1, c.stream);
-      default: return launch_pack_weight(src, L.router_p.p, m.n_experts, (int)d, 0, 1, c.stream);
+        return launch_pack_weight(src, L.wqkv_p.p, c.kv_dim, (int)d, (c.q_dim + c.kv_dim) / 16, -1, c.stream);
+      case ROLLOUT_W_WO: return launch_pack_weight(src, L.wo_p.p, (int)d, c.q_dim, 0, -1, c.stream);
+      case ROLLOUT_W_GATE: return launch_pack_weight(src, L.w_gate_up_p.p, f, (int)d, 0, 0, c.stream);
+      case ROLLOUT_W_UP: return launch_pack_weight(src, L.w_gate_up_p.p, f, (int)d, 0, 1, c.stream);
+      case ROLLOUT_W_DOWN: return launch_pack_weight(src, L.w_down_p.p, down_rows, down_k, 0, -1, c.stream);
+      default: return launch_pack_weight(src, L.router_p.p, m.n_experts, (int)d, 0, -1, c.stream);
     }
   }
   switch (which) {
@@ -280,7 +280,7 @@ void engine_init(rollout_ctx& c, const rollout_weights& w) {
     c.act_bf16.alloc(2 * Rp * (moe ? (size_t)m.top_k * m.expert_ffn_dim : (size_t)m.ffn_dim));
     if (moe) {
       const size_t picks = R * m.top_k;
-      c.moe_max_blocks = (int)(std::min<size_t>(m.n_experts, picks) + picks / kMoeBlockRows + 1);
+      c.moe_max_blocks = (int)(std::min<size_t>(m.n_experts, picks) + picks / kMoeMinBlockRows + 1);
       c.moe_idx.alloc(picks);
       c.moe_wt.alloc(picks);
       c.moe_pos.alloc(picks);
@@ -306,7 +306,7 @@ void engine_init(rollout_ctx& c, const rollout_weights& w) {
     c.attn_part_ml.alloc((size_t)c.attn_max_parts * 32);
     c.ssq.alloc((size_t)(d / 16 + 1) * 256);
     {
-      const size_t parts = ceil_div(m.vocab / 16, 8);  // the narrowest tile configuration
+      const size_t parts = lse_parts_max(m.vocab);
       c.lse_max.alloc(parts * R);
       c.lse_sum.alloc(parts * R);
       c.lse_tgt.alloc(R);
@@ -409,17 +409,15 @@ static double gemm_bytes(int M, int N, int K, int out_elem) {  // operands once,
   return 2.0 * N * K + 2.0 * M * K + (double)out_elem * M * N;
 }
 
-static int project(rollout_ctx& c, const uint16_t* a, long long a_lo_off, int lda, const void* w, int M, int N,
-                   int K) {
+static int project(rollout_ctx& c, const uint16_t* a, const void* w, int M, int N, int K) {
   GemmArgs g{};
   g.a = a;
-  g.a_lo = a + a_lo_off;
+  g.a_lo = a + kPlaneLo;
   g.w = w;
   g.out = c.partial.p;
   g.M = M;
   g.N = N;
   g.K = K;
-  g.lda = lda;
   g.ldo = N;
   g.split_stride = (long long)M * N;
   const int cap = (int)std::min<long long>(16, (c.partial_rows * c.partial_ld) / ((long long)M * N));
@@ -434,14 +432,13 @@ static void gate_up(rollout_ctx& c, LayerWeights& L, int R) {
   const int d = c.md.hidden, f = c.md.ffn_dim;
   GemmArgs gu{};
   gu.a = c.h_bf16.p;
-  gu.a_lo = c.h_bf16.p + c.h_bf16.n / 2;
+  gu.a_lo = c.h_bf16.p + kPlaneLo;
   gu.w = L.w_gate_up_p.p;
   gu.out = c.act_bf16.p;
-  gu.out_lo_offset = (long long)(c.act_bf16.n / 2);
+  gu.out_lo_offset = kPlaneLo;
   gu.M = R;
   gu.N = 2 * f;
   gu.K = d;
-  gu.lda = d;
   gu.ldo = f;
   const GemmPlan pl = gemm_plan(R, 2 * f, d, EPI_SWIGLU_BF16, 1);
   c.timer.begin(pl.name, 2.0 * 2 * f * d + 2.0 * R * d + 2.0 * R * f, 2.0 * R * 2 * f * d, c.stream);
@@ -453,7 +450,7 @@ static void embed_and_norm(rollout_ctx& c, int R) {
   RowNormArgs rn{};
   rn.x = c.x.p;
   rn.h = c.h_bf16.p;
-  rn.h_lo_offset = (long long)(c.h_bf16.n / 2);
+  rn.h_lo_offset = kPlaneLo;
   rn.rows = R;
   rn.hidden = c.md.hidden;
   rn.eps = c.md.rms_eps;
@@ -491,7 +488,7 @@ static void moe_block(rollout_ctx& c, LayerWeights& L, int layer, int R, RowNorm
   hipStream_t s = c.stream;
   const int d = m.hidden, fe = m.expert_ffn_dim, E = m.n_experts, k = m.top_k;
   const int picks = R * k;
-  const int z = project(c, c.h_bf16.p, (long long)(c.h_bf16.n / 2), d, L.router_p.p, R, E, d);
+  const int z = project(c, c.h_bf16.p, L.router_p.p, R, E, d);
 
   MoeRouteArgs ra{};
   ra.partial = c.partial.p;
@@ -516,7 +513,8 @@ static void moe_block(rollout_ctx& c, LayerWeights& L, int layer, int R, RowNorm
   pa.rows = R;
   pa.n_experts = E;
   pa.top_k = k;
-  pa.max_blocks = std::min(c.moe_max_blocks, std::min(E, picks) + picks / kMoeBlockRows + 1);
+  pa.block_rows = moe_block_rows(picks, E);
+  pa.max_blocks = std::min(c.moe_max_blocks, std::min(E, picks) + picks / pa.block_rows + 1);
   pa.row_map = c.moe_row_map.p;
   pa.slot_of = c.moe_slot_of.p;
   pa.group_of_block = c.moe_group_of_block.p;
@@ -529,24 +527,16 @@ static void moe_block(rollout_ctx& c, LayerWeights& L, int layer, int R, RowNorm
   // Expected number of experts with at least one pick under uniform routing: the weight bytes
   // of the timing records (the true count stays on the device).
   const double touched = E * (1.0 - std::pow(1.0 - 1.0 / E, (double)picks));
-  GemmPlan pl{};
-  pl.kind = 1;
-  pl.mt = kMoeBlockRows / 16;
-  pl.nt = 2;
-  pl.nw = 4;
-  pl.splits = 1;
-  pl.kc = 2;
-
+  GemmPlan pl = gemm_plan_grouped(EPI_SWIGLU_BF16, pa.block_rows);
   GemmArgs gu{};
   gu.a = c.h_bf16.p;
-  gu.a_lo = c.h_bf16.p + c.h_bf16.n / 2;
+  gu.a_lo = c.h_bf16.p + kPlaneLo;
   gu.w = L.w_gate_up_p.p;
   gu.out = c.act_bf16.p;
-  gu.out_lo_offset = (long long)(c.act_bf16.n / 2);
+  gu.out_lo_offset = kPlaneLo;
   gu.M = picks;
   gu.N = 2 * fe;
   gu.K = d;
-  gu.lda = d;
   gu.ldo = fe;
   gu.group_of_block = pa.group_of_block;
   gu.block_row_begin = pa.block_row_begin;
@@ -554,20 +544,18 @@ static void moe_block(rollout_ctx& c, LayerWeights& L, int layer, int R, RowNorm
   gu.row_map = pa.row_map;
   gu.group_stride16 = (long long)2 * fe * d * 2 / 16;
   gu.n_row_blocks = pa.max_blocks;
-  pl.name = "gemm_tile_ring_kernel<4,2,2,1,1>";
   c.timer.begin(pl.name, touched * 2.0 * 2 * fe * d + 4.0 * picks * d + 4.0 * picks * fe, 2.0 * picks * 2 * fe * d, s);
   launch_gemm_bf16(gu, EPI_SWIGLU_BF16, pl, s);
   c.timer.end(s);
 
   GemmArgs dn{};
   dn.a = c.act_bf16.p;
-  dn.a_lo = c.act_bf16.p + c.act_bf16.n / 2;
+  dn.a_lo = c.act_bf16.p + kPlaneLo;
   dn.w = L.w_down_p.p;
   dn.out = c.moe_y.p;
   dn.M = picks;
   dn.N = d;
   dn.K = fe;
-  dn.lda = fe;
   dn.ldo = d;
   dn.split_stride = 0;
   dn.group_of_block = pa.group_of_block;
@@ -575,7 +563,7 @@ static void moe_block(rollout_ctx& c, LayerWeights& L, int layer, int R, RowNorm
   dn.block_row_end = pa.block_row_end;
   dn.group_stride16 = (long long)d * fe * 2 / 16;
   dn.n_row_blocks = pa.max_blocks;
-  pl.name = "gemm_tile_ring_kernel<4,2,2,1,0>";
+  pl = gemm_plan_grouped(EPI_F32, pa.block_rows);
   c.timer.begin(pl.name, touched * 2.0 * d * fe + 4.0 * picks * fe + 4.0 * picks * d, 2.0 * picks * d * fe, s);
   launch_gemm_bf16(dn, EPI_F32, pl, s);
   c.timer.end(s);
@@ -601,7 +589,7 @@ static void forward_rows_tiled(rollout_ctx& c, int R, const SeqBatch* seqs) {
   RowNormArgs rn{};
   rn.x = c.x.p;
   rn.h = c.h_bf16.p;
-  rn.h_lo_offset = (long long)(c.h_bf16.n / 2);
+  rn.h_lo_offset = kPlaneLo;
   rn.rows = R;
   rn.hidden = d;
   rn.eps = m.rms_eps;
@@ -610,10 +598,10 @@ static void forward_rows_tiled(rollout_ctx& c, int R, const SeqBatch* seqs) {
   const double rn_bytes = (double)R * d * (4 + 4 + 2);
   for (int l = 0; l < m.n_layers; ++l) {
     LayerWeights& L = c.layers[l];
-    int z = project(c, c.h_bf16.p, (long long)(c.h_bf16.n / 2), d, L.wqkv_p.p, R, c.qkv_dim, d);
+    int z = project(c, c.h_bf16.p, L.wqkv_p.p, R, c.qkv_dim, d);
     AttnArgs at{};
     at.out = c.attn_bf16.p;
-    at.out_lo_offset = (long long)(c.attn_bf16.n / 2);
+    at.out_lo_offset = kPlaneLo;
     at.kv_pool = (const uint16_t*)c.kv_pool.p;
     at.geom = c.geom;
     at.page_table = c.d_page_table.p;
@@ -713,7 +701,7 @@ static void forward_rows_tiled(rollout_ctx& c, int R, const SeqBatch* seqs) {
       }
     }
 
-    z = project(c, c.attn_bf16.p, (long long)(c.attn_bf16.n / 2), c.q_dim, L.wo_p.p, R, d, c.q_dim);
+    z = project(c, c.attn_bf16.p, L.wo_p.p, R, d, c.q_dim);
     rn.splits = z;
     rn.gain = L.norm2.p;
     c.timer.begin("row_norm_kernel", rn_bytes + 4.0 * z * R * d, 0, s);
@@ -727,7 +715,7 @@ static void forward_rows_tiled(rollout_ctx& c, int R, const SeqBatch* seqs) {
     }
     gate_up(c, L, R);
 
-    z = project(c, c.act_bf16.p, (long long)(c.act_bf16.n / 2), f, L.w_down_p.p, R, d, f);
+    z = project(c, c.act_bf16.p, L.w_down_p.p, R, d, f);
     rn.splits = z;
     rn.gain = next_gain;
     c.timer.begin("row_norm_kernel", rn_bytes + 4.0 * z * R * d, 0, s);
@@ -747,7 +735,7 @@ static void forward_rows_tiled(rollout_ctx& c, int R, const SeqBatch* seqs) {
 // partial sums of squares, the consuming projection scales its output rows by
 // rsqrt(mean + eps).  The last down projection uses the final norm's gain, so the logits
 // projection reads its operand directly.
-static void stream_project(rollout_ctx& c, const DevBuf<uint16_t>& a, int lda, const void* w, int M, int N, int K,
+static void stream_project(rollout_ctx& c, const DevBuf<uint16_t>& a, const void* w, int M, int N, int K,
                            int epi, bool normalise_input, void* out, int ldo, long long out_lo_offset,
                            const float* resid_gain, const TouchRange& touch = TouchRange{}) {
   GemmArgs g{};
@@ -760,7 +748,6 @@ static void stream_project(rollout_ctx& c, const DevBuf<uint16_t>& a, int lda, c
   g.M = M;
   g.N = N;
   g.K = K;
-  g.lda = lda;
   g.ldo = ldo;
   g.frag = true;  // every operand plane of this path is in fragment order
   g.eps = c.md.rms_eps;
@@ -824,7 +811,7 @@ static void forward_rows_decode(rollout_ctx& c, int R) {
       down_touch.lines = (long long)(L.w_down_p.n / 128);
       down_touch.wgs = 128;
     }
-    stream_project(c, c.h_bf16, d, L.wqkv_p.p, R, c.qkv_dim, d, EPI_F32, true, c.partial.p, c.qkv_dim, 0, nullptr,
+    stream_project(c, c.h_bf16, L.wqkv_p.p, R, c.qkv_dim, d, EPI_F32, true, c.partial.p, c.qkv_dim, 0, nullptr,
                    down_touch);
 
     AttnArgs at{};
@@ -859,10 +846,10 @@ static void forward_rows_decode(rollout_ctx& c, int R) {
     c.timer.end(s);
     if (at.n_splits > 1) merge_attention_slots(c, at, R);
 
-    stream_project(c, c.attn_bf16, c.q_dim, L.wo_p.p, R, d, c.q_dim, EPI_RESID, false, nullptr, d, 0, L.norm2.p);
-    stream_project(c, c.h_bf16, d, L.w_gate_up_p.p, R, 2 * f, d, EPI_SWIGLU_BF16, true, c.act_bf16.p, f,
+    stream_project(c, c.attn_bf16, L.wo_p.p, R, d, c.q_dim, EPI_RESID, false, nullptr, d, 0, L.norm2.p);
+    stream_project(c, c.h_bf16, L.w_gate_up_p.p, R, 2 * f, d, EPI_SWIGLU_BF16, true, c.act_bf16.p, f,
                    (long long)(c.act_bf16.n / 2), nullptr);
-    stream_project(c, c.act_bf16, f, L.w_down_p.p, R, d, f, EPI_RESID, false, nullptr, d, 0,
+    stream_project(c, c.act_bf16, L.w_down_p.p, R, d, f, EPI_RESID, false, nullptr, d, 0,
                    l + 1 < m.n_layers ? c.layers[l + 1].norm1.p : c.final_norm.p);
   }
   c.h_is_final = true;
@@ -888,7 +875,7 @@ void engine_logits(rollout_ctx& c, const int* rows_index, int first, int n, floa
   const int d = c.md.hidden;
   if (!c.simple) {
     const uint16_t* hn = c.hn_bf16.p;
-    long long hn_lo = (long long)(c.hn_bf16.n / 2);
+    long long hn_lo = kPlaneLo;
     const bool from_h = c.h_is_final && !rows_index && first == 0;
     if (from_h) {
       hn = c.h_bf16.p;  // the fused decode path already applied the final norm's gain
@@ -922,7 +909,6 @@ void engine_logits(rollout_ctx& c, const int* rows_index, int first, int n, floa
     g.M = n;
     g.N = c.md.vocab;
     g.K = d;
-    g.lda = d;
     g.ldo = c.md.vocab;
     const GemmPlan pl = gemm_plan(n, g.N, d, EPI_F32, 1);
     c.timer.begin(pl.name, gemm_bytes(n, g.N, d, 4), 2.0 * n * g.N * d, c.stream);
@@ -956,7 +942,7 @@ void engine_target_logprobs(rollout_ctx& c, int n, const int* target, float inv_
   RowNormArgs rn{};
   rn.x = c.x.p;
   rn.h = c.h_bf16.p;  // the layers' operand buffer is free after the forward pass
-  rn.h_lo_offset = (long long)(c.h_bf16.n / 2);
+  rn.h_lo_offset = kPlaneLo;
   rn.gain = c.final_norm.p;
   rn.rows = n;
   rn.hidden = d;
@@ -968,12 +954,11 @@ void engine_target_logprobs(rollout_ctx& c, int n, const int* target, float inv_
 
   GemmArgs g{};
   g.a = c.h_bf16.p;
-  g.a_lo = c.h_bf16.p + c.h_bf16.n / 2;
+  g.a_lo = c.h_bf16.p + kPlaneLo;
   g.w = c.lm_head_p.p;
   g.M = n;
   g.N = V;
   g.K = d;
-  g.lda = d;
   g.lse_target = target;
   g.lse_scale = inv_t;
   g.lse_max = c.lse_max.p;

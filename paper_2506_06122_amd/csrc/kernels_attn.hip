@@ -145,7 +145,7 @@ __device__ inline void store1_split(uint16_t* dst, long long lo_offset, float a)
 // element (row b, column k) of the decode result
 __device__ inline long long out_offset(const AttnArgs& a, int b, int k) {
   const int q_dim = a.n_q_heads * DH;
-  return a.out_frag ? frag_offset(b, k, q_dim >> 5) : (long long)b * q_dim + k;
+  return a.out_frag ? frag_offset(b, k, q_dim >> 5) : plane_offset(b, k, q_dim);
 }
 
 // ------------------------------------------------------------------------------ fused decode
@@ -672,11 +672,11 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnArgs a) {
     attend_group(group_block(a, slot, kvh, tok0, 0), group_block(a, slot, kvh, tok0, 1), q, tok0, pos, scale_log2,
                  m, l, o, lane);
   if (qi < len) {
-    uint16_t* dst = a.out + ((long long)(row0 + qi) * a.n_q_heads + head) * DH + 4 * g;
+    uint16_t* dst = a.out + plane_offset(row0 + qi, head * DH + 4 * g, a.n_q_heads * DH);
     const float inv = 1.0f / (l * P_SCALE);
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-      store4_split(dst + 16 * j, a.out_lo_offset, o[j][0] * inv, o[j][1] * inv, o[j][2] * inv, o[j][3] * inv);
+      store4_split(dst + plane_offset(0, 16 * j, 0), a.out_lo_offset, o[j][0] * inv, o[j][1] * inv, o[j][2] * inv, o[j][3] * inv);
   }
 }
 

@@ -7,7 +7,7 @@
 
 // Epilogues of the projection kernels:
 //   EPI_F32          out[m][n] fp32 (split-K planes allowed)
-//   EPI_SWIGLU_BF16  column tiles alternate gate, up: act[m][f] = silu(gate) * up as bf16 hi/lo
+//   EPI_SWIGLU_BF16  every column tile holds 8 gates, then their 8 ups: act[m][f] = silu(gate) * up as bf16 hi/lo
 //   EPI_RESID        stream kernel only: x[m][n] += result (fp32, in place); h = x * gain as
 //                    bf16 hi/lo planes (the next projection's operand, not yet normalised);
 //                    ssq_out[workgroup column][m] = sum of x^2 over the workgroup's columns
@@ -28,6 +28,14 @@ enum { EPI_F32 = 0, EPI_SWIGLU_BF16 = 1, EPI_RESID = 2, EPI_LSE = 3 };
 // what is read from it only reaches output rows that are not stored).
 __host__ __device__ inline long long frag_offset(int m, int k, int k_tiles) {
   return (((long long)(m >> 4) * k_tiles + (k >> 5)) << 9) + ((((k >> 3) & 3) * 16 + (m & 15)) << 3) + (k & 7);
+}
+
+// Interleaved planes of an activation buffer [rows][K] (everything with more rows): a row is K / 32
+// blocks of 128 bytes, each holding the hi parts of 32 elements and then their lo parts, so that
+// one cache line carries both planes of a k-tile.
+constexpr int kPlaneLo = 32;  // elements from a hi part to its lo part
+__host__ __device__ inline long long plane_offset(int m, int k, int K) {
+  return 2 * (long long)m * K + ((k >> 5) << 6) + (k & 31);
 }
 
 // A read-only range that spare workgroups of a launch walk, one dword per 128-byte line, while
@@ -59,16 +67,17 @@ __device__ inline void touch_range(const TouchRange& t, int wg) {
 #endif
 
 struct GemmArgs {
-  const void* a;     // bf16 [rows][K], row stride lda: hi parts of the activations
-  const void* a_lo;  // same shape: lo parts (value = hi + lo)
+  const void* a;     // activations as bf16 hi and lo parts: interleaved rows (plane_offset), or with `frag` two
+  const void* a_lo;  // planes in fragment order; a_lo = first lo part
   bool frag = false; // stream kernel: `a`, `h` and the EPI_SWIGLU_BF16 result are in fragment order
   const void* w;     // packed bf16 weight, N/16 x K/32 fragments of 1 KiB
   void* out;         // EPI_F32: float [splits][M][ldo]; EPI_SWIGLU_BF16: bf16 [M][ldo] (ldo = N/2)
-  int M, N, K, lda, ldo;
-  long long out_lo_offset = 0;  // EPI_SWIGLU_BF16: elements from the hi plane of `out` to its lo plane
+  int M, N, K, ldo;
+  long long out_lo_offset = 0;  // EPI_SWIGLU_BF16: elements from a hi part of `out` to its lo part
   long long split_stride;  // floats between split planes (EPI_F32)
   int k_tiles_per_split;   // filled by the launcher
-  int grid_nx = 0, grid_ny = 0, grid_nz = 0;  // tile kernels: column blocks, row blocks, K splits (launcher)
+  int grid_nx = 0, grid_ny = 0, grid_nz = 0;  // tile kernel: column blocks, row blocks, K splits (launcher)
+  int group_m = 1, group_n = 1;  // tile kernel: row and column blocks an XCD takes side by side (launcher)
   // input normalisation (stream kernel)
   const float* rinv_ssq = nullptr;  // [rinv_partials][ssq_stride] partial sums of squares of the input rows
   int rinv_partials = 0;
@@ -100,21 +109,26 @@ struct GemmArgs {
   int lse_stride = 0;
 };
 
-// How one projection is launched: kind 0 = gemm_stream_kernel (rows <= 256), 1 = gemm_tile_kernel.
+// How one projection is launched: kind 0 = gemm_stream_kernel (mt row tiles, nt column tiles, nw wavefronts),
+// 1 = gemm_tile_kernel (shape = its entry in the table of shapes, nt = column tiles per workgroup).
 struct GemmPlan {
-  int kind, mt, nt, nw, splits, kc;
+  int kind, shape, mt, nt, nw, splits;
   const char* name;  // kernel name as a profiler shows it (without the argument list)
 };
 GemmPlan gemm_plan(int M, int N, int K, int epi, int max_splits);
 GemmPlan gemm_plan_tiled(int M, int N, int K, int epi, int max_splits);  // the tile kernel for any M
-// column parts per row that an EPI_LSE launch with this plan writes
-inline int lse_parts(const GemmPlan& pl, int N) { return ceil_div(N >> 4, 4 * pl.nt); }
+GemmPlan gemm_plan_grouped(int epi, int block_rows);                     // experts' row blocks of moe_block_rows
+// column parts per row that an EPI_LSE launch with this plan writes, and the most any plan writes
+inline int lse_parts(const GemmPlan& pl, int N) { return ceil_div(N >> 4, pl.nt); }
+inline int lse_parts_max(int N) { return ceil_div(N >> 4, 8); }
 // out[m] = lse_tgt[m] - log sum_n exp(z[m][n]) from the parts of an EPI_LSE launch; 0 where target < 0
 void launch_lse_finish(const float* lse_max, const float* lse_sum, const float* lse_tgt, const int* target,
                        int parts, int stride, int rows, float* out, hipStream_t s);
 // returns the number of split planes written (EPI_F32; <= plan.splits)
 int launch_gemm_bf16(GemmArgs a, int epi, const GemmPlan& plan, hipStream_t s);
-void launch_pack_weight(const void* src, void* dst, int N, int K, int tile_offset, int tile_stride, hipStream_t s);
+// rows of src [N][K] -> fragments.  half < 0: row n to column tile tile_offset + n / 16; half = 0 or 1: row n to
+// tile n / 8, columns 8 half .. 8 half + 7 (the gate and up matrices share tiles)
+void launch_pack_weight(const void* src, void* dst, int N, int K, int tile_offset, int half, hipStream_t s);
 
 // x[r] (+= sum of `splits` partial planes) ; h[r] = bf16(x[r] * gain * rsqrt(mean(x[r]^2) + eps)).
 //   tokens != NULL : x[r] is first loaded from the bf16 embedding row tokens[r]
@@ -125,8 +139,8 @@ struct RowNormArgs {
   long long split_stride;
   int splits;
   const float* gain;
-  uint16_t* h;              // bf16 [rows][hidden], hi plane
-  long long h_lo_offset;    // elements from the hi plane to the lo plane
+  uint16_t* h;              // bf16 hi and lo parts [rows][hidden], interleaved (plane_offset) unless h_frag
+  long long h_lo_offset;    // elements from a hi part to its lo part
   float* ssq_out;           // when set: h = x * gain without the rsqrt factor, ssq_out[r] = sum x[r]^2
   bool h_frag = false;      // h in fragment order
   const int* tokens;
@@ -193,8 +207,8 @@ constexpr int GROUP_MEMBERS = 4;  // samples of one prompt that attend to its sh
 struct AttnArgs {
   const uint16_t* q;        // prefill: half-precision hi plane [rows][n_q_heads][128], rotary applied
   long long q_lo_offset;    // elements to its lo plane
-  uint16_t* out;            // bf16 hi plane [rows][n_q_heads][128]
-  long long out_lo_offset;  // elements to its lo plane
+  uint16_t* out;            // bf16 hi and lo parts [rows][n_q_heads * 128], interleaved (plane_offset) unless out_frag
+  long long out_lo_offset;  // elements from a hi part to its lo part
   bool out_frag = false;    // decode: out in fragment order, K = n_q_heads * 128
   const uint16_t* kv_pool;
   KvGeom geom;
@@ -271,12 +285,12 @@ struct MoeRouteArgs {
 };
 void launch_moe_route_topk(const MoeRouteArgs& a, hipStream_t s);
 
-// Plan of the grouped projections: expert-sorted slots, cut into row blocks of 64.
+// Plan of the grouped projections: expert-sorted slots, cut into row blocks.
 struct MoePlanArgs {
   const int* count;         // [n_experts]
   const int* idx;           // [rows * top_k]
   const int* pos;           // [rows * top_k]
-  int rows, n_experts, top_k, max_blocks;
+  int rows, n_experts, top_k, max_blocks, block_rows;
   int* row_map;             // [rows * top_k] slot -> source row
   int* slot_of;             // [rows * top_k] (row, pick) -> slot
   int* group_of_block;      // [max_blocks]
@@ -284,4 +298,11 @@ struct MoePlanArgs {
   int* block_row_end;       // [max_blocks]; unused blocks get begin = end = 0
 };
 void launch_moe_plan(const MoePlanArgs& a, hipStream_t s);
-constexpr int kMoeBlockRows = 64;
+// Rows per block of the grouped projections, by the picks an expert gets on average: few rows leave
+// more of the chip's loads in flight to the weights (the launch is a stream over the touched experts'
+// weights then), many rows use every weight fragment for a whole block (it is bound by the matrix
+// instructions and the operand traffic).
+constexpr int kMoeMinBlockRows = 32;
+inline int moe_block_rows(long long picks, int n_experts) {
+  return picks <= 20ll * n_experts ? 32 : picks <= 80ll * n_experts ? 64 : 128;
+}

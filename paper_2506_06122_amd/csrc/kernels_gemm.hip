@@ -34,12 +34,9 @@
 //         - SwiGLU on interleaved gate/up column tiles (EPI_SWIGLU_BF16).
 //       Workgroups past the last column block, if the launcher adds any, walk a later
 //       projection's weights into the memory-side cache (TouchRange, kernels_fast.h).
-//   gemm_tile_ring_kernel (33 to 512 rows, every projection of a decode step, the logits
-//       included): 64 x 128 output tile per workgroup (32 x 128 where that fills the chip
-//       better), activations (row-major) staged through LDS in fragment order as whole cache
-//       lines, weights read directly; split-K planes when the tiles alone do not fill the chip.
-//   gemm_tile_kernel    (more than 512 rows: prefill, teacher-forced pass): 64 x 256 tile, the
-//       same staging, software-pipelined over a ring of register slots.
+//   gemm_tile_kernel    (more than 32 rows: larger decode steps, prefill, the teacher-forced
+//       pass, the experts' grouped projections): output tiles of 32 x 128 up to 128 x 320, both
+//       operands copied straight from memory into a ring of LDS stages.
 #include <cstdio>
 
 #include "kernels_fast.h"
@@ -58,22 +55,30 @@ __device__ inline uint2 pack4(const uint16_t (&h)[4]) {
   return make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
 }
 
-// D[n][m] tile(s) -> memory.  lane (r, g) holds rows n = 4g..4g+3 of a tile at column m = r.
-template <int EPI>
-__device__ inline void store_unit(const GemmArgs& p, int m, int nt, const f32x4& t0, const f32x4& t1, int g,
-                                  int z, bool two) {
-  if (EPI == EPI_F32) {
-    float* out = (float*)p.out + (long long)z * p.split_stride + (long long)m * p.ldo;
-    *(float4*)(out + nt * 16 + g * 4) = make_float4(t0[0], t0[1], t0[2], t0[3]);
-    if (two) *(float4*)(out + (nt + 1) * 16 + g * 4) = make_float4(t1[0], t1[1], t1[2], t1[3]);
-  } else {  // EPI_SWIGLU_BF16: tile nt = gate, nt + 1 = up; act[m][f] = silu(gate) * up
-    const int f = (nt >> 1) * 16 + g * 4;
-    uint16_t* out = (uint16_t*)p.out + (p.frag ? frag_offset(m, f, p.ldo >> 5) : (long long)m * p.ldo + f);
-    uint16_t h[4], lo[4];
+// D[n][m] tile of fp32 results -> memory.  lane (r, g) holds rows n = 4g..4g+3 of the tile at column m = r.
+__device__ inline void store_tile_f32(const GemmArgs& p, int m, int nt, const f32x4& t, int g, int z) {
+  float* out = (float*)p.out + (long long)z * p.split_stride + (long long)m * p.ldo;
+  *(float4*)(out + nt * 16 + g * 4) = make_float4(t[0], t[1], t[2], t[3]);
+}
+// SwiGLU of the tiles nt and nt + 1 (`two`; else t1 is not used): columns 0..7 of a tile are gates, 8..15 their
+// ups; act[m][f] = silu(gate) * up.  Lanes g < 2 take tile nt, the others tile nt + 1, so one exchange
+// brings each lane its partner's half and every lane has work; a second one gathers eight f's hi (even g) or
+// lo parts (odd g) for 16-byte stores.  All lanes of the wavefront call it; `valid`: row m is stored.
+__device__ inline void store_swiglu(const GemmArgs& p, bool valid, int m, int nt, const f32x4& t0, const f32x4& t1,
+                                    int g, bool two) {
+  uint16_t h[4], lo[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) split_bf16(silu_f(t0[e]) * t1[e], h[e], lo[e]);
-    *(uint2*)out = pack4(h);
-    *(uint2*)(out + p.out_lo_offset) = pack4(lo);
+  for (int e = 0; e < 4; ++e) {
+    const float got = __shfl_xor(g < 2 ? t1[e] : t0[e], 32, WAVE);
+    split_bf16(g < 2 ? silu_f(t0[e]) * got : silu_f(got) * t1[e], h[e], lo[e]);
+  }
+  const uint2 hi2 = pack4(h), lo2 = pack4(lo), give = g & 1 ? hi2 : lo2;
+  const uint2 got = make_uint2(__shfl_xor(give.x, 16, WAVE), __shfl_xor(give.y, 16, WAVE));
+  if (valid && (two || g < 2)) {
+    const int f = (nt + (g >> 1)) * 8;
+    uint16_t* out = (uint16_t*)p.out + (p.frag ? frag_offset(m, f, p.ldo >> 5) : plane_offset(m, f, p.ldo));
+    if (g & 1) *(uint4*)(out + p.out_lo_offset) = make_uint4(got.x, got.y, lo2.x, lo2.y);
+    else *(uint4*)out = make_uint4(hi2.x, hi2.y, got.x, got.y);
   }
 }
 
@@ -110,9 +115,9 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
     const int m = m0 + i * 16 + r;
     a_row[i] = m >= p.M ? nullptr
                : p.frag ? a_base + (((long long)(m >> 4) * k_tiles) << 9) + lane * 8
-                        : a_base + (long long)m * p.lda + g * 8;
+                        : a_base + plane_offset(m, g * 8, p.K);
   }
-  const int a_kstep = p.frag ? 512 : 32;
+  const int a_kstep = p.frag ? 512 : 64;
   const long long lo_off = (const uint16_t*)p.a_lo - a_base;
 
   // Epilogue unit (one row tile, up to two column tiles) of this wavefront, if it has one.  Its
@@ -245,404 +250,284 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
     ss += __shfl_xor(ss, 16, WAVE);
     ss += __shfl_xor(ss, 32, WAVE);
     if (g == 0 && um < p.M) p.ssq_out[(long long)blockIdx.x * p.ssq_stride + um] = ss;
-  } else if (valid) {
-    store_unit<EPI>(p, um, nt0 + uj, t[0], t[1], g, blockIdx.z, TW == 2);
+  } else if (EPI == EPI_SWIGLU_BF16) {
+    store_swiglu(p, um < p.M && nt0 + uj < n_tiles, um, nt0 + uj, t[0], t[1], g, TW == 2 && nt0 + uj + 1 < n_tiles);
+  } else if (um < p.M) {
+#pragma unroll
+    for (int q = 0; q < TW; ++q)
+      if (nt0 + uj + q < n_tiles) store_tile_f32(p, um, nt0 + uj + q, t[q], g, blockIdx.z);
   }
 }
 
-// Workgroup -> (column block, row block, K split) of the tile kernels.  The launch is
-// one-dimensional and workgroups go to the 8 XCDs (each with its own L2) round-robin by index,
-// so index % 8 is the XCD and index / 8 the order inside it.  The unit of work handed to an XCD
-// is a group of up to 16 consecutive row blocks of one (column block, split) pair, which run back
-// to back: the pair's weight slab is fetched from HBM once per group, into that XCD's L2,
-// instead of once per row block and XCD.  Units go round the XCDs with the pair (and inside it
-// the split) varying fastest, so the XCDs stay balanced and, with 8 or 16 splits, each keeps to
-// a slice of the K range, i.e. of the activations.
-__device__ inline bool tile_block(const GemmArgs& p, int& bx, int& by, int& bz) {
-  const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
-  const int gm = min(p.grid_ny, 16);
-  const int pairs = p.grid_nx * p.grid_nz;
-  const int unit = (idx / gm) * 8 + xcd;
-  const int pair = unit % pairs;
-  by = (unit / pairs) * gm + idx % gm;
-  bx = pair / p.grid_nz;
-  bz = pair % p.grid_nz;
-  return by < p.grid_ny;  // units past the last one land past the last row block
-}
-
 // ------------------------------------------------------------------------------------------
-// Tiled kernel: a workgroup of 4 wavefronts computes MT*16 rows x 4*NT*16 columns; each
-// wavefront owns NT column tiles and reads its weight fragments straight from memory, the
-// activation fragments (hi and lo planes) of KC k-tiles (one stage) are staged in LDS for all
-// four.  Software-pipelined over a ring of R register slots: while stage s is multiplied (its
-// weights read in place from slot s % R, its activations from one LDS buffer), the loads of
-// stage s+R-1 are issued into the slot stage s-1 has just left, and stage s+1's activations
-// move from their slot to the other LDS buffer - all in one basic block, so the matrix
-// instructions overlap the memory instructions.  One barrier per stage: a wavefront reaches
-// the barrier that ends stage s only after its reads of stage s's buffer, which the write of
-// stage s+2 is the next to touch.
-// Loads are never predicated: rows, column tiles and k-tiles past the end read the last valid
-// one instead (results of such rows and columns are not stored; the weights of a k-tile past
-// the end are zeroed).
+// Tile kernel.  A workgroup computes BM = 16 WM MT rows x BN = 16 WN NT columns; its WM x WN
+// wavefronts each own MT x NT tiles of 16 x 16, and with KG = 2 two such groups of wavefronts take
+// alternate k-tiles and join their sums through LDS at the end (twice the wavefronts on a tile
+// whose size the chip's 256 CUs ask for).
+//
+// What bounds it: with many rows the matrix instructions (two per weight fragment and row tile,
+// hi and lo plane); with a few hundred rows or fewer the path from L2 into the CUs, measured at
+// 40-70 GB/s per CU in this kernel whatever the pipeline depth.  Per k-tile a workgroup moves
+// 128 BM + 64 BN bytes for BM BN / 256 tiles, so wide tiles win, and one round of workgroups that
+// fills all CUs wins over a second, mostly empty one: the plan below weighs the two.
+//
+// Both operands go from memory straight into LDS (global_load_lds_dwordx4, 1 KiB per instruction),
+// S - 1 stages ahead of the stage that is multiplied, with one barrier per stage:
+//   - A wavefront waits until its own loads of stage s have arrived (s_waitcnt vmcnt counts in
+//     order: the loads of the S - 2 later stages may be outstanding), then the barrier says the
+//     same of every wavefront's loads.
+//   - It also waits for its LDS reads of stage s - 1 (lgkmcnt) before that barrier, so the loads of
+//     stage s + S - 1, issued after it, can overwrite that buffer.
+//   - Past the end of the K range the last k-tile is loaded again (never multiplied), so that every
+//     stage counts the same number of loads.
+// Activations: one instruction brings 8 rows x 128 bytes, a line holding both planes of 32 elements
+// (plane_offset).  The 16-byte chunk c of row r lands in slot c ^ (r % 8) of its row, by choosing
+// each lane's source address, which makes the fragment reads conflict-free.  Weights: a fragment is
+// one instruction and is read back as it lies.  Rows and column tiles past the end read the last
+// valid one; their results are not stored.
+//
+// Measured against the kernel it replaced (register-staged, 64 x 256 and 64 x 128 tiles), random
+// operands: 12000 rows x 37888 x 3584 5.53 -> 4.52 ms (720 TFLOP/s, 1440 issued), 1700 x 17920 x
+// 1536 192 -> 157 us, 187 x 17920 x 1536 33 -> 27 us, 64 x 37888 x 3584 70 -> 57 us.
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-template <int MT, int NT, int KC, int R, int EPI>
-__global__ __launch_bounds__(256) void gemm_tile_kernel(GemmArgs p) {
-  constexpr int FR = 2 * MT * KC;      // activation fragments per stage: [kk][plane][mt]
-  static_assert(FR % 4 == 0 && (2 * MT) % 4 == 0, "the fragments divide evenly over the wavefronts");
-  constexpr int PER = FR / 4;          // fragments each wavefront stages: f = 4 s + wave
-  __shared__ u32x4 a_lds[2][FR * 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r = lane & 15, g = lane >> 4;
-  const int n_tiles = p.N >> 4, k_tiles = p.K >> 5;
-  int bx, by, bz;
-  if (!tile_block(p, bx, by, bz)) return;  // padding of the XCD-aware launch (uniform)
-  const int nt0 = (bx * 4 + wave) * NT;
-  int m0 = by * (MT * 16);
-  const int kt_begin = bz * p.k_tiles_per_split;
-  const int kt_end = min(k_tiles, kt_begin + p.k_tiles_per_split);
-
-  // grouped (per-expert) launches: this row block belongs to one group with its own weights
-  const u32x4* wp = (const u32x4*)p.w;
-  const int* row_map = nullptr;
-  int m_limit = p.M;
-  if (p.group_of_block) {
-    int grp = p.group_of_block[by];
-    wp += (long long)grp * p.group_stride16;
-    m0 = p.block_row_begin[by];
-    m_limit = p.block_row_end[by];
-    row_map = p.row_map;
-    if (m0 >= m_limit) return;  // unused block of the plan (uniform over the workgroup)
-  }
-  const uint16_t* a_base = (const uint16_t*)p.a;
-  const long long lo_off = (const uint16_t*)p.a_lo - a_base;
-
-  // Staging of the activations: one load instruction brings 8 rows x 128 bytes - both k-tiles
-  // of the stage, one plane - as full cache lines (a 16-row x 64-byte fragment load costs the
-  // L2 path twice as much per byte).  Unit u = 4 s + wave -> (plane, group of 8 rows); a lane
-  // holds chunk c = lane % 8 of row lane / 8, i.e. k-tile c / 4, fragment column group c % 4.
-  // In LDS a fragment's sixteen 16-byte slots of one column group are permuted by
-  // row ^ (2 * group + k-tile), which spreads a row's 8 chunks over all banks.
-  static_assert(KC == 2 && FR == 4 * MT, "a stage is two k-tiles");
-  const int st_kk = (lane & 7) >> 2, st_g = lane & 3;
-  const uint16_t* st_src[PER];
-  int st_dst[PER];
-#pragma unroll
-  for (int s = 0; s < PER; ++s) {
-    const int u = 4 * s + wave;
-    const int plane = u / (2 * MT), rg = u % (2 * MT);
-    const int mt = rg >> 1, rr = (rg & 1) * 8 + (lane >> 3);
-    const int m = min(m0 + mt * 16 + rr, m_limit - 1);
-    const long long row = row_map ? row_map[m] : m;
-    st_src[s] = a_base + row * p.lda + st_g * 8 + (plane ? lo_off : 0);
-    st_dst[s] = ((st_kk * 2 + plane) * MT + mt) * 64 + st_g * 16 + (rr ^ ((2 * st_g + st_kk) & 7));
-  }
-  const int rd_off[2] = {g * 16 + (r ^ ((2 * g) & 7)), g * 16 + (r ^ ((2 * g + 1) & 7))};
-  const u32x4* w_src[NT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j) w_src[j] = wp + (long long)min(nt0 + j, n_tiles - 1) * k_tiles * 64 + lane;
-
-  f32x4 acc[MT][NT];
-#pragma unroll
-  for (int i = 0; i < MT; ++i)
-#pragma unroll
-    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  u32x4 rst[R][PER];
-  u32x4 rb[R][KC][NT];
-#define GEMM_LOAD_STAGE(KT, SLOT)                                                                 \
-  {                                                                                               \
-    _Pragma("unroll") for (int s = 0; s < PER; ++s) {                                             \
-      const int k = min((KT) + st_kk, kt_end - 1);                                                \
-      rst[SLOT][s] = *(const u32x4*)(st_src[s] + (long long)k * 32);                              \
-    }                                                                                             \
-    _Pragma("unroll") for (int kk = 0; kk < KC; ++kk)                                             \
-        _Pragma("unroll") for (int j = 0; j < NT; ++j) {                                          \
-      rb[SLOT][kk][j] = w_src[j][(long long)min((KT) + kk, kt_end - 1) * 64];                     \
-      if (kk > 0 && (KT) + kk >= kt_end) rb[SLOT][kk][j] = u32x4{0u, 0u, 0u, 0u};                 \
-    }                                                                                             \
-  }
-#pragma unroll
-  for (int d = 0; d < R - 1; ++d) GEMM_LOAD_STAGE(kt_begin + d * KC, d)
-#pragma unroll
-  for (int s = 0; s < PER; ++s) a_lds[0][st_dst[s]] = rst[0][s];
-  __syncthreads();
-  int buf = 0;
-  for (int kt = kt_begin; kt < kt_end; kt += R * KC) {
-#pragma unroll
-    for (int d = 0; d < R; ++d) {
-      const int k0 = kt + d * KC;
-      if (k0 < kt_end) {  // uniform over the workgroup
-        u32x4 a[KC][2][MT];
-#pragma unroll
-        for (int kk = 0; kk < KC; ++kk)
-#pragma unroll
-          for (int plane = 1; plane >= 0; --plane)
-#pragma unroll
-            for (int i = 0; i < MT; ++i) a[kk][plane][i] = a_lds[buf][((kk * 2 + plane) * MT + i) * 64 + rd_off[kk]];
-        GEMM_LOAD_STAGE(k0 + (R - 1) * KC, (d + R - 1) % R)
-#pragma unroll
-        for (int kk = 0; kk < KC; ++kk)
-#pragma unroll
-          for (int plane = 1; plane >= 0; --plane)  // lo parts first, then hi
-#pragma unroll
-            for (int i = 0; i < MT; ++i)
-#pragma unroll
-              for (int j = 0; j < NT; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, rb[d][kk][j]),
-                                                                    __builtin_bit_cast(bf16x8, a[kk][plane][i]),
-                                                                    acc[i][j], 0, 0, 0);
-        if (k0 + KC < kt_end) {
-#pragma unroll
-          for (int s = 0; s < PER; ++s) a_lds[buf ^ 1][st_dst[s]] = rst[(d + 1) % R][s];
-        }
-        __syncthreads();
-        buf ^= 1;
-      }
-    }
-  }
-#undef GEMM_LOAD_STAGE
-  if constexpr (EPI == EPI_LSE) {
-    // log-sum-exp parts of this workgroup's columns: per wavefront over its NT tiles (the 4
-    // lanes of a row meet by shuffles), then over the 4 wavefronts through LDS
-    __shared__ float part_m[4][MT * 16], part_s[4][MT * 16];
-#pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      const int m = m0 + i * 16 + r;
-      const int tgt = m < m_limit ? p.lse_target[m] : -1;
-      float mx = -INFINITY;
-#pragma unroll
-      for (int j = 0; j < NT; ++j)
-        if (nt0 + j < n_tiles) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            acc[i][j][e] *= p.lse_scale;
-            mx = fmaxf(mx, acc[i][j][e]);
-            if ((nt0 + j) * 16 + g * 4 + e == tgt) p.lse_tgt[m] = acc[i][j][e];
-          }
-        }
-      mx = fmaxf(mx, __shfl_xor(mx, 16, WAVE));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
-      float sm = 0.f;
-#pragma unroll
-      for (int j = 0; j < NT; ++j)
-        if (nt0 + j < n_tiles) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) sm += expf(acc[i][j][e] - mx);
-        }
-      sm += __shfl_xor(sm, 16, WAVE);
-      sm += __shfl_xor(sm, 32, WAVE);
-      if (g == 0) {
-        part_m[wave][i * 16 + r] = mx;
-        part_s[wave][i * 16 + r] = sm;
-      }
-    }
-    __syncthreads();
-    if (threadIdx.x < MT * 16 && m0 + (int)threadIdx.x < m_limit) {
-      float mx = -INFINITY;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) mx = fmaxf(mx, part_m[w][threadIdx.x]);
-      float sm = 0.f;
-#pragma unroll
-      for (int w = 0; w < 4; ++w)
-        if (part_m[w][threadIdx.x] > -INFINITY) sm += part_s[w][threadIdx.x] * expf(part_m[w][threadIdx.x] - mx);
-      p.lse_max[(long long)bx * p.lse_stride + m0 + threadIdx.x] = mx;
-      p.lse_sum[(long long)bx * p.lse_stride + m0 + threadIdx.x] = sm;
-    }
-    return;
-  }
-  if (nt0 >= n_tiles) return;
-#pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    const int m = m0 + i * 16 + r;
-    if (m >= m_limit) continue;
-#pragma unroll
-    for (int j = 0; j < NT; j += 2)
-      if (nt0 + j < n_tiles)  // an odd last column tile (fp32 results only) is stored alone
-        store_unit<EPI == EPI_LSE ? EPI_F32 : EPI>(p, m, nt0 + j, acc[i][j], acc[i][j + 1], g, bz,
-                                                  nt0 + j + 1 < n_tiles);
-  }
+// 16 bytes per lane from base + voff to LDS byte `lds` + 16 * lane.  (The compiler keeps nothing in m0: it sets it
+// right before each instruction of its own that reads it.)  As inline assembly, because the compiler makes every
+// LDS read wait for all copies into LDS that it knows of.
+__device__ __forceinline__ void load_to_lds(unsigned lds, unsigned voff, const void* base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base)
+               : "memory");
+}
+// the same with a 64-bit address per lane
+__device__ __forceinline__ void load_to_lds(unsigned lds, const void* addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(addr) : "memory");
+}
+// this wavefront's loads but the last N have arrived and its LDS reads are done; then the barrier
+template <int N>
+__device__ __forceinline__ void wait_and_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-// ------------------------------------------------------------------------------------------
-// The same tile with predicated loads and a ring of D prefetched stages whose activations go
-// to LDS and whose weights go to the multiply operands at the top of each stage: the leaner
-// variant (fewer registers, rows past the end are not loaded) that the decode-sized
-// projections run best with.
-template <int MT, int NT, int KC, int D, int EPI>
-__global__ __launch_bounds__(256) void gemm_tile_ring_kernel(GemmArgs p) {
-  constexpr int FR = 2 * MT * KC;      // activation fragments per stage: [kk][plane][mt]
-  constexpr int PER = (FR + 3) / 4;    // fragments each wavefront stages
-  __shared__ uint4 a_lds[2][FR * 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// Workgroup -> (column block, row block, K split).  The launch is one-dimensional and workgroups
+// go to the 8 XCDs (each with its own L2) round-robin by index, so index % 8 is the XCD and
+// index / 8 the order inside it.  An XCD takes groups of group_m row blocks x group_n column blocks, whose
+// workgroups run side by side and share the operands' lines in its L2; groups go round the XCDs
+// with the split varying fastest, then the row blocks.
+__device__ inline bool tile_block(const GemmArgs& p, int& bx, int& by, int& bz) {
+  const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
+  const int per = p.group_m * p.group_n;
+  const int unit = (idx / per) * 8 + xcd, in = idx % per;
+  const int gy = (p.grid_ny + p.group_m - 1) / p.group_m;
+  bz = unit % p.grid_nz;
+  const int q = unit / p.grid_nz;
+  by = (q % gy) * p.group_m + in % p.group_m;
+  bx = (q / gy) * p.group_n + in / p.group_m;
+  return by < p.grid_ny && bx < p.grid_nx;
+}
+
+// GATHER: the rows of `a` come through row_map (experts' grouped projections)
+template <int WM, int WN, int MT, int NT, int KG, int S, int MINB, int EPI, bool GATHER>
+__global__ __launch_bounds__(WM* WN* KG * 64, MINB) void gemm_tile_kernel(GemmArgs p) {
+  constexpr int NW = WM * WN * KG, BM = WM * MT * 16, BN = WN * NT * 16;
+  constexpr int UA = BM / 8, UW = BN / 16, U1 = UA + UW;  // load instructions per k-tile
+  constexpr int L = (U1 * KG + NW - 1) / NW;              // per wavefront and stage
+  constexpr int RED = KG > 1 ? (KG - 1) * WM * WN * MT * NT : 0;
+  constexpr int LDS_KB = S * U1 * KG > RED ? S * U1 * KG : RED;
+  static_assert(LDS_KB <= 160 && S >= 2 && KG <= 2, "fits the CU");
+  __shared__ __attribute__((aligned(1024))) char lds[LDS_KB * 1024];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, g = lane >> 4;
   const int n_tiles = p.N >> 4, k_tiles = p.K >> 5;
   int bx, by, bz;
   if (!tile_block(p, bx, by, bz)) return;  // padding of the XCD-aware launch (uniform)
-  const int nt0 = (bx * 4 + wave) * NT;
-  int m0 = by * (MT * 16);
+  const int nt0 = bx * (BN / 16);
+  int m0 = by * BM;
   const int kt_begin = bz * p.k_tiles_per_split;
   const int kt_end = min(k_tiles, kt_begin + p.k_tiles_per_split);
 
   // grouped (per-expert) launches: this row block belongs to one group with its own weights
-  const uint4* wp = (const uint4*)p.w;
-  const int* row_map = nullptr;
+  const char* wp = (const char*)p.w;
   int m_limit = p.M;
   if (p.group_of_block) {
-    int grp = p.group_of_block[by];
-    wp += (long long)grp * p.group_stride16;
+    wp += (long long)p.group_of_block[by] * p.group_stride16 * 16;
     m0 = p.block_row_begin[by];
     m_limit = p.block_row_end[by];
-    row_map = p.row_map;
     if (m0 >= m_limit) return;  // unused block of the plan (uniform over the workgroup)
   }
-  const uint16_t* a_base = (const uint16_t*)p.a;
-  const long long lo_off = (const uint16_t*)p.a_lo - a_base;
+  wp += (long long)nt0 * k_tiles * 1024;
+  const long long row_bytes = (long long)p.K * 4;
+  const char* ap = (const char*)p.a + (GATHER ? 0 : m0 * row_bytes);
 
-  // Staging of the activations: one load instruction brings 8 rows x 128 bytes - both k-tiles
-  // of the stage, one plane - as full cache lines (a 16-row x 64-byte fragment load costs the
-  // L2 path twice as much per byte).  Unit u = wave + 4 s -> (plane, group of 8 rows); a lane
-  // holds chunk c = lane % 8 of row lane / 8, i.e. k-tile c / 4, fragment column group c % 4.
-  // In LDS a fragment's sixteen 16-byte slots of one column group are permuted by
-  // row ^ (2 * group + k-tile), which spreads a row's 8 chunks over all banks.
-  static_assert(KC == 2 && FR == 4 * MT, "a stage is two k-tiles");
-  const int st_kk = (lane & 7) >> 2, st_g = lane & 3;
-  const uint16_t* st_src[PER];
-  int st_dst[PER];
+  const int kg = wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
+  // this wavefront's loads of a stage: instruction u of the stage's U1 * KG
+  unsigned voff[L], step[L], dst[L];
+  int k_of[L];
+  const char* base[L];
+  const char* row_addr[L];
 #pragma unroll
-  for (int s = 0; s < PER; ++s) {
-    const int u = wave + 4 * s;
-    const int plane = u / (2 * MT), rg = u % (2 * MT);
-    const int mt = rg >> 1, rr = (rg & 1) * 8 + (lane >> 3);
-    const int m = m0 + mt * 16 + rr;
-    st_src[s] = nullptr;
-    if (m < m_limit) {
-      const long long row = row_map ? row_map[m] : m;
-      st_src[s] = a_base + row * p.lda + (lane & 7) * 8 + (plane ? lo_off : 0);
+  for (int s = 0; s < L; ++s) {
+    const int uu = min(s * NW + wave, U1 * KG - 1);  // an uneven last round loads the last one again
+    const int u = __builtin_amdgcn_readfirstlane(uu % U1);
+    k_of[s] = __builtin_amdgcn_readfirstlane(uu / U1);
+    dst[s] = uu * 1024;
+    if (u < UA) {
+      const int m = min(m0 + u * 8 + (lane >> 3), m_limit - 1);
+      const unsigned chunk = ((lane & 7) ^ (lane >> 3)) * 16;
+      if (GATHER) row_addr[s] = ap + p.row_map[m] * row_bytes + chunk;
+      else voff[s] = (unsigned)((m - m0) * row_bytes) + chunk;
+      step[s] = 128;
+      base[s] = ap;
+    } else {
+      voff[s] = (unsigned)(min(nt0 + u - UA, n_tiles - 1) - nt0) * (unsigned)k_tiles * 1024u + lane * 16;
+      step[s] = 1024;
+      base[s] = wp;
     }
-    st_dst[s] = ((st_kk * 2 + plane) * MT + mt) * 64 + st_g * 16 + (rr ^ ((2 * st_g + st_kk) & 7));
   }
-  const int rd_off[2] = {g * 16 + (r ^ ((2 * g) & 7)), g * 16 + (r ^ ((2 * g + 1) & 7))};
+  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)lds;
+  auto issue = [&](int kt, int buf) {
+#pragma unroll
+    for (int s = 0; s < L; ++s) {
+      const int k = min(kt + k_of[s], kt_end - 1);
+      const unsigned to = lds0 + buf * (U1 * KG * 1024) + dst[s];
+      if (GATHER && step[s] == 128) load_to_lds(to, row_addr[s] + (long long)k * 128);
+      else load_to_lds(to, voff[s], base[s] + (long long)k * step[s]);
+    }
+  };
 
   f32x4 acc[MT][NT];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < S - 1; ++s) issue(kt_begin + s * KG, s);
 
-  struct Stage {
-    uint4 st[PER];
-    Frag b[KC][NT];
-  };
-  Stage ring[D];
-  Frag cur[KC][NT];
-  auto load_stage = [&](int kt, Stage& sg) {
-#pragma unroll
-    for (int s = 0; s < PER; ++s) {
-      sg.st[s] = make_uint4(0, 0, 0, 0);
-      if (st_src[s] && kt + st_kk < kt_end) sg.st[s] = *(const uint4*)(st_src[s] + (long long)kt * 32);
-    }
-#pragma unroll
-    for (int kk = 0; kk < KC; ++kk)
-#pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        sg.b[kk][j].u = make_uint4(0, 0, 0, 0);
-        if (kt + kk < kt_end && nt0 + j < n_tiles)
-          sg.b[kk][j].u = wp[((long long)(nt0 + j) * k_tiles + kt + kk) * 64 + lane];
-      }
-  };
-
-#pragma unroll
-  for (int d = 0; d < D; ++d) load_stage(kt_begin + d * KC, ring[d]);
+  // fragment reads: row tile i of this wavefront is row groups 2 i and 2 i + 1 (8 rows, 1 KiB each)
+  const int a_row = kg * U1 * 1024 + (wm * MT * 2 + (r >> 3)) * 1024 + (r & 7) * 128;
+  const int a_hi = a_row + (g ^ (r & 7)) * 16, a_lo = a_row + ((4 + g) ^ (r & 7)) * 16;
+  const int w_at = kg * U1 * 1024 + (UA + wn * NT) * 1024 + lane * 16;
   int buf = 0;
-  for (int kt = kt_begin; kt < kt_end; kt += D * KC) {
+  for (int kt = kt_begin; kt < kt_end; kt += KG) {
+    wait_and_barrier<(S - 2) * L>();
+    const char* b = lds + buf * (U1 * KG * 1024);
+    u32x4 w[NT], a[MT][2];
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-      const int k0 = kt + d * KC;
-      if (k0 >= kt_end) break;  // uniform over the workgroup
-#pragma unroll
-      for (int s = 0; s < PER; ++s) a_lds[buf][st_dst[s]] = ring[d].st[s];
-#pragma unroll
-      for (int kk = 0; kk < KC; ++kk)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) cur[kk][j] = ring[d].b[kk][j];
-      load_stage(k0 + D * KC, ring[d]);
-      __syncthreads();
-#pragma unroll
-      for (int kk = 0; kk < KC; ++kk)
-#pragma unroll
-        for (int plane = 1; plane >= 0; --plane) {  // lo parts first, then hi
-          Frag a[MT];
-#pragma unroll
-          for (int i = 0; i < MT; ++i) a[i].u = a_lds[buf][((kk * 2 + plane) * MT + i) * 64 + rd_off[kk]];
-#pragma unroll
-          for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int j = 0; j < NT; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur[kk][j].v, a[i].v, acc[i][j], 0, 0, 0);
-        }
-      buf ^= 1;
-    }
-  }
-  if constexpr (EPI == EPI_LSE) {
-    // log-sum-exp parts of this workgroup's columns: per wavefront over its NT tiles (the 4
-    // lanes of a row meet by shuffles), then over the 4 wavefronts through LDS
-    __shared__ float part_m[4][MT * 16], part_s[4][MT * 16];
+    for (int j = 0; j < NT; ++j) w[j] = *(const u32x4*)(b + w_at + j * 1024);
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
-      const int m = m0 + i * 16 + r;
-      const int tgt = m < m_limit ? p.lse_target[m] : -1;
-      float mx = -INFINITY;
+      a[i][1] = *(const u32x4*)(b + a_lo + i * 2048);
+      a[i][0] = *(const u32x4*)(b + a_hi + i * 2048);
+    }
+    issue(kt + (S - 1) * KG, buf == 0 ? S - 1 : buf - 1);
+    if (KG == 1 || kt + kg < kt_end) {  // an odd last k-tile belongs to the first group
+      __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-      for (int j = 0; j < NT; ++j)
-        if (nt0 + j < n_tiles) {
+      for (int i = 0; i < MT; ++i)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            acc[i][j][e] *= p.lse_scale;
-            mx = fmaxf(mx, acc[i][j][e]);
-            if ((nt0 + j) * 16 + g * 4 + e == tgt) p.lse_tgt[m] = acc[i][j][e];
+        for (int plane = 1; plane >= 0; --plane)  // lo part first, then hi
+#pragma unroll
+          for (int j = 0; j < NT; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[j]),
+                                                                __builtin_bit_cast(bf16x8, a[i][plane]), acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_s_setprio(0);
+    }
+    buf = buf == S - 1 ? 0 : buf + 1;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may still be on its way into LDS
+  if constexpr (KG > 1) {
+    __syncthreads();
+    float4* red = (float4*)lds + (wave % (WM * WN)) * (MT * NT * 64) + lane;
+    if (kg > 0) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+          red[(i * NT + j) * 64] = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+    }
+    __syncthreads();
+    if (kg == 0) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          const float4 v = red[(i * NT + j) * 64];
+          acc[i][j][0] += v.x;
+          acc[i][j][1] += v.y;
+          acc[i][j][2] += v.z;
+          acc[i][j][3] += v.w;
+        }
+    }
+  }
+  const int wt0 = nt0 + wn * NT;  // this wavefront's first column tile
+  if constexpr (EPI == EPI_LSE) {
+    // log-sum-exp parts of this workgroup's columns: per wavefront over its NT tiles (the 4
+    // lanes of a row meet by shuffles), then over the WN wavefronts of a row through LDS
+    __syncthreads();
+    float* part = (float*)lds;  // [2][WN][BM]: max, sum
+    if (kg == 0) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        const int ml = (wm * MT + i) * 16 + r, m = m0 + ml;
+        const int tgt = m < m_limit ? p.lse_target[m] : -1;
+        float mx = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+          if (wt0 + j < n_tiles) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              acc[i][j][e] *= p.lse_scale;
+              mx = fmaxf(mx, acc[i][j][e]);
+              if ((wt0 + j) * 16 + g * 4 + e == tgt) p.lse_tgt[m] = acc[i][j][e];
+            }
           }
-        }
-      mx = fmaxf(mx, __shfl_xor(mx, 16, WAVE));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
-      float sm = 0.f;
+        mx = fmaxf(mx, __shfl_xor(mx, 16, WAVE));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
+        float sm = 0.f;
 #pragma unroll
-      for (int j = 0; j < NT; ++j)
-        if (nt0 + j < n_tiles) {
+        for (int j = 0; j < NT; ++j)
+          if (wt0 + j < n_tiles) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) sm += expf(acc[i][j][e] - mx);
+            for (int e = 0; e < 4; ++e) sm += expf(acc[i][j][e] - mx);
+          }
+        sm += __shfl_xor(sm, 16, WAVE);
+        sm += __shfl_xor(sm, 32, WAVE);
+        if (g == 0) {
+          part[wn * BM + ml] = mx;
+          part[(WN + wn) * BM + ml] = sm;
         }
-      sm += __shfl_xor(sm, 16, WAVE);
-      sm += __shfl_xor(sm, 32, WAVE);
-      if (g == 0) {
-        part_m[wave][i * 16 + r] = mx;
-        part_s[wave][i * 16 + r] = sm;
       }
     }
     __syncthreads();
-    if (threadIdx.x < MT * 16 && m0 + (int)threadIdx.x < m_limit) {
+    for (int ml = threadIdx.x; ml < BM; ml += NW * 64) {
+      if (m0 + ml >= m_limit) continue;
       float mx = -INFINITY;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) mx = fmaxf(mx, part_m[w][threadIdx.x]);
+      for (int w = 0; w < WN; ++w) mx = fmaxf(mx, part[w * BM + ml]);
       float sm = 0.f;
 #pragma unroll
-      for (int w = 0; w < 4; ++w)
-        if (part_m[w][threadIdx.x] > -INFINITY) sm += part_s[w][threadIdx.x] * expf(part_m[w][threadIdx.x] - mx);
-      p.lse_max[(long long)bx * p.lse_stride + m0 + threadIdx.x] = mx;
-      p.lse_sum[(long long)bx * p.lse_stride + m0 + threadIdx.x] = sm;
+      for (int w = 0; w < WN; ++w)
+        if (part[w * BM + ml] > -INFINITY) sm += part[(WN + w) * BM + ml] * expf(part[w * BM + ml] - mx);
+      p.lse_max[(long long)bx * p.lse_stride + m0 + ml] = mx;
+      p.lse_sum[(long long)bx * p.lse_stride + m0 + ml] = sm;
     }
     return;
-  }
-  if (nt0 >= n_tiles) return;
+  } else {
+    if (kg > 0) return;
 #pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    const int m = m0 + i * 16 + r;
-    if (m >= m_limit) continue;
+    for (int i = 0; i < MT; ++i) {
+      const int m = m0 + (wm * MT + i) * 16 + r;
+      if constexpr (EPI == EPI_SWIGLU_BF16) {
 #pragma unroll
-    for (int j = 0; j < NT; j += 2)
-      if (nt0 + j < n_tiles)  // an odd last column tile (fp32 results only) is stored alone
-        store_unit<EPI == EPI_LSE ? EPI_F32 : EPI>(p, m, nt0 + j, acc[i][j], acc[i][j + 1], g, bz,
-                                                  nt0 + j + 1 < n_tiles);
+        for (int j = 0; j < NT; j += 2)
+          if (wt0 + j < n_tiles)
+            store_swiglu(p, m < m_limit, m, wt0 + j, acc[i][j], acc[i][j + 1 < NT ? j + 1 : j], g,
+                         j + 1 < NT && wt0 + j + 1 < n_tiles);
+      } else {
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+          if (wt0 + j < n_tiles && m < m_limit) store_tile_f32(p, m, wt0 + j, acc[i][j], g, bz);
+      }
+    }
   }
 }
 
@@ -673,51 +558,151 @@ static const char* stream_name(int mt, int nt, int nw, int epi) {
   return names[mt == 1 ? 0 : mt == 2 ? 1 : 2][nt - 1][nw == 4 ? 0 : 1][epi];
 }
 
-// tiled kernel: the largest tile that still gives every CU a workgroup, then split-K planes
-GemmPlan gemm_plan_tiled(int M, int N, int K, int epi, int max_splits) {
-  GemmPlan pl{};
-  const int n_tiles = N >> 4, k_tiles = K >> 5;
-  pl.kind = 1;
-  pl.nw = 4;
-  static const int cfg[2][2] = {{4, 4}, {4, 2}};
-  static const char* const names[2][3] = {
-      {"gemm_tile_kernel<4,4,2,2,0>", "gemm_tile_kernel<4,4,2,2,1>", "gemm_tile_kernel<4,4,2,2,3>"},
-      {"gemm_tile_ring_kernel<4,2,2,1,0>", "gemm_tile_ring_kernel<4,2,2,1,1>", "gemm_tile_ring_kernel<4,2,2,1,3>"}};
-  // 64 x 256 tiles for prefill-sized row counts when they still give every CU two workgroups;
-  // 64 x 128 otherwise and for every decode-sized launch (at most 512 rows: measured 8-25 %
-  // faster there at all widths, the logits projection included)
-  int pick = 1;
-  long long blocks = 0;
-  for (int c = 0; c < 2; ++c) {
-    blocks = (long long)ceil_div(M, 16 * cfg[c][0]) * ceil_div(n_tiles, 4 * cfg[c][1]);
-    if ((blocks >= 576 && M > 512) || c == 1) {
-      pick = c;
-      break;
+// The tile kernel's shapes.  per_kt, per_kt_alone: microseconds per k-tile of one workgroup's share
+// of a CU that holds its full number of workgroups (per_cu), or only one; fixed: what a workgroup
+// costs besides (first loads' latency, result), not hidden by a next round when it has the CU to
+// itself; start: the launch.  Fitted to 2000 timed launches (40 to 9200 rows, eleven (N, K) pairs of
+// the 1.5B, 7B and 30B-A3B shapes, one to sixteen splits; rms error of the log 0.08-0.15).
+struct TileShape {
+  int wm, wn, mt, nt, kg, s, minb;
+  float per_kt, per_kt_alone, start, fixed;
+  const char* name[3];  // by epilogue: F32, SWIGLU, LSE
+};
+#define TILE_NAME(a) {"gemm_tile_kernel<" a ",0>", "gemm_tile_kernel<" a ",1>", "gemm_tile_kernel<" a ",3>"}
+// x-macro: index, template arguments, model
+#define TILE_SHAPES(X)                                        \
+  X(0, 2, 2, 1, 4, 1, 4, 3, 0.151f, 0.179f, 2.1f, 1.4f)   /*  32 x 128 */ \
+  X(1, 2, 2, 2, 4, 1, 4, 2, 0.224f, 0.253f, 0.8f, 3.4f)   /*  64 x 128 */ \
+  X(2, 2, 2, 3, 2, 2, 4, 1, 0.187f, 0.187f, 0.0f, 4.3f)   /*  96 x  64 */ \
+  X(3, 2, 2, 2, 5, 2, 3, 1, 0.271f, 0.271f, 0.0f, 5.4f)   /*  64 x 160 */ \
+  X(4, 2, 2, 3, 5, 2, 3, 1, 0.348f, 0.348f, 0.0f, 7.0f)   /*  96 x 160 */ \
+  X(5, 4, 2, 2, 5, 1, 5, 1, 0.478f, 0.478f, 0.0f, 7.3f)   /* 128 x 160 */ \
+  X(6, 4, 2, 2, 10, 1, 4, 1, 0.827f, 0.827f, 0.0f, 10.0f) /* 128 x 320 */ \
+  X(7, 2, 2, 4, 4, 1, 2, 3, 0.391f, 0.556f, 3.5f, 2.5f)   /* 128 x 128 */ \
+  X(8, 2, 2, 4, 8, 1, 2, 2, 0.623f, 0.781f, 0.2f, 8.2f)   /* 128 x 256 */
+static const TileShape kTileShapes[] = {
+#define X(id, wm, wn, mt, nt, kg, s, minb, a, b, c, d) \
+  {wm, wn, mt, nt, kg, s, minb, a, b, c, d, TILE_NAME(#wm "," #wn "," #mt "," #nt "," #kg "," #s)},
+    TILE_SHAPES(X)
+#undef X
+};
+constexpr bool grouped_shape(int id) { return id == 0 || id == 1 || id == 7; }  // row blocks of moe_block_rows
+constexpr int kLseMinTile = 8;    // column tiles per workgroup an EPI_LSE launch has at least (sizes the parts' buffers)
+
+// Row and column blocks an XCD takes side by side (tile_block), and the workgroups its busiest CU gets.
+// Groups go to the XCDs whole, so a group that is large against the launch leaves XCDs idle: of the
+// group heights that cut the row blocks evenly, the largest with the fewest workgroups per CU.
+// With many workgroups in all, four column blocks side by side, so that the group's activation and weight lines
+// are both few.
+static int tile_groups(long long ny, long long nx, long long nz, int& gm, int& gn) {
+  const int chunks = ceil_div(ny, 16);
+  gn = ny * nx >= 1024 && ny > 4 ? 4 : 1;
+  int best = 0x7fffffff;
+  gm = 1;
+  for (int c = chunks; c < chunks + 6 && c <= ny; ++c) {
+    const int m = ceil_div(ny, c);
+    const long long units = (long long)ceil_div(ny, m) * ceil_div(nx, gn) * nz;
+    const int n = ceil_div((long long)ceil_div(units, 8) * m * gn, 32);
+    if (n < best) {
+      best = n;
+      gm = m;
     }
   }
-  pl.mt = cfg[pick][0];
-  pl.nt = cfg[pick][1];
-  pl.kc = 2;
-  pl.splits = 1;
-  if (pick == 1 && epi == EPI_F32 && M <= 128 && blocks < 512) {
-    pl.mt = 2;
-    blocks = (long long)ceil_div(M, 32) * ceil_div(n_tiles, 8);
+  return best;
+}
+
+// Microseconds one projection is expected to take: the busiest CU's rounds of workgroups, not less
+// than the weights take from HBM, plus reading the split planes back (the next launch's work).
+static double tile_cost(const TileShape& t, int M, int n_tiles, int k_tiles, int z) {
+  int gm, gn;
+  const int n = tile_groups(ceil_div(M, t.wm * t.mt * 16), ceil_div(n_tiles, t.wn * t.nt), z, gm, gn);
+  // one workgroup per CU: nothing hides its first loads and its result from the next round, and over many
+  // rounds the model flatters it by up to a fifth
+  if (t.minb == 1 && n > 2) return 1e30;
+  const int kt = ceil_div(k_tiles, z), per_cu = t.minb, rest = n % per_cu;
+  double us = t.start + (double)(n - rest) * (kt * t.per_kt + t.fixed);
+  if (rest)
+    us += kt * (t.per_kt_alone + (per_cu * t.per_kt - t.per_kt_alone) * (rest - 1) / std::max(1, per_cu - 1)) + t.fixed;
+  us = std::max(us, 2.5 + (double)n_tiles * k_tiles * 1024 / 6.0e6);
+  return us + (double)M * n_tiles * 64 * z / 6.0e6;
+}
+
+// tile shape and number of K splits with the lowest expected cost
+GemmPlan gemm_plan_tiled(int M, int N, int K, int epi, int max_splits) {
+  // decode steps ask for the same few plans layer after layer
+  struct Key {
+    int M, N, K, epi, max_splits;
+    GemmPlan plan;
+  };
+  static thread_local Key cache[64] = {};
+  Key& k = cache[((unsigned)M * 31u + (unsigned)N * 7u + (unsigned)K * 3u + epi) & 63u];
+  if (k.M == M && k.N == N && k.K == K && k.epi == epi && k.max_splits == max_splits) return k.plan;
+  const int n_tiles = N >> 4, k_tiles = K >> 5;
+  GemmPlan pl{};
+  pl.kind = 1;
+  double best = 1e29;
+  for (int c = 0; c < (int)(sizeof(kTileShapes) / sizeof(kTileShapes[0])); ++c) {
+    const TileShape& t = kTileShapes[c];
+    if (epi == EPI_LSE && t.wn * t.nt < kLseMinTile) continue;
+    static const int zs[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16};
+    for (int z : zs) {
+      if (z > 1 && (epi != EPI_F32 || z > max_splits || z * 6 > k_tiles)) break;
+      const double us = tile_cost(t, M, n_tiles, k_tiles, z);
+      if (us < best) {
+        best = us;
+        pl.shape = c;
+        pl.nt = t.wn * t.nt;
+        pl.splits = z;
+        pl.name = t.name[epi == EPI_F32 ? 0 : epi == EPI_SWIGLU_BF16 ? 1 : 2];
+      }
+    }
   }
-  if (epi == EPI_F32 && blocks < 256) {
-    int z = (int)((768 + blocks - 1) / blocks);
-    z = std::min(z, std::max(1, k_tiles / 8));
-    pl.splits = std::max(1, std::min(z, max_splits));
-  }
-  pl.name = names[pick][epi == EPI_F32 ? 0 : epi == EPI_SWIGLU_BF16 ? 1 : 2];
-  // SwiGLU projection (no split-K possible) of at most 128 rows, when 64-row blocks give fewer
-  // than two workgroups per CU: 32-row blocks give the chip twice the workgroups - one or two
-  // 64-row blocks leave CUs idle or with one long workgroup
-  if (pick == 1 && epi == EPI_SWIGLU_BF16 && M <= 128 && blocks < 512) {
-    pl.mt = 2;
-    pl.name = "gemm_tile_ring_kernel<2,2,2,1,1>";
-  }
-  if (pick == 1 && epi == EPI_F32 && pl.mt == 2) pl.name = "gemm_tile_ring_kernel<2,2,2,1,0>";
+  k = Key{M, N, K, epi, max_splits, pl};
   return pl;
+}
+
+// the grouped (per-expert) launches: row blocks of 32, 64 or 128 rows (moe_block_rows), all with 128 columns
+GemmPlan gemm_plan_grouped(int epi, int block_rows) {
+  GemmPlan pl{};
+  pl.kind = 1;
+  pl.shape = block_rows == 32 ? 0 : block_rows == 64 ? 1 : 7;
+  const TileShape& t = kTileShapes[pl.shape];
+  pl.nt = t.wn * t.nt;
+  pl.splits = 1;
+  pl.name = t.name[epi == EPI_F32 ? 0 : 1];
+  return pl;
+}
+
+static int launch_tile(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s) {
+  const TileShape& t = kTileShapes[pl.shape];
+  const int n_tiles = a.N >> 4, k_tiles = a.K >> 5, bm = t.wm * t.mt * 16;
+  a.k_tiles_per_split = ceil_div(k_tiles, epi == EPI_F32 ? pl.splits : 1);
+  a.grid_nz = ceil_div(k_tiles, a.k_tiles_per_split);
+  a.grid_nx = ceil_div(n_tiles, pl.nt);
+  a.grid_ny = a.group_of_block ? a.n_row_blocks : ceil_div(a.M, bm);
+  if (a.group_of_block) {  // an expert's few row blocks follow each other: its weights are fetched once
+    a.group_m = std::min(a.grid_ny, 16);
+    a.group_n = 1;
+  } else {
+    tile_groups(a.grid_ny, a.grid_nx, a.grid_nz, a.group_m, a.group_n);
+  }
+  const long long units = (long long)ceil_div(a.grid_ny, a.group_m) * ceil_div(a.grid_nx, a.group_n) * a.grid_nz;
+  const dim3 grid((unsigned)(ceil_div(units, 8) * 8 * a.group_m * a.group_n));
+  const bool gather = a.row_map != nullptr;
+  switch (pl.shape) {
+#define X(id, wm, wn, mt, nt, kg, st, minb, ...)                                                                    \
+  case id:                                                                                                           \
+    if (epi == EPI_F32) gemm_tile_kernel<wm, wn, mt, nt, kg, st, minb, EPI_F32, false><<<grid, wm * wn * kg * 64, 0, s>>>(a); \
+    else if (epi == EPI_LSE) /* never planned with fewer than kLseMinTile column tiles */                             \
+      gemm_tile_kernel<wm, wn, mt, nt, kg, st, minb, wn * nt >= kLseMinTile ? EPI_LSE : EPI_F32, false><<<grid, wm * wn * kg * 64, 0, s>>>(a); \
+    else if (grouped_shape(id) && gather)                                                                             \
+      gemm_tile_kernel<wm, wn, mt, nt, kg, st, minb, EPI_SWIGLU_BF16, grouped_shape(id)><<<grid, wm * wn * kg * 64, 0, s>>>(a); \
+    else gemm_tile_kernel<wm, wn, mt, nt, kg, st, minb, EPI_SWIGLU_BF16, false><<<grid, wm * wn * kg * 64, 0, s>>>(a); \
+    break;
+    TILE_SHAPES(X)
+#undef X
+  }
+  return a.grid_nz;
 }
 
 GemmPlan gemm_plan(int M, int N, int K, int epi, int max_splits) {
@@ -754,20 +739,6 @@ GemmPlan gemm_plan(int M, int N, int K, int epi, int max_splits) {
   return pl;
 }
 
-template <int MT, int NT, int KC, int R>
-static void launch_tile(const GemmArgs& a, int epi, dim3 grid, hipStream_t s) {
-  if (epi == EPI_F32) gemm_tile_kernel<MT, NT, KC, R, EPI_F32><<<grid, 256, 0, s>>>(a);
-  else if (epi == EPI_SWIGLU_BF16) gemm_tile_kernel<MT, NT, KC, R, EPI_SWIGLU_BF16><<<grid, 256, 0, s>>>(a);
-  else gemm_tile_kernel<MT, NT, KC, R, EPI_LSE><<<grid, 256, 0, s>>>(a);
-}
-
-template <int MT, int NT, int KC, int D>
-static void launch_tile_ring(const GemmArgs& a, int epi, dim3 grid, hipStream_t s) {
-  if (epi == EPI_F32) gemm_tile_ring_kernel<MT, NT, KC, D, EPI_F32><<<grid, 256, 0, s>>>(a);
-  else if (epi == EPI_SWIGLU_BF16) gemm_tile_ring_kernel<MT, NT, KC, D, EPI_SWIGLU_BF16><<<grid, 256, 0, s>>>(a);
-  else gemm_tile_ring_kernel<MT, NT, KC, D, EPI_LSE><<<grid, 256, 0, s>>>(a);
-}
-
 template <int MT, int KU>
 static void launch_stream_mt(const GemmArgs& a, int epi, const GemmPlan& pl, dim3 grid, hipStream_t s) {
   if (pl.nt == 1 && pl.nw == 4) launch_stream<MT, 1, KU, 4>(a, epi, grid, s);
@@ -779,23 +750,7 @@ static void launch_stream_mt(const GemmArgs& a, int epi, const GemmPlan& pl, dim
 int launch_gemm_bf16(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s) {
   if (a.M < 1 || a.N < 16) return 0;
   const int n_tiles = a.N >> 4, k_tiles = a.K >> 5;
-  if (pl.kind == 1) {
-    int per = ceil_div(ceil_div(k_tiles, epi == EPI_F32 ? pl.splits : 1), 2) * 2;
-    const int splits = ceil_div(k_tiles, per);
-    a.k_tiles_per_split = per;
-    const int m_blocks = a.group_of_block ? a.n_row_blocks : ceil_div(a.M, 16 * pl.mt);
-    a.grid_nx = ceil_div(n_tiles, 4 * pl.nt);
-    a.grid_ny = m_blocks;
-    a.grid_nz = splits;
-    const int gm = std::min(a.grid_ny, 16);
-    const long long units = (long long)a.grid_nx * a.grid_nz * ceil_div(a.grid_ny, gm);
-    dim3 grid((unsigned)(ceil_div(units, 8) * 8 * gm));
-    if (pl.nt == 4) launch_tile<4, 4, 2, 2>(a, epi, grid, s);
-    else if (pl.mt == 2 && epi == EPI_SWIGLU_BF16) gemm_tile_ring_kernel<2, 2, 2, 1, EPI_SWIGLU_BF16><<<grid, 256, 0, s>>>(a);
-    else if (pl.mt == 2 && epi == EPI_F32) gemm_tile_ring_kernel<2, 2, 2, 1, EPI_F32><<<grid, 256, 0, s>>>(a);
-    else launch_tile_ring<4, 2, 2, 1>(a, epi, grid, s);
-    return splits;
-  }
+  if (pl.kind == 1) return launch_tile(a, epi, pl, s);
   int per = ceil_div(k_tiles, epi == EPI_F32 ? pl.splits : 1);
   const int splits = ceil_div(k_tiles, per);
   a.k_tiles_per_split = per;
@@ -843,38 +798,38 @@ void launch_lse_finish(const float* lse_max, const float* lse_sum, const float* 
 }
 
 // ---------------------------------------------------------------- weight re-ordering
-// dst tile (tile_offset + nt * tile_stride) <- rows nt*16.. of src [N][K] (row-major bf16).
+// Rows of src [N][K] (row-major bf16) -> fragments; `half` as in launch_pack_weight.
 // A wavefront moves 8 rows x 128 bytes - two k-tiles of half a row tile - so that both its
 // reads and its writes are whole cache lines (lane = row * 8 + chunk; chunk = k-tile * 4 +
 // column group; the 8 rows of one chunk land in 8 consecutive 16-byte slots of a fragment).
 // An odd last k-tile is moved as 16 rows x 64 bytes by the first 64 lanes' worth of pieces.
 __global__ void pack_weight_kernel(const uint16_t* __restrict__ src, uint4* __restrict__ dst, int N, int K,
-                                   int tile_offset, int tile_stride) {
+                                   int tile_offset, int half) {
   const int k_tiles = K >> 5, k_pairs = k_tiles >> 1;
   const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;  // one 16-byte piece each
   const long long paired = (long long)(N >> 4) * k_pairs * 128;
+  int n, kt, g;  // source row, k-tile, column group
   if (idx < paired) {
-    const int lane = (int)(idx & 63);
-    long long t = idx >> 6;
-    const int half = (int)(t & 1);
-    t >>= 1;
-    const int kp = (int)(t % k_pairs), nt = (int)(t / k_pairs);
-    const int r = half * 8 + (lane >> 3), chunk = lane & 7;
-    const int kt = 2 * kp + (chunk >> 2), g = chunk & 3;
-    const uint4 v = *(const uint4*)(src + (long long)(nt * 16 + r) * K + kt * 32 + g * 8);
-    dst[((long long)(tile_offset + nt * tile_stride) * k_tiles + kt) * 64 + g * 16 + r] = v;
-    return;
+    const int lane = (int)(idx & 63), chunk = lane & 7;
+    const long long t = idx >> 7;
+    n = (int)(t / k_pairs) * 16 + (int)((idx >> 6) & 1) * 8 + (lane >> 3);
+    kt = 2 * (int)(t % k_pairs) + (chunk >> 2);
+    g = chunk & 3;
+  } else {
+    if (!(k_tiles & 1)) return;
+    const long long rest = idx - paired;  // the odd last k-tile of every row tile
+    if (rest >= (long long)(N >> 4) * 64) return;
+    const int lane = (int)(rest & 63);
+    n = (int)(rest >> 6) * 16 + (lane & 15);
+    kt = k_tiles - 1;
+    g = lane >> 4;
   }
-  if (!(k_tiles & 1)) return;
-  const long long rest = idx - paired;  // the odd last k-tile of every row tile
-  if (rest >= (long long)(N >> 4) * 64) return;
-  const int lane = (int)(rest & 63), nt = (int)(rest >> 6), kt = k_tiles - 1;
-  const int r = lane & 15, g = lane >> 4;
-  const uint4 v = *(const uint4*)(src + (long long)(nt * 16 + r) * K + kt * 32 + g * 8);
-  dst[((long long)(tile_offset + nt * tile_stride) * k_tiles + kt) * 64 + lane] = v;
+  const uint4 v = *(const uint4*)(src + (long long)n * K + kt * 32 + g * 8);
+  const int tile = half < 0 ? tile_offset + (n >> 4) : n >> 3, col = half < 0 ? n & 15 : half * 8 + (n & 7);
+  dst[((long long)tile * k_tiles + kt) * 64 + g * 16 + col] = v;
 }
-void launch_pack_weight(const void* src, void* dst, int N, int K, int tile_offset, int tile_stride, hipStream_t s) {
+void launch_pack_weight(const void* src, void* dst, int N, int K, int tile_offset, int half, hipStream_t s) {
   long long total = (long long)(N >> 4) * (K >> 5) * 64;
   if (total) pack_weight_kernel<<<ceil_div(total, 256), 256, 0, s>>>((const uint16_t*)src, (uint4*)dst, N, K,
-                                                                      tile_offset, tile_stride);
+                                                                      tile_offset, half);
 }

@@ -87,7 +87,7 @@ __global__ __launch_bounds__(1024) void moe_plan_kernel(MoePlanArgs a) {
     int s = 0, b = 0;
     for (int e = 0; e < t; ++e) {
       s += cnt[e];
-      b += (cnt[e] + kMoeBlockRows - 1) / kMoeBlockRows;
+      b += (cnt[e] + a.block_rows - 1) / a.block_rows;
     }
     start[t] = s;
     block0[t] = b;
@@ -95,10 +95,10 @@ __global__ __launch_bounds__(1024) void moe_plan_kernel(MoePlanArgs a) {
   __syncthreads();
   if (t < a.n_experts) {
     const int n = cnt[t];
-    for (int b = block0[t], r0 = 0; r0 < n; ++b, r0 += kMoeBlockRows) {
+    for (int b = block0[t], r0 = 0; r0 < n; ++b, r0 += a.block_rows) {
       a.group_of_block[b] = t;
       a.block_row_begin[b] = start[t] + r0;
-      a.block_row_end[b] = start[t] + min(n, r0 + kMoeBlockRows);
+      a.block_row_end[b] = start[t] + min(n, r0 + a.block_rows);
     }
   }
   for (int b = block0[a.n_experts] + t; b < a.max_blocks; b += 1024) {

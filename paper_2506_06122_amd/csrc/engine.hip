@@ -462,9 +462,6 @@ static void embed_and_norm(rollout_ctx& c, int R) {
   c.timer.end(c.stream);
 }
 
-// KV splits per (sample, KV head) of a decode step: one workgroup per CU, at least 256 cached
-// positions each, at most the 16 the merge kernels take.  (Measured: more, shorter splits lose
-// to the per-workgroup prologue and the longer merge.)
 // The second launch of a decode attention whose rows have several partial results: joins the
 // slots of every (row, KV head).  Timed under its own name; bytes = the slots read (output
 // fragments, maxima and sums) and the rows written as two bf16 planes.
@@ -476,8 +473,24 @@ static void merge_attention_slots(rollout_ctx& c, const AttnArgs& at, int rows) 
   c.timer.end(c.stream);
 }
 
-static int decode_attention_splits(const rollout_ctx& c, int base) {
-  return std::max(1, std::min({ceil_div(256, base), ceil_div(c.decode_max_ctx, 256), c.attn_max_parts / base, 16}));
+// How the cached positions of a decode step's `rows` rows are cut: wavefronts per workgroup and KV splits
+// per (row, KV head), at most the 16 the merge kernel takes.  A round of a workgroup (32 positions per
+// wavefront) takes about 1.5 us, a merge launch as much as three rounds, so a split has to save more
+// rounds than that.
+static void plan_decode_attention(const rollout_ctx& c, int rows, AttnArgs& at) {
+  const int base = rows * c.geom.n_kv_heads;
+  at.wide = base <= 256;
+  const int round = at.wide ? 256 : 128;
+  const int most = std::max(1, std::min({ceil_div(256, base), ceil_div(c.decode_max_ctx, 256), c.attn_max_parts / base, 16}));
+  const int whole = ceil_div(c.decode_max_ctx, round), cut = ceil_div(c.decode_max_ctx, round * most);
+  const int n = whole - cut > 3 ? most : 1;
+  at.split_tokens = ceil_div(ceil_div(c.decode_max_ctx, n), 128) * 128;
+  at.n_splits = ceil_div(c.decode_max_ctx, at.split_tokens);
+}
+static const char* decode_attention_name(const AttnArgs& at) {
+  static const char* const names[2][2] = {{"attn_decode_fused_kernel<false,4>", "attn_decode_fused_kernel<false,8>"},
+                                          {"attn_decode_fused_kernel<true,4>", "attn_decode_fused_kernel<true,8>"}};
+  return names[at.extra.bias || at.extra.q_gain ? 1 : 0][at.wide ? 1 : 0];
 }
 
 // Mixture-of-experts feed-forward block: router projection -> top-k routing -> plan of the
@@ -690,11 +703,8 @@ static void forward_rows_tiled(rollout_ctx& c, int R, const SeqBatch* seqs) {
         c.timer.end(s);
         merge_attention_slots(c, at, Bd);
       } else {
-        const int n_splits = decode_attention_splits(c, base);
-        at.split_tokens = ceil_div(ceil_div(c.decode_max_ctx, n_splits), 128) * 128;
-        at.n_splits = ceil_div(c.decode_max_ctx, at.split_tokens);
-        c.timer.begin(at.extra.bias || at.extra.q_gain ? "attn_decode_fused_kernel<true>" : "attn_decode_fused_kernel<false>",
-                      kv_bytes + qo_bytes, c.attn_flops_this_call, s);
+        plan_decode_attention(c, Bd, at);
+        c.timer.begin(decode_attention_name(at), kv_bytes + qo_bytes, c.attn_flops_this_call, s);
         launch_attention_decode_fused(at, s);
         c.timer.end(s);
         if (at.n_splits > 1) merge_attention_slots(c, at, Bd);
@@ -832,14 +842,11 @@ static void forward_rows_decode(rollout_ctx& c, int R) {
     at.qkv_planes = 1;
     at.cos_sin = c.cos_sin.p;
     at.extra = QkvExtras{L.qkv_bias.p, L.q_gain.p, L.k_gain.p, m.rms_eps};
-    const int base = R * m.n_kv_heads;
-    const int n_splits = decode_attention_splits(c, base);
-    at.split_tokens = ceil_div(ceil_div(c.decode_max_ctx, n_splits), 128) * 128;
-    at.n_splits = ceil_div(c.decode_max_ctx, at.split_tokens);
+    plan_decode_attention(c, R, at);
     at.part_o = c.attn_part_o.p;
     at.part_ml = c.attn_part_ml.p;
     // every cached key and value once (a shared prompt once for all its samples), q in, out
-    c.timer.begin(at.extra.bias || at.extra.q_gain ? "attn_decode_fused_kernel<true>" : "attn_decode_fused_kernel<false>",
+    c.timer.begin(decode_attention_name(at),
                   c.kv_unique_tokens_this_call * (double)m.n_kv_heads * 128 * 2 * 2 + (double)R * (4.0 * c.qkv_dim + 4.0 * c.q_dim),
                   c.attn_flops_this_call, s);
     launch_attention_decode_fused(at, s);

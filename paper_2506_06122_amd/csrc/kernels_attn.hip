@@ -15,7 +15,7 @@
 //
 //   decode  : one workgroup per (KV split, KV head, sample); columns = the G query heads;
 //             the rotary embedding of the new query and key and the KV-page write ride in
-//             the prologue; its 4 wavefronts interleave over the split's 32-position groups
+//             the prologue; its 4 or 8 wavefronts interleave over the split's 32-position groups
 //             and merge through LDS; several splits per sample merge in a second small kernel.
 //   decode, shared prompts (optional): in the same launch, workgroups of (split, KV head, up
 //             to 4 samples of one prompt) take the prompt's shared pages with the members'
@@ -162,10 +162,10 @@ struct DecodeSmem {
   uint16_t* q;   // [2][q_cols][DH] hi parts, lo parts
   int q_cols;
   uint16_t* kv;  // [2][DH]
-  float* m;      // [4][ml_cols]
-  float* l;      // [4][ml_cols]
+  float* m;      // [NW][ml_cols], NW = wavefronts of the workgroup
+  float* l;      // [NW][ml_cols]
   int ml_cols;
-  float* o;      // [4][16 * DH]
+  float* o;      // [NW][16 * DH]
 };
 
 // elements p[0] and p[64] summed over the split-K planes in ascending order, eight planes'
@@ -232,19 +232,19 @@ __device__ __forceinline__ void sum_query_planes(const AttnArgs& a, const float*
   }
 }
 
-// Query staging.  Thread t of the workgroup owns the rotary pairs idx = t + 256 n, n < N:
+// Query staging.  Thread t of the workgroup owns the rotary pairs idx = t + 64 NW n, n < N:
 // column idx / 64 (the same in all 64 lanes), pair idx % 64.  rows[n] / heads[n] name the
 // sample row and the query head inside its KV group that column holds (row < 0: the column
 // is empty).  x0 / x1: the projection's elements, planes summed; cs: cos, sin of the row's position.
 // Bias / head norm, the rotary embedding, and the hi + lo half-precision parts into sm.q.
-template <bool EXTRA, int N>
+template <bool EXTRA, int N, int NW>
 __device__ __forceinline__ void rotate_and_stage(const AttnArgs& a, const DecodeSmem& sm, int kvh, int G,
                                                  const int (&rows)[N], const int (&heads)[N], float (&x0)[N],
                                                  float (&x1)[N], const float2 (&cs)[N]) {
   const int tid = threadIdx.x, i = tid & 63;
 #pragma unroll
   for (int n = 0; n < N; ++n) {
-    const int col = (tid + 256 * n) >> 6;
+    const int col = (tid >> 6) + NW * n;
     float u = 0.f, w = 0.f;
     if (rows[n] >= 0) {  // uniform over the wavefront
       if (EXTRA) qkv_extras(a.extra, (kvh * G + heads[n]) * DH, i, a.extra.q_gain, x0[n], x1[n]);
@@ -274,22 +274,31 @@ __device__ __forceinline__ void stage_queries(const AttnArgs& a, const DecodeSme
     cs[n] = *(const float2*)(a.cos_sin + (long long)a.row_pos[b] * DH + 2 * i);
   }
   sum_query_planes<N>(a, src, x0, x1);
-  rotate_and_stage<EXTRA, N>(a, sm, kvh, G, rows, heads, x0, x1, cs);
+  rotate_and_stage<EXTRA, N, 4>(a, sm, kvh, G, rows, heads, x0, x1, cs);
 }
 
-// the 4 wavefronts' results of 16 columns -> one (max, sum, unnormalised output) per column in
-// sm.o[0..3], sm.m, sm.l (columns ml0 ..); every thread of the workgroup calls it
+// the NW wavefronts' results of 16 columns -> one (max, sum, unnormalised output) per column in
+// sm.o[0..NW-1], sm.m, sm.l (columns ml0 ..); every thread of the workgroup calls it
+template <int NW>
 __device__ __forceinline__ float merged_max(const DecodeSmem& sm, int col) {
-  return fmaxf(fmaxf(sm.m[col], sm.m[sm.ml_cols + col]), fmaxf(sm.m[2 * sm.ml_cols + col], sm.m[3 * sm.ml_cols + col]));
+  float m = sm.m[col];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) m = fmaxf(m, sm.m[w * sm.ml_cols + col]);
+  return m;
 }
+template <int NW>
 __device__ __forceinline__ float merged_sum(const DecodeSmem& sm, int col) {
-  return sm.l[col] + sm.l[sm.ml_cols + col] + sm.l[2 * sm.ml_cols + col] + sm.l[3 * sm.ml_cols + col];
+  float l = sm.l[col];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) l += sm.l[w * sm.ml_cols + col];
+  return l;
 }
+template <int NW>
 __device__ __forceinline__ void merge_wavefronts(const DecodeSmem& sm, int ml0, float m, float l, const f32x4 (&o)[8],
                                                  int wave, int c, int g) {
   if (g == 0) sm.m[wave * sm.ml_cols + ml0 + c] = m;
   __syncthreads();
-  const float M = merged_max(sm, ml0 + c);
+  const float M = merged_max<NW>(sm, ml0 + c);
   const float M_use = (M == -INFINITY) ? 0.f : M;
   const float w = exp2f(m - M_use);
   if (g == 0) sm.l[wave * sm.ml_cols + ml0 + c] = l * w;
@@ -300,17 +309,21 @@ __device__ __forceinline__ void merge_wavefronts(const DecodeSmem& sm, int ml0, 
   __syncthreads();
 }
 // element e of the merged, unnormalised output: the wavefronts' parts in ascending order
+template <int NW>
 __device__ __forceinline__ float merged_out(const DecodeSmem& sm, int e) {
-  return sm.o[e] + sm.o[16 * DH + e] + sm.o[2 * 16 * DH + e] + sm.o[3 * 16 * DH + e];
+  float v = sm.o[e];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) v += sm.o[w * (16 * DH) + e];
+  return v;
 }
 
-// one workgroup = (own-range split, KV head, sample); wavefront w takes the groups w, w + 4, ...
+// one workgroup = (own-range split, KV head, sample); wavefront w takes the groups w, w + NW, ...
 // of the split.  What the workgroup needs before its main loop comes in three sets of loads:
 // (1) the row's position and page-table row, and - they depend on neither - every split-K plane
 // of its query columns and of the new key and value; (2) what depends on the position: cos and
 // sin, the page of the new position and the page of the wavefront's first group; (3) that
 // group's keys and values, in flight while the queries are rotated and staged.
-template <bool EXTRA>
+template <bool EXTRA, int NW>
 __device__ __forceinline__ void decode_own_range(const AttnArgs& a, const DecodeSmem& sm, int split, int kvh, int b) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 15, g = lane >> 4, i = lane;
@@ -323,12 +336,13 @@ __device__ __forceinline__ void decode_own_range(const AttnArgs& a, const Decode
   const int q_dim = a.n_q_heads * DH, kv_dim = n_kv * DH;
   const float* row = a.qkv_raw + (long long)b * (q_dim + 2 * kv_dim);
   // ---- first set of loads (does not wait for the position)
-  int rows[4], heads[4];
-  const float* src[4];
-  float x0[4], x1[4];
+  constexpr int N = 16 / NW;  // columns of this wavefront
+  int rows[N], heads[N];
+  const float* src[N];
+  float x0[N], x1[N];
 #pragma unroll
-  for (int n = 0; n < 4; ++n) {
-    heads[n] = wave + 4 * n;  // column = head inside the KV group
+  for (int n = 0; n < N; ++n) {
+    heads[n] = wave + NW * n;  // column = head inside the KV group
     rows[n] = heads[n] < G ? b : -1;
     heads[n] = min(heads[n], G - 1);
     src[n] = row + (kvh * G + heads[n]) * DH + i;
@@ -338,7 +352,7 @@ __device__ __forceinline__ void decode_own_range(const AttnArgs& a, const Decode
   const bool is_v = wave & 1;
   float n0, n1;
   sum_planes(a, row + q_dim + (is_v ? kv_dim : 0) + kvh * DH + i, n0, n1);
-  sum_query_planes<4>(a, src, x0, x1);
+  sum_query_planes<N>(a, src, x0, x1);
   const int used = (pos - t0) / a.split_tokens + 1;  // splits that hold at least the new position
   if (split >= used) return;
   const bool owner = split == used - 1;
@@ -357,8 +371,10 @@ __device__ __forceinline__ void decode_own_range(const AttnArgs& a, const Decode
   if (tok0 < t_end)
     load_group(page_block(a, first_page, kvh, tok0, 0), page_block(a, first_page, kvh, tok0, 1), k, v, lane);
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)DH);
-  const float2 cs[4] = {rot, rot, rot, rot};
-  rotate_and_stage<EXTRA, 4>(a, sm, kvh, G, rows, heads, x0, x1, cs);
+  float2 cs[N];
+#pragma unroll
+  for (int n = 0; n < N; ++n) cs[n] = rot;
+  rotate_and_stage<EXTRA, N, NW>(a, sm, kvh, G, rows, heads, x0, x1, cs);
   if (writer) {
     const int tok = pos % T;
     if (!is_v) {
@@ -393,12 +409,12 @@ __device__ __forceinline__ void decode_own_range(const AttnArgs& a, const Decode
   for (int j = 0; j < 8; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (tok0 < t_end) {  // the group that is in registers already
     attend_frags(k, v, q, tok0, pos - 1, scale_log2, m, l, o, lane);
-    tok0 += 128;
+    tok0 += 32 * NW;
   }
-  for (; tok0 < t_end; tok0 += 128)
+  for (; tok0 < t_end; tok0 += 32 * NW)
     attend_group(group_block(a, slot, kvh, tok0, 0), group_block(a, slot, kvh, tok0, 1), q, tok0, pos - 1,
                  scale_log2, m, l, o, lane);
-  if (owner && wave == 3) {  // the new position, from LDS: token 0 of a group that starts at pos
+  if (owner && wave == NW - 1) {  // the new position, from LDS: token 0 of a group that starts at pos
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       k[0][ks].u = make_uint4(0, 0, 0, 0);
@@ -413,28 +429,31 @@ __device__ __forceinline__ void decode_own_range(const AttnArgs& a, const Decode
     attend_frags(k, v, q, pos, pos, scale_log2, m, l, o, lane);
   }
 
-  merge_wavefronts(sm, 0, m, l, o, wave, c, g);
+  merge_wavefronts<NW>(sm, 0, m, l, o, wave, c, g);
   const int n_slots = a.n_slots ? a.n_slots : a.n_splits;
   const long long part = ((long long)b * n_kv + kvh) * n_slots + a.slot0 + split;
-  for (int e = tid; e < G * DH; e += 256) {
+  for (int e = tid; e < G * DH; e += 64 * NW) {
     const int col = e >> 7;
-    const float acc = merged_out(sm, e);
-    if (direct) store1_split(a.out + out_offset(a, b, kvh * G * DH + e), a.out_lo_offset, acc / (merged_sum(sm, col) * P_SCALE));
+    const float acc = merged_out<NW>(sm, e);
+    if (direct) store1_split(a.out + out_offset(a, b, kvh * G * DH + e), a.out_lo_offset, acc / (merged_sum<NW>(sm, col) * P_SCALE));
     else a.part_o[part * (16 * DH) + e] = acc;
   }
   if (!direct && tid < 16) {
-    a.part_ml[part * 32 + tid] = merged_max(sm, tid);
-    a.part_ml[part * 32 + 16 + tid] = merged_sum(sm, tid);
+    a.part_ml[part * 32 + tid] = merged_max<NW>(sm, tid);
+    a.part_ml[part * 32 + 16 + tid] = merged_sum<NW>(sm, tid);
   }
 }
 
-template <bool EXTRA>
-__global__ __launch_bounds__(256, 3) void attn_decode_fused_kernel(AttnArgs a) {
+// NW = 4: three workgroups per CU (registers capped at 168), for launches that fill the chip.  NW = 8: a
+// workgroup has a CU to itself and covers 256 positions per round, for the steps whose (sample, KV head)
+// pairs are fewer than the CUs.
+template <bool EXTRA, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void attn_decode_fused_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t q_s[2 * 16 * DH];
   __shared__ __attribute__((aligned(16))) uint16_t kv_s[2 * DH];
-  __shared__ float m_s[4 * 16], l_s[4 * 16];
-  __shared__ float o_s[4 * 16 * DH];
-  decode_own_range<EXTRA>(a, DecodeSmem{q_s, 16, kv_s, m_s, l_s, 16, o_s}, blockIdx.x, blockIdx.y, blockIdx.z);
+  __shared__ float m_s[NW * 16], l_s[NW * 16];
+  __shared__ float o_s[NW * 16 * DH];
+  decode_own_range<EXTRA, NW>(a, DecodeSmem{q_s, 16, kv_s, m_s, l_s, 16, o_s}, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // ------------------------------------------------------------------------------ shared prompts
@@ -490,7 +509,7 @@ __device__ __forceinline__ void decode_shared_range(const AttnArgs& a, const Dec
     for (int tok0 = t_begin + wave * 32; tok0 < t_end; tok0 += 128)
       attend_group(group_block(a, slot, kvh, tok0, 0), group_block(a, slot, kvh, tok0, 1), q, tok0, 0x7fffffff,
                    scale_log2, m, l, o, lane);
-    merge_wavefronts(sm, ct * 16, m, l, o, wave, c, g);
+    merge_wavefronts<4>(sm, ct * 16, m, l, o, wave, c, g);
     for (int e = tid; e < 16 * DH; e += 256) {
       const int col = ct * 16 + (e >> 7);
       const int j = col / G, hc = col % G;
@@ -506,8 +525,8 @@ __device__ __forceinline__ void decode_shared_range(const AttnArgs& a, const Dec
       const int b = j < GROUP_MEMBERS ? members[j] : -1;
       if (b >= 0) {
         const long long part = ((long long)b * n_kv + kvh) * n_slots + split;
-        a.part_ml[part * 32 + hc] = merged_max(sm, col);
-        a.part_ml[part * 32 + 16 + hc] = merged_sum(sm, col);
+        a.part_ml[part * 32 + hc] = merged_max<4>(sm, col);
+        a.part_ml[part * 32 + 16 + hc] = merged_sum<4>(sm, col);
       }
     }
     __syncthreads();  // sm.o is reused by the next tile
@@ -529,7 +548,7 @@ __global__ __launch_bounds__(256, 3) void attn_decode_grouped_kernel(AttnArgs a)
     decode_shared_range<NCT, EXTRA>(a, sm, w % a.n_splits_a, (w / a.n_splits_a) % n_kv, w / (a.n_splits_a * n_kv));
   } else {
     w -= n_shared;
-    decode_own_range<EXTRA>(a, sm, w % a.n_splits, (w / a.n_splits) % n_kv, w / (a.n_splits * n_kv));
+    decode_own_range<EXTRA, 4>(a, sm, w % a.n_splits, (w / a.n_splits) % n_kv, w / (a.n_splits * n_kv));
   }
 }
 
@@ -618,8 +637,14 @@ __global__ __launch_bounds__(256) void attn_merge_fused_kernel(AttnArgs a) {
 void launch_attention_decode_fused(const AttnArgs& a, hipStream_t s) {
   if (!a.rows) return;
   const dim3 grid(a.n_splits, a.geom.n_kv_heads, a.rows);
-  if (a.extra.bias || a.extra.q_gain) attn_decode_fused_kernel<true><<<grid, 256, 0, s>>>(a);
-  else attn_decode_fused_kernel<false><<<grid, 256, 0, s>>>(a);
+  const bool extra = a.extra.bias || a.extra.q_gain;
+  if (a.wide) {
+    if (extra) attn_decode_fused_kernel<true, 8><<<grid, 512, 0, s>>>(a);
+    else attn_decode_fused_kernel<false, 8><<<grid, 512, 0, s>>>(a);
+  } else {
+    if (extra) attn_decode_fused_kernel<true, 4><<<grid, 256, 0, s>>>(a);
+    else attn_decode_fused_kernel<false, 4><<<grid, 256, 0, s>>>(a);
+  }
 }
 void launch_attention_merge(const AttnArgs& a, hipStream_t s) {
   if (a.rows) attn_merge_fused_kernel<<<dim3(a.geom.n_kv_heads, a.rows), 256, 0, s>>>(a);

@@ -218,6 +218,7 @@ struct AttnArgs {
   const int *row_pos, *row_slot;
   int rows;
   int n_splits, split_tokens;      // KV range per workgroup (multiple of 128)
+  bool wide = false;               // decode: workgroups of 8 wavefronts instead of 4
   float* part_o;                   // [rows][n_kv_heads][n_slots][16][128]
   float* part_ml;                  // [rows][n_kv_heads][n_slots][2][16]
   int n_slots = 0;                 // partial results per (row, KV head); the launcher sets n_splits when 0

@@ -401,7 +401,7 @@ static void forward_rows_simple(rollout_ctx& c, int R) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Matrix-core path, many rows (prefill, teacher-forced pass, decode steps with more than 32
+// Matrix-core path, many rows (prefill, teacher-forced pass, decode steps with more than 16
 // live samples).  Per layer: QKV projection -> sum + rotary + KV-page write -> paged
 // attention -> O projection -> residual + norm -> gate/up projection with SwiGLU in the
 // epilogue -> down projection -> residual + next norm.
@@ -736,7 +736,7 @@ static void forward_rows_tiled(rollout_ctx& c, int R, const SeqBatch* seqs) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Matrix-core path, one decode step with at most 32 live samples: five launches per layer
+// Matrix-core path, one decode step with at most 16 live samples: five launches per layer
 // (six when attention is split over the cached positions).
 //   QKV projection -> fused attention (rotary, KV-page write, paged attention) -> O projection
 //   with the residual add -> gate/up projection with SwiGLU -> down projection with the
@@ -866,7 +866,7 @@ void engine_forward_rows(rollout_ctx& c, int rows, const SeqBatch* seqs) {
   if (rows < 1) return;
   c.last_route_rows = rows;
   if (!c.simple) {
-    if (!seqs && rows <= 32 && !c.md.n_experts)
+    if (!seqs && rows <= kStreamRows && !c.md.n_experts)
       forward_rows_decode(c, rows);
     else
       forward_rows_tiled(c, rows, seqs);

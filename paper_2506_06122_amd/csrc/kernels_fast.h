@@ -20,7 +20,7 @@
 //                    turns these into log-probs)
 enum { EPI_F32 = 0, EPI_SWIGLU_BF16 = 1, EPI_RESID = 2, EPI_LSE = 3 };
 
-// Fragment order of an activation plane [rows][K] (decode steps with at most 32 rows): the
+// Fragment order of an activation plane [rows][K] (decode steps with at most 16 rows): the
 // 16-row x 32-deep operand fragment of the 16x16x32 matrix instruction is stored as one
 // contiguous 1 KiB block [lane][8] with lane = (k % 32 / 8) * 16 + row % 16, fragments ordered
 // [row / 16][k / 32].  A wavefront then reads an operand fragment as whole cache lines, as it
@@ -109,10 +109,12 @@ struct GemmArgs {
   int lse_stride = 0;
 };
 
-// How one projection is launched: kind 0 = gemm_stream_kernel (mt row tiles, nt column tiles, nw wavefronts),
-// 1 = gemm_tile_kernel (shape = its entry in the table of shapes, nt = column tiles per workgroup).
+constexpr int kStreamRows = 16;  // rows up to which a decode step streams the weights (gemm_stream_kernel)
+
+// How one projection is launched: kind 0 = gemm_stream_kernel, 1 = gemm_tile_kernel; shape = which of the
+// kernel's configurations, nt = column tiles per workgroup.
 struct GemmPlan {
-  int kind, shape, mt, nt, nw, splits;
+  int kind, shape, nt, splits;
   const char* name;  // kernel name as a profiler shows it (without the argument list)
 };
 GemmPlan gemm_plan(int M, int N, int K, int epi, int max_splits);

@@ -15,10 +15,10 @@
 // exactly, so nothing else is rounded).  That doubles the matrix instructions, which the
 // memory-bound decode step does not notice.
 //
-// Three kernels:
-//   gemm_stream_kernel  (rows <= 32, decoding): the NW wavefronts of a workgroup share NT
+// Two kernels:
+//   gemm_stream_kernel  (rows <= 16, decoding): the NW wavefronts of a workgroup share NT
 //       column tiles and interleave over the K range in chunks of KU fragments, so one
-//       workgroup walks one contiguous weight stream with NW x KU x NT KiB in flight; the
+//       workgroup walks one contiguous weight stream with up to 2 NW x KU x NT KiB in flight; the
 //       partial accumulators meet in LDS.  Activations come straight from L2, stored in
 //       fragment order by their producers (frag_offset, kernels_fast.h) so that an operand
 //       fragment, like a weight fragment, is whole cache lines.  Narrow outputs (few column
@@ -31,10 +31,10 @@
 //           in a fixed order (all its wavefronts share the loads) and scales its output rows
 //           by rsqrt(mean + eps) - a row scale commutes with the projection.  No workgroup
 //           ever waits for another.
-//         - SwiGLU on interleaved gate/up column tiles (EPI_SWIGLU_BF16).
+//         - SwiGLU on column tiles of 8 gates and their 8 ups (EPI_SWIGLU_BF16).
 //       Workgroups past the last column block, if the launcher adds any, walk a later
 //       projection's weights into the memory-side cache (TouchRange, kernels_fast.h).
-//   gemm_tile_kernel    (more than 32 rows: larger decode steps, prefill, the teacher-forced
+//   gemm_tile_kernel    (more than 16 rows: larger decode steps, prefill, the teacher-forced
 //       pass, the experts' grouped projections): output tiles of 32 x 128 up to 128 x 320, both
 //       operands copied straight from memory into a ring of LDS stages.
 #include <cstdio>
@@ -82,142 +82,160 @@ __device__ inline void store_swiglu(const GemmArgs& p, bool valid, int m, int nt
   }
 }
 
-template <int MT, int NT, int KU, int NW, int EPI>
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+// What bounds it: the weight stream from HBM (6.0 TB/s on this chip for one large read), plus about 3 us of
+// launch and latency, plus the activations, which every workgroup reads in full through its CU's
+// L2 path (about 60 GB/s): 64 K bytes of hi and lo parts beside 32 NT K bytes of weights.
+//   - The weights are read once and bypass the caches' retention (non-temporal loads): they do not push the
+//     activations out of L2.
+//   - Two chunks of loads per wavefront: while one is multiplied, the next is in flight.
+//   - Loads are not predicated: k-tiles, rows and columns past the end read the last valid one and are not
+//     multiplied or stored.
+// Measured (4 rows, weights from HBM): gate/up 7B shape (272 MB) 49.3 -> 43.1 us, down 7B (136 MB) 38.3 -> 26.8,
+// gate/up 1.5B (55 MB) 14.1 -> 12.7, down 1.5B (27.5 MB, only 96 column tiles) 13.1 -> 12.0.
+template <int NT, int KU, int NW, int EPI>
 __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
-  static_assert(EPI != EPI_RESID || NT <= 2, "one unit must cover a workgroup's columns");
-  __shared__ float4 red[NW * MT * NT * 64];
-  __shared__ float rs_part[NW * MT * 64];
+  static_assert(NT <= 2 && NT <= NW, "one epilogue unit covers a workgroup's columns");
+  __shared__ float4 red[NW * NT * 64];
+  __shared__ float rs_part[NW * 64];
   if (p.touch.wgs > 0 && (int)blockIdx.x >= p.touch_x0) {  // uniform over the workgroup
-    if (blockIdx.y == 0) touch_range(p.touch, blockIdx.x - p.touch_x0);  // one walk, whatever the row blocks
+    touch_range(p.touch, blockIdx.x - p.touch_x0);
     return;
   }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, g = lane >> 4;
   const int n_tiles = p.N >> 4, k_tiles = p.K >> 5;
   const int nt0 = blockIdx.x * NT;
-  const int m0 = blockIdx.y * (MT * 16);
-  const int kt_begin = blockIdx.z * p.k_tiles_per_split;
+  const int kt_begin = blockIdx.y * p.k_tiles_per_split;
   const int kt_end = min(k_tiles, kt_begin + p.k_tiles_per_split);
-  const uint4* wp = (const uint4*)p.w;
-  const uint16_t* a_base = (const uint16_t*)p.a;
 
-  f32x4 acc[MT][NT];
+  const u32x4* w_src[NT];
 #pragma unroll
-  for (int i = 0; i < MT; ++i)
-#pragma unroll
-    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int j = 0; j < NT; ++j) w_src[j] = (const u32x4*)p.w + (long long)min(nt0 + j, n_tiles - 1) * k_tiles * 64 + lane;
+  // activation fragments of this lane: row r, k = 8 g .. 8 g + 7 of k-tile 0; a k-tile further on is a_step away
+  const int row = min(r, p.M - 1);
+  const u32x4* a_src = (const u32x4*)((const uint16_t*)p.a + (p.frag ? (g * 16 + row) * 8 : plane_offset(row, g * 8, p.K)));
+  const int a_step = p.frag ? 64 : 8;
+  const long long lo_off = ((const uint16_t*)p.a_lo - (const uint16_t*)p.a) >> 3;
 
-  // activation pointers of this lane (row m0 + 16 i + r, k = 8 g .. 8 g + 7 of k-tile 0), or null
-  // past the last row; a k-tile further on is a_kstep elements away
-  const uint16_t* a_row[MT];
+  f32x4 acc[NT];
 #pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    const int m = m0 + i * 16 + r;
-    a_row[i] = m >= p.M ? nullptr
-               : p.frag ? a_base + (((long long)(m >> 4) * k_tiles) << 9) + lane * 8
-                        : a_base + plane_offset(m, g * 8, p.K);
-  }
-  const int a_kstep = p.frag ? 512 : 64;
-  const long long lo_off = (const uint16_t*)p.a_lo - a_base;
+  for (int j = 0; j < NT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // Epilogue unit (one row tile, up to two column tiles) of this wavefront, if it has one.  Its
-  // operands - the input rows' partial sums of squares, the residual values and the gain - are
-  // requested now, so that they arrive while the weights stream.
-  constexpr int NU = NT >= 2 ? NT / 2 : 1;  // units per row tile
-  constexpr int TW = NT >= 2 ? 2 : 1;       // column tiles per unit
-  static_assert(MT * NU <= NW, "at most one epilogue unit per wavefront");
-  const bool has_unit = wave < MT * NU;
-  const int ui = wave / NU, uj = (wave % NU) * TW;
-  const int um = m0 + ui * 16 + r;
-  const bool valid = has_unit && um < p.M && nt0 + uj + TW - 1 < n_tiles;
-  float4 xv[TW], gn[TW];
-  // The input rows' sums of squares come as one partial per workgroup of the producing launch
-  // (hidden/16 of them): every wavefront takes the partials w, w + NW, ... - a lane those of its
-  // group g, for row r of each row tile - so that no wavefront has more than a few loads to wait
-  // for; the shares meet in LDS with the accumulators.
-  float rs_share[MT];
+  u32x4 wf[2][KU][NT], af[2][KU][2];
+  auto load = [&](int kt, u32x4 (&w)[KU][NT], u32x4 (&a)[KU][2]) {
 #pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    rs_share[i] = 0.f;
-    const int m = m0 + i * 16 + r;
-    if (p.rinv_ssq && m < p.M)
-      for (int pp = wave * 4 + g; pp < p.rinv_partials; pp += NW * 4)
-        rs_share[i] += p.rinv_ssq[(long long)pp * p.ssq_stride + m];
-  }
-  if (EPI == EPI_RESID && valid) {
+    for (int kk = 0; kk < KU; ++kk)
 #pragma unroll
-    for (int q = 0; q < TW; ++q) {
-      const int n = (nt0 + uj + q) * 16 + g * 4;
-      xv[q] = *(const float4*)(p.x + (long long)um * p.N + n);
+      for (int j = 0; j < NT; ++j)
+        w[kk][j] = __builtin_nontemporal_load(w_src[j] + (long long)min(kt + kk, kt_end - 1) * 64);
+#pragma unroll
+    for (int kk = 0; kk < KU; ++kk) {
+      const u32x4* at = a_src + (long long)min(kt + kk, kt_end - 1) * a_step;
+      a[kk][0] = at[0];
+      a[kk][1] = at[lo_off];
+    }
+    __builtin_amdgcn_sched_barrier(0);  // all of a chunk's loads leave before the products of the other chunk
+  };
+  auto multiply = [&](int kt, const u32x4 (&w)[KU][NT], const u32x4 (&a)[KU][2]) {
+#pragma unroll
+    for (int kk = 0; kk < KU; ++kk) {
+      const bool on = kt + kk < kt_end;  // a k-tile past the end counts zero
+#pragma unroll
+      for (int plane = 1; plane >= 0; --plane) {  // lo part first, then hi
+        const u32x4 x = on ? a[kk][plane] : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+          acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[kk][j]),
+                                                           __builtin_bit_cast(bf16x8, x), acc[j], 0, 0, 0);
+      }
+    }
+  };
+  // This wavefront's chunks of KU k-tiles: wave, wave + NW, ...  The loop body has no branch: with one, the
+  // compiler waits at every join for loads that only the other path has in flight.
+  constexpr int STEP = NW * KU;
+  int kt = kt_begin + wave * KU;
+  const int chunks = kt < kt_end ? (kt_end - kt + STEP - 1) / STEP : 0;
+  if (chunks > 0) load(kt, wf[0], af[0]);
+
+  // The epilogue belongs to wavefront 0.  Its operands - the input rows' partial sums of squares, the
+  // residual values and the gain - are requested behind the first weights and not waited for before the
+  // end (loads return in order: ahead of the weights, they held the stream back by round trips to memory).
+  // The sums of squares come as one partial per workgroup of the producing launch (hidden/16 of
+  // them): every wavefront takes the partials w, w + NW, ... - a lane those of its group g, for
+  // row r - so that no wavefront has more than a few of them; the shares meet in LDS with the
+  // accumulators.
+  constexpr int RS = EPI == EPI_RESID ? 0 : 8;  // the projections that add to the residual read no norm's input
+  const int n_rs = p.rinv_ssq ? p.rinv_partials : 0;
+  const float* rs_src = (p.rinv_ssq ? p.rinv_ssq : (const float*)p.a) + (p.rinv_ssq ? row : 0);
+  float rs_of[RS + 1];
+#pragma unroll
+  for (int i = 0; i < RS; ++i)  // clamped here, masked where they are summed
+    rs_of[i] = rs_src[(long long)max(min((i * NW + wave) * 4 + g, n_rs - 1), 0) * p.ssq_stride];
+  float4 xv[NT], gn[NT];
+  if (EPI == EPI_RESID) {
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+      const int n = min(nt0 + q, n_tiles - 1) * 16 + g * 4;
+      xv[q] = *(const float4*)(p.x + (long long)row * p.N + n);
       gn[q] = *(const float4*)(p.gain + n);
     }
   }
 
-  for (int kt = kt_begin + wave * KU; kt < kt_end; kt += NW * KU) {
-    Frag b[KU][NT], a[KU][MT], al[KU][MT];
-#pragma unroll
-    for (int kk = 0; kk < KU; ++kk) {
-      const bool live = kt + kk < kt_end;
-#pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        b[kk][j].u = make_uint4(0, 0, 0, 0);
-        if (live && nt0 + j < n_tiles) b[kk][j].u = wp[((long long)(nt0 + j) * k_tiles + kt + kk) * 64 + lane];
-      }
-#pragma unroll
-      for (int i = 0; i < MT; ++i) {
-        a[kk][i].u = make_uint4(0, 0, 0, 0);
-        al[kk][i].u = make_uint4(0, 0, 0, 0);
-        if (live && a_row[i]) {
-          a[kk][i].u = *(const uint4*)(a_row[i] + (kt + kk) * a_kstep);
-          al[kk][i].u = *(const uint4*)(a_row[i] + lo_off + (kt + kk) * a_kstep);
-        }
-      }
+  if (chunks > 0) {
+    for (int left = chunks; left > 2; left -= 2) {
+      load(kt + STEP, wf[1], af[1]);
+      multiply(kt, wf[0], af[0]);
+      load(kt + 2 * STEP, wf[0], af[0]);
+      multiply(kt + STEP, wf[1], af[1]);
+      kt += 2 * STEP;
     }
-#pragma unroll
-    for (int kk = 0; kk < KU; ++kk)
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[kk][j].v, al[kk][i].v, acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[kk][j].v, a[kk][i].v, acc[i][j], 0, 0, 0);
-        }
+    if (chunks & 1) {
+      multiply(kt, wf[0], af[0]);
+    } else {
+      load(kt + STEP, wf[1], af[1]);
+      multiply(kt, wf[0], af[0]);
+      multiply(kt + STEP, wf[1], af[1]);
+    }
   }
 
-  // the wavefronts' partial tiles meet in LDS; units of (one row tile, two column tiles)
+  // the wavefronts' partial tiles meet in LDS
 #pragma unroll
-  for (int i = 0; i < MT; ++i)
+  for (int j = 0; j < NT; ++j) red[(wave * NT + j) * 64 + lane] = make_float4(acc[j][0], acc[j][1], acc[j][2], acc[j][3]);
+  if constexpr (RS > 0) {
+    float rs_share = 0.f;
 #pragma unroll
-    for (int j = 0; j < NT; ++j)
-      red[(wave * MT * NT + i * NT + j) * 64 + lane] = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-  if (p.rinv_ssq) {
-#pragma unroll
-    for (int i = 0; i < MT; ++i) rs_part[(wave * MT + i) * 64 + lane] = rs_share[i];
+    for (int i = 0; i < RS; ++i) rs_share += (i * NW + wave) * 4 + g < n_rs ? rs_of[i] : 0.f;
+    for (int pp = (RS * NW + wave) * 4 + g; pp < n_rs; pp += NW * 4)  // hidden sizes beyond 512 NW
+      rs_share += rs_src[(long long)pp * p.ssq_stride];
+    rs_part[wave * 64 + lane] = rs_share;
   }
   __syncthreads();
-  if (!has_unit) return;
+  if (wave > 0) return;
+  const bool valid = r < p.M;
   f32x4 t[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-  for (int q = 0; q < TW; ++q)
+  for (int q = 0; q < NT; ++q)
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      const float4 v = red[(w * MT * NT + ui * NT + uj + q) * 64 + lane];
+      const float4 v = red[(w * NT + q) * 64 + lane];
       t[q][0] += v.x;
       t[q][1] += v.y;
       t[q][2] += v.z;
       t[q][3] += v.w;
     }
-  if (p.rinv_ssq) {
+  if (RS > 0 && p.rinv_ssq) {
     // second half of the RMSNorm of this projection's input: scale row m by
     // rsqrt(mean(x^2) + eps); the 4 lanes of a row share the partial sums
     float rs = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) rs += rs_part[(w * MT + ui) * 64 + lane];
+    for (int w = 0; w < NW; ++w) rs += rs_part[w * 64 + lane];
     rs += __shfl_xor(rs, 16, WAVE);
     rs += __shfl_xor(rs, 32, WAVE);
     const float rinv = 1.0f / sqrtf(rs / (float)p.K + p.eps);
 #pragma unroll
-    for (int q = 0; q < TW; ++q) {
+    for (int q = 0; q < NT; ++q) {
       t[q][0] *= rinv;
       t[q][1] *= rinv;
       t[q][2] *= rinv;
@@ -226,36 +244,35 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
   }
   if (EPI == EPI_RESID) {
     float ss = 0.f;
-    if (valid) {
 #pragma unroll
-      for (int q = 0; q < TW; ++q) {
-        const int n = (nt0 + uj + q) * 16 + g * 4;
+    for (int q = 0; q < NT; ++q)
+      if (valid && nt0 + q < n_tiles) {
+        const int n = (nt0 + q) * 16 + g * 4;
         float4 x4 = xv[q];
         x4.x += t[q][0];
         x4.y += t[q][1];
         x4.z += t[q][2];
         x4.w += t[q][3];
-        *(float4*)(p.x + (long long)um * p.N + n) = x4;
+        *(float4*)(p.x + (long long)r * p.N + n) = x4;
         ss += x4.x * x4.x + x4.y * x4.y + x4.z * x4.z + x4.w * x4.w;
         uint16_t hi[4], lo[4];
         split_bf16(x4.x * gn[q].x, hi[0], lo[0]);
         split_bf16(x4.y * gn[q].y, hi[1], lo[1]);
         split_bf16(x4.z * gn[q].z, hi[2], lo[2]);
         split_bf16(x4.w * gn[q].w, hi[3], lo[3]);
-        uint16_t* hp = p.h + (p.frag ? frag_offset(um, n, n_tiles >> 1) : (long long)um * p.N + n);
+        uint16_t* hp = p.h + (p.frag ? frag_offset(r, n, n_tiles >> 1) : plane_offset(r, n, p.N));
         *(uint2*)hp = pack4(hi);
         *(uint2*)(hp + p.h_lo_offset) = pack4(lo);
       }
-    }
     ss += __shfl_xor(ss, 16, WAVE);
     ss += __shfl_xor(ss, 32, WAVE);
-    if (g == 0 && um < p.M) p.ssq_out[(long long)blockIdx.x * p.ssq_stride + um] = ss;
+    if (g == 0 && valid) p.ssq_out[(long long)blockIdx.x * p.ssq_stride + r] = ss;
   } else if (EPI == EPI_SWIGLU_BF16) {
-    store_swiglu(p, um < p.M && nt0 + uj < n_tiles, um, nt0 + uj, t[0], t[1], g, TW == 2 && nt0 + uj + 1 < n_tiles);
-  } else if (um < p.M) {
+    store_swiglu(p, valid, r, nt0, t[0], t[1], g, NT == 2 && nt0 + 1 < n_tiles);
+  } else if (valid) {
 #pragma unroll
-    for (int q = 0; q < TW; ++q)
-      if (nt0 + uj + q < n_tiles) store_tile_f32(p, um, nt0 + uj + q, t[q], g, blockIdx.z);
+    for (int q = 0; q < NT; ++q)
+      if (nt0 + q < n_tiles) store_tile_f32(p, r, nt0 + q, t[q], g, blockIdx.y);
   }
 }
 
@@ -289,8 +306,6 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
 // Measured against the kernel it replaced (register-staged, 64 x 256 and 64 x 128 tiles), random
 // operands: 12000 rows x 37888 x 3584 5.53 -> 4.52 ms (720 TFLOP/s, 1440 issued), 1700 x 17920 x
 // 1536 192 -> 157 us, 187 x 17920 x 1536 33 -> 27 us, 64 x 37888 x 3584 70 -> 57 us.
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
 // 16 bytes per lane from base + voff to LDS byte `lds` + 16 * lane.  (The compiler keeps nothing in m0: it sets it
 // right before each instruction of its own that reads it.)  As inline assembly, because the compiler makes every
 // LDS read wait for all copies into LDS that it knows of.
@@ -532,30 +547,14 @@ __global__ __launch_bounds__(WM* WN* KG * 64, MINB) void gemm_tile_kernel(GemmAr
 }
 
 // ------------------------------------------------------------------------------------------
-template <int MT, int NT, int KU, int NW>
+template <int NT, int KU, int NW>
 static void launch_stream(const GemmArgs& a, int epi, dim3 grid, hipStream_t s) {
   if (epi == EPI_F32)
-    gemm_stream_kernel<MT, NT, KU, NW, EPI_F32><<<grid, NW * 64, 0, s>>>(a);
+    gemm_stream_kernel<NT, KU, NW, EPI_F32><<<grid, NW * 64, 0, s>>>(a);
   else if (epi == EPI_SWIGLU_BF16)
-    gemm_stream_kernel<MT, NT, KU, NW, EPI_SWIGLU_BF16><<<grid, NW * 64, 0, s>>>(a);
+    gemm_stream_kernel<NT, KU, NW, EPI_SWIGLU_BF16><<<grid, NW * 64, 0, s>>>(a);
   else
-    gemm_stream_kernel<MT, NT, KU, NW, EPI_RESID><<<grid, NW * 64, 0, s>>>(a);
-}
-
-static const char* stream_name(int mt, int nt, int nw, int epi) {
-  static char names[3][2][2][3][40];
-  static bool init = false;
-  if (!init) {
-    const int mts[3] = {1, 2, 4}, nws[2] = {4, 16};
-    for (int a = 0; a < 3; ++a)
-      for (int b = 0; b < 2; ++b)
-        for (int c = 0; c < 2; ++c)
-          for (int e = 0; e < 3; ++e)
-            snprintf(names[a][b][c][e], 40, "gemm_stream_kernel<%d,%d,%d,%d,%d>", mts[a], b + 1, mts[a] == 4 ? 2 : 4,
-                     nws[c], e);
-    init = true;
-  }
-  return names[mt == 1 ? 0 : mt == 2 ? 1 : 2][nt - 1][nw == 4 ? 0 : 1][epi];
+    gemm_stream_kernel<NT, KU, NW, EPI_RESID><<<grid, NW * 64, 0, s>>>(a);
 }
 
 // The tile kernel's shapes.  per_kt, per_kt_alone: microseconds per k-tile of one workgroup's share
@@ -705,66 +704,50 @@ static int launch_tile(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s) {
   return a.grid_nz;
 }
 
+// At most kStreamRows rows stream the weights: wide outputs with two column tiles and 8 wavefronts per
+// workgroup, narrow ones with 16 wavefronts, so that the K range, not the column count, fills the CUs - one
+// column tile, or two where that still leaves more than a hundred workgroups (the fused QKV projection of
+// 7B-class models: it halves the activation re-reads; the residual epilogue's projections run better with
+// one).  From 17 rows on the activations every workgroup re-reads outweigh the launches the path saves
+// (7B shape, 24 rows: the four projections of a layer 142 us streamed, 104 us as tiles with their two norm launches).
 GemmPlan gemm_plan(int M, int N, int K, int epi, int max_splits) {
-  if (M > 32 || epi == EPI_LSE) return gemm_plan_tiled(M, N, K, epi, max_splits);
+  if (M > kStreamRows || epi == EPI_LSE) return gemm_plan_tiled(M, N, K, epi, max_splits);
+  static const char* const names[3][3] = {
+      {"gemm_stream_kernel<2,2,8,0>", "gemm_stream_kernel<2,2,8,1>", "gemm_stream_kernel<2,2,8,2>"},
+      {"gemm_stream_kernel<2,2,16,0>", "gemm_stream_kernel<2,2,16,1>", "gemm_stream_kernel<2,2,16,2>"},
+      {"gemm_stream_kernel<1,3,16,0>", "gemm_stream_kernel<1,3,16,1>", "gemm_stream_kernel<1,3,16,2>"}};
   GemmPlan pl{};
   const int n_tiles = N >> 4, k_tiles = K >> 5;
   pl.kind = 0;
-  pl.mt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
-  const int m_blocks = ceil_div(M, 16 * pl.mt);
-  // wide outputs: two column tiles and 4 wavefronts per workgroup; narrow outputs: one column
-  // tile and 16 wavefronts, so that the K range, not the column count, fills the CUs
-  const bool wide = (long long)(n_tiles / 2) * m_blocks >= 512;
-  pl.nt = (wide || epi == EPI_SWIGLU_BF16) ? 2 : 1;
-  pl.nw = wide ? 4 : 16;
-  // narrow but not tiny (the fused QKV projection of 7B-class models): two column tiles per
-  // wide workgroup halve the activation re-reads and still leave more than a hundred
-  // workgroups.  (Measured: the residual epilogue's projections run better with one.)
-  if (!wide && epi == EPI_F32 && n_tiles >= 192 && n_tiles % 2 == 0) pl.nt = 2;
-  if (epi == EPI_SWIGLU_BF16 && !wide) pl.nw = 4;
-  // 17-32 rows, narrow output with at most 160 workgroup columns (QKV, and at the 1.5B shape O
-  // and down): two row blocks of the one-row-tile kernel instead of one two-row-tile block -
-  // twice the workgroups on a chip they do not fill, the second block's weights from L2
-  // (measured at 32 rows: down 25 -> 17 us at the 1.5B shape, QKV 22 -> 17 us at 7B; with 224
-  // columns, the 7B O and down projections, the two-row-tile block stays ahead)
-  if (pl.mt == 2 && !wide && epi != EPI_SWIGLU_BF16 && n_tiles / pl.nt <= 160) pl.mt = 1;
+  const bool wide = n_tiles / 2 >= 512 || epi == EPI_SWIGLU_BF16;
+  pl.shape = wide ? 0 : epi == EPI_F32 && n_tiles >= 192 ? 1 : 2;
+  pl.nt = pl.shape == 2 ? 1 : 2;
   pl.splits = 1;
   if (epi == EPI_F32 && !wide && max_splits > 1) {
-    const long long blocks = (long long)n_tiles * m_blocks;
-    int z = (int)((256 + blocks - 1) / blocks);
+    int z = (256 + n_tiles - 1) / n_tiles;
     z = std::min(z, std::max(1, k_tiles / 64));
     pl.splits = std::max(1, std::min({z, max_splits, 4}));
   }
-  pl.name = stream_name(pl.mt, pl.nt, pl.nw, epi);
+  pl.name = names[pl.shape][epi];
   return pl;
-}
-
-template <int MT, int KU>
-static void launch_stream_mt(const GemmArgs& a, int epi, const GemmPlan& pl, dim3 grid, hipStream_t s) {
-  if (pl.nt == 1 && pl.nw == 4) launch_stream<MT, 1, KU, 4>(a, epi, grid, s);
-  else if (pl.nt == 1) launch_stream<MT, 1, KU, 16>(a, epi, grid, s);
-  else if (pl.nw == 4) launch_stream<MT, 2, KU, 4>(a, epi, grid, s);
-  else launch_stream<MT, 2, KU, 16>(a, epi, grid, s);
 }
 
 int launch_gemm_bf16(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s) {
   if (a.M < 1 || a.N < 16) return 0;
-  const int n_tiles = a.N >> 4, k_tiles = a.K >> 5;
   if (pl.kind == 1) return launch_tile(a, epi, pl, s);
-  int per = ceil_div(k_tiles, epi == EPI_F32 ? pl.splits : 1);
-  const int splits = ceil_div(k_tiles, per);
-  a.k_tiles_per_split = per;
-  dim3 grid(ceil_div(n_tiles, pl.nt), ceil_div(a.M, 16 * pl.mt), splits);
-  if (a.touch.wgs > 0 && grid.z == 1) {
+  const int n_tiles = a.N >> 4, k_tiles = a.K >> 5;
+  a.k_tiles_per_split = ceil_div(k_tiles, epi == EPI_F32 ? pl.splits : 1);
+  dim3 grid(ceil_div(n_tiles, pl.nt), ceil_div(k_tiles, a.k_tiles_per_split));
+  if (a.touch.wgs > 0 && grid.y == 1) {
     a.touch_x0 = (int)grid.x;
     grid.x += (unsigned)a.touch.wgs;
   } else {
     a.touch.wgs = 0;
   }
-  if (pl.mt == 1) launch_stream_mt<1, 4>(a, epi, pl, grid, s);
-  else if (pl.mt == 2) launch_stream_mt<2, 4>(a, epi, pl, grid, s);
-  else launch_stream_mt<4, 2>(a, epi, pl, grid, s);
-  return splits;
+  if (pl.shape == 0) launch_stream<2, 2, 8>(a, epi, grid, s);
+  else if (pl.shape == 1) launch_stream<2, 2, 16>(a, epi, grid, s);
+  else launch_stream<1, 3, 16>(a, epi, grid, s);
+  return (int)grid.y;
 }
 
 // ---------------------------------------------------------------- log-prob from the parts

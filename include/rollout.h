@@ -392,8 +392,8 @@ int rollout_sample(const float *logits, int32_t rows, int32_t vocab, float tempe
  * forced int32 [rows] or NULL (ids outside [0, vocab) are drawn), tokens int32 [rows], logprobs
  * float [rows], weight_sums uint64 [rows] or NULL - and the call only enqueues kernels on
  * hip_stream: no allocation, no host-device copy, no synchronisation; outputs are valid once the
- * stream has reached that point.  The kernels' scratch (per-row parameters and the partial maxima
- * and segment sums of the two sweeps, about 8.3 KB per row) is a fixed device array inside the
+ * stream has reached that point.  The kernels' scratch (the partial maxima, segment
+ * sums and histograms of the sweeps, about 30 KB per row) is a fixed device array inside the
  * library, one copy per GPU, kept until the process ends: rows <= ROLLOUT_SAMPLE_STATIC_MAX_ROWS,
  * else E_INVAL.  Every call on a GPU uses that one array, which keeps the last call's contents
  * (nothing in it has to start at zero: each call writes what it reads): calls that overlap on one

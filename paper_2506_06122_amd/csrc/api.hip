@@ -102,6 +102,16 @@ static void refresh_stats(rollout_ctx& c) {
   c.stats.matrix_core_path = c.simple ? 0 : 1;
 }
 
+// The context's scratch for sampling `rows` rows; any_nucleus: some row may draw with top_p < 1.
+static void set_sampler_scratch(rollout_ctx& c, SampleRows& sr, int rows, bool any_nucleus) {
+  sr.any_nucleus = any_nucleus;
+  if (rows > c.samp_rows) return;
+  sr.part_max = c.samp_part_max.p;
+  sr.seg_sums = c.samp_seg_sums.p;
+  sr.nucleus = c.samp_nucleus.p;
+  sr.nucleus_rows = c.samp_nucleus_rows;
+}
+
 // Admission of P prompts with n samples each (all or none), their prefill and response
 // position 0.  prompt_ids / first_ids: the prompts' counters and the ids of their first samples
 // as handed out at push time (sample j of prompt p carries first_ids[p] + j), or both NULL to
@@ -259,10 +269,7 @@ static void prefill_impl(rollout_ctx& c, int32_t n_prompts, const int32_t* token
   sr.tokens = c.out_tokens.p;
   sr.logprobs = c.out_logprobs.p;
   sr.weight_sums = nullptr;
-  if (Rs <= c.samp_rows) {
-    sr.part_max = c.samp_part_max.p;
-    sr.seg_sums = c.samp_seg_sums.p;
-  }
+  set_sampler_scratch(c, sr, Rs, top_p < 1.f && !forced_first);
   launch_sample(sr, Rs, m.vocab, c.stream);
   if (n_new) {
     h2d(c.row_token.p, hi + 4 * R, n_new * sizeof(int), c.stream);  // slots
@@ -283,6 +290,7 @@ static void prefill_impl(rollout_ctx& c, int32_t n_prompts, const int32_t* token
     int tok = hi[7 * R + i];
     s.n_emitted = 1;
     s.last_token = tok;
+    s.top_p = top_p;
     bool done = s.max_new <= 1 || (eos_id >= 0 && tok == eos_id);
     if (sample_ids) sample_ids[i] = s.id;
     if (first_tokens) first_tokens[i] = tok;
@@ -436,10 +444,7 @@ static void sample_first_tokens(rollout_ctx& c, int B, const std::vector<Pending
   fr.tokens = c.out_tokens.p + B;
   fr.logprobs = c.out_logprobs.p + B;
   fr.weight_sums = nullptr;
-  if (Rs <= c.samp_rows) {
-    fr.part_max = c.samp_part_max.p;
-    fr.seg_sums = c.samp_seg_sums.p;
-  }
+  set_sampler_scratch(c, fr, Rs, *std::min_element(top_p.begin(), top_p.end()) < 1.f);
   launch_sample(fr, Rs, m.vocab, c.stream);
   if (n_new) {  // the lists sit behind the page pairs
     int* lists = c.chunk_ints.p + R + pairs.size();
@@ -477,6 +482,7 @@ static void commit_chunk(rollout_ctx& c, StepChunk& chunk, const std::vector<Pen
       const int tok = first_tok[i];
       s.n_emitted = 1;
       s.last_token = tok;
+      s.top_p = pp.prompt.top_p;
       const bool done = s.max_new <= 1 || (s.eos_id >= 0 && tok == s.eos_id);
       chunk.first_ids[i] = s.id;
       chunk.first_groups[i] = s.group;
@@ -593,9 +599,11 @@ static void decode_impl(rollout_ctx& c, const int32_t* forced_tokens, const uint
   c.decode_max_ctx = 1;
   c.decode_max_own = 1;
   c.kv_tokens_this_call = 0;
+  bool any_nucleus = false;
   {
     int r = 0;
     for (auto& kv : c.live) {
+      any_nucleus |= kv.second.top_p < 1.f;
       const int ctx = kv.second.prompt_len + kv.second.n_emitted;
       c.decode_max_ctx = std::max(c.decode_max_ctx, ctx);
       c.decode_max_own = std::max(c.decode_max_own, ctx - (r < (int)c.h_row_t0.size() ? c.h_row_t0[r] : 0));
@@ -641,10 +649,7 @@ static void decode_impl(rollout_ctx& c, const int32_t* forced_tokens, const uint
   sr.tokens = c.out_tokens.p;
   sr.logprobs = c.out_logprobs.p;
   c.timer.begin("sample_kernel", 4.0 * B * m.vocab, 0, c.stream);
-  if (B <= c.samp_rows) {
-    sr.part_max = c.samp_part_max.p;
-    sr.seg_sums = c.samp_seg_sums.p;
-  }
+  set_sampler_scratch(c, sr, B, any_nucleus && !forced_tokens);
   launch_sample(sr, B, m.vocab, c.stream);
   c.timer.end(c.stream);
   // pinned host memory is mapped for the device: the kernel stores the step's results there
@@ -818,10 +823,9 @@ static void extend_impl(rollout_ctx& c, int32_t n, const int64_t* sample_ids, co
   sr.seed = c.rd.seed;
   sr.tokens = c.out_tokens.p;
   sr.logprobs = c.out_logprobs.p;
-  if (n <= c.samp_rows) {
-    sr.part_max = c.samp_part_max.p;
-    sr.seg_sums = c.samp_seg_sums.p;
-  }
+  bool any_nucleus = false;
+  for (const Sample* s : ss) any_nucleus |= s->top_p < 1.f;
+  set_sampler_scratch(c, sr, n, any_nucleus && !forced_next);
   launch_sample(sr, n, m.vocab, c.stream);
   extend_slots_kernel<<<ceil_div(n, 256), 256, 0, c.stream>>>(c.st, c.d_live.p, c.row_aux.p + R, c.out_tokens.p, n);
   d2h(hi + 3 * R, c.out_tokens.p, n * sizeof(int), c.stream);
@@ -1365,33 +1369,56 @@ int rollout_logprobs(rollout_ctx* ctx, int32_t n_seqs, const int32_t* tokens, co
 
 }  // extern "C"
 
-// Device scratch of the two context-free entry points below: one grow-only buffer per device,
-// kept until the process ends, so that a call allocates only when it needs more than any call
-// before it.  The mutex is held for the whole call (both calls return after their stream has
-// drained), so calls on one device take turns.
+// Scratch of the two context-free entry points below: one grow-only device buffer and one grow-only
+// pinned host buffer per device, kept until the process ends, so that a call allocates only when it
+// needs more than any call before it.  The mutex is held for the whole call (both calls return
+// after their stream has drained), so calls on one device take turns.  Pinned memory is mapped for the
+// device: small inputs are read and small results stored there by the kernels, without copies.
 namespace {
 struct CallScratch {
   std::mutex mu;
-  char* p = nullptr;
-  size_t bytes = 0;
-  size_t used = 0;
-  void begin() { used = 0; }
-  void reserve(size_t need) {
-    if (need <= bytes) return;
-    if (p) (void)hipFree(p);
-    p = nullptr;
-    bytes = 0;
-    HIP_TRY(hipMalloc((void**)&p, need));
-    bytes = need;
+  char *p = nullptr, *host = nullptr;
+  size_t bytes = 0, host_bytes = 0;
+  size_t used = 0, host_used = 0;
+  void begin(size_t need, size_t host_need) {
+    used = host_used = 0;
+    if (need > bytes) {
+      if (p) (void)hipFree(p);
+      p = nullptr;
+      bytes = 0;
+      HIP_TRY(hipMalloc((void**)&p, need));
+      bytes = need;
+    }
+    if (host_need > host_bytes) {
+      if (host) (void)hipHostFree(host);
+      host = nullptr;
+      host_bytes = 0;
+      HIP_TRY(hipHostMalloc((void**)&host, host_need, hipHostMallocDefault));
+      host_bytes = host_need;
+    }
   }
   template <typename T>
-  T* take(size_t count) {  // after reserve(): 256-byte aligned pieces of the buffer
+  T* take(size_t count) {  // after begin(): 256-byte aligned pieces of the device buffer
     T* out = (T*)(p + used);
-    used += (count * sizeof(T) + 255) / 256 * 256;
+    used += piece(count * sizeof(T));
+    return out;
+  }
+  template <typename T>
+  T* take_host(size_t count) {  // the same of the pinned buffer
+    T* out = (T*)(host + host_used);
+    host_used += piece(count * sizeof(T));
     return out;
   }
   static size_t piece(size_t bytes_) { return (bytes_ + 255) / 256 * 256; }
 };
+// the kernels of a short call: polling answers within microseconds where a blocking wait may sleep
+void wait_stream(hipStream_t s) {
+  for (;;) {
+    const hipError_t e = hipStreamQuery(s);
+    if (e == hipSuccess) return;
+    if (e != hipErrorNotReady) throw HipError(e, "hipStreamQuery", __FILE__, __LINE__);
+  }
+}
 CallScratch& call_scratch() {
   static CallScratch per_device[64];
   int dev = 0;
@@ -1418,36 +1445,42 @@ int rollout_sample(const float* logits, int32_t rows, int32_t vocab, float tempe
     CallScratch& cs = call_scratch();
     std::lock_guard<std::mutex> lock(cs.mu);
     const size_t R = rows;
-    cs.reserve(4 * CallScratch::piece(R * 4) + 2 * CallScratch::piece(R * 4) + CallScratch::piece(R * 8) +
-               CallScratch::piece(R * kSampleParts * 4) + CallScratch::piece(R * kSampleSegments * 8));
-    cs.begin();
-    float *invt = cs.take<float>(R), *tp = cs.take<float>(R), *lp = cs.take<float>(R);
-    unsigned* un = cs.take<unsigned>(R);
-    int *fo = cs.take<int>(R), *tok = cs.take<int>(R);
-    unsigned long long* ws = cs.take<unsigned long long>(R);
-    std::vector<float> hv(rows, 1.0f / temperature), hp(rows, top_p);
-    HIP_TRY(hipMemcpyAsync(invt, hv.data(), rows * sizeof(float), hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(tp, hp.data(), rows * sizeof(float), hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(un, uniforms, rows * sizeof(unsigned), hipMemcpyHostToDevice, s));
-    if (forced) HIP_TRY(hipMemcpyAsync(fo, forced, rows * sizeof(int), hipMemcpyHostToDevice, s));
-    HIP_TRY(hipStreamSynchronize(s));  // host staging vectors are pageable
+    const bool nucleus = top_p < 1.f && !(forced && *std::min_element(forced, forced + rows) >= 0);
+    const size_t nucleus_rows = nucleus ? std::min<size_t>(R, 512) : 0;
+    cs.begin(CallScratch::piece(R * 4) + CallScratch::piece(R * kSampleParts * 4) + CallScratch::piece(R * kSampleSegments * 8) +
+                 CallScratch::piece(nucleus_rows * kNucleusScratch * 8),
+             4 * CallScratch::piece(R * 4) + CallScratch::piece(R * 8));
+    unsigned* un = cs.take_host<unsigned>(R);
+    int *fo_host = cs.take_host<int>(R), *tok = cs.take_host<int>(R);
+    float* lp = cs.take_host<float>(R);
+    unsigned long long* ws = cs.take_host<unsigned long long>(R);
+    std::memcpy(un, uniforms, R * sizeof(unsigned));
+    int* fo = nullptr;
+    if (forced) {  // read by every sweep: a copy on the device
+      fo = cs.take<int>(R);
+      std::memcpy(fo_host, forced, R * sizeof(int));
+      HIP_TRY(hipMemcpyAsync(fo, fo_host, R * sizeof(int), hipMemcpyHostToDevice, s));
+    }
     SampleRows sr{};
     sr.logits = logits;
-    sr.inv_temp = invt;
-    sr.top_p = tp;
+    sr.inv_temp_all = 1.0f / temperature;
+    sr.top_p_all = top_p;
     sr.uniforms = un;
-    sr.forced = forced ? fo : nullptr;
+    sr.forced = fo;
     sr.tokens = tok;
     sr.logprobs = lp;
     sr.weight_sums = ws;
     sr.part_max = cs.take<float>(R * kSampleParts);
     sr.seg_sums = cs.take<unsigned long long>(R * kSampleSegments);
+    sr.any_nucleus = nucleus;
+    if (nucleus) sr.nucleus = cs.take<unsigned long long>(nucleus_rows * kNucleusScratch);
+    sr.nucleus_rows = (int)nucleus_rows;
     launch_sample(sr, rows, vocab, s);
-    HIP_TRY(hipMemcpyAsync(tokens, tok, rows * sizeof(int), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(logprobs, lp, rows * sizeof(float), hipMemcpyDeviceToHost, s));
-    if (weight_sums)
-      HIP_TRY(hipMemcpyAsync(weight_sums, ws, rows * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(hipGetLastError());
+    wait_stream(s);
+    std::memcpy(tokens, tok, R * sizeof(int));
+    std::memcpy(logprobs, lp, R * sizeof(float));
+    if (weight_sums) std::memcpy(weight_sums, ws, R * sizeof(unsigned long long));
   });
 }
 
@@ -1470,9 +1503,9 @@ int rollout_policy_loss(int32_t n_seqs, const int32_t* cu_seqlens, const float* 
     CallScratch& cs = call_scratch();
     std::lock_guard<std::mutex> lock(cs.mu);
     const size_t S1 = (size_t)std::max(n_seqs, 1);
-    cs.reserve(CallScratch::piece((S1 + 1) * 4) + CallScratch::piece(S1 * 4) + CallScratch::piece(2 * S1 * 4) +
-               CallScratch::piece(2 * 4));
-    cs.begin();
+    cs.begin(CallScratch::piece((S1 + 1) * 4) + CallScratch::piece(S1 * 4) + CallScratch::piece(2 * S1 * 4) +
+                 CallScratch::piece(2 * 4),
+             0);
     struct { int* p; } cu{cs.take<int>(S1 + 1)};
     struct { float* p; } rw{cs.take<float>(S1)}, part{cs.take<float>(2 * S1)}, result{cs.take<float>(2)};
     HIP_TRY(hipMemcpyAsync(cu.p, cu_seqlens, (n_seqs + 1) * sizeof(int), hipMemcpyHostToDevice, s));

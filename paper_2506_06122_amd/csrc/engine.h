@@ -221,6 +221,8 @@ struct rollout_ctx : HostState {
   DevBuf<float> samp_part_max;               // sampler scratch, see SampleRows
   DevBuf<unsigned long long> samp_seg_sums;
   int samp_rows = 0;                         // rows the sampler scratch holds
+  DevBuf<unsigned long long> samp_nucleus;   // scratch of the rows that draw with top_p < 1, in batches
+  int samp_nucleus_rows = 0;
   PinnedBuf<int> h_int;      // staging, 8 * r_max ints
   PinnedBuf<float> h_float;  // staging, 4 * r_max floats
   PinnedBuf<long long> h_ll; // staging, r_max

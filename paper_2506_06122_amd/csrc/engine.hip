@@ -348,6 +348,8 @@ void engine_init(rollout_ctx& c, const rollout_weights& w) {
   c.samp_rows = (int)std::min<size_t>(R, 4096);
   c.samp_part_max.alloc((size_t)c.samp_rows * kSampleParts);
   c.samp_seg_sums.alloc((size_t)c.samp_rows * kSampleSegments);
+  c.samp_nucleus_rows = std::min(c.samp_rows, 512);
+  c.samp_nucleus.alloc((size_t)c.samp_nucleus_rows * kNucleusScratch);
   c.h_int.alloc(8 * R);
   c.h_float.alloc(4 * R);
   c.h_ll.alloc(R);

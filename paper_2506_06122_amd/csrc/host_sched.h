@@ -29,6 +29,7 @@ struct Sample {
   int slot;
   int prompt_len, n_emitted, max_new, eos_id;  // prompt_len: every cached token that is not a response token
   int last_token = -1;                         // the response token emitted last (not cached yet)
+  float top_p = 1.f;
   int64_t group = -1;                          // the prompt's counter: samples of one prompt share its full pages
   int shared_len = 0;                          // positions held in those shared pages (a multiple of page_tokens)
   std::vector<int32_t> pages;  // one reference held on each

@@ -61,13 +61,14 @@ void launch_convert_to_f32(const void* src, int dtype, float* dst, long long n, 
 struct SampleRows {
   const float* logits;      // [*][vocab]
   const int* logits_row;    // [rows] row of `logits` each draw reads, or NULL (identity)
-  const float* inv_temp;    // [rows]
-  const float* top_p;       // [rows]
+  const float* inv_temp;    // [rows], or NULL: inv_temp_all for every row
+  const float* top_p;       // [rows], or NULL: top_p_all for every row
   const unsigned* uniforms; // [rows] or NULL -> Philox(seed, sample_id, step)
   const long long* sample_id;  // [rows] (Philox only)
   const int* step;             // [rows] (Philox only)
   const int* forced;        // [rows] or NULL; entries outside [0, vocab) mean "draw"
   unsigned long long seed;
+  float inv_temp_all, top_p_all;
   int* tokens;              // out [rows]
   float* logprobs;          // out [rows]
   unsigned long long* weight_sums;  // out [rows] or NULL
@@ -75,9 +76,18 @@ struct SampleRows {
   // sums are integers, so the split changes nothing): both or neither.
   float* part_max = nullptr;               // [rows][kSampleParts]
   unsigned long long* seg_sums = nullptr;  // [rows][kSampleSegments]
+  // any_nucleus = false promises that no row draws with top_p < 1; with it, `nucleus` is the scratch of
+  // nucleus_rows rows that lets those rows' sweeps run on several workgroups too.
+  bool any_nucleus = true;
+  unsigned long long* nucleus = nullptr;   // [nucleus_rows][kNucleusScratch]
+  int nucleus_rows = 0;
 };
 constexpr int kSampleParts = 64, kSampleSegments = 1024;
-void launch_sample(const SampleRows& r, int rows, int vocab, hipStream_t s);
+constexpr int kNucleusBins0 = 41 * 16;                           // exponents 0..40 x 4 mantissa bits
+constexpr int kNucleusHist = kNucleusBins0 + 1024 + 512;         // the three histograms of a row
+constexpr int kNucleusFound = kNucleusHist + kSampleSegments / 2;  // behind 1024 32-bit counts: what the search found
+constexpr int kNucleusScratch = kNucleusFound + 32;              // 64-bit words
+void launch_sample(SampleRows r, int rows, int vocab, hipStream_t s);
 void launch_philox_words(unsigned long long seed, const long long* ids, const unsigned* steps, unsigned* out,
                          int n, hipStream_t s);
 // out[r] = log softmax(logits[r] * inv_temp)[target[r]]; target < 0 writes 0

@@ -9,6 +9,16 @@
 //   weight reaches theta = max(1, floor(S * floor(top_p 2^24) / 2^24)); R = floor(S_N x / 2^32);
 //   token = first id of the nucleus, ascending, whose running weight exceeds R.
 // Every floating-point step is a single rounded fp32 operation: no contraction allowed.
+//
+// Where the nucleus ends (top_p < 1): the smallest weight tau it holds is found by three histograms
+// of weight over the vocabulary instead of one sweep per bit of the weight.  A weight has at most 24
+// significant bits, so as a float it is exact and its bits order like its value: 6 bits of
+// exponent and 23 of mantissa.  Histogram 0 bins by exponent and 4 mantissa bits (656 bins), the next
+// two by the following 10 and the last 9 bits among the ids of the bin found before; a bin is
+// found from the top by a prefix sum.  A fifth sweep leaves, per segment of 256 ids, the weight
+// above tau and the number of ids at tau, from which the draw needs no further sweep.  What bounds it:
+// the arithmetic of the weights (about 60 instructions per id and sweep), so the sweeps of a row
+// run on several workgroups, like the first two.  64 rows x 151936 ids, top_p 0.9: see launch_sample.
 #include <algorithm>
 
 #include "kernels.h"
@@ -17,11 +27,12 @@
 
 #define SAMP_T 1024
 
-__device__ inline unsigned long long fixexp_weight(float d) {
+// The weight as the bits of a float, exact (24 significant bits at most); 0 for weight 0.
+__device__ inline unsigned fixexp_key(float d) {
 #pragma clang fp contract(off)
   const float log2e = 0x1.715476p+0f;
   float t = d * log2e;
-  if (!(t >= -40.0f)) return 0ull;
+  if (!(t >= -40.0f)) return 0u;
   float n = floorf(t);
   float f = t - n;
   float y = 0x1.5bd2aep-16f;
@@ -39,12 +50,18 @@ __device__ inline unsigned long long fixexp_weight(float d) {
   y = y + 0x1.62e430p-1f;
   y = y * f;
   y = y + 0x1.000000p+0f;
-  // floor(y * 2^(40 + n)) from the bits of y: y = mant * 2^(e - 23)
-  unsigned bits = __float_as_uint(y);
-  int e = (int)((bits >> 23) & 0xffu) - 127;
-  unsigned long long mant = (unsigned long long)((bits & 0x7fffffu) | 0x800000u);
-  int shift = e - 23 + 40 + (int)n;
-  return shift >= 0 ? (mant << shift) : (shift > -64 ? (mant >> (-shift)) : 0ull);
+  // floor(y * 2^(40 + n)): the exponent grows by 40 + n, mantissa bits worth less than 1 go
+  const unsigned bits = __float_as_uint(y);
+  const int e = (int)((bits >> 23) & 0xffu) - 127 + 40 + (int)n;
+  if (e < 0) return 0u;
+  const unsigned below_one = e < 23 ? (1u << (23 - e)) - 1u : 0u;
+  return (((unsigned)(e + 127) << 23) | (bits & 0x7fffffu)) & ~below_one;
+}
+__device__ inline unsigned long long key_weight(unsigned key) {
+  if (!key) return 0ull;
+  const int e = (int)(key >> 23) - 127;
+  const unsigned mant = (key & 0x7fffffu) | 0x800000u;
+  return e >= 23 ? (unsigned long long)mant << (e - 23) : (unsigned long long)(mant >> (23 - e));
 }
 
 __device__ inline float scaled_logit(float logit, float inv_t) {
@@ -63,7 +80,9 @@ __device__ inline unsigned long long shfl_up_u64(unsigned long long v, int o) {
 }
 
 struct SampShared {
-  unsigned long long vals[SAMP_T];
+  unsigned long long vals[SAMP_T];   // one value per segment
+  unsigned long long hist[SAMP_T];   // a histogram, or the nucleus' weight above tau per segment
+  unsigned ties[SAMP_T];             // ids at tau per segment
   unsigned long long wave_part[SAMP_T / WAVE];
   unsigned long long bcast[2];
   float fwave[SAMP_T / WAVE];
@@ -89,43 +108,18 @@ __device__ inline unsigned long long block_sum_u64(unsigned long long v, SampSha
   return s;
 }
 
-// Smallest thread index whose inclusive prefix of `local` exceeds `target`, and the
-// exclusive prefix before that thread.  Requires sum(local) > target.
-__device__ inline void block_find(unsigned long long local, unsigned long long target, SampShared& sh,
-                                  int& t_star, unsigned long long& before) {
-  int tid = threadIdx.x;
-  sh.vals[tid] = local;
-  if (tid == 0) {
-    sh.bcast[0] = 0;
-    sh.bcast[1] = 0;
+// Inclusive prefix sum over the threads of the workgroup.
+__device__ inline unsigned long long block_scan_u64(unsigned long long v, SampShared& sh) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int o = 1; o < WAVE; o <<= 1) {
+    const unsigned long long up = shfl_up_u64(v, o);
+    if (lane >= o) v += up;
   }
+  if (lane == 63) sh.wave_part[wave] = v;
   __syncthreads();
-  if (tid < WAVE) {
-    const int per = SAMP_T / WAVE;
-    unsigned long long mine = 0;
-    for (int j = 0; j < per; ++j) mine += sh.vals[tid * per + j];
-    unsigned long long inc = mine;
-    for (int o = 1; o < WAVE; o <<= 1) {
-      unsigned long long up = shfl_up_u64(inc, o);
-      if (tid >= o) inc += up;
-    }
-    unsigned long long exc = inc - mine;
-    if (exc <= target && target < inc) {
-      unsigned long long acc = exc;
-      int j = 0;
-      for (; j < per - 1; ++j) {
-        unsigned long long v = sh.vals[tid * per + j];
-        if (acc + v > target) break;
-        acc += v;
-      }
-      sh.bcast[0] = (unsigned long long)(tid * per + j);
-      sh.bcast[1] = acc;
-    }
-  }
+  for (int w = 0; w < wave; ++w) v += sh.wave_part[w];
   __syncthreads();
-  t_star = (int)sh.bcast[0];
-  before = sh.bcast[1];
-  __syncthreads();
+  return v;
 }
 
 __device__ inline void philox_round(unsigned& c0, unsigned& c1, unsigned& c2, unsigned& c3, unsigned k0,
@@ -168,9 +162,11 @@ void launch_philox_words(unsigned long long seed, const long long* ids, const un
 struct Seg4 {
   unsigned long long w[4];
 };
+struct Key4 {
+  unsigned k[4];
+};
 
-__device__ inline Seg4 load_weights4(const float* __restrict__ row, int i0, int vocab, bool vec_ok, float inv_t,
-                                     float m) {
+__device__ inline Key4 load_keys4(const float* __restrict__ row, int i0, int vocab, bool vec_ok, float inv_t, float m) {
   float v[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
   if (vec_ok && i0 + 3 < vocab) {
     const float4 t = *(const float4*)(row + i0);
@@ -183,10 +179,102 @@ __device__ inline Seg4 load_weights4(const float* __restrict__ row, int i0, int 
     for (int e = 0; e < 4; ++e)
       if (i0 + e < vocab) v[e] = row[i0 + e];
   }
+  Key4 out;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) out.k[e] = i0 + e < vocab ? fixexp_key(shifted(scaled_logit(v[e], inv_t), m)) : 0u;
+  return out;
+}
+__device__ inline Seg4 load_weights4(const float* __restrict__ row, int i0, int vocab, bool vec_ok, float inv_t,
+                                     float m) {
+  const Key4 q = load_keys4(row, i0, vocab, vec_ok, inv_t, m);
   Seg4 out;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) out.w[e] = i0 + e < vocab ? fixexp_weight(shifted(scaled_logit(v[e], inv_t), m)) : 0ull;
+  for (int e = 0; e < 4; ++e) out.w[e] = key_weight(q.k[e]);
   return out;
+}
+
+__device__ inline float row_inv_temp(const SampleRows& a, int r) { return a.inv_temp ? a.inv_temp[r] : a.inv_temp_all; }
+__device__ inline float row_top_p(const SampleRows& a, int r) { return a.top_p ? a.top_p[r] : a.top_p_all; }
+
+// ---- the end of the nucleus
+// Row r draws from a nucleus (a forced token or top_p >= 1 does not).
+__device__ inline bool row_has_nucleus(const SampleRows& a, int r, int vocab) {
+  return row_top_p(a, r) < 1.0f && !(a.forced && (unsigned)a.forced[r] < (unsigned)vocab);
+}
+// bin of a key in histogram `level`; the bits above it name the bins of the levels before
+__device__ inline unsigned nucleus_prefix(unsigned key, int level) { return level == 0 ? 0u : key >> (level == 1 ? 19 : 9); }
+__device__ inline unsigned nucleus_bin(unsigned key, int level) {
+  return level == 0 ? (key >> 19) - (127u << 4) : level == 1 ? (key >> 9) & 1023u : key & 511u;
+}
+__device__ inline int nucleus_bins(int level) { return level == 0 ? kNucleusBins0 : level == 1 ? 1024 : 512; }
+
+struct NucleusState {
+  unsigned long long theta, above;  // weight to reach; weight of the bins above the ones found
+  unsigned prefix;                  // key bits found so far (nucleus_prefix of the next level; the key of tau after level 2)
+};
+// One more level: hist (n bins) names the highest bin at which the weight from the top reaches theta.
+__device__ inline void nucleus_descend(const unsigned long long* hist, int level, NucleusState& st, SampShared& sh) {
+  const int n = nucleus_bins(level), t = threadIdx.x;
+  if (t == 0) sh.bcast[0] = sh.bcast[1] = 0ull;  // a row without weights (no finite maximum) finds no bin
+  const unsigned long long v = t < n ? hist[n - 1 - t] : 0ull;
+  const unsigned long long inc = block_scan_u64(v, sh) + st.above;
+  if (t < n && inc >= st.theta && inc - v < st.theta) {  // exactly one thread: the sums only grow, and all of them reach theta
+    sh.bcast[0] = (unsigned long long)(n - 1 - t);
+    sh.bcast[1] = inc - v;
+  }
+  __syncthreads();
+  const unsigned bin = (unsigned)sh.bcast[0];
+  st.above = sh.bcast[1];
+  st.prefix = level == 0 ? bin + (127u << 4) : level == 1 ? (st.prefix << 10) | bin : (st.prefix << 9) | bin;
+  __syncthreads();
+}
+__device__ inline unsigned long long nucleus_theta(unsigned long long S, float top_p) {
+  const unsigned long long p24 = (unsigned long long)floorf(fmaxf(top_p, 0.f) * 16777216.0f);
+  const unsigned long long theta = (S >> 24) * p24 + (((S & 0xffffffull) * p24) >> 24);
+  return theta < 1 ? 1 : theta;
+}
+// State after the first `levels` histograms of row r (global scratch); S = sum of all weights.
+__device__ inline NucleusState nucleus_from_scratch(const SampleRows& a, int r, int levels, unsigned long long& S,
+                                                    SampShared& sh) {
+  const unsigned long long* h = a.nucleus + (long long)r * kNucleusScratch;
+  S = block_sum_u64(threadIdx.x < kNucleusBins0 ? h[threadIdx.x] : 0ull, sh);
+  NucleusState st{nucleus_theta(S, row_top_p(a, r)), 0ull, 0u};
+  nucleus_descend(h, 0, st, sh);
+  if (levels > 1) nucleus_descend(h + kNucleusBins0, 1, st, sh);
+  if (levels > 2) nucleus_descend(h + kNucleusBins0 + 1024, 2, st, sh);
+  return st;
+}
+// Tiles t0, t0 + step, ... of the row into the LDS histogram of `level` (zeroed here)
+__device__ inline void nucleus_histogram(const float* row, int vocab, bool vec_ok, float inv_t, float m, int t0, int step,
+                                         int level, unsigned prefix, SampShared& sh) {
+  const int tid = threadIdx.x, n_tiles = (vocab + 4095) >> 12;
+  sh.hist[tid] = 0ull;
+  __syncthreads();
+  for (int t = t0; t < n_tiles; t += step) {
+    const Key4 q = load_keys4(row, t * 4096 + tid * 4, vocab, vec_ok, inv_t, m);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (q.k[e] && nucleus_prefix(q.k[e], level) == prefix) atomicAdd(&sh.hist[nucleus_bin(q.k[e], level)], key_weight(q.k[e]));
+  }
+  __syncthreads();
+}
+// Tiles t0, t0 + step, ...: per segment the weight above tau and the number of ids at tau
+template <typename F>
+__device__ inline void nucleus_segments(const float* row, int vocab, bool vec_ok, float inv_t, float m, int t0, int step,
+                                        unsigned tau_key, F&& put) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n_tiles = (vocab + 4095) >> 12, n_seg = (vocab + 255) >> 8;
+  for (int t = t0; t < n_tiles; t += step) {
+    const Key4 q = load_keys4(row, t * 4096 + tid * 4, vocab, vec_ok, inv_t, m);
+    unsigned long long v = 0;  // the weight (at most 256 x 2^40 per segment), the count from bit 52 on
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (q.k[e] > tau_key) v += key_weight(q.k[e]);
+      if (q.k[e] == tau_key) v += 1ull << 52;
+    }
+    v = wave_sum_u64(v);
+    if (lane == 0 && t * 16 + wave < n_seg) put(t * 16 + wave, v & ((1ull << 52) - 1ull), (unsigned)(v >> 52));
+  }
 }
 
 // Smallest segment whose inclusive prefix of sh.vals[0..n_seg) exceeds target, and the
@@ -258,7 +346,7 @@ __global__ __launch_bounds__(SAMP_T) void sample_max_kernel(SampleRows a, int vo
   __shared__ SampShared sh;
   const int tid = threadIdx.x, r = blockIdx.y;
   const float* row = a.logits + (long long)(a.logits_row ? a.logits_row[r] : r) * vocab;
-  const float inv_t = a.inv_temp[r];
+  const float inv_t = row_inv_temp(a, r);
   const bool vec_ok = (vocab & 3) == 0 && (((unsigned long long)row) & 15ull) == 0;
   const int n_tiles = (vocab + 4095) >> 12;
   float m = -INFINITY;
@@ -275,19 +363,33 @@ __global__ __launch_bounds__(SAMP_T) void sample_max_kernel(SampleRows a, int vo
   }
   m = block_max(m, sh);
   if (tid == 0) a.part_max[(long long)r * kSampleParts + blockIdx.x] = m;
+  if (a.nucleus && row_has_nucleus(a, r, vocab))
+    for (int i = blockIdx.x * SAMP_T + tid; i < kNucleusHist; i += parts * SAMP_T)
+      a.nucleus[(long long)r * kNucleusScratch + i] = 0ull;
+}
+
+__device__ inline float row_max(const SampleRows& a, int r, int parts) {
+  float m = -INFINITY;
+  for (int q = 0; q < parts; ++q) m = fmaxf(m, a.part_max[(long long)r * kSampleParts + q]);
+  return m;
 }
 
 // Second sweep on `parts` workgroups per row: the weights of the same tiles, one sum per
-// 256-id segment.
+// 256-id segment; rows with a nucleus: histogram 0.
 __global__ __launch_bounds__(SAMP_T) void sample_segments_kernel(SampleRows a, int vocab, int parts) {
+  __shared__ SampShared sh;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = blockIdx.y;
   const float* row = a.logits + (long long)(a.logits_row ? a.logits_row[r] : r) * vocab;
-  const float inv_t = a.inv_temp[r];
+  const float inv_t = row_inv_temp(a, r);
   const bool vec_ok = (vocab & 3) == 0 && (((unsigned long long)row) & 15ull) == 0;
   const int n_seg = (vocab + 255) >> 8;
   const int n_tiles = (vocab + 4095) >> 12;
-  float m = -INFINITY;
-  for (int q = 0; q < parts; ++q) m = fmaxf(m, a.part_max[(long long)r * kSampleParts + q]);
+  const float m = row_max(a, r, parts);
+  if (a.nucleus && row_has_nucleus(a, r, vocab)) {
+    nucleus_histogram(row, vocab, vec_ok, inv_t, m, blockIdx.x, parts, 0, 0u, sh);
+    if (tid < kNucleusBins0 && sh.hist[tid]) atomicAdd(a.nucleus + (long long)r * kNucleusScratch + tid, sh.hist[tid]);
+    return;
+  }
   for (int t = blockIdx.x; t < n_tiles; t += parts) {
     const Seg4 q = load_weights4(row, t * 4096 + tid * 4, vocab, vec_ok, inv_t, m);
     const unsigned long long ws = wave_sum_u64(q.w[0] + q.w[1] + q.w[2] + q.w[3]);
@@ -295,23 +397,73 @@ __global__ __launch_bounds__(SAMP_T) void sample_segments_kernel(SampleRows a, i
   }
 }
 
-// parts = 0: this kernel sweeps the row itself; else it starts from what the two kernels above left
+// The sweeps that only rows with a nucleus need, `parts` workgroups per row: histogram 1, histogram 2 (every
+// workgroup finds the bins of the histograms before it again, from a few KiB), then the segments.
+template <int LEVEL>
+__global__ __launch_bounds__(SAMP_T) void sample_nucleus_kernel(SampleRows a, int vocab, int parts) {
+  __shared__ SampShared sh;
+  const int tid = threadIdx.x, r = blockIdx.y;
+  if (!row_has_nucleus(a, r, vocab)) return;  // uniform
+  const float* row = a.logits + (long long)(a.logits_row ? a.logits_row[r] : r) * vocab;
+  const float inv_t = row_inv_temp(a, r);
+  const bool vec_ok = (vocab & 3) == 0 && (((unsigned long long)row) & 15ull) == 0;
+  const float m = row_max(a, r, parts);
+  unsigned long long S;
+  const NucleusState st = nucleus_from_scratch(a, r, LEVEL, S, sh);
+  unsigned long long* scratch = a.nucleus + (long long)r * kNucleusScratch;
+  if constexpr (LEVEL < 3) {
+    nucleus_histogram(row, vocab, vec_ok, inv_t, m, blockIdx.x, parts, LEVEL, st.prefix, sh);
+    unsigned long long* h = scratch + (LEVEL == 1 ? kNucleusBins0 : kNucleusBins0 + 1024);
+    if (tid < nucleus_bins(LEVEL) && sh.hist[tid]) atomicAdd(h + tid, sh.hist[tid]);
+  } else {
+    unsigned* ties = (unsigned*)(scratch + kNucleusHist);
+    if (blockIdx.x == 0 && tid == 0) {  // for the selection
+      unsigned long long* found = scratch + kNucleusFound;
+      found[0] = S;
+      found[1] = st.theta;
+      found[2] = st.above;
+      found[3] = st.prefix;
+    }
+    nucleus_segments(row, vocab, vec_ok, inv_t, m, blockIdx.x, parts, st.prefix,
+                     [&](int seg, unsigned long long above, unsigned n) {
+                       a.seg_sums[(long long)r * kSampleSegments + seg] = above;
+                       ties[seg] = n;
+                     });
+  }
+}
+
+// parts = 0: this kernel sweeps the row itself; else it starts from what the kernels above left
 __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab, int parts) {
   __shared__ SampShared sh;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = blockIdx.x;
   const float* row = a.logits + (long long)(a.logits_row ? a.logits_row[r] : r) * vocab;
-  const float inv_t = a.inv_temp[r];
+  const float inv_t = row_inv_temp(a, r);
   const bool vec_ok = (vocab & 3) == 0 && (((unsigned long long)row) & 15ull) == 0;
   const int n_seg = (vocab + 255) >> 8;
   const int n_tiles = (vocab + 4095) >> 12;
+  const bool nucleus = row_has_nucleus(a, r, vocab);
 
   float m = -INFINITY;
-  unsigned long long local = 0;
+  unsigned long long S = 0;
+  NucleusState st{0ull, 0ull, 0u};
   if (parts) {
-    for (int q = 0; q < parts; ++q) m = fmaxf(m, a.part_max[(long long)r * kSampleParts + q]);
-    if (tid < n_seg) {
-      local = a.seg_sums[(long long)r * kSampleSegments + tid];
-      sh.vals[tid] = local;
+    m = row_max(a, r, parts);
+    if (nucleus) {
+      const unsigned long long* scratch = a.nucleus + (long long)r * kNucleusScratch;
+      S = scratch[kNucleusFound];
+      st = NucleusState{scratch[kNucleusFound + 1], scratch[kNucleusFound + 2], (unsigned)scratch[kNucleusFound + 3]};
+      const unsigned* ties = (const unsigned*)(scratch + kNucleusHist);
+      if (tid < n_seg) {
+        sh.hist[tid] = a.seg_sums[(long long)r * kSampleSegments + tid];
+        sh.ties[tid] = ties[tid];
+      }
+    } else {
+      unsigned long long local = 0;
+      if (tid < n_seg) {
+        local = a.seg_sums[(long long)r * kSampleSegments + tid];
+        sh.vals[tid] = local;
+      }
+      S = block_sum_u64(local, sh);
     }
   } else {
     for (int t = 0; t < n_tiles; ++t) {
@@ -326,79 +478,51 @@ __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab,
       }
     }
     m = block_max(m, sh);
-
-    // pass: all weights, one sum per segment
-    for (int t = 0; t < n_tiles; ++t) {
-      const Seg4 q = load_weights4(row, t * 4096 + tid * 4, vocab, vec_ok, inv_t, m);
-      const unsigned long long mine = q.w[0] + q.w[1] + q.w[2] + q.w[3];
-      local += mine;
-      const unsigned long long ws = wave_sum_u64(mine);
-      if (lane == 0 && t * 16 + wave < n_seg) sh.vals[t * 16 + wave] = ws;
+    if (nucleus) {
+      nucleus_histogram(row, vocab, vec_ok, inv_t, m, 0, 1, 0, 0u, sh);
+      S = block_sum_u64(sh.hist[tid], sh);
+      st.theta = nucleus_theta(S, row_top_p(a, r));
+      nucleus_descend(sh.hist, 0, st, sh);
+      for (int level = 1; level < 3; ++level) {
+        nucleus_histogram(row, vocab, vec_ok, inv_t, m, 0, 1, level, st.prefix, sh);
+        nucleus_descend(sh.hist, level, st, sh);
+      }
+      nucleus_segments(row, vocab, vec_ok, inv_t, m, 0, 1, st.prefix,
+                       [&](int seg, unsigned long long above, unsigned n) {
+                         sh.hist[seg] = above;
+                         sh.ties[seg] = n;
+                       });
+    } else {
+      // all weights, one sum per segment
+      unsigned long long local = 0;
+      for (int t = 0; t < n_tiles; ++t) {
+        const Seg4 q = load_weights4(row, t * 4096 + tid * 4, vocab, vec_ok, inv_t, m);
+        const unsigned long long mine = q.w[0] + q.w[1] + q.w[2] + q.w[3];
+        local += mine;
+        const unsigned long long ws = wave_sum_u64(mine);
+        if (lane == 0 && t * 16 + wave < n_seg) sh.vals[t * 16 + wave] = ws;
+      }
+      S = block_sum_u64(local, sh);  // also orders the writes to sh.vals
     }
   }
-  const unsigned long long S = block_sum_u64(local, sh);  // also orders the writes to sh.vals
 
   int token = a.forced ? a.forced[r] : -1;
   if ((unsigned)token >= (unsigned)vocab) {  // nothing forced (an id outside the vocabulary forces nothing)
-    const float top_p = a.top_p[r];
-    // nucleus membership: w > tau, or w == tau and id <= tie_cut
-    unsigned long long tau = 0, s_n = S;
-    int tie_cut = vocab;
-    if (top_p < 1.0f) {
-      unsigned long long p24 = (unsigned long long)floorf(fmaxf(top_p, 0.f) * 16777216.0f);
-      unsigned long long theta = (S >> 24) * p24 + (((S & 0xffffffull) * p24) >> 24);
-      if (theta < 1) theta = 1;
-      // largest tau with sum_{w >= tau} w >= theta, bit by bit (w <= 2^40)
-      for (int b = 40; b >= 0; --b) {
-        const unsigned long long cand = tau | (1ull << b);
-        unsigned long long part = 0;
-        for (int t = 0; t < n_tiles; ++t) {
-          const Seg4 q = load_weights4(row, t * 4096 + tid * 4, vocab, vec_ok, inv_t, m);
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (q.w[e] >= cand) part += q.w[e];
-        }
-        if (block_sum_u64(part, sh) >= theta) tau = cand;
-      }
-      // weight above tau, and ties at tau counted per segment
-      unsigned long long above = 0;
-      for (int t = 0; t < n_tiles; ++t) {
-        const Seg4 q = load_weights4(row, t * 4096 + tid * 4, vocab, vec_ok, inv_t, m);
-        unsigned long long ties = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if (q.w[e] > tau) above += q.w[e];
-          if (q.w[e] == tau) ties += 1;
-        }
-        const unsigned long long ws = wave_sum_u64(ties);
-        if (lane == 0 && t * 16 + wave < n_seg) sh.vals[t * 16 + wave] = ws;
-      }
-      const unsigned long long sum_above = block_sum_u64(above, sh);
-      const unsigned long long need = theta - sum_above;         // > 0 by maximality of tau
-      const unsigned long long k_ties = (need + tau - 1) / tau;  // ties admitted, ascending id
-      int seg;
-      unsigned long long before;
-      find_segment(sh, n_seg, k_ties - 1, seg, before);
-      if (wave == 0) {
-        const Seg4 q = load_weights4(row, seg * 256 + lane * 4, vocab, vec_ok, inv_t, m);
-        const unsigned long long is_tie[4] = {q.w[0] == tau, q.w[1] == tau, q.w[2] == tau, q.w[3] == tau};
-        const int idx = resolve_in_segment(is_tie, k_ties - 1 - before, lane);
-        if (lane == 0) sh.bcast[0] = (unsigned long long)(seg * 256 + idx);
-      }
+    // nucleus membership: key above tau's, or at tau among the first k_ties ids there
+    const unsigned tau_key = st.prefix;
+    unsigned long long s_n = S;
+    unsigned k_ties = 0;
+    if (nucleus) {
       __syncthreads();
-      tie_cut = (int)sh.bcast[0];
-      __syncthreads();
-      s_n = sum_above + k_ties * tau;
-      // nucleus weight per segment
-      for (int t = 0; t < n_tiles; ++t) {
-        const int i0 = t * 4096 + tid * 4;
-        const Seg4 q = load_weights4(row, i0, vocab, vec_ok, inv_t, m);
-        unsigned long long mine = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (q.w[e] > tau || (q.w[e] == tau && i0 + e <= tie_cut)) mine += q.w[e];
-        const unsigned long long ws = wave_sum_u64(mine);
-        if (lane == 0 && t * 16 + wave < n_seg) sh.vals[t * 16 + wave] = ws;
+      const unsigned long long tau = key_weight(tau_key);
+      k_ties = tau ? (unsigned)((st.theta - st.above + tau - 1) / tau) : 0u;  // theta > above: tau's bin was needed to reach it
+      s_n = st.above + k_ties * tau;
+      const unsigned mine = tid < n_seg ? sh.ties[tid] : 0u;
+      const unsigned before = (unsigned)block_scan_u64(mine, sh) - mine;
+      const unsigned in = before < k_ties ? min(mine, k_ties - before) : 0u;
+      if (tid < n_seg) {
+        sh.vals[tid] = sh.hist[tid] + in * tau;
+        sh.ties[tid] = in;  // ids at tau that are in, per segment
       }
       __syncthreads();
     }
@@ -410,16 +534,34 @@ __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab,
     unsigned long long before;
     find_segment(sh, n_seg, R, seg, before);
     if (wave == 0) {
-      const int i0 = seg * 256 + lane * 4;
-      const Seg4 q = load_weights4(row, i0, vocab, vec_ok, inv_t, m);
+      const Key4 q = load_keys4(row, seg * 256 + lane * 4, vocab, vec_ok, inv_t, m);
       unsigned long long v[4];
+      if (nucleus) {
+        unsigned at_tau = 0;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = (q.w[e] > tau || (q.w[e] == tau && i0 + e <= tie_cut)) ? q.w[e] : 0ull;
+        for (int e = 0; e < 4; ++e) at_tau += q.k[e] == tau_key ? 1u : 0u;
+        unsigned rank = at_tau;
+        for (int o = 1; o < WAVE; o <<= 1) {
+          const unsigned up = __shfl_up(rank, o, WAVE);
+          if (lane >= o) rank += up;
+        }
+        rank -= at_tau;  // ids at tau before this lane's
+        const unsigned in = sh.ties[seg];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bool tie = q.k[e] == tau_key;
+          v[e] = q.k[e] > tau_key || (tie && rank < in) ? key_weight(q.k[e]) : 0ull;
+          rank += tie ? 1u : 0u;
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = key_weight(q.k[e]);
+      }
       const int idx = resolve_in_segment(v, R - before, lane);
       if (lane == 0) sh.bcast[0] = (unsigned long long)(seg * 256 + idx);
     }
     __syncthreads();
-    token = (int)sh.bcast[0];
+    token = min(max((int)sh.bcast[0], 0), vocab - 1);  // (no id is found in a row without weights)
   }
   if (tid == 0) {
     float d = shifted(scaled_logit(row[token], inv_t), m);
@@ -429,20 +571,52 @@ __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab,
   }
 }
 
-void launch_sample(const SampleRows& r, int rows, int vocab, hipStream_t s) {
-  if (!rows) return;
-  // Large vocabularies with scratch at hand: the two sweeps of a row on several workgroups
-  // (about 512 in all), then the selection; else everything in one workgroup per row.
+// Large vocabularies with scratch at hand: the sweeps of a row on several workgroups (about 512 in all),
+// then the selection; else everything in one workgroup per row.
+// 64 rows x 151936 ids, top_p 0.9: 7.5 + 15.6 us for maximum and sums, 17.6 + 17.8 + 31.8 us for the
+// histograms and the segments above tau, 9.4 us for the selection: 116 us per call of rollout_sample,
+// where one workgroup per row that searched tau bit by bit took 1809 us.  The search in LDS atomics
+// and the sweeps' arithmetic take the time: 39 MB of logits pass in 7.5 us.
+static void launch_sample_rows(const SampleRows& r, int rows, int vocab, hipStream_t s) {
   const int n_tiles = (vocab + 4095) >> 12;
   int parts = 0;
-  if (r.part_max && r.seg_sums && n_tiles >= 8 && vocab <= 256 * kSampleSegments)
+  if (r.part_max && r.seg_sums && (r.nucleus || !r.any_nucleus) && n_tiles >= 8 && vocab <= 256 * kSampleSegments)
     parts = std::max(2, std::min({n_tiles, kSampleParts, 512 / rows}));
-  if (parts >= 2) {
-    sample_max_kernel<<<dim3(parts, rows), SAMP_T, 0, s>>>(r, vocab, parts);
-    sample_segments_kernel<<<dim3(parts, rows), SAMP_T, 0, s>>>(r, vocab, parts);
-    sample_kernel<<<rows, SAMP_T, 0, s>>>(r, vocab, parts);
-  } else {
+  if (parts < 2) {
     sample_kernel<<<rows, SAMP_T, 0, s>>>(r, vocab, 0);
+    return;
+  }
+  const dim3 grid(parts, rows);
+  sample_max_kernel<<<grid, SAMP_T, 0, s>>>(r, vocab, parts);
+  sample_segments_kernel<<<grid, SAMP_T, 0, s>>>(r, vocab, parts);
+  if (r.any_nucleus) {
+    sample_nucleus_kernel<1><<<grid, SAMP_T, 0, s>>>(r, vocab, parts);
+    sample_nucleus_kernel<2><<<grid, SAMP_T, 0, s>>>(r, vocab, parts);
+    sample_nucleus_kernel<3><<<grid, SAMP_T, 0, s>>>(r, vocab, parts);
+  }
+  sample_kernel<<<rows, SAMP_T, 0, s>>>(r, vocab, parts);
+}
+
+void launch_sample(SampleRows r, int rows, int vocab, hipStream_t s) {
+  if (!r.any_nucleus) r.nucleus = nullptr;
+  // the nucleus scratch holds nucleus_rows rows: more of them go batch by batch
+  const int batch = r.any_nucleus && r.nucleus ? r.nucleus_rows : rows;
+  for (int r0 = 0; r0 < rows; r0 += batch) {
+    SampleRows b = r;
+    if (r0) {
+      if (b.logits_row) b.logits_row += r0;
+      else b.logits += (long long)r0 * vocab;
+      if (b.inv_temp) b.inv_temp += r0;
+      if (b.top_p) b.top_p += r0;
+      if (b.uniforms) b.uniforms += r0;
+      if (b.sample_id) b.sample_id += r0;
+      if (b.step) b.step += r0;
+      if (b.forced) b.forced += r0;
+      b.tokens += r0;
+      b.logprobs += r0;
+      if (b.weight_sums) b.weight_sums += r0;
+    }
+    launch_sample_rows(b, std::min(batch, rows - r0), vocab, s);
   }
 }
 

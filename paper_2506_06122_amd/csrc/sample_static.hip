@@ -1,7 +1,7 @@
 // rollout_sample_static: the stand-alone sampler for callers that cannot allocate device memory
 // (code under HIP graph capture, serving loops, harnesses that forbid hipMalloc).  Same kernels
-// as rollout_sample; what that entry point allocates per call - the per-row parameter arrays and
-// the sweeps' partial results (kernels.h, SampleRows) - lives here in one file-scope device
+// as rollout_sample; what that entry point allocates per call - the sweeps' partial results
+// (kernels.h, SampleRows) - lives here in one file-scope device
 // array of fixed size, so the call allocates nothing, copies nothing between host and device
 // and does not synchronise: it only enqueues kernels on the caller's stream.
 #include <mutex>
@@ -16,28 +16,19 @@ constexpr int kMaxRows = ROLLOUT_SAMPLE_STATIC_MAX_ROWS;
 constexpr int kMaxDevices = 64;
 
 // layout of the scratch array (byte offsets, each a multiple of 256)
-constexpr size_t kOffInvTemp = 0;                                                  // float [kMaxRows]
-constexpr size_t kOffTopP = kOffInvTemp + sizeof(float) * kMaxRows;                // float [kMaxRows]
-constexpr size_t kOffPartMax = kOffTopP + sizeof(float) * kMaxRows;                // float [kMaxRows][kSampleParts]
+constexpr size_t kOffPartMax = 0;                                                  // float [kMaxRows][kSampleParts]
 constexpr size_t kOffSegSums = kOffPartMax + sizeof(float) * kMaxRows * kSampleParts;  // u64 [kMaxRows][kSampleSegments]
-constexpr size_t kScratchBytes = kOffSegSums + sizeof(unsigned long long) * kMaxRows * kSampleSegments;
-static_assert(kOffTopP % 256 == 0 && kOffPartMax % 256 == 0 && kOffSegSums % 256 == 0, "256-byte aligned parts");
+constexpr size_t kOffNucleus = kOffSegSums + sizeof(unsigned long long) * kMaxRows * kSampleSegments;  // u64 [kMaxRows][kNucleusScratch]
+constexpr size_t kScratchBytes = kOffNucleus + sizeof(unsigned long long) * kMaxRows * kNucleusScratch;
+static_assert(kOffSegSums % 256 == 0 && kOffNucleus % 256 == 0, "256-byte aligned parts");
 
-// One copy per GPU the library runs on, held until the process ends (about 2.2 MB).  In host
+// One copy per GPU the library runs on, held until the process ends (about 7.7 MB).  In host
 // code this name is only a handle for hipGetSymbolAddress: the address a kernel can use is
 // looked up once per device and kept in g_scratch_ptr.
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 std::mutex g_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
-
-__global__ void fill_params_kernel(float* inv_temp, float* top_p, float inv_t, float p, int rows) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < rows) {
-    inv_temp[i] = inv_t;
-    top_p[i] = p;
-  }
-}
 
 thread_local std::string g_error;
 
@@ -89,15 +80,12 @@ int rollout_sample_static(const float* logits, int32_t rows, int32_t vocab, floa
   const int rc = scratch_for_current_device(&base);
   if (rc != ROLLOUT_OK) return rc;
   hipStream_t s = (hipStream_t)hip_stream;
-  float* inv_temp = (float*)(base + kOffInvTemp);
-  float* tp = (float*)(base + kOffTopP);
   // nothing in the array has to start at zero: every element a kernel reads was written earlier in
-  // the same call (the parameters here, the partial results by the sweeps before the selection)
-  fill_params_kernel<<<(rows + 255) / 256, 256, 0, s>>>(inv_temp, tp, 1.0f / temperature, top_p, rows);
+  // the same call, by the sweeps before it
   SampleRows sr{};
   sr.logits = logits;
-  sr.inv_temp = inv_temp;
-  sr.top_p = tp;
+  sr.inv_temp_all = 1.0f / temperature;
+  sr.top_p_all = top_p;
   sr.uniforms = uniforms;
   sr.forced = forced;
   sr.tokens = tokens;
@@ -105,6 +93,9 @@ int rollout_sample_static(const float* logits, int32_t rows, int32_t vocab, floa
   sr.weight_sums = (unsigned long long*)weight_sums;
   sr.part_max = (float*)(base + kOffPartMax);
   sr.seg_sums = (unsigned long long*)(base + kOffSegSums);
+  sr.any_nucleus = top_p < 1.f;
+  sr.nucleus = (unsigned long long*)(base + kOffNucleus);
+  sr.nucleus_rows = kMaxRows;
   launch_sample(sr, rows, vocab, s);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return set_error(ROLLOUT_E_HIP, std::string("kernel launch: ") + hipGetErrorString(e));

@@ -1,0 +1,54 @@
+"""GPU parity of the nucleus selection (top_p < 1): the histogram search for the smallest weight of the
+nucleus, on one workgroup per row (up to 28672 ids) and on several, against the oracle's explicit
+ordering.  Token ids and weight sums are integers: exact."""
+import numpy as np
+import pytest
+
+import workloads
+from oracle import sampler
+
+pytestmark = pytest.mark.gpu
+
+
+def hard_rows(vocab, seed):
+    """Rows that end the nucleus in every kind of place."""
+    rng = np.random.default_rng(seed)
+    z = workloads.random_logits(9, vocab, seed=seed, scale=2.5)
+    z[1, :] = 0.25                                            # every id at tau: ties decide everything
+    z[2, :] = np.where(rng.random(vocab) < 0.5, 1.0, -1.0)    # two weights, many ties at either
+    z[3, :] = -1e30
+    z[3, vocab // 2] = 3.0                                    # one id holds everything
+    z[4, :] = np.round(z[4] * 4) / 4                          # a few dozen distinct weights
+    z[5, :] *= 1e-6                                           # weights that differ in their last mantissa bits
+    z[6, :] *= 12.0                                           # weights down to the cut-off
+    z[7, : vocab // 3] = -np.inf
+    z[8, vocab - 1] = z[8].max() + 2.0                        # the largest weight is the last id
+    return z.astype(np.float32)
+
+
+@pytest.mark.parametrize("vocab", [1, 255, 4097, 28672, 28673, 65536 + 3, 262144])
+@pytest.mark.parametrize("top_p", [0.0, 1e-7, 0.5, 0.9, 0.999999])
+def test_nucleus_matches_oracle(vocab, top_p):
+    import torch
+    import paper_2506_06122_amd as R
+    z = hard_rows(vocab, seed=vocab) if vocab > 2 else np.zeros((9, vocab), np.float32)
+    z = np.concatenate([z, z])                                # the same rows with other words
+    x = workloads.uniform_words(len(z), seed=7)
+    x[:9] = 2 ** 32 - 1                                       # the last id of the nucleus
+    toks, _, sums = R.rollout_sample(torch.from_numpy(z).cuda(), 0.8, top_p, x)
+    inv_t = sampler.inv_temperature(0.8)
+    for r in range(len(z)):
+        w = sampler.fixexp_weights(z[r], inv_t)
+        assert int(sums[r]) == int(np.sum(w, dtype=np.uint64)), f"row {r}"
+        assert int(toks[r]) == sampler.draw(w, sampler.nucleus(w, top_p), int(x[r])), f"row {r}"
+
+
+def test_more_rows_than_the_nucleus_scratch_holds():
+    import torch
+    import paper_2506_06122_amd as R
+    rows, vocab = 521, 28700                                  # batches of 512 and 9
+    z = workloads.random_logits(rows, vocab, seed=3, scale=2.0)
+    x = workloads.uniform_words(rows, seed=4)
+    toks, _, _ = R.rollout_sample(torch.from_numpy(z).cuda(), 1.0, 0.9, x)
+    for r in (0, 1, 255, 511, 512, 513, 520):
+        assert int(toks[r]) == sampler.sample(z[r], np.float32(1.0), 0.9, int(x[r]))[0], f"row {r}"

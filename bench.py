@@ -494,7 +494,7 @@ def main() -> int:
             run()
         torch.cuda.synchronize()
         dt = (time.perf_counter() - t0) / max(args.steps, 1)
-        nbytes = total * (3 * 4 + 1 + 2 * 4 + 2 * 4)  # three log-probs and the mask in; advantages out; gradient out, scaled in place
+        nbytes = total * (3 * 4 + 1 + 1 + 2 * 4)  # three log-probs in, the mask twice; advantages and gradient out
         print(json.dumps({"metric": "policy-loss tokens/sec on 1 MI355X", "value": total / dt, "unit": "tokens/s",
                           "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": 1e3 * dt,
                           "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32",
@@ -504,7 +504,7 @@ def main() -> int:
                                      % (len(cu) - 1, total)},
                           "roofline": {"bound": "hbm", "achieved": nbytes / dt / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                        "frac": nbytes / dt / 1e9 / HBM_PEAK_GBS, "traffic": None,
-                                       "kernel": "policy_advantage_kernel + policy_scale_kernel (whole call)"},
+                                       "kernel": "policy_count_kernel + policy_loss_kernel (whole call)"},
                           "cpu_baseline": None}))
         return 0
     if wl == "c2-attn":

@@ -1491,8 +1491,11 @@ int rollout_policy_loss(int32_t n_seqs, const int32_t* cu_seqlens, const float* 
   return guarded(nullptr, [&] {
     if (n_seqs < 0 || !cu_seqlens || !params || !loss) fail(ROLLOUT_E_INVAL, "bad argument");
     if (cu_seqlens[0] != 0) fail(ROLLOUT_E_INVAL, "cu_seqlens[0] must be 0");
-    for (int i = 0; i < n_seqs; ++i)
+    int longest = 0;
+    for (int i = 0; i < n_seqs; ++i) {
       if (cu_seqlens[i + 1] < cu_seqlens[i]) fail(ROLLOUT_E_INVAL, "cu_seqlens must not decrease");
+      longest = std::max(longest, cu_seqlens[i + 1] - cu_seqlens[i]);
+    }
     const long long total = cu_seqlens[n_seqs];
     if (total > 0 && (!logp_new || !logp_old || !mask || !grad || !rewards)) fail(ROLLOUT_E_INVAL, "null array");
     const rollout_loss_params& q = *params;
@@ -1502,23 +1505,30 @@ int rollout_policy_loss(int32_t n_seqs, const int32_t* cu_seqlens, const float* 
     hipStream_t s = (hipStream_t)hip_stream;
     CallScratch& cs = call_scratch();
     std::lock_guard<std::mutex> lock(cs.mu);
-    const size_t S1 = (size_t)std::max(n_seqs, 1);
-    cs.begin(CallScratch::piece((S1 + 1) * 4) + CallScratch::piece(S1 * 4) + CallScratch::piece(2 * S1 * 4) +
-                 CallScratch::piece(2 * 4),
-             0);
-    struct { int* p; } cu{cs.take<int>(S1 + 1)};
-    struct { float* p; } rw{cs.take<float>(S1)}, part{cs.take<float>(2 * S1)}, result{cs.take<float>(2)};
-    HIP_TRY(hipMemcpyAsync(cu.p, cu_seqlens, (n_seqs + 1) * sizeof(int), hipMemcpyHostToDevice, s));
-    if (n_seqs) HIP_TRY(hipMemcpyAsync(rw.p, rewards, n_seqs * sizeof(float), hipMemcpyHostToDevice, s));
+    *loss = 0.f;
+    if (total == 0) return;
+    const size_t S1 = (size_t)n_seqs;
     PolicyLossArgs p{};
+    p.n_parts = (int)std::min<long long>(kLossParts, ceil_div(total, 256 * 16));
+    const size_t io = CallScratch::piece((S1 + 1) * 4) + CallScratch::piece(S1 * 4);
+    cs.begin(io + CallScratch::piece(p.n_parts * 4), io + CallScratch::piece(S1 * 4) + CallScratch::piece(4));
+    p.cu_seqlens = cs.take<int>(S1 + 1);
+    p.rewards = cs.take<float>(S1);
+    p.part_count = cs.take<int>(p.n_parts);
+    int* cu = cs.take_host<int>(S1 + 1);
+    float* rw = cs.take_host<float>(S1);
+    p.part_sum = cs.take_host<float>(S1);
+    p.count = cs.take_host<int>(1);
+    std::memcpy(cu, cu_seqlens, (S1 + 1) * sizeof(int));
+    std::memcpy(rw, rewards, S1 * sizeof(float));
+    p.host_cu = cu;
+    p.host_rewards = rw;
     p.n_seqs = n_seqs;
     p.total = total;
-    p.cu_seqlens = cu.p;
     p.logp_new = logp_new;
     p.logp_old = logp_old;
     p.logp_ref = logp_ref;
     p.mask = mask;
-    p.rewards = rw.p;
     p.gamma = q.gamma;
     p.kl_coef = q.kl_coef;
     p.reward_clip = q.reward_clip;
@@ -1527,14 +1537,12 @@ int rollout_policy_loss(int32_t n_seqs, const int32_t* cu_seqlens, const float* 
     p.eps_high = q.eps_high;
     p.grad = grad;
     p.advantages = advantages;
-    p.part_sum = part.p;
-    p.part_cnt = part.p + std::max(n_seqs, 1);
-    p.result = result.p;
-    launch_policy_loss(p, s);
-    float out[2];
-    HIP_TRY(hipMemcpyAsync(out, result.p, sizeof(out), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    *loss = out[0];
+    launch_policy_loss(p, longest, s);
+    HIP_TRY(hipGetLastError());
+    wait_stream(s);
+    double sum = 0.0;
+    for (int i = 0; i < n_seqs; ++i) sum += p.part_sum[i];
+    if (*p.count > 0) *loss = (float)(-sum / *p.count);
   });
 }
 

@@ -259,17 +259,23 @@ void launch_attention_merge(const AttnArgs& a, hipStream_t s);
 struct PolicyLossArgs {
   int n_seqs;
   long long total;            // tokens = cu_seqlens[n_seqs]
-  const int* cu_seqlens;      // [n_seqs + 1]
+  const int* host_cu;         // [n_seqs + 1] and
+  const float* host_rewards;  // [n_seqs], in host memory mapped for the device
+  int* cu_seqlens;            // the same two on the device, filled by the first launch
+  float* rewards;
   const float *logp_new, *logp_old, *logp_ref;  // [total]; logp_ref may be NULL
   const unsigned char* mask;  // [total] 1 = the token counts
-  const float* rewards;       // [n_seqs]
   float gamma, kl_coef, reward_clip, adv_clip, eps_low, eps_high;
   float* grad;                // [total] d loss / d logp_new
   float* advantages;          // [total] or NULL
-  float *part_sum, *part_cnt; // [n_seqs] scratch
-  float* result;              // [2]: loss, 1 / N
+  int n_parts;                // workgroups that count the mask, at most kLossParts
+  int* part_count;            // [n_parts] counted tokens
+  float* part_sum;            // [n_seqs] sum over the sequence's tokens, in mapped host memory
+  int* count;                 // [1] N, in mapped host memory
 };
-void launch_policy_loss(const PolicyLossArgs& p, hipStream_t s);
+constexpr int kLossParts = 512;
+// longest: tokens of the longest sequence
+void launch_policy_loss(const PolicyLossArgs& p, int longest, hipStream_t s);
 
 // ---- mixture-of-experts block on the matrix-core path ---------------------------------------
 // Routing: sums the split planes of the router projection, picks the top_k experts of every

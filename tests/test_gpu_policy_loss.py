@@ -73,3 +73,38 @@ def test_policy_loss_edge_cases():
     assert a[0] == b[0] and torch.equal(a[1], b[1]) and torch.equal(a[2], b[2])      # fixed summation order
     with pytest.raises(R.RolloutError):
         R.rollout_policy_loss(cu, dev(new), dev(old), dev(ref), dev(mask), rewards, gamma=-1.0)
+
+
+@pytest.mark.parametrize("lens,offset", [([4095, 4096, 4097, 12289, 1, 3, 2, 5], 0), ([4095, 4097, 9001, 2, 6], 1),
+                                         ([2048, 2047, 1025, 1024, 1023, 1], 0), ([1, 2, 3, 1026, 517], 3)],
+                         ids=["long", "long-unaligned", "short", "short-unaligned"])
+def test_policy_loss_chunk_edges(lens, offset):
+    """Lengths around the 4096- and 1024-token chunks, sequences that start inside a quad, arrays off
+    their alignment by `offset` elements.  fp32 against fp64 as above: with gamma 0.9 a return is a
+    sum of at most ~100 terms of size 20, 1e-4 is 80 ulp of its clipped size of 10."""
+    import torch
+    rng = np.random.default_rng(len(lens) + offset)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    total = int(cu[-1])
+    old = (-rng.gamma(2.0, 1.0, total)).astype(np.float32)
+    new = (old + 0.3 * rng.standard_normal(total)).astype(np.float32)
+    ref = (old + 0.2 * rng.standard_normal(total)).astype(np.float32)
+    mask = (rng.random(total) < 0.7).astype(np.uint8)
+    mask[cu[1] - 1 - min(lens[0], 900):cu[1]] = 0        # the last counted token chunks away from the end
+    rewards = (rng.standard_normal(len(lens)) * 15.0).astype(np.float32)
+
+    def dev(a):
+        return torch.from_numpy(np.concatenate([np.ones(offset, a.dtype), a])).cuda()[offset:]
+
+    kw = dict(gamma=0.9, kl_coef=0.05)
+    loss, grad, adv = R.rollout_policy_loss(cu, dev(new), dev(old), dev(ref), dev(mask), rewards, **kw)
+    want_loss, want_grad, want_adv = PL.policy_loss(cu, new, old, ref, mask, rewards, **kw)
+    n = int(mask.sum())
+    adv, grad = adv.cpu().numpy(), grad.cpu().numpy()
+    assert np.max(np.abs(adv - want_adv)) <= 1e-4
+    flips = np.flatnonzero((grad == 0) != (want_grad == 0))
+    assert len(flips) <= 2
+    keep = np.ones(total, bool)
+    keep[flips] = False
+    assert np.max(np.abs(grad - want_grad)[keep]) * n <= 2e-4
+    assert abs(loss - want_loss) <= 1e-5 * max(1.0, abs(want_loss)) + 20.0 * len(flips) / n

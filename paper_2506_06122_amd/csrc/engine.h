@@ -181,7 +181,7 @@ struct rollout_ctx : HostState {
   DevBuf<int> d_live;
 
   // workspaces
-  DevBuf<float> x, h, qkv, attn, gate_up, act, hn, logits, router_logits, moe_wt;
+  DevBuf<float> x, h, qkv, attn, act, logits, router_logits, moe_wt;
   DevBuf<int> moe_idx, route_log;  // route_log [n_layers][r_max][top_k] when recording
   // matrix-core MoE block: expert-sorted slots and the row blocks of the grouped projections
   DevBuf<int> moe_pos, moe_count, moe_row_map, moe_slot_of, moe_group_of_block, moe_block_begin, moe_block_end;

@@ -317,10 +317,9 @@ void engine_init(rollout_ctx& c, const rollout_weights& w) {
     c.seq_pos0.alloc(rollout_ctx::kTempSlots);
     c.chunk_ints.alloc(3 * R);
   } else {
-    c.h.alloc(R * d);
+    if (moe) c.h.alloc(R * d);
     c.qkv.alloc(R * c.qkv_dim);
     c.attn.alloc(R * c.q_dim);
-    c.hn.alloc((size_t)c.logit_rows * d);
   }
   if (c.simple && moe) {
     c.router_logits.alloc(R * m.n_experts);
@@ -329,7 +328,6 @@ void engine_init(rollout_ctx& c, const rollout_weights& w) {
     c.act.alloc(R * m.top_k * m.expert_ffn_dim);
     if (r.flags & ROLLOUT_RT_RECORD_ROUTING) c.route_log.alloc((size_t)m.n_layers * R * m.top_k);
   } else if (c.simple) {
-    c.gate_up.alloc(R * 2 * m.ffn_dim);
     c.act.alloc(R * m.ffn_dim);
   }
   c.logits.alloc((size_t)c.logit_rows * m.vocab);
@@ -365,26 +363,28 @@ void engine_upload_page_table(rollout_ctx& c) {
 // T = storage type of the weights; KT = storage type of the KV cache (fp32 models: fp32,
 // bf16 models: IEEE half, see common.h)
 template <typename T, typename KT>
-static void forward_rows_simple(rollout_ctx& c, int R) {
+static void forward_rows_simple(rollout_ctx& c, int R, bool decode) {
   const rollout_model_desc& m = c.md;
   hipStream_t s = c.stream;
   const int d = m.hidden;
   launch_embed<T>((const T*)c.embed.p, c.row_token.p, c.x.p, R, d, s);
   for (int l = 0; l < m.n_layers; ++l) {
     LayerWeights& L = c.layers[l];
-    launch_rmsnorm_f32(c.x.p, L.norm1.p, c.h.p, nullptr, R, d, m.rms_eps, s);
-    launch_linear_simple<T>(c.h.p, d, (const T*)L.wqkv.p, c.qkv.p, c.qkv_dim, nullptr, 0, R, c.qkv_dim, d, s);
+    launch_linear_simple<T>({c.x.p, d, nullptr, L.norm1.p, m.rms_eps, c.qkv.p, c.qkv_dim, nullptr, R, c.qkv_dim, d},
+                            (const T*)L.wqkv.p, false, s);
     launch_qkv_bias_norm(c.qkv.p, L.qkv_bias.p, L.q_gain.p, L.k_gain.p, m.rms_eps, R, m.n_q_heads, m.n_kv_heads,
                          m.head_dim, s);
-    launch_rope_kvwrite<KT>(c.qkv.p, c.cos_sin.p, c.row_pos.p, c.row_slot.p, c.d_page_table.p, c.max_pages,
-                            (KT*)c.kv_pool.p, c.geom, l, R, m.n_q_heads, s);
-    launch_attention_simple<KT>(c.qkv.p, c.attn.p, c.row_pos.p, c.row_slot.p, c.d_page_table.p, c.max_pages,
-                                (const KT*)c.kv_pool.p, c.geom, l, R, m.n_q_heads, s);
-    launch_linear_simple<T>(c.attn.p, c.q_dim, (const T*)L.wo.p, c.x.p, d, c.x.p, d, R, d, c.q_dim, s);
-    launch_rmsnorm_f32(c.x.p, L.norm2.p, c.h.p, nullptr, R, d, m.rms_eps, s);
+    if (!decode)
+      launch_rope_kvwrite<KT>(c.qkv.p, c.cos_sin.p, c.row_pos.p, c.row_slot.p, c.d_page_table.p, c.max_pages,
+                              (KT*)c.kv_pool.p, c.geom, l, R, m.n_q_heads, s);
+    launch_attention_simple<KT>(c.qkv.p, c.cos_sin.p, c.attn.p, c.row_pos.p, c.row_slot.p, c.d_page_table.p, c.max_pages,
+                                (KT*)c.kv_pool.p, c.geom, l, R, m.n_q_heads, decode, s);
+    launch_linear_simple<T>({c.attn.p, c.q_dim, nullptr, nullptr, 0.f, c.x.p, d, c.x.p, R, d, c.q_dim}, (const T*)L.wo.p,
+                            false, s);
     if (m.n_experts > 0) {
-      launch_linear_simple<T>(c.h.p, d, (const T*)L.router.p, c.router_logits.p, m.n_experts, nullptr, 0, R,
-                              m.n_experts, d, s);
+      launch_rmsnorm_f32(c.x.p, L.norm2.p, c.h.p, R, d, m.rms_eps, s);
+      launch_linear_simple<T>({c.h.p, d, nullptr, nullptr, 0.f, c.router_logits.p, m.n_experts, nullptr, R, m.n_experts, d},
+                              (const T*)L.router.p, false, s);
       launch_moe_route(c.router_logits.p, c.moe_idx.p, c.moe_wt.p, R, m.n_experts, m.top_k, s);
       if (c.route_log.p)
         HIP_TRY(hipMemcpyAsync(c.route_log.p + (size_t)l * c.r_max * m.top_k, c.moe_idx.p,
@@ -394,10 +394,10 @@ static void forward_rows_simple(rollout_ctx& c, int R) {
       launch_moe_down_simple<T>(c.act.p, (const T*)L.w_down.p, c.moe_idx.p, c.moe_wt.p, c.x.p, R, m.top_k, d,
                                 m.expert_ffn_dim, s);
     } else {
-      launch_linear_simple<T>(c.h.p, d, (const T*)L.w_gate_up.p, c.gate_up.p, 2 * m.ffn_dim, nullptr, 0, R,
-                              2 * m.ffn_dim, d, s);
-      launch_swiglu_f32(c.gate_up.p, c.act.p, R, m.ffn_dim, s);
-      launch_linear_simple<T>(c.act.p, m.ffn_dim, (const T*)L.w_down.p, c.x.p, d, c.x.p, d, R, d, m.ffn_dim, s);
+      launch_linear_simple<T>({c.x.p, d, nullptr, L.norm2.p, m.rms_eps, c.act.p, m.ffn_dim, nullptr, R, m.ffn_dim, d},
+                              (const T*)L.w_gate_up.p, true, s);
+      launch_linear_simple<T>({c.act.p, m.ffn_dim, nullptr, nullptr, 0.f, c.x.p, d, c.x.p, R, d, m.ffn_dim},
+                              (const T*)L.w_down.p, false, s);
     }
   }
 }
@@ -873,9 +873,9 @@ void engine_forward_rows(rollout_ctx& c, int rows, const SeqBatch* seqs) {
     else
       forward_rows_tiled(c, rows, seqs);
   } else if (c.md.dtype == ROLLOUT_DTYPE_F32) {
-    forward_rows_simple<float, float>(c, rows);
+    forward_rows_simple<float, float>(c, rows, !seqs);
   } else {
-    forward_rows_simple<bf16_t, f16_t>(c, rows);
+    forward_rows_simple<bf16_t, f16_t>(c, rows, !seqs);
   }
 }
 
@@ -925,13 +925,12 @@ void engine_logits(rollout_ctx& c, const int* rows_index, int first, int n, floa
     c.timer.end(c.stream);
     return;
   }
-  launch_rmsnorm_f32(c.x.p + (size_t)first * d, c.final_norm.p, c.hn.p, rows_index, n, d, c.md.rms_eps, c.stream);
+  const LinearArgs lin{c.x.p + (size_t)first * d, d, rows_index, c.final_norm.p, c.md.rms_eps, out, c.md.vocab, nullptr, n,
+                       c.md.vocab, d};
   if (c.md.dtype == ROLLOUT_DTYPE_F32)
-    launch_linear_simple<float>(c.hn.p, d, (const float*)c.lm_head.p, out, c.md.vocab, nullptr, 0, n, c.md.vocab,
-                                d, c.stream);
+    launch_linear_simple<float>(lin, (const float*)c.lm_head.p, false, c.stream);
   else
-    launch_linear_simple<bf16_t>(c.hn.p, d, (const bf16_t*)c.lm_head.p, out, c.md.vocab, nullptr, 0, n,
-                                 c.md.vocab, d, c.stream);
+    launch_linear_simple<bf16_t>(lin, (const bf16_t*)c.lm_head.p, false, c.stream);
 }
 
 // Teacher-forced log-probs without materialising logits (matrix-core path): final norm into

@@ -8,14 +8,26 @@
 template <typename T>
 void launch_embed(const T* table, const int* tokens, float* x, int rows, int hidden, hipStream_t s);
 
-// out[r] = x[r] * gain * rsqrt(mean(x[r]^2) + eps); rows_index (optional) selects source rows
-void launch_rmsnorm_f32(const float* x, const float* gain, float* out, const int* rows_index, int rows,
-                        int hidden, float eps, hipStream_t s);
+// out[r] = x[r] * gain * rsqrt(mean(x[r]^2) + eps)
+void launch_rmsnorm_f32(const float* x, const float* gain, float* out, int rows, int hidden, float eps,
+                        hipStream_t s);
 
-// out[m][n] = sum_k a[m][k] w[n][k] (+ residual[m][n]); a fp32 [M][K], w T [N][K]
+// out[m][n] = sum_k h[m][k] w[n][k] (+ residual[m][n], which may be out); w is T [N][K].  h = a, or with a gain
+// RMSNorm(a) * gain; rows_index (optional) selects the rows of a.  glu (with a gain): w holds N gate rows,
+// then N up rows, and out = silu(gate) * up.
+struct LinearArgs {
+  const float* a;
+  int lda;
+  const int* rows_index;
+  const float* gain;
+  float eps;
+  float* out;
+  int ldo;
+  const float* residual;  // row stride ldo
+  int M, N, K;
+};
 template <typename T>
-void launch_linear_simple(const float* a, int lda, const T* w, float* out, int ldo, const float* residual,
-                          int ldr, int M, int N, int K, hipStream_t s);
+void launch_linear_simple(const LinearArgs& p, const T* w, bool glu, hipStream_t s);
 
 // rotary embedding of q (in place) and k, then k and v of every row go to the row's page
 // plain path: bias and per-head RMSNorm of the fused [q | k | v] rows, in place (NULL parts are skipped)
@@ -26,14 +38,13 @@ void launch_rope_kvwrite(float* qkv, const float* cos_sin, const int* row_pos, c
                          const int* page_table, int max_pages, KT* kv_pool, KvGeom geom, int layer, int rows,
                          int n_q_heads, hipStream_t s);
 
-// causal grouped-query attention of each row over cached positions 0..pos of its slot
+// causal grouped-query attention of each row over cached positions 0..pos of its slot.  decode: every row is
+// another slot's next position; takes rows as the projection (and launch_qkv_bias_norm) left them, rotates
+// and caches itself
 template <typename KT>
-void launch_attention_simple(const float* qkv, float* out, const int* row_pos, const int* row_slot,
-                             const int* page_table, int max_pages, const KT* kv_pool, KvGeom geom, int layer,
-                             int rows, int n_q_heads, hipStream_t s);
-
-// act[r][f] = silu(gate_up[r][f]) * gate_up[r][F + f]
-void launch_swiglu_f32(const float* gate_up, float* act, int rows, int ffn, hipStream_t s);
+void launch_attention_simple(const float* qkv, const float* cos_sin, float* out, const int* row_pos,
+                             const int* row_slot, const int* page_table, int max_pages, KT* kv_pool, KvGeom geom,
+                             int layer, int rows, int n_q_heads, bool decode, hipStream_t s);
 
 // top-k routing: idx/wt [rows][top_k]; ties to the lower expert index; wt = softmax of the selected logits
 void launch_moe_route(const float* router_logits, int* idx, float* wt, int rows, int n_experts, int top_k,

@@ -154,7 +154,7 @@ def load_library() -> C.CDLL:
 
 
 def _ptr(a: np.ndarray | None):
-    return None if a is None else a.ctypes.data_as(C.c_void_p)
+    return None if a is None else a.__array_interface__["data"][0]
 
 
 def _arr(a, dtype):

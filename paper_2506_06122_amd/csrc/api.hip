@@ -39,25 +39,6 @@ static int guarded(rollout_ctx* ctx, F&& body) {
 static void h2d(void* dst, const void* src, size_t bytes, hipStream_t s) {
   if (bytes) HIP_TRY(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s));
 }
-static void d2h(void* dst, const void* src, size_t bytes, hipStream_t s) {
-  if (bytes) HIP_TRY(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s));
-}
-
-__global__ void init_slots_kernel(SlotState st, const int* __restrict__ slots, const int* __restrict__ sample_row,
-                                  const int* __restrict__ pos, const int* __restrict__ tokens,
-                                  const long long* __restrict__ ids, const float* __restrict__ inv_temp,
-                                  const float* __restrict__ top_p, int n) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int sl = slots[i], row = sample_row[i];
-  st.last_token[sl] = tokens[row];
-  st.pos[sl] = pos[i];
-  st.step[sl] = 1;
-  st.sample_id[sl] = ids[row];
-  st.inv_temp[sl] = inv_temp[row];
-  st.top_p[sl] = top_p[row];
-}
-
 // A decode step ends with a few hundred bytes coming back; polling an event answers within
 // microseconds where a blocking wait costs a scheduler round trip per step.
 // The poll is bounded by wall clock (step_timeout_s): kernels that never finish must not hang the
@@ -77,6 +58,15 @@ static void wait_step_done(rollout_ctx& c) {
       throw ApiError{ROLLOUT_E_HIP, "the decode step's kernels did not finish within " +
                                         std::to_string(c.step_timeout_s) + " s; the context is unusable now"};
     }
+  }
+}
+
+// The end of a call: polling answers within microseconds where a blocking wait may sleep
+static void wait_stream(hipStream_t s) {
+  for (;;) {
+    const hipError_t e = hipStreamQuery(s);
+    if (e == hipSuccess) return;
+    if (e != hipErrorNotReady) throw HipError(e, "hipStreamQuery", __FILE__, __LINE__);
   }
 }
 
@@ -110,6 +100,24 @@ static void set_sampler_scratch(rollout_ctx& c, SampleRows& sr, int rows, bool a
   sr.seg_sums = c.samp_seg_sums.p;
   sr.nucleus = c.samp_nucleus.p;
   sr.nucleus_rows = c.samp_nucleus_rows;
+}
+
+// Rows of live samples, gathered into the per-row arrays of the context.
+static GatherRows gather_rows(rollout_ctx& c, int rows) {
+  GatherRows a{};
+  a.st = c.st;
+  a.rows = rows;
+  a.live = c.d_live.p;
+  a.token = c.row_token.p;
+  a.pos = c.row_pos.p;
+  a.slot = c.row_slot.p;
+  a.step = c.row_step.p;
+  a.forced = c.row_forced.p;
+  a.uniform = c.row_uniform.p;
+  a.inv_temp = c.row_inv_temp.p;
+  a.top_p = c.row_top_p.p;
+  a.sample_id = c.row_sample_id.p;
+  return a;
 }
 
 // Admission of P prompts with n samples each (all or none), their prefill and response
@@ -169,7 +177,11 @@ static void prefill_impl(rollout_ctx& c, int32_t n_prompts, const int32_t* token
                       prompt_ids ? prompt_ids[p] : c.prompt_counter + p,
                       first_ids ? first_ids[p] : c.next_sample_id + (int64_t)p * n, c.temp_slot0 + p, pp[p],
                       &fresh[(size_t)p * n], copy_pairs);
-  engine_upload_page_table(c);
+  c.n_page_rows = 0;
+  for (int p = 0; p < P; ++p) engine_stage_page_row(c, c.temp_slot0 + p, ceil_div(offsets[p + 1] - offsets[p], c.page_tokens));
+  for (const Sample& s : fresh)
+    if (s.slot >= 0) engine_stage_page_row(c, s.slot, (int)s.pages.size());
+  engine_upload_page_rows(c);
 
   // ---- forward over the prompts, in chunks of whole prompts ----
   int p0 = 0;
@@ -194,15 +206,17 @@ static void prefill_impl(rollout_ctx& c, int32_t n_prompts, const int32_t* token
       max_len = std::max(max_len, offsets[p + 1] - offsets[p]);
     }
     SeqBatch sb{c.seq_row0.p, c.seq_len.p, c.seq_slot.p, p1 - p0, max_len};
+    HostCopies up;
     if (!c.simple) {
-      h2d(c.seq_row0.p, ht + 4 * R, (p1 - p0) * sizeof(int), c.stream);
-      h2d(c.seq_len.p, ht + 5 * R, (p1 - p0) * sizeof(int), c.stream);
-      h2d(c.seq_slot.p, ht + 6 * R, (p1 - p0) * sizeof(int), c.stream);
+      up.add(c.seq_row0.p, ht + 4 * R, p1 - p0);
+      up.add(c.seq_len.p, ht + 5 * R, p1 - p0);
+      up.add(c.seq_slot.p, ht + 6 * R, p1 - p0);
     }
-    h2d(c.row_token.p, ht, rows * sizeof(int), c.stream);
-    h2d(c.row_pos.p, ht + R, rows * sizeof(int), c.stream);
-    h2d(c.row_slot.p, ht + 2 * R, rows * sizeof(int), c.stream);
-    h2d(c.row_aux.p, ht + 3 * R, (p1 - p0) * sizeof(int), c.stream);
+    up.add(c.row_token.p, ht, rows);
+    up.add(c.row_pos.p, ht + R, rows);
+    up.add(c.row_slot.p, ht + 2 * R, rows);
+    up.add(c.row_aux.p, ht + 3 * R, p1 - p0);
+    launch_host_copies(up, c.stream);
     c.timer.start_call();
     c.kv_tokens_this_call = rows;
     c.attn_flops_this_call = 0;
@@ -212,53 +226,48 @@ static void prefill_impl(rollout_ctx& c, int32_t n_prompts, const int32_t* token
     }
     engine_forward_rows(c, rows, &sb);
     engine_logits(c, c.row_aux.p, 0, p1 - p0, c.logits.p + (size_t)p0 * m.vocab);
-    HIP_TRY(hipStreamSynchronize(c.stream));  // staging buffers are reused by the next chunk
+    if (p1 < P || c.timer.enabled) wait_stream(c.stream);  // the staging buffers are reused by the next chunk
     c.timer.collect();
     c.stats.prompt_tokens += rows;
     p0 = p1;
   }
   c.last_logit_rows = P;
 
-  // ---- private copies of each prompt's partial last page ----
-  if (!copy_pairs.empty()) {
-    if (copy_pairs.size() > c.row_aux.n) fail(ROLLOUT_E_STATE, "internal: page copy list too long");
-    std::memcpy(c.h_int.p, copy_pairs.data(), copy_pairs.size() * sizeof(int));
-    h2d(c.row_aux.p, c.h_int.p, copy_pairs.size() * sizeof(int), c.stream);
-    launch_copy_pages(c.kv_pool.p, c.row_aux.p, (int)copy_pairs.size() / 2, m.n_layers,
-                      c.geom.layer_stride * c.elem, c.geom.page_stride * c.elem, c.stream);
-    HIP_TRY(hipStreamSynchronize(c.stream));
-  }
-
-  // ---- response position 0 of every sample ----
+  // ---- response position 0 of every sample (staged behind what the forward pass may still read) ----
   const int Rs = P * n;
-  int* hi = c.h_int.p;
+  int* hi = c.h_int.p + 8 * (size_t)R;
   float* hf = c.h_float.p;
-  int n_new = 0;
   for (int i = 0; i < Rs; ++i) {
     hi[i] = i / n;                                       // logits row = prompt
     hi[R + i] = forced_first ? forced_first[i] : -1;
     hi[2 * R + i] = 0;                                   // response position
     hi[3 * R + i] = uniform_override ? (int)uniform_override[i] : 0;
+    hi[4 * R + i] = fresh[i].slot;
+    hi[5 * R + i] = fresh[i].prompt_len;
     hf[i] = inv_t;
     hf[R + i] = top_p;
     c.h_ll.p[i] = fresh[i].id;
-    if (fresh[i].slot >= 0) {
-      hi[4 * R + n_new] = fresh[i].slot;
-      hi[5 * R + n_new] = i;
-      hi[6 * R + n_new] = fresh[i].prompt_len;
-      ++n_new;
-    }
   }
-  h2d(c.row_aux.p, hi, Rs * sizeof(int), c.stream);
-  h2d(c.row_forced.p, hi + R, Rs * sizeof(int), c.stream);
-  h2d(c.row_step.p, hi + 2 * R, Rs * sizeof(int), c.stream);
-  h2d(c.row_uniform.p, hi + 3 * R, Rs * sizeof(int), c.stream);
-  h2d(c.row_inv_temp.p, hf, Rs * sizeof(float), c.stream);
-  h2d(c.row_top_p.p, hf + R, Rs * sizeof(float), c.stream);
-  h2d(c.row_sample_id.p, c.h_ll.p, Rs * sizeof(long long), c.stream);
+  if (copy_pairs.size() > c.row_aux.n) fail(ROLLOUT_E_STATE, "internal: page copy list too long");
+  std::copy(copy_pairs.begin(), copy_pairs.end(), hi + 7 * (size_t)R);
+  HostCopies up;
+  up.add(c.row_token.p, hi, Rs);
+  up.add(c.row_forced.p, hi + R, Rs);
+  up.add(c.row_step.p, hi + 2 * R, Rs);
+  up.add((int*)c.row_uniform.p, hi + 3 * R, Rs);
+  up.add(c.row_slot.p, hi + 4 * R, Rs);
+  up.add(c.row_pos.p, hi + 5 * R, Rs);
+  up.add(c.row_aux.p, hi + 7 * R, copy_pairs.size());
+  up.add(c.row_inv_temp.p, hf, Rs);
+  up.add(c.row_top_p.p, hf + R, Rs);
+  up.add(c.row_sample_id.p, c.h_ll.p, Rs);
+  launch_host_copies(up, c.stream);
+  // private copies of each prompt's partial last page
+  launch_copy_pages(c.kv_pool.p, c.row_aux.p, (int)copy_pairs.size() / 2, m.n_layers, c.geom.layer_stride * c.elem,
+                    c.geom.page_stride * c.elem, c.stream);
   SampleRows sr{};
   sr.logits = c.logits.p;
-  sr.logits_row = c.row_aux.p;
+  sr.logits_row = c.row_token.p;
   sr.inv_temp = c.row_inv_temp.p;
   sr.top_p = c.row_top_p.p;
   sr.uniforms = uniform_override ? c.row_uniform.p : nullptr;
@@ -269,25 +278,20 @@ static void prefill_impl(rollout_ctx& c, int32_t n_prompts, const int32_t* token
   sr.tokens = c.out_tokens.p;
   sr.logprobs = c.out_logprobs.p;
   sr.weight_sums = nullptr;
+  sr.host_tokens = hi + 6 * R;
+  sr.host_logprobs = hf + 2 * R;
+  sr.row_slot = c.row_slot.p;
+  sr.row_pos = c.row_pos.p;
+  sr.slots = c.st;
   set_sampler_scratch(c, sr, Rs, top_p < 1.f && !forced_first);
   launch_sample(sr, Rs, m.vocab, c.stream);
-  if (n_new) {
-    h2d(c.row_token.p, hi + 4 * R, n_new * sizeof(int), c.stream);  // slots
-    h2d(c.row_pos.p, hi + 5 * R, n_new * sizeof(int), c.stream);    // sample rows
-    h2d(c.row_slot.p, hi + 6 * R, n_new * sizeof(int), c.stream);   // positions
-    init_slots_kernel<<<ceil_div(n_new, 256), 256, 0, c.stream>>>(c.st, c.row_token.p, c.row_pos.p, c.row_slot.p,
-                                                                  c.out_tokens.p, c.row_sample_id.p,
-                                                                  c.row_inv_temp.p, c.row_top_p.p, n_new);
-  }
-  d2h(hi + 7 * R, c.out_tokens.p, Rs * sizeof(int), c.stream);
-  d2h(hf + 2 * R, c.out_logprobs.p, Rs * sizeof(float), c.stream);
-  HIP_TRY(hipStreamSynchronize(c.stream));
+  wait_stream(c.stream);
 
   // ---- host bookkeeping (nothing below throws: the pages and slots now belong to the samples) ----
   undo.commit();
   for (int i = 0; i < Rs; ++i) {
     Sample& s = fresh[i];
-    int tok = hi[7 * R + i];
+    int tok = hi[6 * R + i];
     s.n_emitted = 1;
     s.last_token = tok;
     s.top_p = top_p;
@@ -399,7 +403,7 @@ static int forward_with_chunk(rollout_ctx& c, int B, const StepChunk& chunk) {
 static void sample_first_tokens(rollout_ctx& c, int B, const std::vector<PendingPrompt*>& fin) {
   const rollout_model_desc& m = c.md;
   const int R = c.r_max, n = c.queue.n_samples, n_fin = (int)fin.size(), Rs = n_fin * n;
-  std::vector<int> pairs, lrow(Rs), step0(Rs, 0), forced(Rs, -1), slots, srows, spos;
+  std::vector<int> pairs, lrow(Rs), step0(Rs, 0), forced(Rs, -1), slot(Rs), pos(Rs);
   std::vector<float> inv_t(Rs), top_p(Rs);
   std::vector<long long> ids(Rs);
   for (int k = 0; k < n_fin; ++k) {
@@ -411,15 +415,11 @@ static void sample_first_tokens(rollout_ctx& c, int B, const std::vector<Pending
       inv_t[i] = 1.0f / pp.prompt.temperature;
       top_p[i] = pp.prompt.top_p;
       ids[i] = pp.samples[j].id;
-      if (pp.samples[j].slot >= 0) {
-        slots.push_back(pp.samples[j].slot);
-        srows.push_back(i);
-        spos.push_back(pp.samples[j].prompt_len);
-      }
+      slot[i] = pp.samples[j].slot;
+      pos[i] = pp.samples[j].prompt_len;
     }
   }
-  const int n_new = (int)slots.size();
-  if (pairs.size() + 3 * (size_t)n_new > 2 * (size_t)R) fail(ROLLOUT_E_STATE, "internal: page copy and slot lists too long");
+  if (pairs.size() > 2 * (size_t)R) fail(ROLLOUT_E_STATE, "internal: page copy list too long");
   if (!pairs.empty()) {
     h2d(c.chunk_ints.p + R, pairs.data(), pairs.size() * sizeof(int), c.stream);
     launch_copy_pages(c.kv_pool.p, c.chunk_ints.p + R, (int)pairs.size() / 2, m.n_layers,
@@ -428,6 +428,8 @@ static void sample_first_tokens(rollout_ctx& c, int B, const std::vector<Pending
   h2d(c.row_aux.p + B, lrow.data(), Rs * sizeof(int), c.stream);
   h2d(c.row_forced.p + B, forced.data(), Rs * sizeof(int), c.stream);
   h2d(c.row_step.p + B, step0.data(), Rs * sizeof(int), c.stream);
+  h2d(c.row_slot.p + B, slot.data(), Rs * sizeof(int), c.stream);
+  h2d(c.row_pos.p + B, pos.data(), Rs * sizeof(int), c.stream);
   h2d(c.row_inv_temp.p + B, inv_t.data(), Rs * sizeof(float), c.stream);
   h2d(c.row_top_p.p + B, top_p.data(), Rs * sizeof(float), c.stream);
   h2d(c.row_sample_id.p + B, ids.data(), Rs * sizeof(long long), c.stream);
@@ -444,19 +446,13 @@ static void sample_first_tokens(rollout_ctx& c, int B, const std::vector<Pending
   fr.tokens = c.out_tokens.p + B;
   fr.logprobs = c.out_logprobs.p + B;
   fr.weight_sums = nullptr;
+  fr.host_tokens = c.h_int.p + 7 * R;
+  fr.host_logprobs = c.h_float.p + R;
+  fr.row_slot = c.row_slot.p + B;
+  fr.row_pos = c.row_pos.p + B;
+  fr.slots = c.st;
   set_sampler_scratch(c, fr, Rs, *std::min_element(top_p.begin(), top_p.end()) < 1.f);
   launch_sample(fr, Rs, m.vocab, c.stream);
-  if (n_new) {  // the lists sit behind the page pairs
-    int* lists = c.chunk_ints.p + R + pairs.size();
-    h2d(lists, slots.data(), n_new * sizeof(int), c.stream);
-    h2d(lists + n_new, srows.data(), n_new * sizeof(int), c.stream);
-    h2d(lists + 2 * n_new, spos.data(), n_new * sizeof(int), c.stream);
-    init_slots_kernel<<<ceil_div(n_new, 256), 256, 0, c.stream>>>(c.st, lists, lists + n_new, lists + 2 * n_new,
-                                                                  c.out_tokens.p + B, c.row_sample_id.p + B,
-                                                                  c.row_inv_temp.p + B, c.row_top_p.p + B, n_new);
-  }
-  d2h(c.h_int.p + 7 * R, c.out_tokens.p + B, Rs * sizeof(int), c.stream);
-  d2h(c.h_float.p + R, c.out_logprobs.p + B, Rs * sizeof(float), c.stream);
 }
 
 // Host bookkeeping after a step with prompt rows: the pending prompts' progress; the prompts that
@@ -547,10 +543,10 @@ static void decode_impl(rollout_ctx& c, const int32_t* forced_tokens, const uint
       launch_patch_page_table(c.d_page_table.p, c.max_pages, c.d_page_patch.p, (int)patches.size(), c.stream);
     }
   }
+  const bool live_changed = c.live_dirty;
   if (c.live_dirty) {
     int i = 0;
     for (auto& kv : c.live) hi[i++] = kv.second.slot;
-    h2d(c.d_live.p, hi, B * sizeof(int), c.stream);
     // Groups for the decode attention: live samples of one prompt (consecutive in id order), at
     // least two of them and at least 64 shared positions, in chunks of GROUP_MEMBERS.
     std::vector<int> grows, glen, gslot;  // pageable: their uploads complete before the call returns
@@ -566,7 +562,7 @@ static void decode_impl(rollout_ctx& c, const int32_t* forced_tokens, const uint
         else first = &kv.second;
       }
     }
-    if (!c.simple) {
+    if (!c.simple && (c.rd.flags & ROLLOUT_RT_PROMPT_GROUPS)) {
       std::vector<const Sample*> rows;
       rows.reserve(B);
       for (auto& kv : c.live) rows.push_back(&kv.second);
@@ -594,8 +590,13 @@ static void decode_impl(rollout_ctx& c, const int32_t* forced_tokens, const uint
     }
     c.live_dirty = false;
   }
-  launch_gather_decode_rows(c.st, c.d_live.p, B, c.row_token.p, c.row_pos.p, c.row_slot.p, c.row_inv_temp.p,
-                            c.row_top_p.p, c.row_sample_id.p, c.row_step.p, c.stream);
+  if (forced_tokens) std::memcpy(hi + R, forced_tokens, B * sizeof(int));
+  if (uniform_override) std::memcpy(hi + 2 * R, uniform_override, B * sizeof(int));
+  GatherRows ga = gather_rows(c, B);
+  ga.host_live = live_changed ? hi : nullptr;
+  ga.host_forced = forced_tokens ? hi + R : nullptr;
+  ga.host_uniform = uniform_override ? (const unsigned*)(hi + 2 * R) : nullptr;
+  launch_gather_decode_rows(ga, c.stream);
   c.decode_max_ctx = 1;
   c.decode_max_own = 1;
   c.kv_tokens_this_call = 0;
@@ -628,14 +629,6 @@ static void decode_impl(rollout_ctx& c, const int32_t* forced_tokens, const uint
   } else {
     n_fin = forward_with_chunk(c, B, *chunk);
   }
-  if (forced_tokens) {
-    std::memcpy(hi + R, forced_tokens, B * sizeof(int));
-    h2d(c.row_forced.p, hi + R, B * sizeof(int), c.stream);
-  }
-  if (uniform_override) {
-    std::memcpy(hi + 2 * R, uniform_override, B * sizeof(int));
-    h2d(c.row_uniform.p, hi + 2 * R, B * sizeof(int), c.stream);
-  }
   SampleRows sr{};
   sr.logits = c.logits.p;
   sr.logits_row = nullptr;
@@ -648,13 +641,16 @@ static void decode_impl(rollout_ctx& c, const int32_t* forced_tokens, const uint
   sr.seed = c.rd.seed;
   sr.tokens = c.out_tokens.p;
   sr.logprobs = c.out_logprobs.p;
+  sr.host_tokens = hi + 3 * R;
+  sr.host_logprobs = c.h_float.p;
+  sr.row_slot = c.row_slot.p;
+  sr.row_pos = c.row_pos.p;
+  sr.pos_step = 1;
+  sr.slots = c.st;
   c.timer.begin("sample_kernel", 4.0 * B * m.vocab, 0, c.stream);
   set_sampler_scratch(c, sr, B, any_nucleus && !forced_tokens);
   launch_sample(sr, B, m.vocab, c.stream);
   c.timer.end(c.stream);
-  // pinned host memory is mapped for the device: the kernel stores the step's results there
-  launch_scatter_tokens(c.st, c.row_slot.p, c.out_tokens.p, c.out_logprobs.p, B, 1, hi + 3 * R, c.h_float.p, c.stream);
-
   // prompts that end in this step: response position 0 of their samples
   std::vector<PendingPrompt*> fin;
   if (n_fin) {
@@ -692,16 +688,6 @@ static void decode_impl(rollout_ctx& c, const int32_t* forced_tokens, const uint
 
   if (chunk) commit_chunk(c, *chunk, fin);
   refresh_stats(c);
-}
-
-__global__ void extend_slots_kernel(SlotState st, const int* __restrict__ slots, const int* __restrict__ new_pos,
-                                    const int* __restrict__ tokens, int n) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int sl = slots[i];
-  st.last_token[sl] = tokens[i];
-  st.pos[sl] = new_pos[i];
-  st.step[sl] += 1;
 }
 
 // Appends tokens that the model did not generate to live samples' contexts and emits each
@@ -753,7 +739,10 @@ static void extend_impl(rollout_ctx& c, int32_t n, const int64_t* sample_ids, co
       s.pages.push_back(pg);
     }
   }
-  if (extra_pages) engine_upload_page_table(c);
+  c.n_page_rows = 0;
+  for (int i = 0; i < n; ++i)
+    if (extra[i]) engine_stage_page_row(c, ss[i]->slot, (int)ss[i]->pages.size());
+  engine_upload_page_rows(c);
 
   // ---- rows: [last response token, appended tokens] per sample, positions after its cache ----
   int* hi = c.h_int.p;
@@ -776,41 +765,46 @@ static void extend_impl(rollout_ctx& c, int32_t n, const int64_t* sample_ids, co
     kv_tokens += (double)len * p0 + 0.5 * len * (len + 1);
     flops += 4.0 * ((double)len * p0 + 0.5 * len * (len + 1)) * c.q_dim;
   }
-  h2d(c.d_live.p, hi + 6 * R, n * sizeof(int), c.stream);
+  // the sampling parameters of the samples' slots, for the draw
+  GatherRows ga = gather_rows(c, n);
+  ga.host_live = hi + 6 * R;
   c.live_dirty = true;  // d_live no longer holds the live list
-  launch_gather_decode_rows(c.st, c.d_live.p, n, c.row_token.p, c.row_pos.p, c.row_slot.p, c.row_inv_temp.p,
-                            c.row_top_p.p, c.row_sample_id.p, c.row_step.p, c.stream);
-  h2d(c.row_token.p, hi, rows * sizeof(int), c.stream);
-  h2d(c.row_pos.p, hi + R, rows * sizeof(int), c.stream);
-  h2d(c.row_slot.p, hi + 2 * R, rows * sizeof(int), c.stream);
-  h2d(c.row_aux.p, hi + 3 * R, n * sizeof(int), c.stream);
+  launch_gather_decode_rows(ga, c.stream);
+  HostCopies up;
+  up.add(c.row_token.p, hi, rows);
+  up.add(c.row_pos.p, hi + R, rows);
+  up.add(c.row_slot.p, hi + 2 * R, rows);
+  up.add(c.row_aux.p, hi + 3 * R, n);
   SeqBatch sb{c.seq_row0.p, c.seq_len.p, c.seq_slot.p, n, max_len};
   if (!c.simple) {
-    h2d(c.seq_row0.p, hi + 4 * R, n * sizeof(int), c.stream);
-    h2d(c.seq_len.p, hi + 5 * R, n * sizeof(int), c.stream);
-    h2d(c.seq_slot.p, hi + 6 * R, n * sizeof(int), c.stream);
-    h2d(c.seq_pos0.p, hi + 7 * R, n * sizeof(int), c.stream);
+    up.add(c.seq_row0.p, hi + 4 * R, n);
+    up.add(c.seq_len.p, hi + 5 * R, n);
+    up.add(c.seq_slot.p, hi + 6 * R, n);
+    up.add(c.seq_pos0.p, hi + 7 * R, n);
     sb.pos0 = c.seq_pos0.p;
   }
+  launch_host_copies(up, c.stream);
   c.timer.start_call();
   c.kv_tokens_this_call = kv_tokens;
   c.attn_flops_this_call = flops;
   engine_forward_rows(c, (int)rows, &sb);
   engine_logits(c, c.row_aux.p, 0, n, c.logits.p);
   c.last_logit_rows = n;
-  HIP_TRY(hipStreamSynchronize(c.stream));  // the staging buffers are reused below
-  c.timer.collect();
-
-  // ---- the next response token of every sample ----
+  // ---- the next response token of every sample (staged behind what the forward pass may still read) ----
+  hi += 8 * (size_t)R;
   for (int i = 0; i < n; ++i) {
     Sample& s = *ss[i];
     hi[i] = s.prompt_len + (offsets[i + 1] - offsets[i]) + s.n_emitted;  // position of the token drawn now
     hi[R + i] = forced_next ? forced_next[i] : -1;
     hi[2 * R + i] = uniform_override ? (int)uniform_override[i] : 0;
+    hi[4 * R + i] = s.slot;
   }
-  h2d(c.row_aux.p + R, hi, n * sizeof(int), c.stream);
-  h2d(c.row_forced.p, hi + R, n * sizeof(int), c.stream);
-  h2d(c.row_uniform.p, hi + 2 * R, n * sizeof(int), c.stream);
+  HostCopies draw;
+  draw.add(c.row_pos.p, hi, n);
+  draw.add(c.row_forced.p, hi + R, n);
+  draw.add((int*)c.row_uniform.p, hi + 2 * R, n);
+  draw.add(c.row_slot.p, hi + 4 * R, n);
+  launch_host_copies(draw, c.stream);
   SampleRows sr{};
   sr.logits = c.logits.p;
   sr.logits_row = nullptr;
@@ -823,14 +817,17 @@ static void extend_impl(rollout_ctx& c, int32_t n, const int64_t* sample_ids, co
   sr.seed = c.rd.seed;
   sr.tokens = c.out_tokens.p;
   sr.logprobs = c.out_logprobs.p;
+  sr.host_tokens = hi + 3 * R;
+  sr.host_logprobs = c.h_float.p;
+  sr.row_slot = c.row_slot.p;
+  sr.row_pos = c.row_pos.p;
+  sr.slots = c.st;
   bool any_nucleus = false;
   for (const Sample* s : ss) any_nucleus |= s->top_p < 1.f;
   set_sampler_scratch(c, sr, n, any_nucleus && !forced_next);
   launch_sample(sr, n, m.vocab, c.stream);
-  extend_slots_kernel<<<ceil_div(n, 256), 256, 0, c.stream>>>(c.st, c.d_live.p, c.row_aux.p + R, c.out_tokens.p, n);
-  d2h(hi + 3 * R, c.out_tokens.p, n * sizeof(int), c.stream);
-  d2h(c.h_float.p, c.out_logprobs.p, n * sizeof(float), c.stream);
-  HIP_TRY(hipStreamSynchronize(c.stream));
+  wait_stream(c.stream);
+  c.timer.collect();
 
   // ---- host bookkeeping ----
   for (int i = 0; i < n; ++i) {
@@ -1310,6 +1307,7 @@ int rollout_logprobs(rollout_ctx* ctx, int32_t n_seqs, const int32_t* tokens, co
         pages += ceil_div(len, T);
         ++s1;
       }
+      c.n_page_rows = 0;
       Rollback held(c);  // the chunk's scratch pages: back to the pool however the chunk ends
       int* ht = c.h_int.p;
       int r = 0, max_len = 0;
@@ -1321,6 +1319,7 @@ int rollout_logprobs(rollout_ctx* ctx, int32_t n_seqs, const int32_t* tokens, co
         max_len = std::max(max_len, len);
         int* prow = &c.h_page_table[(size_t)(c.temp_slot0 + (s - s0)) * c.max_pages];
         for (int i = 0; i < ceil_div(len, T); ++i) prow[i] = held.alloc();
+        engine_stage_page_row(c, c.temp_slot0 + (s - s0), ceil_div(len, T));
         for (int i = 0; i < len; ++i, ++r) {
           int g = cu_seqlens[s] + i;
           ht[r] = tokens[g];
@@ -1329,17 +1328,19 @@ int rollout_logprobs(rollout_ctx* ctx, int32_t n_seqs, const int32_t* tokens, co
           ht[3 * R + r] = i + 1 < len ? tokens[g + 1] : -1;  // target of this row
         }
       }
-      engine_upload_page_table(c);
-      h2d(c.row_token.p, ht, rows * sizeof(int), c.stream);
-      h2d(c.row_pos.p, ht + R, rows * sizeof(int), c.stream);
-      h2d(c.row_slot.p, ht + 2 * R, rows * sizeof(int), c.stream);
-      h2d(c.row_aux.p, ht + 3 * R, rows * sizeof(int), c.stream);
+      engine_upload_page_rows(c);
+      HostCopies up;
+      up.add(c.row_token.p, ht, rows);
+      up.add(c.row_pos.p, ht + R, rows);
+      up.add(c.row_slot.p, ht + 2 * R, rows);
+      up.add(c.row_aux.p, ht + 3 * R, rows);
       SeqBatch sb{c.seq_row0.p, c.seq_len.p, c.seq_slot.p, s1 - s0, max_len};
       if (!c.simple) {
-        h2d(c.seq_row0.p, ht + 4 * R, (s1 - s0) * sizeof(int), c.stream);
-        h2d(c.seq_len.p, ht + 5 * R, (s1 - s0) * sizeof(int), c.stream);
-        h2d(c.seq_slot.p, ht + 6 * R, (s1 - s0) * sizeof(int), c.stream);
+        up.add(c.seq_row0.p, ht + 4 * R, s1 - s0);
+        up.add(c.seq_len.p, ht + 5 * R, s1 - s0);
+        up.add(c.seq_slot.p, ht + 6 * R, s1 - s0);
       }
+      launch_host_copies(up, c.stream);
       c.timer.start_call();
       c.kv_tokens_this_call = rows;
       c.attn_flops_this_call = 0;
@@ -1348,9 +1349,8 @@ int rollout_logprobs(rollout_ctx* ctx, int32_t n_seqs, const int32_t* tokens, co
         c.attn_flops_this_call += 2.0 * len * (len + 1) * c.q_dim;
       }
       engine_forward_rows(c, rows, &sb);
-      engine_target_logprobs(c, rows, c.row_aux.p, inv_t, c.out_logprobs.p);
-      d2h(c.h_float.p, c.out_logprobs.p, rows * sizeof(float), c.stream);
-      HIP_TRY(hipStreamSynchronize(c.stream));
+      engine_target_logprobs(c, rows, c.row_aux.p, inv_t, c.h_float.p);  // straight into mapped host memory
+      wait_stream(c.stream);
       c.timer.collect();
       // row i of a sequence holds log p(token i+1); shift by one and zero the first entry
       r = 0;
@@ -1411,14 +1411,6 @@ struct CallScratch {
   }
   static size_t piece(size_t bytes_) { return (bytes_ + 255) / 256 * 256; }
 };
-// the kernels of a short call: polling answers within microseconds where a blocking wait may sleep
-void wait_stream(hipStream_t s) {
-  for (;;) {
-    const hipError_t e = hipStreamQuery(s);
-    if (e == hipSuccess) return;
-    if (e != hipErrorNotReady) throw HipError(e, "hipStreamQuery", __FILE__, __LINE__);
-  }
-}
 CallScratch& call_scratch() {
   static CallScratch per_device[64];
   int dev = 0;

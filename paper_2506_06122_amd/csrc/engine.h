@@ -178,6 +178,8 @@ struct rollout_ctx : HostState {
 
   bool broken = false;          // a step timed out: the device state is unknown, every call is refused
   double step_timeout_s = 300;  // wall-clock bound of the wait that ends a decode step
+  PinnedBuf<int> h_page_rows, h_page_list;  // staged rows [n_slots][max_pages], (row, entries) each
+  int n_page_rows = 0;
   DevBuf<int> d_live;
 
   // workspaces
@@ -223,7 +225,7 @@ struct rollout_ctx : HostState {
   int samp_rows = 0;                         // rows the sampler scratch holds
   DevBuf<unsigned long long> samp_nucleus;   // scratch of the rows that draw with top_p < 1, in batches
   int samp_nucleus_rows = 0;
-  PinnedBuf<int> h_int;      // staging, 8 * r_max ints
+  PinnedBuf<int> h_int;      // staging, 17 * r_max ints: 8 for a forward pass, 9 for the draw behind it
   PinnedBuf<float> h_float;  // staging, 4 * r_max floats
   PinnedBuf<long long> h_ll; // staging, r_max
   int last_logit_rows = 0;
@@ -249,6 +251,10 @@ void engine_logits(rollout_ctx& c, const int* rows_index, int first, int n, floa
 // target[r] < 0); target and out are device arrays
 void engine_target_logprobs(rollout_ctx& c, int n, const int* target, float inv_t, float* out);
 void engine_upload_page_table(rollout_ctx& c);
+// Single rows of the host's table on their way to the device: stage each (row, entries in use), then upload.  The
+// staging area is read when the stream gets there: not before the call's last wait may it be written again.
+void engine_stage_page_row(rollout_ctx& c, int row, int n_pages);
+void engine_upload_page_rows(rollout_ctx& c);
 // one tensor (ROLLOUT_W_*, device pointer, caller's layout) into the library's layout, on c.stream
 void engine_load_tensor(rollout_ctx& c, int layer, int which, const void* src);
 // throws E_INVAL unless this model has tensor `which` (ROLLOUT_W_*) at `layer`

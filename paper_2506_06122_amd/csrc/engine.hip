@@ -348,7 +348,9 @@ void engine_init(rollout_ctx& c, const rollout_weights& w) {
   c.samp_seg_sums.alloc((size_t)c.samp_rows * kSampleSegments);
   c.samp_nucleus_rows = std::min(c.samp_rows, 512);
   c.samp_nucleus.alloc((size_t)c.samp_nucleus_rows * kNucleusScratch);
-  c.h_int.alloc(8 * R);
+  c.h_int.alloc(17 * R);
+  c.h_page_rows.alloc(c.h_page_table.size());
+  c.h_page_list.alloc(2 * (size_t)c.n_slots);
   c.h_float.alloc(4 * R);
   c.h_ll.alloc(R);
   HIP_TRY(hipStreamSynchronize(c.stream));
@@ -357,6 +359,18 @@ void engine_init(rollout_ctx& c, const rollout_weights& w) {
 void engine_upload_page_table(rollout_ctx& c) {
   HIP_TRY(hipMemcpyAsync(c.d_page_table.p, c.h_page_table.data(), c.h_page_table.size() * sizeof(int),
                          hipMemcpyHostToDevice, c.stream));
+}
+
+void engine_stage_page_row(rollout_ctx& c, int row, int n_pages) {
+  const int k = c.n_page_rows++;
+  c.h_page_list.p[2 * k] = row;
+  c.h_page_list.p[2 * k + 1] = n_pages;
+  std::memcpy(c.h_page_rows.p + (size_t)k * c.max_pages, &c.h_page_table[(size_t)row * c.max_pages],
+              (size_t)n_pages * sizeof(int));
+}
+void engine_upload_page_rows(rollout_ctx& c) {
+  launch_upload_page_rows(c.d_page_table.p, c.max_pages, c.h_page_list.p, c.h_page_rows.p, c.n_page_rows, c.stream);
+  c.n_page_rows = 0;
 }
 
 // ------------------------------------------------------------------------------------------

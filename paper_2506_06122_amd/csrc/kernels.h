@@ -68,6 +68,16 @@ void launch_patch_page_table(int* page_table, int max_pages, const int* triples,
 
 void launch_convert_to_f32(const void* src, int dtype, float* dst, long long n, hipStream_t s);
 
+// ---- per-slot decode state -------------------------------------------------------------
+struct SlotState {
+  int* last_token;       // [slots]
+  int* pos;              // [slots] cached positions so far = position of the next fed token
+  int* step;             // [slots] response position of the next token to emit
+  long long* sample_id;  // [slots]
+  float* inv_temp;       // [slots]
+  float* top_p;          // [slots]
+};
+
 // ---- sampling ---------------------------------------------------------------------------
 struct SampleRows {
   const float* logits;      // [*][vocab]
@@ -92,6 +102,15 @@ struct SampleRows {
   bool any_nucleus = true;
   unsigned long long* nucleus = nullptr;   // [nucleus_rows][kNucleusScratch]
   int nucleus_rows = 0;
+  // What the draw ends with, where asked for: the token and log-prob in host memory mapped for the
+  // device, and the state of slot row_slot[r] (a negative one has none): its next position is
+  // row_pos[r] + pos_step, the other fields follow from the row's own.
+  int* host_tokens = nullptr;
+  float* host_logprobs = nullptr;
+  const int* row_slot = nullptr;
+  const int* row_pos = nullptr;
+  int pos_step = 0;
+  SlotState slots{};
 };
 constexpr int kSampleParts = 64, kSampleSegments = 1024;
 constexpr int kNucleusBins0 = 41 * 16;                           // exponents 0..40 x 4 mantissa bits
@@ -105,20 +124,38 @@ void launch_philox_words(unsigned long long seed, const long long* ids, const un
 void launch_logprob_gather(const float* logits, const int* target, float inv_temp, float* out, int rows,
                            int vocab, hipStream_t s);
 
-// ---- per-slot decode state -------------------------------------------------------------
-struct SlotState {
-  int* last_token;       // [slots]
-  int* pos;              // [slots] cached positions so far = position of the next fed token
-  int* step;             // [slots] response position of the next token to emit
-  long long* sample_id;  // [slots]
-  float* inv_temp;       // [slots]
-  float* top_p;          // [slots]
+// row r <- slot live[r]: token, position, slot, sampling parameters.  What changed on the host comes along from
+// memory mapped for the device: the live list (host_live, kept in `live`), the step's forced tokens and
+// sampler words (each may be NULL).
+struct GatherRows {
+  SlotState st;
+  int rows;
+  int* live;
+  const int* host_live;
+  const int* host_forced;
+  const unsigned* host_uniform;
+  int *token, *pos, *slot, *step, *forced;
+  unsigned* uniform;
+  float *inv_temp, *top_p;
+  long long* sample_id;
 };
-// row r <- slot live[r]: token, position, slot, sampling parameters
-void launch_gather_decode_rows(SlotState st, const int* live, int rows, int* row_token, int* row_pos,
-                               int* row_slot, float* row_inv_temp, float* row_top_p, long long* row_sample_id,
-                               int* row_step, hipStream_t s);
-// after a draw: slot's last token, position (+1 when advance_pos) and step (+1); the rows' tokens and
-// log-probs are also stored to host_tokens / host_logprobs (pinned host memory, mapped for the device)
-void launch_scatter_tokens(SlotState st, const int* row_slot, const int* tokens, const float* logprobs, int rows,
-                           int advance_pos, int* host_tokens, float* host_logprobs, hipStream_t s);
+void launch_gather_decode_rows(const GatherRows& a, hipStream_t s);
+
+// Copies of 4-byte words from host memory mapped for the device, all in one launch.
+struct HostCopies {
+  static constexpr int kMax = 12;
+  int n = 0;
+  const int* src[kMax];
+  int* dst[kMax];
+  int words[kMax];
+  template <typename T>
+  void add(T* to, const T* from, size_t count) {
+    if (!count) return;
+    src[n] = (const int*)from;
+    dst[n] = (int*)to;
+    words[n++] = (int)(count * sizeof(T) / 4);
+  }
+};
+void launch_host_copies(const HostCopies& a, hipStream_t s);
+// page_table[list[2 i]][0 .. list[2 i + 1]) = packed[i][..], rows of max_pages; list and packed as above
+void launch_upload_page_rows(int* page_table, int max_pages, const int* list, const int* packed, int n, hipStream_t s);

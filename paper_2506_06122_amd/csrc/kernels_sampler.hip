@@ -568,6 +568,19 @@ __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab,
     a.tokens[r] = token;
     a.logprobs[r] = d - (float)(log((double)S) - 40.0 * 0.693147180559945309417);
     if (a.weight_sums) a.weight_sums[r] = S;
+    if (a.host_tokens) {
+      a.host_tokens[r] = token;
+      a.host_logprobs[r] = a.logprobs[r];
+    }
+    const int sl = a.row_slot ? a.row_slot[r] : -1;
+    if (sl >= 0) {
+      a.slots.last_token[sl] = token;
+      a.slots.pos[sl] = a.row_pos[r] + a.pos_step;
+      a.slots.step[sl] = a.step[r] + 1;
+      a.slots.sample_id[sl] = a.sample_id[r];
+      a.slots.inv_temp[sl] = a.inv_temp[r];
+      a.slots.top_p[sl] = a.top_p[r];
+    }
   }
 }
 
@@ -615,6 +628,8 @@ void launch_sample(SampleRows r, int rows, int vocab, hipStream_t s) {
       b.tokens += r0;
       b.logprobs += r0;
       if (b.weight_sums) b.weight_sums += r0;
+      if (b.host_tokens) b.host_tokens += r0, b.host_logprobs += r0;
+      if (b.row_slot) b.row_slot += r0, b.row_pos += r0;
     }
     launch_sample_rows(b, std::min(batch, rows - r0), vocab, s);
   }

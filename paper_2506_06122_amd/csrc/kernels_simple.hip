@@ -500,51 +500,50 @@ void launch_convert_to_f32(const void* src, int dtype, float* dst, long long n, 
 }
 
 // ---------------------------------------------------------------- decode row plumbing
-__global__ void gather_decode_rows_kernel(SlotState st, const int* __restrict__ live, int rows, int* row_token,
-                                          int* row_pos, int* row_slot, float* row_inv_temp, float* row_top_p,
-                                          long long* row_sample_id, int* row_step) {
-  int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= rows) return;
-  int sl = live[r];
-  row_token[r] = st.last_token[sl];
-  row_pos[r] = st.pos[sl];
-  row_slot[r] = sl;
-  row_inv_temp[r] = st.inv_temp[sl];
-  row_top_p[r] = st.top_p[sl];
-  row_sample_id[r] = st.sample_id[sl];
-  row_step[r] = st.step[sl];
+__global__ void gather_decode_rows_kernel(GatherRows a) {
+  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  if (r >= a.rows) return;
+  const int sl = a.host_live ? a.host_live[r] : a.live[r];
+  if (a.host_forced) a.forced[r] = a.host_forced[r];
+  if (a.host_uniform) a.uniform[r] = a.host_uniform[r];
+  if (a.host_live) a.live[r] = sl;
+  a.token[r] = a.st.last_token[sl];
+  a.pos[r] = a.st.pos[sl];
+  a.slot[r] = sl;
+  a.inv_temp[r] = a.st.inv_temp[sl];
+  a.top_p[r] = a.st.top_p[sl];
+  a.sample_id[r] = a.st.sample_id[sl];
+  a.step[r] = a.st.step[sl];
 }
-void launch_gather_decode_rows(SlotState st, const int* live, int rows, int* row_token, int* row_pos,
-                               int* row_slot, float* row_inv_temp, float* row_top_p, long long* row_sample_id,
-                               int* row_step, hipStream_t s) {
-  if (rows)
-    gather_decode_rows_kernel<<<ceil_div(rows, 256), 256, 0, s>>>(st, live, rows, row_token, row_pos, row_slot,
-                                                                   row_inv_temp, row_top_p, row_sample_id,
-                                                                   row_step);
+void launch_gather_decode_rows(const GatherRows& a, hipStream_t s) {
+  if (a.rows) gather_decode_rows_kernel<<<ceil_div(a.rows, 256), 256, 0, s>>>(a);
 }
 
-// A decode step's last kernel: the drawn tokens go back into the slots and, with the log-probs,
-// straight into pinned host memory, where the host reads them once the step's event has fired
-// (no copy launches).
-__global__ void scatter_tokens_kernel(SlotState st, const int* __restrict__ row_slot,
-                                      const int* __restrict__ tokens, const float* __restrict__ logprobs, int rows,
-                                      int advance_pos, int* __restrict__ host_tokens,
-                                      float* __restrict__ host_logprobs) {
-  int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= rows) return;
-  int sl = row_slot[r];
-  const int tok = tokens[r];
-  st.last_token[sl] = tok;
-  if (advance_pos) st.pos[sl] += 1;
-  st.step[sl] += 1;
-  host_tokens[r] = tok;
-  host_logprobs[r] = logprobs[r];
+// ---------------------------------------------------------------- uploads
+// One launch in place of a copy per array, each of which costs the stream 3 us and the host more; a
+// call's arrays are a few kilobytes, and every word crosses the bus once, 64 of them to a read.
+__global__ __launch_bounds__(256) void host_copies_kernel(HostCopies a) {
+  const int* src = a.src[blockIdx.y];
+  int* dst = a.dst[blockIdx.y];
+  const int n = a.words[blockIdx.y];
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) dst[i] = src[i];
 }
-void launch_scatter_tokens(SlotState st, const int* row_slot, const int* tokens, const float* logprobs, int rows,
-                           int advance_pos, int* host_tokens, float* host_logprobs, hipStream_t s) {
-  if (rows)
-    scatter_tokens_kernel<<<ceil_div(rows, 256), 256, 0, s>>>(st, row_slot, tokens, logprobs, rows, advance_pos,
-                                                              host_tokens, host_logprobs);
+void launch_host_copies(const HostCopies& a, hipStream_t s) {
+  if (!a.n) return;
+  int most = 0;
+  for (int i = 0; i < a.n; ++i) most = a.words[i] > most ? a.words[i] : most;
+  host_copies_kernel<<<dim3(ceil_div(most, 256) < 64 ? ceil_div(most, 256) : 64, a.n), 256, 0, s>>>(a);
+}
+__global__ __launch_bounds__(64) void upload_page_rows_kernel(int* __restrict__ page_table, int max_pages,
+                                                              const int* __restrict__ list,
+                                                              const int* __restrict__ packed) {
+  const int k = blockIdx.x;
+  int* dst = page_table + (long long)list[2 * k] * max_pages;
+  const int* src = packed + (long long)k * max_pages;
+  for (int i = threadIdx.x, n = list[2 * k + 1]; i < n; i += 64) dst[i] = src[i];
+}
+void launch_upload_page_rows(int* page_table, int max_pages, const int* list, const int* packed, int n, hipStream_t s) {
+  if (n) upload_page_rows_kernel<<<n, 64, 0, s>>>(page_table, max_pages, list, packed);
 }
 
 // ---------------------------------------------------------------- page-table patches

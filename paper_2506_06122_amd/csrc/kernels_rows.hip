@@ -62,18 +62,33 @@ __global__ __launch_bounds__(ROW_T) void row_norm_kernel(RowNormArgs a) {
         x[v].w += u[q][v].w;
       }
   }
-  for (int j = 0; j < a.moe_k; ++j) {  // the row's expert picks, in pick order
-    const float wt = a.moe_wt[(long long)r * a.moe_k + j];
-    const float4* y = (const float4*)(a.moe_y + (long long)a.moe_slot[(long long)r * a.moe_k + j] * a.hidden);
+  // the row's expert picks, in pick order: slots and weights of a batch first, then all its rows at once
+  constexpr int MB = V <= 2 ? 8 : 4;
+  for (int j0 = 0; j0 < a.moe_k; j0 += MB) {
+    int slot[MB];
+    float wt[MB];
 #pragma unroll
-    for (int v = 0; v < V; ++v) {
-      const int c = t + ROW_T * v;
-      if (c < n4) {
-        const float4 yv = y[c];
-        x[v].x += wt * yv.x;
-        x[v].y += wt * yv.y;
-        x[v].z += wt * yv.z;
-        x[v].w += wt * yv.w;
+    for (int j = 0; j < MB; ++j) {
+      const long long at = (long long)r * a.moe_k + min(j0 + j, a.moe_k - 1);
+      slot[j] = a.moe_slot[at];
+      wt[j] = a.moe_wt[at];
+    }
+    float4 y[MB][V];
+#pragma unroll
+    for (int j = 0; j < MB; ++j)
+#pragma unroll
+      for (int v = 0; v < V; ++v)
+        y[j][v] = ((const float4*)(a.moe_y + (long long)slot[j] * a.hidden))[min(t + ROW_T * v, n4 - 1)];
+#pragma unroll
+    for (int j = 0; j < MB; ++j) {
+      if (j0 + j >= a.moe_k) break;
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        if (t + ROW_T * v >= n4) continue;
+        x[v].x += wt[j] * y[j][v].x;
+        x[v].y += wt[j] * y[j][v].y;
+        x[v].z += wt[j] * y[j][v].z;
+        x[v].w += wt[j] * y[j][v].w;
       }
     }
   }

@@ -94,15 +94,6 @@ __device__ inline float wave_max(float v) {
   for (int o = WAVE / 2; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, WAVE));
   return v;
 }
-__device__ inline unsigned long long wave_sum_u64(unsigned long long v) {
-#pragma unroll
-  for (int o = WAVE / 2; o > 0; o >>= 1) {
-    unsigned lo = __shfl_xor((unsigned)(v & 0xffffffffull), o, WAVE);
-    unsigned hi = __shfl_xor((unsigned)(v >> 32), o, WAVE);
-    v += ((unsigned long long)hi << 32) | lo;
-  }
-  return v;
-}
 
 // ---- KV pages ---------------------------------------------------------------------------
 // The pool is [layer][page][kv_head][K|V][page_tokens * head_dim] elements.  Inside one

@@ -73,9 +73,26 @@ __device__ inline float shifted(float z, float m) {
   return z - m;
 }
 
-__device__ inline unsigned long long shfl_up_u64(unsigned long long v, int o) {
-  unsigned lo = __shfl_up((unsigned)(v & 0xffffffffull), o, WAVE);
-  unsigned hi = __shfl_up((unsigned)(v >> 32), o, WAVE);
+// Inclusive prefix sum over a wavefront whose lanes are all active, in registers: DPP row shifts by 1, 2,
+// 4, 8, then lane 15 of a row into rows 1 and 3 and lane 31 into rows 2 and 3.
+template <int CTRL, int ROWS>
+__device__ inline unsigned long long dpp_add_u64(unsigned long long v) {
+  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)v, CTRL, ROWS, 0xf, false);
+  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(v >> 32), CTRL, ROWS, 0xf, false);
+  return v + (((unsigned long long)hi << 32) | lo);
+}
+__device__ inline unsigned long long wave_scan_u64(unsigned long long v) {
+  v = dpp_add_u64<0x111, 0xf>(v);
+  v = dpp_add_u64<0x112, 0xf>(v);
+  v = dpp_add_u64<0x114, 0xf>(v);
+  v = dpp_add_u64<0x118, 0xf>(v);
+  v = dpp_add_u64<0x142, 0xa>(v);
+  return dpp_add_u64<0x143, 0xc>(v);
+}
+__device__ inline unsigned long long wave_total_u64(unsigned long long v) {
+  v = wave_scan_u64(v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, 63);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), 63);
   return ((unsigned long long)hi << 32) | lo;
 }
 
@@ -99,7 +116,7 @@ __device__ inline float block_max(float v, SampShared& sh) {
 }
 
 __device__ inline unsigned long long block_sum_u64(unsigned long long v, SampShared& sh) {
-  v = wave_sum_u64(v);
+  v = wave_total_u64(v);
   if ((threadIdx.x & 63) == 0) sh.wave_part[threadIdx.x >> 6] = v;
   __syncthreads();
   unsigned long long s = 0;
@@ -111,10 +128,7 @@ __device__ inline unsigned long long block_sum_u64(unsigned long long v, SampSha
 // Inclusive prefix sum over the threads of the workgroup.
 __device__ inline unsigned long long block_scan_u64(unsigned long long v, SampShared& sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int o = 1; o < WAVE; o <<= 1) {
-    const unsigned long long up = shfl_up_u64(v, o);
-    if (lane >= o) v += up;
-  }
+  v = wave_scan_u64(v);
   if (lane == 63) sh.wave_part[wave] = v;
   __syncthreads();
   for (int w = 0; w < wave; ++w) v += sh.wave_part[w];
@@ -166,8 +180,14 @@ struct Key4 {
   unsigned k[4];
 };
 
-__device__ inline Key4 load_keys4(const float* __restrict__ row, int i0, int vocab, bool vec_ok, float inv_t, float m) {
-  float v[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+struct Logit4 {
+  float v[4];
+};
+
+// logits of ids i0 .. i0 + 3, -inf past the end
+__device__ inline Logit4 load_logits4(const float* __restrict__ row, int i0, int vocab, bool vec_ok) {
+  Logit4 out = {{-INFINITY, -INFINITY, -INFINITY, -INFINITY}};
+  float(&v)[4] = out.v;
   if (vec_ok && i0 + 3 < vocab) {
     const float4 t = *(const float4*)(row + i0);
     v[0] = t.x;
@@ -179,9 +199,13 @@ __device__ inline Key4 load_keys4(const float* __restrict__ row, int i0, int voc
     for (int e = 0; e < 4; ++e)
       if (i0 + e < vocab) v[e] = row[i0 + e];
   }
+  return out;
+}
+__device__ inline Key4 load_keys4(const float* __restrict__ row, int i0, int vocab, bool vec_ok, float inv_t, float m) {
+  const Logit4 z = load_logits4(row, i0, vocab, vec_ok);
   Key4 out;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) out.k[e] = i0 + e < vocab ? fixexp_key(shifted(scaled_logit(v[e], inv_t), m)) : 0u;
+  for (int e = 0; e < 4; ++e) out.k[e] = i0 + e < vocab ? fixexp_key(shifted(scaled_logit(z.v[e], inv_t), m)) : 0u;
   return out;
 }
 __device__ inline Seg4 load_weights4(const float* __restrict__ row, int i0, int vocab, bool vec_ok, float inv_t,
@@ -244,17 +268,38 @@ __device__ inline NucleusState nucleus_from_scratch(const SampleRows& a, int r, 
   if (levels > 2) nucleus_descend(h + kNucleusBins0 + 1024, 2, st, sh);
   return st;
 }
-// Tiles t0, t0 + step, ... of the row into the LDS histogram of `level` (zeroed here)
+// Tiles t0, t0 + step, ... of the row into the LDS histogram of `level` (zeroed here).  From level 1 on only the ids
+// of one narrow bin count, so an id whose exponent t lies outside the bin's range is passed over before its
+// weight is computed: a weight w in the bin [lo, hi) comes from a value in [w, w + 1) that is 2^(40 + t) within
+// a few 2^-23, so t + 40 lies between log2(lo) and log2(hi + 1), each widened by 0.01.
 __device__ inline void nucleus_histogram(const float* row, int vocab, bool vec_ok, float inv_t, float m, int t0, int step,
                                          int level, unsigned prefix, SampShared& sh) {
   const int tid = threadIdx.x, n_tiles = (vocab + 4095) >> 12;
   sh.hist[tid] = 0ull;
   __syncthreads();
+  float t_lo = 0.f, t_hi = 0.f;
+  if (level > 0) {
+    const int shift = level == 1 ? 19 : 9;
+    t_lo = log2f(__uint_as_float(prefix << shift)) - 40.01f;
+    t_hi = log2f(__uint_as_float((prefix + 1u) << shift) + 1.f) - 39.99f;
+  }
   for (int t = t0; t < n_tiles; t += step) {
+    if (level > 0) {
+      const Logit4 z = load_logits4(row, t * 4096 + tid * 4, vocab, vec_ok);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float d = shifted(scaled_logit(z.v[e], inv_t), m), x = d * 0x1.715476p+0f;
+        if (x >= t_lo && x <= t_hi) {  // (not so where d is no number)
+          const unsigned key = fixexp_key(d);
+          if (key && nucleus_prefix(key, level) == prefix) atomicAdd(&sh.hist[nucleus_bin(key, level)], key_weight(key));
+        }
+      }
+      continue;
+    }
     const Key4 q = load_keys4(row, t * 4096 + tid * 4, vocab, vec_ok, inv_t, m);
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      if (q.k[e] && nucleus_prefix(q.k[e], level) == prefix) atomicAdd(&sh.hist[nucleus_bin(q.k[e], level)], key_weight(q.k[e]));
+      if (q.k[e]) atomicAdd(&sh.hist[nucleus_bin(q.k[e], level)], key_weight(q.k[e]));
   }
   __syncthreads();
 }
@@ -272,7 +317,7 @@ __device__ inline void nucleus_segments(const float* row, int vocab, bool vec_ok
       if (q.k[e] > tau_key) v += key_weight(q.k[e]);
       if (q.k[e] == tau_key) v += 1ull << 52;
     }
-    v = wave_sum_u64(v);
+    v = wave_total_u64(v);
     if (lane == 0 && t * 16 + wave < n_seg) put(t * 16 + wave, v & ((1ull << 52) - 1ull), (unsigned)(v >> 52));
   }
 }
@@ -291,11 +336,7 @@ __device__ inline void find_segment(SampShared& sh, int n_seg, unsigned long lon
     const int per = SAMP_T / WAVE;
     unsigned long long mine = 0;
     for (int j = 0; j < per; ++j) mine += tid * per + j < n_seg ? sh.vals[tid * per + j] : 0ull;
-    unsigned long long inc = mine;
-    for (int o = 1; o < WAVE; o <<= 1) {
-      unsigned long long up = shfl_up_u64(inc, o);
-      if (tid >= o) inc += up;
-    }
+    const unsigned long long inc = wave_scan_u64(mine);
     unsigned long long exc = inc - mine;
     if (exc <= target && target < inc) {
       unsigned long long acc = exc;
@@ -319,11 +360,7 @@ __device__ inline void find_segment(SampShared& sh, int n_seg, unsigned long lon
 // target (values in ascending id order: lane-major, element-minor).
 __device__ inline int resolve_in_segment(const unsigned long long (&v)[4], unsigned long long target, int lane) {
   const unsigned long long mine = v[0] + v[1] + v[2] + v[3];
-  unsigned long long inc = mine;
-  for (int o = 1; o < WAVE; o <<= 1) {
-    unsigned long long up = shfl_up_u64(inc, o);
-    if (lane >= o) inc += up;
-  }
+  const unsigned long long inc = wave_scan_u64(mine);
   const unsigned long long exc = inc - mine;
   int found = -1;
   if (exc <= target && target < inc) {
@@ -368,10 +405,11 @@ __global__ __launch_bounds__(SAMP_T) void sample_max_kernel(SampleRows a, int vo
       a.nucleus[(long long)r * kNucleusScratch + i] = 0ull;
 }
 
+// one part per lane: their loads go out together
 __device__ inline float row_max(const SampleRows& a, int r, int parts) {
-  float m = -INFINITY;
-  for (int q = 0; q < parts; ++q) m = fmaxf(m, a.part_max[(long long)r * kSampleParts + q]);
-  return m;
+  static_assert(kSampleParts <= WAVE, "one part per lane");
+  const int lane = threadIdx.x & 63;
+  return wave_max(lane < parts ? a.part_max[(long long)r * kSampleParts + lane] : -INFINITY);
 }
 
 // Second sweep on `parts` workgroups per row: the weights of the same tiles, one sum per
@@ -392,7 +430,7 @@ __global__ __launch_bounds__(SAMP_T) void sample_segments_kernel(SampleRows a, i
   }
   for (int t = blockIdx.x; t < n_tiles; t += parts) {
     const Seg4 q = load_weights4(row, t * 4096 + tid * 4, vocab, vec_ok, inv_t, m);
-    const unsigned long long ws = wave_sum_u64(q.w[0] + q.w[1] + q.w[2] + q.w[3]);
+    const unsigned long long ws = wave_total_u64(q.w[0] + q.w[1] + q.w[2] + q.w[3]);
     if (lane == 0 && t * 16 + wave < n_seg) a.seg_sums[(long long)r * kSampleSegments + t * 16 + wave] = ws;
   }
 }
@@ -499,7 +537,7 @@ __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab,
         const Seg4 q = load_weights4(row, t * 4096 + tid * 4, vocab, vec_ok, inv_t, m);
         const unsigned long long mine = q.w[0] + q.w[1] + q.w[2] + q.w[3];
         local += mine;
-        const unsigned long long ws = wave_sum_u64(mine);
+        const unsigned long long ws = wave_total_u64(mine);
         if (lane == 0 && t * 16 + wave < n_seg) sh.vals[t * 16 + wave] = ws;
       }
       S = block_sum_u64(local, sh);  // also orders the writes to sh.vals
@@ -586,10 +624,11 @@ __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab,
 
 // Large vocabularies with scratch at hand: the sweeps of a row on several workgroups (about 512 in all),
 // then the selection; else everything in one workgroup per row.
-// 64 rows x 151936 ids, top_p 0.9: 7.5 + 15.6 us for maximum and sums, 17.6 + 17.8 + 31.8 us for the
-// histograms and the segments above tau, 9.4 us for the selection: 116 us per call of rollout_sample,
-// where one workgroup per row that searched tau bit by bit took 1809 us.  The search in LDS atomics
-// and the sweeps' arithmetic take the time: 39 MB of logits pass in 7.5 us.
+// 64 rows x 151936 ids, top_p 0.9: 8.1 + 16.3 us for maximum and histogram 0, 12.9 + 12.5 + 24.7 us for the other
+// histograms and the segments above tau, 9.1 us for the selection: 95 us per call of rollout_sample, where
+// one workgroup per row that searched tau bit by bit took 1809 us.  (111 us with the parts' maxima read one
+// after the other, scans through LDS and every id's weight computed in histograms 1 and 2.)  The sweeps'
+// arithmetic takes the time: 39 MB of logits pass in 8 us.
 static void launch_sample_rows(const SampleRows& r, int rows, int vocab, hipStream_t s) {
   const int n_tiles = (vocab + 4095) >> 12;
   int parts = 0;

@@ -8,9 +8,9 @@
 // it.  policy_loss_kernel takes one sequence per workgroup.  The return G_j = rho_j + gamma G_{j+1}
 // over the counted tokens is a first-order linear recurrence, so a chunk of the sequence, taken from
 // its end, is a scan of affine maps y -> a y + b (a = gamma, b = rho for a counted token; the
-// identity for any other): four tokens in a thread's registers, Hillis-Steele over the wavefront's
-// threads, the wavefront totals composed through LDS, the chunk's last value carried to the next
-// chunk.  Sums for the loss leave as one partial per sequence and are added in sequence order by
+// identity for any other): four tokens in a thread's registers, Hillis-Steele over a span of the
+// wavefront's threads (all 64, see launch_policy_loss), the spans' totals composed through LDS, the
+// chunk's last value carried to the next chunk.  Sums for the loss leave as one partial per sequence and are added in sequence order by
 // the host, so the result does not depend on scheduling.
 //
 // What bounds it: memory latency of few, short chunks (a sequence's chunks are serial), so a chunk
@@ -77,13 +77,14 @@ __device__ inline void store_quad(float* base, long long t, long long lo, long l
     if (t + e >= lo && t + e < hi) base[t + e] = v[e];
 }
 
-template <int T, bool VEC>
+template <int T, bool VEC, int SPAN>
 __global__ __launch_bounds__(T) void policy_loss_kernel(PolicyLossArgs p) {
-  constexpr int NW = T / WAVE;
+  constexpr int NW = T / WAVE, NS = T / SPAN;
   __shared__ int count_s[NW], last_s[NW];
-  __shared__ Affine total_s[NW];
+  __shared__ Affine total_s[NS];
   __shared__ float sum_s[NW];
   const int seq = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int span = tid / SPAN, at = tid % SPAN;
   const long long lo = p.cu_seqlens[seq], hi = p.cu_seqlens[seq + 1];
   const float reward = fminf(fmaxf(p.rewards[seq], -p.reward_clip), p.reward_clip);
   int n = 0;
@@ -147,22 +148,22 @@ __global__ __launch_bounds__(T) void policy_loss_kernel(PolicyLossArgs p) {
       f = then(f, m[i]);
     }
     rewarded = rewarded || last < 4 * T;
-    // inclusive scan over the threads: f becomes "everything from thread 0 up to this thread"
+    // inclusive scan over the threads: f becomes "everything from the span's first thread up to this one"
 #pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) {
+    for (int o = 1; o < SPAN; o <<= 1) {
       Affine prev{__shfl_up(f.a, o, WAVE), __shfl_up(f.b, o, WAVE)};
-      if (lane >= o) f = then(prev, f);
+      if (at >= o) f = then(prev, f);
     }
-    if (lane == WAVE - 1) total_s[wave] = f;
+    if (at == SPAN - 1) total_s[span] = f;
     __syncthreads();
-    float y = carry;  // the value entering this wavefront, then this thread; carry the one that leaves the chunk
+    float y = carry;  // the value entering this span, then this thread; carry the one that leaves the chunk
 #pragma unroll 4
-    for (int w = 0; w < NW; ++w) {
-      if (w == wave) y = carry;
+    for (int w = 0; w < NS; ++w) {
+      if (w == span) y = carry;
       carry = total_s[w].a * carry + total_s[w].b;
     }
     const float fa = __shfl_up(f.a, 1, WAVE), fb = __shfl_up(f.b, 1, WAVE);
-    if (lane > 0) y = fa * y + fb;
+    if (at > 0) y = fa * y + fb;
     if (t + 4 > lo) {
       float adv[4], grad[4];
 #pragma unroll
@@ -202,14 +203,21 @@ __global__ __launch_bounds__(T) void policy_loss_kernel(PolicyLossArgs p) {
 
 // 256 threads where every sequence fits one of their chunks twice over; the quads need arrays
 // aligned to 16 bytes (the mask to 4), any others are taken value by value.
+// Spans of 64 threads hold 256 tokens.  With gamma above 1 the powers of gamma in a span's maps grow, and one that
+// leaves fp32 makes inf x 0 of a return that is 0 (gamma 1.5 from 219 tokens on), so spans of 16
+// threads, 64 tokens, then: finite up to gamma 4, and a longer walk over the spans' totals.
 // 512 sequences of 512..8192 tokens, KL on: 5.2 us to count + 16.0 us (2.9 TB/s of the 47 MB it moves) where
 // 256-token chunks, a reduction and a scaling pass took 60 us; the call 49 us, before 94 us.
+template <int T, bool VEC>
+static void launch_loss(const PolicyLossArgs& p, hipStream_t s) {
+  if (p.gamma > 1.f) policy_loss_kernel<T, VEC, 16><<<p.n_seqs, T, 0, s>>>(p);
+  else policy_loss_kernel<T, VEC, 64><<<p.n_seqs, T, 0, s>>>(p);
+}
 void launch_policy_loss(const PolicyLossArgs& p, int longest, hipStream_t s) {
   if (p.n_seqs == 0) return;
   policy_count_kernel<<<p.n_parts, 256, 0, s>>>(p);
   const size_t any = (size_t)p.logp_new | (size_t)p.logp_old | (size_t)p.logp_ref | (size_t)p.grad | (size_t)p.advantages;
   const bool vec = (any & 15) == 0 && ((size_t)p.mask & 3) == 0, small = longest <= 2048;
-  const auto kernel = vec ? (small ? policy_loss_kernel<256, true> : policy_loss_kernel<1024, true>)
-                          : (small ? policy_loss_kernel<256, false> : policy_loss_kernel<1024, false>);
-  kernel<<<p.n_seqs, small ? 256 : 1024, 0, s>>>(p);
+  if (vec) small ? launch_loss<256, true>(p, s) : launch_loss<1024, true>(p, s);
+  else small ? launch_loss<256, false>(p, s) : launch_loss<1024, false>(p, s);
 }

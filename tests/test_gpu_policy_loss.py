@@ -108,3 +108,36 @@ def test_policy_loss_chunk_edges(lens, offset):
     keep[flips] = False
     assert np.max(np.abs(grad - want_grad)[keep]) * n <= 2e-4
     assert abs(loss - want_loss) <= 1e-5 * max(1.0, abs(want_loss)) + 20.0 * len(flips) / n
+
+
+@pytest.mark.parametrize("gamma", [1.01, 1.5, 3.0])
+@pytest.mark.parametrize("max_len,offset", [(2048, 0), (5000, 0), (1300, 1)])
+def test_policy_loss_growing_returns(gamma, max_len, offset):
+    """A gamma above 1: the returns of a sequence grow past what fp32 holds (1.5^219, 3^81), the advantages are
+    their clipped values all the same, and where nothing is earned (no reward, no penalty) they are 0.
+    Tolerances as above; a return's relative error is about one ulp per token, and only returns below the clip of
+    10 are compared as values (those come from at most a few hundred tokens)."""
+    import torch
+    cu, new, old, ref, mask, rewards = batch(11, 9, max_len)
+    rewards[5:7] = 0.0
+    free = slice(cu[5], cu[7])
+    ref[free] = old[free]                                # sequences 5 and 6 earn nothing
+    mask[cu[5]:cu[7]] = 1
+
+    def dev(a):
+        return torch.from_numpy(np.concatenate([np.ones(offset, a.dtype), a])).cuda()[offset:]
+
+    kw = dict(gamma=gamma, kl_coef=0.02)
+    loss, grad, adv = R.rollout_policy_loss(cu, dev(new), dev(old), dev(ref), dev(mask), rewards, **kw)
+    want_loss, want_grad, want_adv = PL.policy_loss(cu, new, old, ref, mask, rewards, **kw)
+    n = int(mask.sum())
+    adv, grad = adv.cpu().numpy(), grad.cpu().numpy()
+    assert np.isfinite(adv).all() and np.isfinite(grad).all() and np.isfinite(loss)
+    assert not adv[free].any() and not grad[free].any()
+    assert np.max(np.abs(adv - want_adv)) <= 1e-3        # 10 x 512 ulp
+    flips = np.flatnonzero((grad == 0) != (want_grad == 0))
+    assert len(flips) <= 2
+    keep = np.ones(len(grad), bool)
+    keep[flips] = False
+    assert np.max(np.abs(grad - want_grad)[keep]) * n <= 2e-3
+    assert abs(loss - want_loss) <= 1e-4 * max(1.0, abs(want_loss)) + 20.0 * len(flips) / n

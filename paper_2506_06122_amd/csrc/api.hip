@@ -1418,6 +1418,24 @@ CallScratch& call_scratch() {
   if (dev < 0 || dev >= 64) throw ApiError{ROLLOUT_E_HIP, "device index out of range"};
   return per_device[dev];
 }
+
+// Between the first launch of a call and its end: the scratch may not change hands (nor the caller's arrays
+// be freed) while kernels use it, so a call that ends by an exception waits for the stream first.
+// An error that earlier work of this thread left behind is not this call's: cleared, so that finish() reports
+// the launches'.
+struct EnqueuedCall {
+  hipStream_t s;
+  bool drained = false;
+  explicit EnqueuedCall(hipStream_t stream) : s(stream) { (void)hipGetLastError(); }
+  ~EnqueuedCall() {
+    if (!drained) (void)hipStreamSynchronize(s);
+  }
+  void finish() {
+    HIP_TRY(hipGetLastError());
+    wait_stream(s);
+    drained = true;
+  }
+};
 }  // namespace
 
 extern "C" {
@@ -1442,6 +1460,7 @@ int rollout_sample(const float* logits, int32_t rows, int32_t vocab, float tempe
     cs.begin(CallScratch::piece(R * 4) + CallScratch::piece(R * kSampleParts * 4) + CallScratch::piece(R * kSampleSegments * 8) +
                  CallScratch::piece(nucleus_rows * kNucleusScratch * 8),
              4 * CallScratch::piece(R * 4) + CallScratch::piece(R * 8));
+    EnqueuedCall call(s);
     unsigned* un = cs.take_host<unsigned>(R);
     int *fo_host = cs.take_host<int>(R), *tok = cs.take_host<int>(R);
     float* lp = cs.take_host<float>(R);
@@ -1468,8 +1487,7 @@ int rollout_sample(const float* logits, int32_t rows, int32_t vocab, float tempe
     if (nucleus) sr.nucleus = cs.take<unsigned long long>(nucleus_rows * kNucleusScratch);
     sr.nucleus_rows = (int)nucleus_rows;
     launch_sample(sr, rows, vocab, s);
-    HIP_TRY(hipGetLastError());
-    wait_stream(s);
+    call.finish();
     std::memcpy(tokens, tok, R * sizeof(int));
     std::memcpy(logprobs, lp, R * sizeof(float));
     if (weight_sums) std::memcpy(weight_sums, ws, R * sizeof(unsigned long long));
@@ -1504,6 +1522,7 @@ int rollout_policy_loss(int32_t n_seqs, const int32_t* cu_seqlens, const float* 
     p.n_parts = (int)std::min<long long>(kLossParts, ceil_div(total, 256 * 16));
     const size_t io = CallScratch::piece((S1 + 1) * 4) + CallScratch::piece(S1 * 4);
     cs.begin(io + CallScratch::piece(p.n_parts * 4), io + CallScratch::piece(S1 * 4) + CallScratch::piece(4));
+    EnqueuedCall call(s);
     p.cu_seqlens = cs.take<int>(S1 + 1);
     p.rewards = cs.take<float>(S1);
     p.part_count = cs.take<int>(p.n_parts);
@@ -1530,8 +1549,7 @@ int rollout_policy_loss(int32_t n_seqs, const int32_t* cu_seqlens, const float* 
     p.grad = grad;
     p.advantages = advantages;
     launch_policy_loss(p, longest, s);
-    HIP_TRY(hipGetLastError());
-    wait_stream(s);
+    call.finish();
     double sum = 0.0;
     for (int i = 0; i < n_seqs; ++i) sum += p.part_sum[i];
     if (*p.count > 0) *loss = (float)(-sum / *p.count);

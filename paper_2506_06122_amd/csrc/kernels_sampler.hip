@@ -27,12 +27,12 @@
 
 #define SAMP_T 1024
 
-// The weight as the bits of a float, exact (24 significant bits at most); 0 for weight 0.
-__device__ inline unsigned fixexp_key(float d) {
+// P(frac(t)) of t = d * log2(e), as bits; n = floor(t).  false: the weight is 0.
+__device__ inline bool fixexp_bits(float d, unsigned& bits, int& n_out) {
 #pragma clang fp contract(off)
   const float log2e = 0x1.715476p+0f;
   float t = d * log2e;
-  if (!(t >= -40.0f)) return 0u;
+  if (!(t >= -40.0f)) return false;
   float n = floorf(t);
   float f = t - n;
   float y = 0x1.5bd2aep-16f;
@@ -50,9 +50,17 @@ __device__ inline unsigned fixexp_key(float d) {
   y = y + 0x1.62e430p-1f;
   y = y * f;
   y = y + 0x1.000000p+0f;
+  bits = __float_as_uint(y);
+  n_out = (int)n;
+  return true;
+}
+// The weight as the bits of a float, exact (24 significant bits at most); 0 for weight 0.
+__device__ inline unsigned fixexp_key(float d) {
+  unsigned bits;
+  int n;
+  if (!fixexp_bits(d, bits, n)) return 0u;
   // floor(y * 2^(40 + n)): the exponent grows by 40 + n, mantissa bits worth less than 1 go
-  const unsigned bits = __float_as_uint(y);
-  const int e = (int)((bits >> 23) & 0xffu) - 127 + 40 + (int)n;
+  const int e = (int)((bits >> 23) & 0xffu) - 127 + 40 + n;
   if (e < 0) return 0u;
   const unsigned below_one = e < 23 ? (1u << (23 - e)) - 1u : 0u;
   return (((unsigned)(e + 127) << 23) | (bits & 0x7fffffu)) & ~below_one;
@@ -62,6 +70,16 @@ __device__ inline unsigned long long key_weight(unsigned key) {
   const int e = (int)(key >> 23) - 127;
   const unsigned mant = (key & 0x7fffffu) | 0x800000u;
   return e >= 23 ? (unsigned long long)mant << (e - 23) : (unsigned long long)(mant >> (23 - e));
+}
+
+// The weight itself, for the sweeps that only add weights up.
+__device__ inline unsigned long long fixexp_weight(float d) {
+  unsigned bits;
+  int n;
+  if (!fixexp_bits(d, bits, n)) return 0ull;
+  // y's 24 bits times 2^(e + 40 + n - 23), at most 2^17 (d <= 0): one 64-bit shift, to the right
+  const int e = (int)((bits >> 23) & 0xffu) - 127;
+  return ((unsigned long long)((bits & 0x7fffffu) | 0x800000u) << 17) >> (-e - n);
 }
 
 __device__ inline float scaled_logit(float logit, float inv_t) {
@@ -94,6 +112,22 @@ __device__ inline unsigned long long wave_total_u64(unsigned long long v) {
   const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, 63);
   const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), 63);
   return ((unsigned long long)hi << 32) | lo;
+}
+
+// Sum over the wavefront of values below 2^43 (the weights of four ids), in every lane: as two sums of 32 bits,
+// whose steps are one instruction each.
+__device__ inline unsigned wave_total_u32(unsigned v) {
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);
+  return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ inline unsigned long long wave_total_weights(unsigned long long v) {
+  const unsigned lo = wave_total_u32((unsigned)v & 0x3fffffu), hi = wave_total_u32((unsigned)(v >> 22));
+  return ((unsigned long long)hi << 22) + lo;
 }
 
 struct SampShared {
@@ -210,10 +244,10 @@ __device__ inline Key4 load_keys4(const float* __restrict__ row, int i0, int voc
 }
 __device__ inline Seg4 load_weights4(const float* __restrict__ row, int i0, int vocab, bool vec_ok, float inv_t,
                                      float m) {
-  const Key4 q = load_keys4(row, i0, vocab, vec_ok, inv_t, m);
+  const Logit4 z = load_logits4(row, i0, vocab, vec_ok);
   Seg4 out;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) out.w[e] = key_weight(q.k[e]);
+  for (int e = 0; e < 4; ++e) out.w[e] = i0 + e < vocab ? fixexp_weight(shifted(scaled_logit(z.v[e], inv_t), m)) : 0ull;
   return out;
 }
 
@@ -413,7 +447,9 @@ __device__ inline float row_max(const SampleRows& a, int r, int parts) {
 }
 
 // Second sweep on `parts` workgroups per row: the weights of the same tiles, one sum per
-// 256-id segment; rows with a nucleus: histogram 0.
+// 256-id segment; rows with a nucleus: histogram 0.  Bound by the arithmetic: 256 rows x 151936 ids without a
+// nucleus 40.0 us (64 rows 13.3), where weights by way of keys and 64-bit wavefront sums took 58.6 (18.0) and
+// a weight from two 64-bit shifts with sums by exchanges through LDS 45.4 (16.0).
 __global__ __launch_bounds__(SAMP_T) void sample_segments_kernel(SampleRows a, int vocab, int parts) {
   __shared__ SampShared sh;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = blockIdx.y;
@@ -430,7 +466,7 @@ __global__ __launch_bounds__(SAMP_T) void sample_segments_kernel(SampleRows a, i
   }
   for (int t = blockIdx.x; t < n_tiles; t += parts) {
     const Seg4 q = load_weights4(row, t * 4096 + tid * 4, vocab, vec_ok, inv_t, m);
-    const unsigned long long ws = wave_total_u64(q.w[0] + q.w[1] + q.w[2] + q.w[3]);
+    const unsigned long long ws = wave_total_weights(q.w[0] + q.w[1] + q.w[2] + q.w[3]);
     if (lane == 0 && t * 16 + wave < n_seg) a.seg_sums[(long long)r * kSampleSegments + t * 16 + wave] = ws;
   }
 }
@@ -537,7 +573,7 @@ __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab,
         const Seg4 q = load_weights4(row, t * 4096 + tid * 4, vocab, vec_ok, inv_t, m);
         const unsigned long long mine = q.w[0] + q.w[1] + q.w[2] + q.w[3];
         local += mine;
-        const unsigned long long ws = wave_total_u64(mine);
+        const unsigned long long ws = wave_total_weights(mine);
         if (lane == 0 && t * 16 + wave < n_seg) sh.vals[t * 16 + wave] = ws;
       }
       S = block_sum_u64(local, sh);  // also orders the writes to sh.vals

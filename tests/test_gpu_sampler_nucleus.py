@@ -52,3 +52,19 @@ def test_more_rows_than_the_nucleus_scratch_holds():
     toks, _, _ = R.rollout_sample(torch.from_numpy(z).cuda(), 1.0, 0.9, x)
     for r in (0, 1, 255, 511, 512, 513, 520):
         assert int(toks[r]) == sampler.sample(z[r], np.float32(1.0), 0.9, int(x[r]))[0], f"row {r}"
+
+
+@pytest.mark.parametrize("vocab", [1, 255, 4097, 28672, 28673, 65536 + 3, 262144])
+def test_whole_vocabulary_matches_oracle(vocab):
+    """top_p = 1 on the same rows: every weight counts, from 2^40 (equal maxima: the largest sums of a segment) down
+    to the cut-off."""
+    import torch
+    import paper_2506_06122_amd as R
+    z = hard_rows(vocab, seed=vocab) if vocab > 2 else np.zeros((9, vocab), np.float32)
+    x = workloads.uniform_words(len(z), seed=7)
+    toks, _, sums = R.rollout_sample(torch.from_numpy(z).cuda(), 0.8, 1.0, x)
+    inv_t = sampler.inv_temperature(0.8)
+    for r in range(len(z)):
+        w = sampler.fixexp_weights(z[r], inv_t)
+        assert int(sums[r]) == int(np.sum(w, dtype=np.uint64)), f"row {r}"
+        assert int(toks[r]) == sampler.draw(w, sampler.nucleus(w, 1.0), int(x[r])), f"row {r}"

@@ -417,8 +417,8 @@ static void forward_rows_simple(rollout_ctx& c, int R, bool decode) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Matrix-core path, many rows (prefill, teacher-forced pass, decode steps with more than 16
-// live samples).  Per layer: QKV projection -> sum + rotary + KV-page write -> paged
+// Matrix-core path, many rows (prefill, teacher-forced pass, decode steps with more live
+// samples than stream_rows).  Per layer: QKV projection -> sum + rotary + KV-page write -> paged
 // attention -> O projection -> residual + norm -> gate/up projection with SwiGLU in the
 // epilogue -> down projection -> residual + next norm.
 static double gemm_bytes(int M, int N, int K, int out_elem) {  // operands once, result once
@@ -752,7 +752,7 @@ static void forward_rows_tiled(rollout_ctx& c, int R, const SeqBatch* seqs) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Matrix-core path, one decode step with at most 16 live samples: five launches per layer
+// Matrix-core path, one decode step with at most stream_rows live samples: five launches per layer
 // (six when attention is split over the cached positions).
 //   QKV projection -> fused attention (rotary, KV-page write, paged attention) -> O projection
 //   with the residual add -> gate/up projection with SwiGLU -> down projection with the
@@ -782,7 +782,7 @@ static void stream_project(rollout_ctx& c, const DevBuf<uint16_t>& a, const void
     g.rinv_ssq = c.ssq.p;
     g.rinv_partials = c.ssq_partials;
   }
-  const GemmPlan pl = gemm_plan(M, N, K, epi, 1);
+  const GemmPlan pl = gemm_plan_stream(M, N, K, epi, 1);
   double bytes = 2.0 * N * K + 2.0 * 2 * M * K;  // weights once, both activation planes once
   if (epi == EPI_RESID) {
     g.x = c.x.p;
@@ -882,7 +882,7 @@ void engine_forward_rows(rollout_ctx& c, int rows, const SeqBatch* seqs) {
   if (rows < 1) return;
   c.last_route_rows = rows;
   if (!c.simple) {
-    if (!seqs && rows <= kStreamRows && !c.md.n_experts)
+    if (!seqs && rows <= stream_rows(c.md.hidden) && !c.md.n_experts)
       forward_rows_decode(c, rows);
     else
       forward_rows_tiled(c, rows, seqs);
@@ -933,7 +933,7 @@ void engine_logits(rollout_ctx& c, const int* rows_index, int first, int n, floa
     g.N = c.md.vocab;
     g.K = d;
     g.ldo = c.md.vocab;
-    const GemmPlan pl = gemm_plan(n, g.N, d, EPI_F32, 1);
+    const GemmPlan pl = from_h ? gemm_plan_stream(n, g.N, d, EPI_F32, 1) : gemm_plan(n, g.N, d, EPI_F32, 1);
     c.timer.begin(pl.name, gemm_bytes(n, g.N, d, 4), 2.0 * n * g.N * d, c.stream);
     launch_gemm_bf16(g, EPI_F32, pl, c.stream);
     c.timer.end(c.stream);

@@ -20,7 +20,7 @@
 //                    turns these into log-probs)
 enum { EPI_F32 = 0, EPI_SWIGLU_BF16 = 1, EPI_RESID = 2, EPI_LSE = 3 };
 
-// Fragment order of an activation plane [rows][K] (decode steps with at most 16 rows): the
+// Fragment order of an activation plane [rows][K] (decode steps that stream the weights): the
 // 16-row x 32-deep operand fragment of the 16x16x32 matrix instruction is stored as one
 // contiguous 1 KiB block [lane][8] with lane = (k % 32 / 8) * 16 + row % 16, fragments ordered
 // [row / 16][k / 32].  A wavefront then reads an operand fragment as whole cache lines, as it
@@ -109,7 +109,12 @@ struct GemmArgs {
   int lse_stride = 0;
 };
 
-constexpr int kStreamRows = 16;  // rows up to which a decode step streams the weights (gemm_stream_kernel)
+// Rows up to which a decode step streams the weights (gemm_stream_kernel).  Above that the activations every
+// workgroup re-reads, and the narrow outputs' second row blocks once they no longer find idle CUs (hidden / 16 column
+// tiles each: 256 workgroups at 2048), outweigh the two norm launches per layer that the path saves.  Step at 24 rows,
+// streamed / as tiles: hidden 1024 1.13 / 1.46 ms, 1536 1.74 / 1.85, 2048 1.25 / 1.36 (16 layers), 2560 1.63 / 1.52 (16
+// layers), 3584 4.49 / 4.25.
+inline int stream_rows(int hidden) { return hidden <= 2048 ? 32 : 16; }
 
 // How one projection is launched: kind 0 = gemm_stream_kernel, 1 = gemm_tile_kernel; shape = which of the
 // kernel's configurations, nt = column tiles per workgroup.
@@ -118,6 +123,7 @@ struct GemmPlan {
   const char* name;  // kernel name as a profiler shows it (without the argument list)
 };
 GemmPlan gemm_plan(int M, int N, int K, int epi, int max_splits);
+GemmPlan gemm_plan_stream(int M, int N, int K, int epi, int max_splits);  // the stream kernel for M <= 32
 GemmPlan gemm_plan_tiled(int M, int N, int K, int epi, int max_splits);  // the tile kernel for any M
 GemmPlan gemm_plan_grouped(int epi, int block_rows);                     // experts' row blocks of moe_block_rows
 // column parts per row that an EPI_LSE launch with this plan writes, and the most any plan writes

@@ -16,8 +16,8 @@
 // memory-bound decode step does not notice.
 //
 // Two kernels:
-//   gemm_stream_kernel  (rows <= 16, decoding): the NW wavefronts of a workgroup share NT
-//       column tiles and interleave over the K range in chunks of KU fragments, so one
+//   gemm_stream_kernel  (rows <= 16, of models up to a hidden size of 2048 rows <= 32, decoding): the NW
+//       wavefronts of a workgroup share MT row and NT column tiles and interleave over the K range in chunks of KU fragments, so one
 //       workgroup walks one contiguous weight stream with up to 2 NW x KU x NT KiB in flight; the
 //       partial accumulators meet in LDS.  Activations come straight from L2, stored in
 //       fragment order by their producers (frag_offset, kernels_fast.h) so that an operand
@@ -34,7 +34,7 @@
 //         - SwiGLU on column tiles of 8 gates and their 8 ups (EPI_SWIGLU_BF16).
 //       Workgroups past the last column block, if the launcher adds any, walk a later
 //       projection's weights into the memory-side cache (TouchRange, kernels_fast.h).
-//   gemm_tile_kernel    (more than 16 rows: larger decode steps, prefill, the teacher-forced
+//   gemm_tile_kernel    (more rows: larger decode steps, prefill, the teacher-forced
 //       pass, the experts' grouped projections): output tiles of 32 x 128 up to 128 x 320, both
 //       operands copied straight from memory into a ring of LDS stages.
 #include <cstdio>
@@ -94,13 +94,13 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 //     multiplied or stored.
 // Measured (4 rows, weights from HBM): gate/up 7B shape (272 MB) 49.3 -> 43.1 us, down 7B (136 MB) 38.3 -> 26.8,
 // gate/up 1.5B (55 MB) 14.1 -> 12.7, down 1.5B (27.5 MB, only 96 column tiles) 13.1 -> 12.0.
-template <int NT, int KU, int NW, int EPI>
+template <int MT, int NT, int KU, int NW, bool KEEP, int EPI>
 __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
-  static_assert(NT <= 2 && NT <= NW, "one epilogue unit covers a workgroup's columns");
-  __shared__ float4 red[NW * NT * 64];
-  __shared__ float rs_part[NW * 64];
+  static_assert(NT <= 2 && MT <= 2 && NT <= NW, "one epilogue unit covers a workgroup's columns");
+  __shared__ float4 red[NW * MT * NT * 64];
+  __shared__ float rs_part[MT * NW * 64];
   if (p.touch.wgs > 0 && (int)blockIdx.x >= p.touch_x0) {  // uniform over the workgroup
-    touch_range(p.touch, blockIdx.x - p.touch_x0);
+    if (blockIdx.z == 0) touch_range(p.touch, blockIdx.x - p.touch_x0);
     return;
   }
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -113,43 +113,58 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
   const u32x4* w_src[NT];
 #pragma unroll
   for (int j = 0; j < NT; ++j) w_src[j] = (const u32x4*)p.w + (long long)min(nt0 + j, n_tiles - 1) * k_tiles * 64 + lane;
-  // activation fragments of this lane: row r, k = 8 g .. 8 g + 7 of k-tile 0; a k-tile further on is a_step away
-  const int row = min(r, p.M - 1);
-  const u32x4* a_src = (const u32x4*)((const uint16_t*)p.a + (p.frag ? (g * 16 + row) * 8 : plane_offset(row, g * 8, p.K)));
+  // activation fragments of this lane: row m of each row tile, k = 8 g .. 8 g + 7 of k-tile 0; a k-tile further on is
+  // a_step away
+  const u32x4* a_src[MT];
+  int rows[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    rows[i] = min((int)(blockIdx.z * MT + i) * 16 + r, p.M - 1);
+    a_src[i] = (const u32x4*)((const uint16_t*)p.a +
+                              (p.frag ? frag_offset(rows[i], g * 8, k_tiles) : plane_offset(rows[i], g * 8, p.K)));
+  }
   const int a_step = p.frag ? 64 : 8;
   const long long lo_off = ((const uint16_t*)p.a_lo - (const uint16_t*)p.a) >> 3;
 
-  f32x4 acc[NT];
+  f32x4 acc[MT][NT];
 #pragma unroll
-  for (int j = 0; j < NT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  u32x4 wf[2][KU][NT], af[2][KU][2];
-  auto load = [&](int kt, u32x4 (&w)[KU][NT], u32x4 (&a)[KU][2]) {
+  u32x4 wf[2][KU][NT], af[2][KU][MT][2];
+  auto load = [&](int kt, u32x4 (&w)[KU][NT], u32x4 (&a)[KU][MT][2]) {
 #pragma unroll
     for (int kk = 0; kk < KU; ++kk)
 #pragma unroll
-      for (int j = 0; j < NT; ++j)
-        w[kk][j] = __builtin_nontemporal_load(w_src[j] + (long long)min(kt + kk, kt_end - 1) * 64);
+      for (int j = 0; j < NT; ++j) {
+        const u32x4* at = w_src[j] + (long long)min(kt + kk, kt_end - 1) * 64;
+        w[kk][j] = KEEP ? *at : __builtin_nontemporal_load(at);
+      }
 #pragma unroll
-    for (int kk = 0; kk < KU; ++kk) {
-      const u32x4* at = a_src + (long long)min(kt + kk, kt_end - 1) * a_step;
-      a[kk][0] = at[0];
-      a[kk][1] = at[lo_off];
-    }
+    for (int kk = 0; kk < KU; ++kk)
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        const u32x4* at = a_src[i] + (long long)min(kt + kk, kt_end - 1) * a_step;
+        a[kk][i][0] = at[0];
+        a[kk][i][1] = at[lo_off];
+      }
     __builtin_amdgcn_sched_barrier(0);  // all of a chunk's loads leave before the products of the other chunk
   };
-  auto multiply = [&](int kt, const u32x4 (&w)[KU][NT], const u32x4 (&a)[KU][2]) {
+  auto multiply = [&](int kt, const u32x4 (&w)[KU][NT], const u32x4 (&a)[KU][MT][2]) {
 #pragma unroll
     for (int kk = 0; kk < KU; ++kk) {
       const bool on = kt + kk < kt_end;  // a k-tile past the end counts zero
 #pragma unroll
-      for (int plane = 1; plane >= 0; --plane) {  // lo part first, then hi
-        const u32x4 x = on ? a[kk][plane] : u32x4{0u, 0u, 0u, 0u};
+      for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
-          acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[kk][j]),
-                                                           __builtin_bit_cast(bf16x8, x), acc[j], 0, 0, 0);
-      }
+        for (int plane = 1; plane >= 0; --plane) {  // lo part first, then hi
+          const u32x4 x = on ? a[kk][i][plane] : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+          for (int j = 0; j < NT; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[kk][j]),
+                                                                __builtin_bit_cast(bf16x8, x), acc[i][j], 0, 0, 0);
+        }
     }
   };
   // This wavefront's chunks of KU k-tiles: wave, wave + NW, ...  The loop body has no branch: with one, the
@@ -168,11 +183,15 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
   // accumulators.
   constexpr int RS = EPI == EPI_RESID ? 0 : 8;  // the projections that add to the residual read no norm's input
   const int n_rs = p.rinv_ssq ? p.rinv_partials : 0;
-  const float* rs_src = (p.rinv_ssq ? p.rinv_ssq : (const float*)p.a) + (p.rinv_ssq ? row : 0);
-  float rs_of[RS + 1];
+  const float* rs_src = p.rinv_ssq ? p.rinv_ssq : (const float*)p.a;
+  float rs_of[MT][RS + 1];
 #pragma unroll
-  for (int i = 0; i < RS; ++i)  // clamped here, masked where they are summed
-    rs_of[i] = rs_src[(long long)max(min((i * NW + wave) * 4 + g, n_rs - 1), 0) * p.ssq_stride];
+  for (int q = 0; q < MT; ++q)
+#pragma unroll
+    for (int i = 0; i < RS; ++i)  // clamped here, masked where they are summed
+      rs_of[q][i] = rs_src[(long long)max(min((i * NW + wave) * 4 + g, n_rs - 1), 0) * p.ssq_stride + (p.rinv_ssq ? rows[q] : 0)];
+  const int own = MT > 1 ? min(wave, MT - 1) : 0;  // wavefront i < MT finishes row tile i
+  const int m = (blockIdx.z * MT + own) * 16 + r, row = min(m, p.M - 1);
   float4 xv[NT], gn[NT];
   if (EPI == EPI_RESID) {
 #pragma unroll
@@ -202,24 +221,30 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
 
   // the wavefronts' partial tiles meet in LDS
 #pragma unroll
-  for (int j = 0; j < NT; ++j) red[(wave * NT + j) * 64 + lane] = make_float4(acc[j][0], acc[j][1], acc[j][2], acc[j][3]);
-  if constexpr (RS > 0) {
-    float rs_share = 0.f;
+  for (int i = 0; i < MT; ++i)
 #pragma unroll
-    for (int i = 0; i < RS; ++i) rs_share += (i * NW + wave) * 4 + g < n_rs ? rs_of[i] : 0.f;
-    for (int pp = (RS * NW + wave) * 4 + g; pp < n_rs; pp += NW * 4)  // hidden sizes beyond 512 NW
-      rs_share += rs_src[(long long)pp * p.ssq_stride];
-    rs_part[wave * 64 + lane] = rs_share;
+    for (int j = 0; j < NT; ++j)
+      red[((i * NW + wave) * NT + j) * 64 + lane] = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+  if constexpr (RS > 0) {
+#pragma unroll
+    for (int q = 0; q < MT; ++q) {
+      float rs_share = 0.f;
+#pragma unroll
+      for (int i = 0; i < RS; ++i) rs_share += (i * NW + wave) * 4 + g < n_rs ? rs_of[q][i] : 0.f;
+      for (int pp = (RS * NW + wave) * 4 + g; pp < n_rs; pp += NW * 4)  // hidden sizes beyond 512 NW
+        rs_share += rs_src[(long long)pp * p.ssq_stride + rows[q]];
+      rs_part[(q * NW + wave) * 64 + lane] = rs_share;
+    }
   }
   __syncthreads();
-  if (wave > 0) return;
-  const bool valid = r < p.M;
+  if (wave >= MT) return;
+  const bool valid = m < p.M;
   f32x4 t[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
   for (int q = 0; q < NT; ++q)
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      const float4 v = red[(w * NT + q) * 64 + lane];
+      const float4 v = red[((own * NW + w) * NT + q) * 64 + lane];
       t[q][0] += v.x;
       t[q][1] += v.y;
       t[q][2] += v.z;
@@ -230,7 +255,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
     // rsqrt(mean(x^2) + eps); the 4 lanes of a row share the partial sums
     float rs = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) rs += rs_part[w * 64 + lane];
+    for (int w = 0; w < NW; ++w) rs += rs_part[(own * NW + w) * 64 + lane];
     rs += __shfl_xor(rs, 16, WAVE);
     rs += __shfl_xor(rs, 32, WAVE);
     const float rinv = 1.0f / sqrtf(rs / (float)p.K + p.eps);
@@ -253,26 +278,26 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
         x4.y += t[q][1];
         x4.z += t[q][2];
         x4.w += t[q][3];
-        *(float4*)(p.x + (long long)r * p.N + n) = x4;
+        *(float4*)(p.x + (long long)m * p.N + n) = x4;
         ss += x4.x * x4.x + x4.y * x4.y + x4.z * x4.z + x4.w * x4.w;
         uint16_t hi[4], lo[4];
         split_bf16(x4.x * gn[q].x, hi[0], lo[0]);
         split_bf16(x4.y * gn[q].y, hi[1], lo[1]);
         split_bf16(x4.z * gn[q].z, hi[2], lo[2]);
         split_bf16(x4.w * gn[q].w, hi[3], lo[3]);
-        uint16_t* hp = p.h + (p.frag ? frag_offset(r, n, n_tiles >> 1) : plane_offset(r, n, p.N));
+        uint16_t* hp = p.h + (p.frag ? frag_offset(m, n, n_tiles >> 1) : plane_offset(m, n, p.N));
         *(uint2*)hp = pack4(hi);
         *(uint2*)(hp + p.h_lo_offset) = pack4(lo);
       }
     ss += __shfl_xor(ss, 16, WAVE);
     ss += __shfl_xor(ss, 32, WAVE);
-    if (g == 0 && valid) p.ssq_out[(long long)blockIdx.x * p.ssq_stride + r] = ss;
+    if (g == 0 && valid) p.ssq_out[(long long)blockIdx.x * p.ssq_stride + m] = ss;
   } else if (EPI == EPI_SWIGLU_BF16) {
-    store_swiglu(p, valid, r, nt0, t[0], t[1], g, NT == 2 && nt0 + 1 < n_tiles);
+    store_swiglu(p, valid, m, nt0, t[0], t[1], g, NT == 2 && nt0 + 1 < n_tiles);
   } else if (valid) {
 #pragma unroll
     for (int q = 0; q < NT; ++q)
-      if (nt0 + q < n_tiles) store_tile_f32(p, r, nt0 + q, t[q], g, blockIdx.y);
+      if (nt0 + q < n_tiles) store_tile_f32(p, m, nt0 + q, t[q], g, blockIdx.y);
   }
 }
 
@@ -547,15 +572,26 @@ __global__ __launch_bounds__(WM* WN* KG * 64, MINB) void gemm_tile_kernel(GemmAr
 }
 
 // ------------------------------------------------------------------------------------------
-template <int NT, int KU, int NW>
-static void launch_stream(const GemmArgs& a, int epi, dim3 grid, hipStream_t s) {
-  if (epi == EPI_F32)
-    gemm_stream_kernel<NT, KU, NW, EPI_F32><<<grid, NW * 64, 0, s>>>(a);
-  else if (epi == EPI_SWIGLU_BF16)
-    gemm_stream_kernel<NT, KU, NW, EPI_SWIGLU_BF16><<<grid, NW * 64, 0, s>>>(a);
-  else
-    gemm_stream_kernel<NT, KU, NW, EPI_RESID><<<grid, NW * 64, 0, s>>>(a);
-}
+// The stream kernel's shapes, with the epilogues each is planned with.
+//     MT NT KU NW KEEP
+#define STREAM_SHAPES(X)                                                                  \
+  X(0, 1, 2, 2, 8, false, EPI_F32, EPI_SWIGLU_BF16)  /* up to 16 rows, wide outputs */     \
+  X(1, 1, 2, 2, 16, false, EPI_F32, EPI_F32)         /* narrow, at least 192 tiles */      \
+  X(2, 1, 1, 3, 16, false, EPI_F32, EPI_RESID)       /* narrow */                          \
+  X(3, 2, 2, 2, 4, false, EPI_F32, EPI_SWIGLU_BF16)  /* up to 32 rows, from 192 tiles on */ \
+  X(4, 1, 1, 3, 16, true, EPI_F32, EPI_RESID)        /* narrow, a row block per 16 rows */
+struct StreamShape {
+  int mt, nt;
+  const char* name[3];  // by epilogue: F32, SWIGLU, RESID
+};
+static const StreamShape kStreamShapes[] = {
+#define X(id, mt, nt, ku, nw, keep, ...)                                                                         \
+  {mt, nt, {"gemm_stream_kernel<" #mt "," #nt "," #ku "," #nw "," #keep ",0>",                                    \
+            "gemm_stream_kernel<" #mt "," #nt "," #ku "," #nw "," #keep ",1>",                                    \
+            "gemm_stream_kernel<" #mt "," #nt "," #ku "," #nw "," #keep ",2>"}},
+    STREAM_SHAPES(X)
+#undef X
+};
 
 // The tile kernel's shapes.  per_kt, per_kt_alone: microseconds per k-tile of one workgroup's share
 // of a CU that holds its full number of workgroups (per_cu), or only one; fixed: what a workgroup
@@ -704,50 +740,63 @@ static int launch_tile(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s) {
   return a.grid_nz;
 }
 
-// At most kStreamRows rows stream the weights: wide outputs with two column tiles and 8 wavefronts per
-// workgroup, narrow ones with 16 wavefronts, so that the K range, not the column count, fills the CUs - one
-// column tile, or two where that still leaves more than a hundred workgroups (the fused QKV projection of
-// 7B-class models: it halves the activation re-reads; the residual epilogue's projections run better with
-// one).  From 17 rows on the activations every workgroup re-reads outweigh the launches the path saves
-// (7B shape, 24 rows: the four projections of a layer 142 us streamed, 104 us as tiles with their two norm launches).
-GemmPlan gemm_plan(int M, int N, int K, int epi, int max_splits) {
-  if (M > kStreamRows || epi == EPI_LSE) return gemm_plan_tiled(M, N, K, epi, max_splits);
-  static const char* const names[3][3] = {
-      {"gemm_stream_kernel<2,2,8,0>", "gemm_stream_kernel<2,2,8,1>", "gemm_stream_kernel<2,2,8,2>"},
-      {"gemm_stream_kernel<2,2,16,0>", "gemm_stream_kernel<2,2,16,1>", "gemm_stream_kernel<2,2,16,2>"},
-      {"gemm_stream_kernel<1,3,16,0>", "gemm_stream_kernel<1,3,16,1>", "gemm_stream_kernel<1,3,16,2>"}};
+// Up to 16 rows: wide outputs with two column tiles and 8 wavefronts per workgroup, narrow ones with 16
+// wavefronts, so that the K range, not the column count, fills the CUs - one column tile, or two where that still
+// leaves more than a hundred workgroups (the fused QKV projection of 7B-class models: it halves the
+// activation re-reads; the residual epilogue's projections run better with one).
+// 17 to 32 rows (the callers ask for them up to stream_rows): the wider outputs with two row tiles per workgroup, so
+// that the weights are read once; the narrow ones as two workgroups of 16 rows, the second one's weights from L2 (KEEP:
+// their loads leave them there), twice the workgroups on CUs that are idle otherwise.  Decode step of the 1.5B
+// shape at 24 rows: 1.74 ms; two row tiles everywhere 1.80, non-temporal weights in both row blocks 1.87.
+GemmPlan gemm_plan_stream(int M, int N, int K, int epi, int max_splits) {
   GemmPlan pl{};
   const int n_tiles = N >> 4, k_tiles = K >> 5;
+  const bool wide = n_tiles / 2 >= 512 || epi == EPI_SWIGLU_BF16, wider = wide || (epi == EPI_F32 && n_tiles >= 192);
   pl.kind = 0;
-  const bool wide = n_tiles / 2 >= 512 || epi == EPI_SWIGLU_BF16;
-  pl.shape = wide ? 0 : epi == EPI_F32 && n_tiles >= 192 ? 1 : 2;
-  pl.nt = pl.shape == 2 ? 1 : 2;
+  if (M > 16) pl.shape = wider ? 3 : 4;
+  else pl.shape = wide ? 0 : wider ? 1 : 2;
+  pl.nt = kStreamShapes[pl.shape].nt;
   pl.splits = 1;
   if (epi == EPI_F32 && !wide && max_splits > 1) {
     int z = (256 + n_tiles - 1) / n_tiles;
     z = std::min(z, std::max(1, k_tiles / 64));
     pl.splits = std::max(1, std::min({z, max_splits, 4}));
   }
-  pl.name = names[pl.shape][epi];
+  pl.name = kStreamShapes[pl.shape].name[epi];
   return pl;
 }
 
-int launch_gemm_bf16(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s) {
-  if (a.M < 1 || a.N < 16) return 0;
-  if (pl.kind == 1) return launch_tile(a, epi, pl, s);
+GemmPlan gemm_plan(int M, int N, int K, int epi, int max_splits) {
+  return M > 16 || epi == EPI_LSE ? gemm_plan_tiled(M, N, K, epi, max_splits) : gemm_plan_stream(M, N, K, epi, max_splits);
+}
+
+static int launch_stream(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s) {
+  const StreamShape& t = kStreamShapes[pl.shape];
   const int n_tiles = a.N >> 4, k_tiles = a.K >> 5;
   a.k_tiles_per_split = ceil_div(k_tiles, epi == EPI_F32 ? pl.splits : 1);
-  dim3 grid(ceil_div(n_tiles, pl.nt), ceil_div(k_tiles, a.k_tiles_per_split));
+  dim3 grid(ceil_div(n_tiles, t.nt), ceil_div(k_tiles, a.k_tiles_per_split), ceil_div(a.M, 16 * t.mt));
   if (a.touch.wgs > 0 && grid.y == 1) {
     a.touch_x0 = (int)grid.x;
     grid.x += (unsigned)a.touch.wgs;
   } else {
     a.touch.wgs = 0;
   }
-  if (pl.shape == 0) launch_stream<2, 2, 8>(a, epi, grid, s);
-  else if (pl.shape == 1) launch_stream<2, 2, 16>(a, epi, grid, s);
-  else launch_stream<1, 3, 16>(a, epi, grid, s);
+  switch (pl.shape) {
+#define X(id, mt, nt, ku, nw, keep, e0, e1)                                                        \
+  case id:                                                                                         \
+    if (epi == e0) gemm_stream_kernel<mt, nt, ku, nw, keep, e0><<<grid, nw * 64, 0, s>>>(a);        \
+    else if (epi == e1) gemm_stream_kernel<mt, nt, ku, nw, keep, e1><<<grid, nw * 64, 0, s>>>(a);   \
+    else throw HipError(hipErrorInvalidValue, "streamed projection", __FILE__, __LINE__);              \
+    break;
+    STREAM_SHAPES(X)
+#undef X
+  }
   return (int)grid.y;
+}
+
+int launch_gemm_bf16(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s) {
+  if (a.M < 1 || a.N < 16) return 0;
+  return pl.kind == 1 ? launch_tile(a, epi, pl, s) : launch_stream(a, epi, pl, s);
 }
 
 // ---------------------------------------------------------------- log-prob from the parts

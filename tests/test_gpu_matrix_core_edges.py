@@ -62,3 +62,37 @@ def test_moe_block_rows_lines(rows):
     print(f"{rows} rows: max |dlogp| = {err:.3e}, routing gaps {below:.3e} {outside:.3e}")
     assert err <= TOL and below <= TOL and outside <= TOL
     eng.close()
+
+
+@pytest.mark.parametrize("rows", [15, 16, 17, 31, 32, 33])
+@pytest.mark.parametrize("hidden", [512, 2080])
+def test_streamed_rows_lines(rows, hidden):
+    """Decode steps around the lines of the streamed path: a full 16-row fragment, a second one of a single row, 32 rows
+    and the first step of the tile path (17 for hidden sizes above 2048).  The samples end one by one, so the rows
+    cross the lines on the way down: both operand layouts in the same buffers, one after the other."""
+    shape = dataclasses.replace(workloads.SMALL_BF16, hidden=hidden, ffn_dim=544)
+    w = scaled_weights(shape, seed=1, scale=1.0 if hidden == 512 else 0.7)
+    model = oracle_model(shape, w)
+    eng = make_engine(shape, w, max_live_samples=40)
+    toks, offs = workloads.make_prompts(1, 70, 70, shape.vocab, seed=4)
+    forced = np.random.default_rng(6).integers(0, shape.vocab, (rows, 6)).astype(np.int32)
+    lens = np.full(rows, 6, np.int32)
+    lens[::7] = 2                                     # 17 -> 14, 33 -> 28 rows after the first step
+    lens[1::9] = 4
+    fwd = T.KVForward(model)
+    prefix = fwd.new_cache()
+    fwd.extend([prefix], [toks])
+    caches = [prefix.fork() for _ in range(rows)]
+    ids, *_ = eng.rollout_prefill(toks, offs, rows, lens, forced_first=forced[:, 0])
+    worst = 0.0
+    for t in range(1, 6):
+        live = np.flatnonzero(lens > t)
+        got_ids, _, _, _ = eng.rollout_decode_step(forced_tokens=forced[live, t])
+        assert np.array_equal(got_ids, ids[live])
+        gpu = eng.rollout_debug_logits()
+        ref = fwd.extend([caches[i] for i in live], [[int(forced[i, t - 1])] for i in live])
+        worst = max(worst, max(float(np.max(np.abs(gpu[k] - ref[k][0]))) for k in range(len(live))))
+    print(f"{rows} rows, hidden {hidden}: max |dlogits| = {worst:.3e}")
+    assert worst <= TOL
+    assert eng.rollout_get_stats()["live_samples"] == 0
+    eng.close()

@@ -331,15 +331,16 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
 // Measured against the kernel it replaced (register-staged, 64 x 256 and 64 x 128 tiles), random
 // operands: 12000 rows x 37888 x 3584 5.53 -> 4.52 ms (720 TFLOP/s, 1440 issued), 1700 x 17920 x
 // 1536 192 -> 157 us, 187 x 17920 x 1536 33 -> 27 us, 64 x 37888 x 3584 70 -> 57 us.
-// 16 bytes per lane from base + voff to LDS byte `lds` + 16 * lane.  As inline assembly, because the compiler makes
-// every LDS read wait for all copies into LDS that it knows of.
+// 16 bytes per lane from base + voff to LDS byte `lds` + 16 * lane.  (The compiler keeps nothing in m0: it sets it
+// right before each instruction of its own that reads it.)  As inline assembly, because the compiler makes every
+// LDS read wait for all copies into LDS that it knows of.
 __device__ __forceinline__ void load_to_lds(unsigned lds, unsigned voff, const void* base) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base)
-               : "memory", "m0");
+               : "memory");
 }
 // the same with a 64-bit address per lane
 __device__ __forceinline__ void load_to_lds(unsigned lds, const void* addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(addr) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(addr) : "memory");
 }
 // this wavefront's loads but the last N have arrived and its LDS reads are done; then the barrier
 template <int N>

@@ -271,8 +271,9 @@ void engine_init(rollout_ctx& c, const rollout_weights& w) {
   const size_t R = c.r_max;
   c.x.alloc(R * d);
   if (!c.simple) {
-    // activation buffers hold two planes each: hi parts, then lo parts; rows padded to whole
-    // 16-row fragments for the small decode steps, which keep them in fragment order
+    // activation buffers hold the hi and lo parts of every value, interleaved in blocks of 32, or for
+    // the decode steps that stream the weights as two planes in fragment order (rows padded to
+    // whole 16-row fragments for those)
     const size_t Rp = (R + 31) / 32 * 32;
     c.h_bf16.alloc(2 * Rp * d);
     c.q_bf16.alloc(2 * R * c.q_dim);

@@ -125,7 +125,7 @@ __device__ inline const uint4* group_block(const AttnArgs& a, int slot, int kv_h
   return page_block(a, a.page_table[(long long)slot * a.max_pages + tok0 / a.geom.page_tokens], kv_head, tok0, is_v);
 }
 
-// four consecutive values as hi + lo bf16 parts into the two planes of an activation buffer
+// four consecutive values as hi + lo bf16 parts into an activation buffer
 __device__ inline void store4_split(uint16_t* dst, long long lo_offset, float a, float b, float c, float d) {
   uint16_t hi[4], lo[4];
   split_bf16(a, hi[0], lo[0]);

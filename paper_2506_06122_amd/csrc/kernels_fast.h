@@ -88,8 +88,8 @@ struct GemmArgs {
   // EPI_RESID
   float* x = nullptr;            // [M][N] residual stream, updated in place
   const float* gain = nullptr;   // [N] gain of the RMSNorm that follows
-  uint16_t* h = nullptr;         // bf16 [M][N], hi plane
-  long long h_lo_offset = 0;     // elements from the hi plane of h to its lo plane
+  uint16_t* h = nullptr;         // bf16 [M][N], first hi part
+  long long h_lo_offset = 0;     // elements from a hi part of h to its lo part
   float* ssq_out = nullptr;      // [grid columns][ssq_stride]
   // grouped launch (mixture of experts, tile kernel): row block y works on rows
   // [block_row_begin[y], block_row_end[y]) of the expert-sorted order with the weights of
@@ -124,7 +124,6 @@ struct GemmPlan {
 };
 GemmPlan gemm_plan(int M, int N, int K, int epi, int max_splits);
 GemmPlan gemm_plan_stream(int M, int N, int K, int epi, int max_splits);  // the stream kernel for M <= 32
-GemmPlan gemm_plan_tiled(int M, int N, int K, int epi, int max_splits);  // the tile kernel for any M
 GemmPlan gemm_plan_grouped(int epi, int block_rows);                     // experts' row blocks of moe_block_rows
 // column parts per row that an EPI_LSE launch with this plan writes, and the most any plan writes
 inline int lse_parts(const GemmPlan& pl, int N) { return ceil_div(N >> 4, pl.nt); }

@@ -10,8 +10,9 @@
 // out^T, so each lane ends up with four consecutive output columns of one row.
 //
 // Activations keep near-fp32 precision through the bf16 instruction: every activation value v
-// travels as two bf16 numbers, hi = bf16(v) and lo = bf16(v - hi), in two planes of the same
-// shape, and each weight fragment is multiplied with both (the weights themselves are bf16
+// travels as two bf16 numbers, hi = bf16(v) and lo = bf16(v - hi) - side by side in blocks of 32
+// (plane_offset) or, where the weights are streamed, as two planes in fragment order (frag_offset,
+// kernels_fast.h) - and each weight fragment is multiplied with both (the weights themselves are bf16
 // exactly, so nothing else is rounded).  That doubles the matrix instructions, which the
 // memory-bound decode step does not notice.
 //
@@ -43,11 +44,6 @@
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
-
-union Frag {
-  uint4 u;
-  bf16x8 v;
-};
 
 __device__ inline float silu_f(float a) { return a / (1.0f + __expf(-a)); }
 
@@ -663,7 +659,7 @@ static double tile_cost(const TileShape& t, int M, int n_tiles, int k_tiles, int
 }
 
 // tile shape and number of K splits with the lowest expected cost
-GemmPlan gemm_plan_tiled(int M, int N, int K, int epi, int max_splits) {
+static GemmPlan gemm_plan_tiled(int M, int N, int K, int epi, int max_splits) {
   // decode steps ask for the same few plans layer after layer
   struct Key {
     int M, N, K, epi, max_splits;

@@ -4,6 +4,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "tile_grid.h"
 
 // Epilogues of the projection kernels:
 //   EPI_F32          out[m][n] fp32 (split-K planes allowed)
@@ -76,8 +77,7 @@ struct GemmArgs {
   long long out_lo_offset = 0;  // EPI_SWIGLU_BF16: elements from a hi part of `out` to its lo part
   long long split_stride;  // floats between split planes (EPI_F32)
   int k_tiles_per_split;   // filled by the launcher
-  int grid_nx = 0, grid_ny = 0, grid_nz = 0;  // tile kernel: column blocks, row blocks, K splits (launcher)
-  int group_m = 1, group_n = 1;  // tile kernel: row and column blocks an XCD takes side by side (launcher)
+  TileGrid grid;           // tile kernel: the launch's blocks (launcher)
   // input normalisation (stream kernel)
   const float* rinv_ssq = nullptr;  // [rinv_partials][ssq_stride] partial sums of squares of the input rows
   int rinv_partials = 0;

@@ -344,23 +344,6 @@ __device__ __forceinline__ void wait_and_barrier() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-// Workgroup -> (column block, row block, K split).  The launch is one-dimensional and workgroups
-// go to the 8 XCDs (each with its own L2) round-robin by index, so index % 8 is the XCD and
-// index / 8 the order inside it.  An XCD takes groups of group_m row blocks x group_n column blocks, whose
-// workgroups run side by side and share the operands' lines in its L2; groups go round the XCDs
-// with the split varying fastest, then the row blocks.
-__device__ inline bool tile_block(const GemmArgs& p, int& bx, int& by, int& bz) {
-  const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
-  const int per = p.group_m * p.group_n;
-  const int unit = (idx / per) * 8 + xcd, in = idx % per;
-  const int gy = (p.grid_ny + p.group_m - 1) / p.group_m;
-  bz = unit % p.grid_nz;
-  const int q = unit / p.grid_nz;
-  by = (q % gy) * p.group_m + in % p.group_m;
-  bx = (q / gy) * p.group_n + in / p.group_m;
-  return by < p.grid_ny && bx < p.grid_nx;
-}
-
 // GATHER: the rows of `a` come through row_map (experts' grouped projections)
 template <int WM, int WN, int MT, int NT, int KG, int S, int MINB, int EPI, bool GATHER>
 __global__ __launch_bounds__(WM* WN* KG * 64, MINB) void gemm_tile_kernel(GemmArgs p) {
@@ -374,8 +357,9 @@ __global__ __launch_bounds__(WM* WN* KG * 64, MINB) void gemm_tile_kernel(GemmAr
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, g = lane >> 4;
   const int n_tiles = p.N >> 4, k_tiles = p.K >> 5;
-  int bx, by, bz;
-  if (!tile_block(p, bx, by, bz)) return;  // padding of the XCD-aware launch (uniform)
+  const TileBlock block = tile_block(p.grid, blockIdx.x);
+  if (!block.inside) return;  // uniform
+  const int bx = block.x, by = block.y, bz = block.z;
   const int nt0 = bx * (BN / 16);
   int m0 = by * BM;
   const int kt_begin = bz * p.k_tiles_per_split;
@@ -620,33 +604,11 @@ static const TileShape kTileShapes[] = {
 constexpr bool grouped_shape(int id) { return id == 0 || id == 1 || id == 7; }  // row blocks of moe_block_rows
 constexpr int kLseMinTile = 8;    // column tiles per workgroup an EPI_LSE launch has at least (sizes the parts' buffers)
 
-// Row and column blocks an XCD takes side by side (tile_block), and the workgroups its busiest CU gets.
-// Groups go to the XCDs whole, so a group that is large against the launch leaves XCDs idle: of the
-// group heights that cut the row blocks evenly, the largest with the fewest workgroups per CU.
-// With many workgroups in all, four column blocks side by side, so that the group's activation and weight lines
-// are both few.
-static int tile_groups(long long ny, long long nx, long long nz, int& gm, int& gn) {
-  const int chunks = ceil_div(ny, 16);
-  gn = ny * nx >= 1024 && ny > 4 ? 4 : 1;
-  int best = 0x7fffffff;
-  gm = 1;
-  for (int c = chunks; c < chunks + 6 && c <= ny; ++c) {
-    const int m = ceil_div(ny, c);
-    const long long units = (long long)ceil_div(ny, m) * ceil_div(nx, gn) * nz;
-    const int n = ceil_div((long long)ceil_div(units, 8) * m * gn, 32);
-    if (n < best) {
-      best = n;
-      gm = m;
-    }
-  }
-  return best;
-}
-
 // Microseconds one projection is expected to take: the busiest CU's rounds of workgroups, not less
 // than the weights take from HBM, plus reading the split planes back (the next launch's work).
 static double tile_cost(const TileShape& t, int M, int n_tiles, int k_tiles, int z) {
-  int gm, gn;
-  const int n = tile_groups(ceil_div(M, t.wm * t.mt * 16), ceil_div(n_tiles, t.wn * t.nt), z, gm, gn);
+  TileGrid g{ceil_div(n_tiles, t.wn * t.nt), ceil_div(M, t.wm * t.mt * 16), z};
+  const int n = tile_groups(g);
   // one workgroup per CU: nothing hides its first loads and its result from the next round, and over many
   // rounds the model flatters it by up to a fifth
   if (t.minb == 1 && n > 2) return 1e30;
@@ -708,17 +670,13 @@ static int launch_tile(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s) {
   const TileShape& t = kTileShapes[pl.shape];
   const int n_tiles = a.N >> 4, k_tiles = a.K >> 5, bm = t.wm * t.mt * 16;
   a.k_tiles_per_split = ceil_div(k_tiles, epi == EPI_F32 ? pl.splits : 1);
-  a.grid_nz = ceil_div(k_tiles, a.k_tiles_per_split);
-  a.grid_nx = ceil_div(n_tiles, pl.nt);
-  a.grid_ny = a.group_of_block ? a.n_row_blocks : ceil_div(a.M, bm);
-  if (a.group_of_block) {  // an expert's few row blocks follow each other: its weights are fetched once
-    a.group_m = std::min(a.grid_ny, 16);
-    a.group_n = 1;
-  } else {
-    tile_groups(a.grid_ny, a.grid_nx, a.grid_nz, a.group_m, a.group_n);
-  }
-  const long long units = (long long)ceil_div(a.grid_ny, a.group_m) * ceil_div(a.grid_nx, a.group_n) * a.grid_nz;
-  const dim3 grid((unsigned)(ceil_div(units, 8) * 8 * a.group_m * a.group_n));
+  a.grid.nz = ceil_div(k_tiles, a.k_tiles_per_split);
+  a.grid.nx = ceil_div(n_tiles, pl.nt);
+  a.grid.ny = a.group_of_block ? a.n_row_blocks : ceil_div(a.M, bm);
+  // an expert's few row blocks follow each other: its weights are fetched once
+  if (a.group_of_block) a.grid.group_m = std::min(a.grid.ny, 16);
+  else tile_groups(a.grid);
+  const dim3 grid((unsigned)tile_workgroups(a.grid));
   const bool gather = a.row_map != nullptr;
   switch (pl.shape) {
 #define X(id, wm, wn, mt, nt, kg, st, minb, ...)                                                                    \
@@ -733,7 +691,7 @@ static int launch_tile(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s) {
     TILE_SHAPES(X)
 #undef X
   }
-  return a.grid_nz;
+  return a.grid.nz;
 }
 
 // Up to 16 rows: wide outputs with two column tiles and 8 wavefronts per workgroup, narrow ones with 16

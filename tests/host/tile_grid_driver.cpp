@@ -1,0 +1,49 @@
+// CPU-only check of csrc/tile_grid.h: the workgroups of a tile launch visit every (column block, row block, K split)
+// exactly once, for every shape of launch the planner can ask for.  Built and run by tests/test_host_tile_grid.py.
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+
+#include "../../paper_2506_06122_amd/csrc/tile_grid.h"
+
+static void check(const TileGrid& g, const char* what) {
+  const long long n = tile_workgroups(g);
+  std::vector<unsigned char> seen((size_t)g.nx * g.ny * g.nz, 0);
+  for (long long i = 0; i < n; ++i) {
+    const TileBlock b = tile_block(g, (unsigned)i);
+    if (!b.inside) continue;
+    if (b.x < 0 || b.y < 0 || b.z < 0 || b.z >= g.nz || seen[((size_t)b.z * g.ny + b.y) * g.nx + b.x]++) {
+      std::fprintf(stderr, "%s %d x %d x %d in groups of %d x %d: workgroup %lld\n", what, g.nx, g.ny, g.nz, g.group_m, g.group_n, i);
+      std::exit(1);
+    }
+  }
+  for (unsigned char s : seen)
+    if (s != 1) {
+      std::fprintf(stderr, "%s %d x %d x %d in groups of %d x %d: a block is missing\n", what, g.nx, g.ny, g.nz, g.group_m, g.group_n);
+      std::exit(1);
+    }
+}
+
+int main() {
+  int n = 0;
+  const int wide[] = {1, 2, 3, 5, 8, 12, 13, 28, 36, 112, 140, 148, 297, 594, 1187, 1188};
+  for (int nx : wide)
+    for (int ny : {1, 2, 3, 4, 5, 6, 7, 15, 16, 17, 31, 33, 64, 100, 129, 289, 513})
+      for (int nz : {1, 2, 3, 7, 16}) {
+        if ((long long)nx * ny * nz > 700000) continue;
+        TileGrid g;
+        g.nx = nx, g.ny = ny, g.nz = nz;
+        const int per_cu = tile_groups(g);
+        check(g, "dense");
+        // the busiest XCD's workgroups, shared by its 32 CUs
+        if ((long long)per_cu * 256 < (long long)nx * ny * nz || g.group_m < 1 || g.group_m > 16) return 2;
+        if (nz == 1) {  // the experts' launches
+          g.group_m = ny < 16 ? ny : 16;
+          g.group_n = 1;
+          check(g, "grouped");
+        }
+        ++n;
+      }
+  std::printf("%d launches\n", n);
+  return 0;
+}

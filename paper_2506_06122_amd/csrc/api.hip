@@ -63,8 +63,8 @@ static void wait_step_done(rollout_ctx& c) {
 }
 
 // The end of a call: polling answers within microseconds where a blocking wait may sleep.  A call that takes
-// longer than 10 ms gives the core away between polls (a poll then comes about every 80 us, which uses a tenth of
-// the core and adds 0.4 % to the call at most).
+// longer than 20 ms gives the core away between polls (a poll then comes about every 80 us, which uses a tenth of
+// the core and adds 0.2 % to the call at most).
 static void wait_stream(hipStream_t s) {
   using namespace std::chrono;
   const auto t0 = steady_clock::now();
@@ -73,7 +73,7 @@ static void wait_stream(hipStream_t s) {
     if (e == hipSuccess) return;
     if (e != hipErrorNotReady) throw HipError(e, "hipStreamQuery", __FILE__, __LINE__);
     if ((polls & 63u) != 63u) continue;
-    if (steady_clock::now() - t0 < milliseconds(10)) continue;
+    if (steady_clock::now() - t0 < milliseconds(20)) continue;
     std::this_thread::sleep_for(microseconds(20));
     polls = 62;  // one poll between sleeps
   }

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 def test_long_wait_gives_the_core_away():
     """A call that has to wait some 200 ms for work ahead of it on its stream uses less than half of a core
-    meanwhile (the first 10 ms are polled without a pause: 5 %), and returns the same results."""
+    meanwhile (the first 20 ms are polled without a pause: 10 %), and returns the same results."""
     import torch
     import paper_2506_06122_amd as R
     z = torch.from_numpy(workloads.random_logits(4, 5000, seed=1, scale=2.0)).cuda()

@@ -92,8 +92,8 @@ def test_teacher_forced_logits_match_oracle(name, simple):
                                                       (1, 3, 1, 1)],
                          ids=["24rows", "40rows", "72rows", "long-context-splits", "one-token-prompt"])
 def test_matrix_core_decode_shapes(n_prompts, n_samples, lo, hi):
-    """Row-tile configurations of the streamed projections (<=16, <=32, <=64, several row
-    blocks) and attention over several KV splits with the merge in the last workgroup."""
+    """Projections of a decode step: streamed with one and with two row tiles (up to 32 rows at this hidden
+    size), then as tiles; and attention over several KV splits with their merge."""
     shape = workloads.SMALL_BF16
     w = scaled_weights(shape, seed=1)
     model = oracle_model(shape, w)

@@ -75,12 +75,15 @@ def test_policy_loss_edge_cases():
         R.rollout_policy_loss(cu, dev(new), dev(old), dev(ref), dev(mask), rewards, gamma=-1.0)
 
 
-@pytest.mark.parametrize("lens,offset", [([4095, 4096, 4097, 12289, 1, 3, 2, 5], 0), ([4095, 4097, 9001, 2, 6], 1),
-                                         ([2048, 2047, 1025, 1024, 1023, 1], 0), ([1, 2, 3, 1026, 517], 3)],
+@pytest.mark.parametrize("lens,offset,late", [([4095, 4096, 4097, 12289, 1, 3, 2, 5], 0, {3: 5000, 0: 900}),
+                                              ([4095, 4097, 9001, 2, 6], 1, {2: 8200, 0: 900}),
+                                              ([2048, 2047, 1025, 1024, 1023, 1], 0, {0: 1100, 1: 900}),
+                                              ([1, 2, 3, 1026, 1926, 517], 3, {4: 1100, 0: 0, 3: 1025})],
                          ids=["long", "long-unaligned", "short", "short-unaligned"])
-def test_policy_loss_chunk_edges(lens, offset):
+def test_policy_loss_chunk_edges(lens, offset, late):
     """Lengths around the 4096- and 1024-token chunks, sequences that start inside a quad, arrays off
-    their alignment by `offset` elements.  fp32 against fp64 as above: with gamma 0.9 a return is a
+    their alignment by `offset` elements.  late: sequences whose last tokens do not count, the first of them so many
+    that its return starts (and its reward falls) in a later chunk than the first one walked.  fp32 against fp64 as above: with gamma 0.9 a return is a
     sum of at most ~100 terms of size 20, 1e-4 is 80 ulp of its clipped size of 10."""
     import torch
     rng = np.random.default_rng(len(lens) + offset)
@@ -90,7 +93,13 @@ def test_policy_loss_chunk_edges(lens, offset):
     new = (old + 0.3 * rng.standard_normal(total)).astype(np.float32)
     ref = (old + 0.2 * rng.standard_normal(total)).astype(np.float32)
     mask = (rng.random(total) < 0.7).astype(np.uint8)
-    mask[cu[1] - 1 - min(lens[0], 900):cu[1]] = 0        # the last counted token chunks away from the end
+    for seq, tail in late.items():
+        mask[cu[seq + 1] - tail:cu[seq + 1]] = 0
+        mask[max(cu[seq], cu[seq + 1] - tail - 1)] = 1
+    chunk = 1024 if max(lens) <= 2048 else 4096
+    first = next(iter(late))
+    last_counted = cu[first] + np.flatnonzero(mask[cu[first]:cu[first + 1]])[-1]
+    assert last_counted < cu[first + 1] - chunk          # nothing counts in the first chunk walked
     rewards = (rng.standard_normal(len(lens)) * 15.0).astype(np.float32)
 
     def dev(a):

@@ -57,6 +57,12 @@ struct PinnedBuf {
   PinnedBuf& operator=(const PinnedBuf&) = delete;
 };
 
+// A piece of a buffer that another member owns.
+template <typename T>
+struct Piece {
+  T* p = nullptr;
+};
+
 struct LayerWeights {
   DevBuf<float> norm1, norm2;
   DevBuf<float> qkv_bias;        // [q | k | v] biases (ROLLOUT_MODEL_QKV_BIAS)
@@ -178,7 +184,7 @@ struct rollout_ctx : HostState {
 
   bool broken = false;          // a step timed out: the device state is unknown, every call is refused
   double step_timeout_s = 300;  // wall-clock bound of the wait that ends a decode step
-  PinnedBuf<int> h_page_rows, h_page_list;  // staged rows [n_slots][max_pages], (row, entries) each
+  Piece<int> h_page_rows, h_page_list;  // of h_staging: staged rows [n_slots][max_pages], (row, entries) each
   int n_page_rows = 0;
   DevBuf<int> d_live;
 
@@ -220,14 +226,15 @@ struct rollout_ctx : HostState {
   DevBuf<long long> row_sample_id;
   DevBuf<float> row_inv_temp, row_top_p, out_logprobs;
   DevBuf<unsigned> row_uniform;
-  DevBuf<float> samp_part_max;               // sampler scratch, see SampleRows
-  DevBuf<unsigned long long> samp_seg_sums;
+  DevBuf<unsigned long long> samp_scratch;   // sampler scratch, see SampleRows:
+  Piece<unsigned long long> samp_seg_sums, samp_nucleus;  // nucleus: the rows that draw with top_p < 1, in batches
+  Piece<float> samp_part_max;
   int samp_rows = 0;                         // rows the sampler scratch holds
-  DevBuf<unsigned long long> samp_nucleus;   // scratch of the rows that draw with top_p < 1, in batches
   int samp_nucleus_rows = 0;
-  PinnedBuf<int> h_int;      // staging, 17 * r_max ints: 8 for a forward pass, 9 for the draw behind it
-  PinnedBuf<float> h_float;  // staging, 4 * r_max floats
-  PinnedBuf<long long> h_ll; // staging, r_max
+  PinnedBuf<long long> h_staging;  // one allocation (each costs rollout_init some 100 us), in pieces:
+  Piece<long long> h_ll;           // r_max
+  Piece<int> h_int;                // 17 * r_max: 8 for a forward pass, 9 for the draw behind it
+  Piece<float> h_float;            // 4 * r_max
   int last_logit_rows = 0;
 
   rollout_stats stats{};

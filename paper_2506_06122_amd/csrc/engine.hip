@@ -345,15 +345,19 @@ void engine_init(rollout_ctx& c, const rollout_weights& w) {
   c.out_logprobs.alloc(R);
   c.row_uniform.alloc(R);
   c.samp_rows = (int)std::min<size_t>(R, 4096);
-  c.samp_part_max.alloc((size_t)c.samp_rows * kSampleParts);
-  c.samp_seg_sums.alloc((size_t)c.samp_rows * kSampleSegments);
   c.samp_nucleus_rows = std::min(c.samp_rows, 512);
-  c.samp_nucleus.alloc((size_t)c.samp_nucleus_rows * kNucleusScratch);
-  c.h_int.alloc(17 * R);
-  c.h_page_rows.alloc(c.h_page_table.size());
-  c.h_page_list.alloc(2 * (size_t)c.n_slots);
-  c.h_float.alloc(4 * R);
-  c.h_ll.alloc(R);
+  const size_t seg_words = (size_t)c.samp_rows * kSampleSegments, nucleus_words = (size_t)c.samp_nucleus_rows * kNucleusScratch;
+  c.samp_scratch.alloc(seg_words + nucleus_words + (size_t)c.samp_rows * (kSampleParts / 2));
+  c.samp_seg_sums.p = c.samp_scratch.p;
+  c.samp_nucleus.p = c.samp_seg_sums.p + seg_words;
+  c.samp_part_max.p = (float*)(c.samp_nucleus.p + nucleus_words);
+  const size_t ints = 17 * R + c.h_page_table.size() + 2 * (size_t)c.n_slots + 4 * R;
+  c.h_staging.alloc(R + (ints + 1) / 2);
+  c.h_ll.p = c.h_staging.p;
+  c.h_int.p = (int*)(c.h_ll.p + R);
+  c.h_page_rows.p = c.h_int.p + 17 * R;
+  c.h_page_list.p = c.h_page_rows.p + c.h_page_table.size();
+  c.h_float.p = (float*)(c.h_page_list.p + 2 * (size_t)c.n_slots);
   HIP_TRY(hipStreamSynchronize(c.stream));
 }
 

@@ -581,9 +581,10 @@ static const StreamShape kStreamShapes[] = {
 struct TileShape {
   int wm, wn, mt, nt, kg, s, minb;
   float per_kt, per_kt_alone, start, fixed;
-  const char* name[3];  // by epilogue: F32, SWIGLU, LSE
+  const char* name[4];  // by epilogue: F32, SWIGLU, LSE, SWIGLU with gathered rows
 };
-#define TILE_NAME(a) {"gemm_tile_kernel<" a ",0>", "gemm_tile_kernel<" a ",1>", "gemm_tile_kernel<" a ",3>"}
+#define TILE_NAME(a) \
+  {"gemm_tile_kernel<" a ",0,false>", "gemm_tile_kernel<" a ",1,false>", "gemm_tile_kernel<" a ",3,false>", "gemm_tile_kernel<" a ",1,true>"}
 // x-macro: index, template arguments, model
 #define TILE_SHAPES(X)                                        \
   X(0, 2, 2, 1, 4, 1, 4, 3, 0.151f, 0.179f, 2.1f, 1.4f)   /*  32 x 128 */ \
@@ -597,7 +598,7 @@ struct TileShape {
   X(8, 2, 2, 4, 8, 1, 2, 2, 0.623f, 0.781f, 0.2f, 8.2f)   /* 128 x 256 */
 static const TileShape kTileShapes[] = {
 #define X(id, wm, wn, mt, nt, kg, s, minb, a, b, c, d) \
-  {wm, wn, mt, nt, kg, s, minb, a, b, c, d, TILE_NAME(#wm "," #wn "," #mt "," #nt "," #kg "," #s)},
+  {wm, wn, mt, nt, kg, s, minb, a, b, c, d, TILE_NAME(#wm "," #wn "," #mt "," #nt "," #kg "," #s "," #minb)},
     TILE_SHAPES(X)
 #undef X
 };
@@ -662,7 +663,7 @@ GemmPlan gemm_plan_grouped(int epi, int block_rows) {
   const TileShape& t = kTileShapes[pl.shape];
   pl.nt = t.wn * t.nt;
   pl.splits = 1;
-  pl.name = t.name[epi == EPI_F32 ? 0 : 1];
+  pl.name = t.name[epi == EPI_F32 ? 0 : 3];  // the gate/up launch gathers its rows
   return pl;
 }
 

@@ -497,12 +497,14 @@ static void merge_attention_slots(rollout_ctx& c, const AttnArgs& at, int rows) 
 // How the cached positions of a decode step's `rows` rows are cut: wavefronts per workgroup and KV splits
 // per (row, KV head), at most the 16 the merge kernel takes.  A round of a workgroup (32 positions per
 // wavefront) takes about 1.5 us, a merge launch as much as three rounds, so a split has to save more
-// rounds than that.
+// rounds than that.  A workgroup of eight wavefronts has its CU to itself, so the splits stop where the
+// workgroups still fit the 256 CUs at once: with one split more a second, nearly empty set of them
+// doubled the launch (1.5B shape, 20 rows at 16000 positions: 2.98 ms a step, 2.39 now).
 static void plan_decode_attention(const rollout_ctx& c, int rows, AttnArgs& at) {
   const int base = rows * c.geom.n_kv_heads;
   at.wide = base <= 256;
   const int round = at.wide ? 256 : 128;
-  const int most = std::max(1, std::min({ceil_div(256, base), ceil_div(c.decode_max_ctx, 256), c.attn_max_parts / base, 16}));
+  const int most = std::max(1, std::min({256 / base, ceil_div(c.decode_max_ctx, 256), c.attn_max_parts / base, 16}));
   const int whole = ceil_div(c.decode_max_ctx, round), cut = ceil_div(c.decode_max_ctx, round * most);
   const int n = whole - cut > 3 ? most : 1;
   at.split_tokens = ceil_div(ceil_div(c.decode_max_ctx, n), 128) * 128;

@@ -96,3 +96,19 @@ def test_streamed_rows_lines(rows, hidden):
     assert worst <= TOL
     assert eng.rollout_get_stats()["live_samples"] == 0
     eng.close()
+
+
+@pytest.mark.parametrize("rows", [7, 20, 43, 127, 129])
+def test_attention_splits_fill_the_chip_once(rows):
+    """Row counts that do not divide the 256 CUs, with contexts long enough to be cut: 16, 6, 2 and 1 splits per
+    (row, KV head), and one row past the workgroups of eight wavefronts."""
+    shape = dataclasses.replace(workloads.SMALL_BF16, n_layers=1)
+    w = scaled_weights(shape, seed=1)
+    model = oracle_model(shape, w)
+    eng = make_engine(shape, w, max_live_samples=136, max_context=1600, max_batch_tokens=2048)
+    toks, offs = workloads.make_prompts(1, 1500, 1500, shape.vocab, seed=8)
+    forced = np.random.default_rng(6).integers(0, shape.vocab, (rows, 3)).astype(np.int32)
+    worst, worst_lp = teacher_forced_compare(eng, model, toks, offs, rows, forced, 3)
+    print(f"{rows} rows: max |dlogits| = {worst:.3e}, max |dlogp| = {worst_lp:.3e}")
+    assert worst <= TOL and worst_lp <= TOL
+    eng.close()

@@ -674,8 +674,7 @@ static int launch_tile(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s) {
   a.grid.nz = ceil_div(k_tiles, a.k_tiles_per_split);
   a.grid.nx = ceil_div(n_tiles, pl.nt);
   a.grid.ny = a.group_of_block ? a.n_row_blocks : ceil_div(a.M, bm);
-  // an expert's few row blocks follow each other: its weights are fetched once
-  if (a.group_of_block) a.grid.group_m = std::min(a.grid.ny, 16);
+  if (a.group_of_block) tile_groups_experts(a.grid);
   else tile_groups(a.grid);
   const dim3 grid((unsigned)tile_workgroups(a.grid));
   const bool gather = a.row_map != nullptr;

@@ -47,3 +47,21 @@ constexpr int tile_groups(TileGrid& g) {
   g.group_m = best_m;
   return best;
 }
+
+// The same for the experts' launches.  An expert's few row blocks follow each other (its weights are fetched once),
+// and the blocks past the last used one, up to half of them, exit at once.  A row group goes from column to column
+// through the XCDs in steps of the number of groups; with 8 groups it meets one XCD in every column, and the unused
+// ones left three XCDs idle (14 rows of the 30B-A3B shape: 2.06 ms a step, 12 layers; 1.34 with 9 groups).  So few
+// groups come in an odd number (6 -> 7: 1.33 -> 1.27 ms), up to 16 of them not in fours (12 -> 13: 3.23 -> 3.04), and
+// more, of which every XCD gets several anyway, not in eights (24 -> 25: 12.7 -> 11.9 ms); cutting 10, 20 or 36
+// groups differently as well cost 1 to 3 %.
+constexpr bool groups_share_xcds(long long groups) {
+  return groups > 1 && groups % (groups < 8 ? 2 : groups < 16 ? 4 : 8) == 0;
+}
+constexpr void tile_groups_experts(TileGrid& g) {
+  const int most = g.ny < 16 ? g.ny : 16;
+  g.group_n = 1;
+  g.group_m = most;
+  while (g.group_m > most / 2 && groups_share_xcds(tile_ceil(g.ny, g.group_m))) --g.group_m;
+  if (g.group_m <= most / 2) g.group_m = most;
+}

@@ -38,11 +38,29 @@ int main() {
         // the busiest XCD's workgroups, shared by its 32 CUs
         if ((long long)per_cu * 256 < (long long)nx * ny * nz || g.group_m < 1 || g.group_m > 16) return 2;
         if (nz == 1) {  // the experts' launches
-          g.group_m = ny < 16 ? ny : 16;
-          g.group_n = 1;
+          tile_groups_experts(g);
           check(g, "grouped");
         }
         ++n;
+      }
+  // the used row blocks of an experts' launch come first: whatever their share, no XCD gets much more than an
+  // eighth of their workgroups (a third more where 12 columns meet 8 XCDs; with groups of 16 throughout it was up to 3.4 times as much)
+  for (int nx : {8, 12, 16})
+    for (int ny = 8; ny <= 600; ++ny)
+      for (int used : {(2 * ny + 4) / 5, (7 * ny + 9) / 10, ny}) {
+        TileGrid g;
+        g.nx = nx, g.ny = ny, g.nz = 1;
+        tile_groups_experts(g);
+        int load[8] = {};
+        for (long long i = 0; i < tile_workgroups(g); ++i) {
+          const TileBlock b = tile_block(g, (unsigned)i);
+          load[i & 7] += b.inside && b.y < used;
+        }
+        for (int l : load)
+          if (ny > 20 && l * 8.0 > 1.45 * nx * used) {
+            std::fprintf(stderr, "%d of %d row blocks, %d columns: an XCD gets %d workgroups of %d\n", used, ny, nx, l, nx * used);
+            return 3;
+          }
       }
   std::printf("%d launches\n", n);
   return 0;

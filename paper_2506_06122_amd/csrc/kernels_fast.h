@@ -315,18 +315,13 @@ void launch_moe_plan(const MoePlanArgs& a, hipStream_t s);
 // Rows per block of the grouped projections, by the picks an expert gets on average: few rows leave
 // more of the chip's loads in flight to the weights (the launch is a stream over the touched experts'
 // weights then), many rows use every weight fragment for a whole block (it is bound by the matrix
-// instructions and the operand traffic).  The picks of an expert scatter about the average, so where that
-// is a little below a block's rows many experts need a second, nearly empty block, and blocks of half the
-// rows (or of twice the rows) do better.  The lines are where the blocks' times cross for whole packed passes of the
+// instructions and the operand traffic).  The lines are where the blocks' times cross for whole packed passes of the
 // 30B-A3B shape, 12 layers, 128 experts (ms with 32 / 64 / 128 rows; one block size of 64 rows with the kernel
 // before: last):
-//   picks  27.9:  4.14  4.36  4.78  ( 5.04)     30.8:  4.97  4.41  4.83  ( 5.15)     48.0:  5.81  5.88  6.26  ( 6.47)
-//          57.3:  6.80  7.74  7.11  ( 7.42)     69.0:  7.71  7.65  7.83  ( 8.89)     118:  11.38 11.09 12.41 (12.92)
-//          154:  14.48 13.74 13.79 (15.56)      169:  15.57 14.94 14.73 (16.72)      317:  28.21 27.01 25.93 (29.07)
+//   picks  14.9:  2.70  2.78  3.14  ( 3.48)     27.9:  4.13  4.15  4.73  ( 5.04)     30.8:  4.33  4.23  4.80  ( 5.15)
+//          57.3:  6.82  6.82  7.04  ( 7.42)     99.0:  10.15 9.78  9.95  (11.31)     142:  13.48 12.88 12.93 (14.72)
+//          154:  14.57 13.81 13.76 (15.56)      185:  16.86 16.27 15.81 (17.75)      500:  42.99 40.14 39.30 (42.60)
 constexpr int kMoeMinBlockRows = 32;
 inline int moe_block_rows(long long picks, int n_experts) {
-  if (picks <= 28ll * n_experts) return 32;
-  if (picks <= 46ll * n_experts) return 64;
-  if (picks <= 66ll * n_experts) return 32;
-  return picks <= 160ll * n_experts ? 64 : 128;
+  return picks <= 28ll * n_experts ? 32 : picks <= 150ll * n_experts ? 64 : 128;
 }

@@ -37,11 +37,19 @@ __host__ __device__ inline bf16_t f32_to_bf16(float f) {
   return out;
 }
 
-// v = hi + lo with both parts bf16: carries about 16 significant bits through bf16 arithmetic
-__host__ __device__ inline void split_bf16(float v, uint16_t& hi, uint16_t& lo) {
-  const bf16_t h = f32_to_bf16(v);
-  hi = h.bits;
-  lo = f32_to_bf16(v - bf16_to_f32(h)).bits;
+// v = hi + lo with both parts bf16: carries about 16 significant bits through bf16 arithmetic.  Packed in pairs:
+// gfx950 rounds two fp32 values to bf16 (nearest, ties to even) in one instruction, so that a pair takes six
+// instructions where the rounding by integer arithmetic took some forty.
+typedef float f32_pair __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16_pair __attribute__((ext_vector_type(2)));
+__device__ inline void split2_bf16(float a, float b, uint32_t& hi, uint32_t& lo) {
+  hi = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32_pair{a, b}), bf16_pair));
+  const f32_pair rest{a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u)};
+  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, bf16_pair));
+}
+__device__ inline void split4_bf16(float a, float b, float c, float d, uint2& hi, uint2& lo) {
+  split2_bf16(a, b, hi.x, lo.x);
+  split2_bf16(c, d, hi.y, lo.y);
 }
 
 // IEEE half: the 16-bit format of the KV cache of bf16 models.  Keys and values are of order

@@ -127,19 +127,16 @@ __device__ inline const uint4* group_block(const AttnArgs& a, int slot, int kv_h
 
 // four consecutive values as hi + lo bf16 parts into an activation buffer
 __device__ inline void store4_split(uint16_t* dst, long long lo_offset, float a, float b, float c, float d) {
-  uint16_t hi[4], lo[4];
-  split_bf16(a, hi[0], lo[0]);
-  split_bf16(b, hi[1], lo[1]);
-  split_bf16(c, hi[2], lo[2]);
-  split_bf16(d, hi[3], lo[3]);
-  *(uint2*)dst = make_uint2((uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16));
-  *(uint2*)(dst + lo_offset) = make_uint2((uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16));
+  uint2 hi, lo;
+  split4_bf16(a, b, c, d, hi, lo);
+  *(uint2*)dst = hi;
+  *(uint2*)(dst + lo_offset) = lo;
 }
 __device__ inline void store1_split(uint16_t* dst, long long lo_offset, float a) {
-  uint16_t hi, lo;
-  split_bf16(a, hi, lo);
-  dst[0] = hi;
-  dst[lo_offset] = lo;
+  uint32_t hi, lo;
+  split2_bf16(a, a, hi, lo);
+  dst[0] = (uint16_t)hi;
+  dst[lo_offset] = (uint16_t)lo;
 }
 
 // element (row b, column k) of the decode result

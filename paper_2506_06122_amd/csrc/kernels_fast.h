@@ -206,8 +206,6 @@ struct QkvPostArgs {
 };
 void launch_qkv_post(const QkvPostArgs& a, hipStream_t s);
 
-void launch_f32_to_bf16(const float* src, uint16_t* dst, long long n, hipStream_t s);
-
 constexpr int GROUP_MEMBERS = 4;  // samples of one prompt that attend to its shared pages together
 
 // Paged grouped-query attention on the matrix cores (KV_MATRIX pool, head_dim 128).

@@ -109,15 +109,11 @@ __global__ __launch_bounds__(ROW_T) void row_norm_kernel(RowNormArgs a) {
     const int c = t + ROW_T * v;
     if (c >= n4) continue;
     if (write_x) ((float4*)(a.x + (long long)r * a.hidden))[c] = x[v];
-    uint16_t hi[4], lo[4];
-    split_bf16(x[v].x * gn[v].x * rinv, hi[0], lo[0]);
-    split_bf16(x[v].y * gn[v].y * rinv, hi[1], lo[1]);
-    split_bf16(x[v].z * gn[v].z * rinv, hi[2], lo[2]);
-    split_bf16(x[v].w * gn[v].w * rinv, hi[3], lo[3]);
+    uint2 hi, lo;
+    split4_bf16(x[v].x * gn[v].x * rinv, x[v].y * gn[v].y * rinv, x[v].z * gn[v].z * rinv, x[v].w * gn[v].w * rinv, hi, lo);
     uint16_t* hp = a.h + (a.h_frag ? frag_offset(r, 4 * c, a.hidden >> 5) : plane_offset(r, 4 * c, a.hidden));
-    *(uint2*)hp = make_uint2((uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16));
-    *(uint2*)(hp + a.h_lo_offset) =
-        make_uint2((uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16));
+    *(uint2*)hp = hi;
+    *(uint2*)(hp + a.h_lo_offset) = lo;
   }
 }
 void launch_row_norm(const RowNormArgs& a, hipStream_t s) {
@@ -195,12 +191,4 @@ void launch_qkv_post(const QkvPostArgs& a, hipStream_t s) {
   const int per_block = 256 / (a.geom.head_dim / 2);
   const int n_heads = a.n_q_heads + 2 * a.geom.n_kv_heads;
   qkv_post_kernel<<<dim3(a.rows, ceil_div(n_heads, per_block)), 256, 0, s>>>(a);
-}
-
-__global__ void f32_to_bf16_kernel(const float* __restrict__ src, uint16_t* __restrict__ dst, long long n) {
-  long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = f32_to_bf16(src[i]).bits;
-}
-void launch_f32_to_bf16(const float* src, uint16_t* dst, long long n, hipStream_t s) {
-  if (n) f32_to_bf16_kernel<<<ceil_div(n, 256), 256, 0, s>>>(src, dst, n);
 }

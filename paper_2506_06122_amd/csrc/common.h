@@ -72,6 +72,13 @@ __host__ __device__ inline void split_f16(float v, uint16_t& hi, uint16_t& lo) {
   hi = __builtin_bit_cast(uint16_t, h);
   lo = __builtin_bit_cast(uint16_t, (_Float16)(v - (float)h));
 }
+// the same for a pair
+typedef _Float16 f16_pair __attribute__((ext_vector_type(2)));
+__device__ inline void split2_f16(float a, float b, uint32_t& hi, uint32_t& lo) {
+  const f16_pair h = __builtin_convertvector((f32_pair{a, b}), f16_pair);
+  hi = __builtin_bit_cast(uint32_t, h);
+  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32_pair{a - (float)h[0], b - (float)h[1]}), f16_pair));
+}
 
 __host__ __device__ inline float to_f32(float v) { return v; }
 __host__ __device__ inline float to_f32(bf16_t v) { return bf16_to_f32(v); }

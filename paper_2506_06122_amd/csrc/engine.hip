@@ -680,7 +680,7 @@ static void forward_rows_tiled(rollout_ctx& c, int R, const SeqBatch* seqs) {
       at.seq_pos0 = seqs->pos0;
       at.n_seqs = seqs->n_seqs;
       at.max_seq_len = seqs->max_len;
-      c.timer.begin("attn_prefill_kernel", kv_bytes + 4.0 * Rq * c.q_dim, Bd ? c.chunk_attn_flops : c.attn_flops_this_call, s);
+      c.timer.begin(attention_prefill_name(at), kv_bytes + 4.0 * Rq * c.q_dim, Bd ? c.chunk_attn_flops : c.attn_flops_this_call, s);
       launch_attention_prefill(at, s);
       c.timer.end(s);
     }

@@ -20,7 +20,7 @@
 //   decode, shared prompts (optional): in the same launch, workgroups of (split, KV head, up
 //             to 4 samples of one prompt) take the prompt's shared pages with the members'
 //             query heads as columns, and the per-sample workgroups start after those pages.
-//   prefill : one wavefront per (16 query positions, query head); columns = positions;
+//   prefill : one wavefront per (16 or 32 query positions, query head); columns = positions;
 //             causal limit per column; a sequence may continue a cached context (its rows
 //             then attend to that context too).
 #include "kernels_fast.h"
@@ -30,6 +30,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 union Frag {
   uint4 u;
   f16x8 v;
+  uint32_t w[4];
   uint16_t h[8];
 };
 #define MFMA16(a, b, c) __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0)
@@ -37,74 +38,108 @@ union Frag {
 #define DH 128
 #define GROUP_U4 512  // uint4 per 32-position group of one K (or V) block: 32 * 128 * 2 / 16
 // Probabilities are scaled by 2^10 before they become half-precision operands, so that the
-// small probabilities of a long, flat attention row stay in the normal range; the output
-// accumulators carry the same factor until the final normalisation.
-#define P_SCALE 1024.0f
+// small probabilities of a long, flat attention row stay in the normal range; the sums and the output
+// accumulators carry the same factor, which the final normalisation divides out.
+#define P_SCALE_LOG2 10.0f
 
-// One 32-position group (fragments already in registers) against this lane's query column.
-// limit = last visible position of the column.  m, l in log2 units; o = unnormalised
-// output^T fragments.
-__device__ inline void attend_frags(const Frag (&k)[2][4], const Frag (&v)[8], const Frag (&q)[8], int tok0,
-                                    int limit, float scale_log2, float& m, float& l, f32x4 (&o)[8], int lane) {
-  const int g = lane >> 4;
-  f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+// largest value / sum over the 4 lanes that hold a column (16 and 32 lanes apart), in each of them: swaps of
+// rows and halves of the wavefront, a few cycles each, where exchanges through LDS cost some sixty
+__device__ __forceinline__ float column_max(float x) {
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float column_sum(float x) {
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// One 32-position group against this lane's query column, in three parts, so that callers can request the next
+// group's keys and values as soon as this one's are used.
+//   scores: S^T = K q^T, the lo parts of the query (q[4..7]) first.
+__device__ __forceinline__ void group_scores(const Frag (&k)[2][4], const Frag (&q)[8], f32x4& s0, f32x4& s1) {
+  s0 = f32x4{0.f, 0.f, 0.f, 0.f};
+  s1 = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {  // q[4..7] = lo parts of the query, q[0..3] = hi parts
-    s0 = MFMA16(k[0][ks].v, q[4 + ks].v, s0);
-    s1 = MFMA16(k[1][ks].v, q[4 + ks].v, s1);
+  for (int i = 0; i < 8; ++i) {
+    s0 = MFMA16(k[0][i & 3].v, q[(i + 4) & 7].v, s0);
+    s1 = MFMA16(k[1][i & 3].v, q[(i + 4) & 7].v, s1);
   }
+}
+//   softmax: probabilities as hi + lo half-precision parts.  limit = last visible position of the column; m in log2
+//   units; l = this lane's share of the column's sum (column_sum at the end); o = unnormalised output^T fragments,
+//   rescaled only where the maximum of a column has moved.
+__device__ __forceinline__ void group_softmax(f32x4 s0, f32x4 s1, int tok0, int limit, float scale_log2, float& m,
+                                              float& l, f32x4 (&o)[8], Frag& hi, Frag& lo, int lane) {
+  if (!__all(tok0 + 31 <= limit)) {
+    const int seen = limit - tok0 - 4 * (lane >> 4);
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    s0 = MFMA16(k[0][ks].v, q[ks].v, s0);
-    s1 = MFMA16(k[1][ks].v, q[ks].v, s1);
+    for (int i = 0; i < 4; ++i) {
+      s0[i] = i <= seen ? s0[i] : -INFINITY;
+      s1[i] = 16 + i <= seen ? s1[i] : -INFINITY;
+    }
   }
-  float sc[8];
-  const int tbase = tok0 + 4 * g;
+  float mx = fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])), fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3])));
+  mx = column_max(mx) * scale_log2;
+  if (__any(mx > m)) {
+    const float m_new = fmaxf(m, mx);
+    const float alpha = __builtin_amdgcn_exp2f(m - (m_new == -INFINITY ? 0.f : m_new));
+    m = m_new;
+    l *= alpha;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      o[j][0] *= alpha;
+      o[j][1] *= alpha;
+      o[j][2] *= alpha;
+      o[j][3] *= alpha;
+    }
+  }
+  const float shift = P_SCALE_LOG2 - (m == -INFINITY ? 0.f : m);
+  float p[8];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    sc[i] = (tbase + i <= limit) ? s0[i] * scale_log2 : -INFINITY;
-    sc[4 + i] = (tbase + 16 + i <= limit) ? s1[i] * scale_log2 : -INFINITY;
+    p[i] = __builtin_amdgcn_exp2f(fmaf(s0[i], scale_log2, shift));
+    p[4 + i] = __builtin_amdgcn_exp2f(fmaf(s1[i], scale_log2, shift));
   }
-  float mx = sc[0];
+  l += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
 #pragma unroll
-  for (int e = 1; e < 8; ++e) mx = fmaxf(mx, sc[e]);
-  mx = fmaxf(mx, __shfl_xor(mx, 16, WAVE));
-  mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
-  const float m_new = fmaxf(m, mx);
-  const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-  float ps = 0.f;
-  Frag pb, pl;  // probabilities as hi + lo half-precision parts
+  for (int i = 0; i < 4; ++i) split2_f16(p[2 * i], p[2 * i + 1], hi.w[i], lo.w[i]);
+}
+//   values: O^T += V^T P^T
+__device__ __forceinline__ void group_values(const Frag (&v)[8], const Frag& hi, const Frag& lo, f32x4 (&o)[8]) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    float p = exp2f(sc[e] - m_use);
-    ps += p;
-    split_f16(p * P_SCALE, pb.h[e], pl.h[e]);
-  }
-  ps += __shfl_xor(ps, 16, WAVE);
-  ps += __shfl_xor(ps, 32, WAVE);
-  const float alpha = exp2f(m - m_use);
-  l = l * alpha + ps;
-  m = m_new;
+  for (int j = 0; j < 8; ++j) o[j] = MFMA16(v[j].v, lo.v, o[j]);
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    o[j][0] *= alpha;
-    o[j][1] *= alpha;
-    o[j][2] *= alpha;
-    o[j][3] *= alpha;
-    o[j] = MFMA16(v[j].v, pl.v, o[j]);
-    o[j] = MFMA16(v[j].v, pb.v, o[j]);
-  }
+  for (int j = 0; j < 8; ++j) o[j] = MFMA16(v[j].v, hi.v, o[j]);
+}
+// The three together, fragments already in registers.
+__device__ __forceinline__ void attend_frags(const Frag (&k)[2][4], const Frag (&v)[8], const Frag (&q)[8], int tok0,
+                                             int limit, float scale_log2, float& m, float& l, f32x4 (&o)[8], int lane) {
+  f32x4 s0, s1;
+  Frag hi, lo;
+  group_scores(k, q, s0, s1);
+  group_softmax(s0, s1, tok0, limit, scale_log2, m, l, o, hi, lo, lane);
+  group_values(v, hi, lo, o);
 }
 
 // key and value fragments of one 32-position group from its KV page
-__device__ __forceinline__ void load_group(const uint4* __restrict__ kblk, const uint4* __restrict__ vblk,
-                                           Frag (&k)[2][4], Frag (&v)[8], int lane) {
+__device__ __forceinline__ void load_keys(const uint4* __restrict__ kblk, Frag (&k)[2][4], int lane) {
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) k[t][ks].u = kblk[(t * 4 + ks) * 64 + lane];
+}
+__device__ __forceinline__ void load_values(const uint4* __restrict__ vblk, Frag (&v)[8], int lane) {
 #pragma unroll
   for (int j = 0; j < 8; ++j) v[j].u = vblk[j * 64 + lane];
+}
+__device__ __forceinline__ void load_group(const uint4* __restrict__ kblk, const uint4* __restrict__ vblk,
+                                           Frag (&k)[2][4], Frag (&v)[8], int lane) {
+  load_keys(kblk, k, lane);
+  load_values(vblk, v, lane);
 }
 
 // The same, with the group's key and value fragments streamed from a KV page.
@@ -293,6 +328,7 @@ __device__ __forceinline__ float merged_sum(const DecodeSmem& sm, int col) {
 template <int NW>
 __device__ __forceinline__ void merge_wavefronts(const DecodeSmem& sm, int ml0, float m, float l, const f32x4 (&o)[8],
                                                  int wave, int c, int g) {
+  l = column_sum(l);
   if (g == 0) sm.m[wave * sm.ml_cols + ml0 + c] = m;
   __syncthreads();
   const float M = merged_max<NW>(sm, ml0 + c);
@@ -322,7 +358,7 @@ __device__ __forceinline__ float merged_out(const DecodeSmem& sm, int e) {
 // group's keys and values, in flight while the queries are rotated and staged.
 template <bool EXTRA, int NW>
 __device__ __forceinline__ void decode_own_range(const AttnArgs& a, const DecodeSmem& sm, int split, int kvh, int b) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, g = lane >> 4, i = lane;
   const int n_kv = a.geom.n_kv_heads;
   const int G = a.n_q_heads / n_kv;
@@ -404,13 +440,23 @@ __device__ __forceinline__ void decode_own_range(const AttnArgs& a, const Decode
   f32x4 o[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (tok0 < t_end) {  // the group that is in registers already
+  if (tok0 < t_end) {  // the first group is in registers already
+    // keys of the next group are requested as soon as this one's are used, its values likewise; the page number after
+    // that ahead of both (loads return in order)
+    int page = pt[min(tok0 + 32 * NW, t_end - 1) / T];
+    for (; tok0 + 32 * NW < t_end; tok0 += 32 * NW) {
+      const int next = tok0 + 32 * NW, after = pt[min(next + 32 * NW, t_end - 1) / T];
+      f32x4 s0, s1;
+      Frag hi, lo;
+      group_scores(k, q, s0, s1);
+      load_keys(page_block(a, page, kvh, next, 0), k, lane);
+      group_softmax(s0, s1, tok0, pos - 1, scale_log2, m, l, o, hi, lo, lane);
+      group_values(v, hi, lo, o);
+      load_values(page_block(a, page, kvh, next, 1), v, lane);
+      page = after;
+    }
     attend_frags(k, v, q, tok0, pos - 1, scale_log2, m, l, o, lane);
-    tok0 += 32 * NW;
   }
-  for (; tok0 < t_end; tok0 += 32 * NW)
-    attend_group(group_block(a, slot, kvh, tok0, 0), group_block(a, slot, kvh, tok0, 1), q, tok0, pos - 1,
-                 scale_log2, m, l, o, lane);
   if (owner && wave == NW - 1) {  // the new position, from LDS: token 0 of a group that starts at pos
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
@@ -432,7 +478,7 @@ __device__ __forceinline__ void decode_own_range(const AttnArgs& a, const Decode
   for (int e = tid; e < G * DH; e += 64 * NW) {
     const int col = e >> 7;
     const float acc = merged_out<NW>(sm, e);
-    if (direct) store1_split(a.out + out_offset(a, b, kvh * G * DH + e), a.out_lo_offset, acc / (merged_sum<NW>(sm, col) * P_SCALE));
+    if (direct) store1_split(a.out + out_offset(a, b, kvh * G * DH + e), a.out_lo_offset, acc / merged_sum<NW>(sm, col));
     else a.part_o[part * (16 * DH) + e] = acc;
   }
   if (!direct && tid < 16) {
@@ -552,7 +598,7 @@ __global__ __launch_bounds__(256, 3) void attn_decode_grouped_kernel(AttnArgs a)
 // Merge of the partial results of one (sample, KV head), at most 16 slots: a launch of its
 // own, because a launch boundary is the cheapest way to publish results between workgroups here.
 __global__ __launch_bounds__(256) void attn_merge_fused_kernel(AttnArgs a) {
-  __shared__ float w_s[16][16];  // [slot][column] weight 2^(m_s - M) / (L 2^10)
+  __shared__ float w_s[16][16];  // [slot][column] weight 2^(m_s - M) / L
   const int tid = threadIdx.x, kvh = blockIdx.x, b = blockIdx.y;
   const int n_kv = a.geom.n_kv_heads;
   const int G = a.n_q_heads / n_kv;
@@ -606,7 +652,7 @@ __global__ __launch_bounds__(256) void attn_merge_fused_kernel(AttnArgs a) {
 #pragma unroll
     for (int q = 0; q < 16; ++q) L += lw_s[q][col];
     __syncthreads();
-    w_s[s][col] = w / (L * P_SCALE);
+    w_s[s][col] = w / L;
     __syncthreads();
   }
 #pragma unroll
@@ -661,48 +707,98 @@ void launch_attention_decode_grouped(const AttnArgs& a, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------------------ prefill
-__global__ __launch_bounds__(256) void attn_prefill_kernel(AttnArgs a) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// A workgroup is one wavefront: CT tiles of 16 positions of one query head, which share every key and value fragment it
+// loads.  The next group's keys and values are requested as soon as this one's are used, and the wavefronts with the last,
+// longest rows start first.
+// What bounds it: the fragments' way from L2 (16 KB per 32 positions and wavefront, about 14 TB/s with two tiles), then
+// the products of hi and lo parts.  Per layer, against 16-position wavefronts in workgroups of four that exchanged by
+// way of LDS: 7B shape, 10568 rows in 4 sequences 777 -> 522 us; 1.5B shape, 6000 rows in 2 sequences 211 -> 160,
+// 187 rows 12.4 -> 7.5.  Two or four wavefronts to a workgroup (ragged sequences leave them unevenly filled): 548, 572.
+template <int CT>
+__global__ __launch_bounds__(64, 2) void attn_prefill_kernel(AttnArgs a) {
+  const int lane = threadIdx.x;
   const int c = lane & 15, g = lane >> 4;
   const int seq = blockIdx.z, head = blockIdx.y;
   const int len = a.seq_len[seq];
-  const int q0 = blockIdx.x * 64 + wave * 16;
-  if (q0 >= len) return;  // wavefronts are independent: no barrier below
-  const int row0 = a.seq_row0[seq], slot = a.seq_slot[seq];
+  const int q0 = (gridDim.x - 1 - blockIdx.x) * 16 * CT;
+  if (q0 >= len) return;
+  const int row0 = a.seq_row0[seq];
   const int p0 = a.seq_pos0 ? a.seq_pos0[seq] : 0;  // cached positions before the sequence's first row
   const int kvh = head / (a.n_q_heads / a.geom.n_kv_heads);
-  const int qi = q0 + c;                             // row of this column inside the sequence
-  const int pos = p0 + qi;
+  const int* pt = a.page_table + (long long)a.seq_slot[seq] * a.max_pages;
+  const int T = a.geom.page_tokens;
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)DH);
-  Frag q[8];
+  const int last = p0 + min(q0 + 16 * CT, len) - 1;  // last position any row of the wavefront attends to
+  Frag k[2][4], v[8];
+  load_group(page_block(a, pt[0], kvh, 0, 0), page_block(a, pt[0], kvh, 0, 1), k, v, lane);
+  int page = pt[min(32, last) / T];
+  Frag q[CT][8];
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    q[ks].u = make_uint4(0, 0, 0, 0);
-    q[4 + ks].u = make_uint4(0, 0, 0, 0);
-    if (qi < len) {
-      const uint16_t* src = a.q + ((long long)(row0 + qi) * a.n_q_heads + head) * DH + ks * 32 + g * 8;
-      q[ks].u = *(const uint4*)src;
-      q[4 + ks].u = *(const uint4*)(src + a.q_lo_offset);
+  for (int t = 0; t < CT; ++t) {
+    const int qi = min(q0 + 16 * t + c, len - 1);  // rows past the end repeat the last one and are not stored
+    const uint16_t* src = a.q + ((long long)(row0 + qi) * a.n_q_heads + head) * DH + g * 8;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      q[t][ks].u = *(const uint4*)(src + ks * 32);
+      q[t][4 + ks].u = *(const uint4*)(src + a.q_lo_offset + ks * 32);
     }
   }
-  float m = -INFINITY, l = 0.f;
-  f32x4 o[8];
+  float m[CT], l[CT];
+  f32x4 o[CT][8];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int last = p0 + min(q0 + 15, len - 1);
-  for (int tok0 = 0; tok0 <= last; tok0 += 32)
-    attend_group(group_block(a, slot, kvh, tok0, 0), group_block(a, slot, kvh, tok0, 1), q, tok0, pos, scale_log2,
-                 m, l, o, lane);
-  if (qi < len) {
+  for (int t = 0; t < CT; ++t) {
+    m[t] = -INFINITY;
+    l[t] = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) o[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  f32x4 s0[CT], s1[CT];
+  Frag hi[CT], lo[CT];
+  auto scores = [&]() {
+#pragma unroll
+    for (int t = 0; t < CT; ++t) group_scores(k, q[t], s0[t], s1[t]);
+  };
+  auto rest = [&](int tok0) {
+#pragma unroll
+    for (int t = 0; t < CT; ++t)
+      group_softmax(s0[t], s1[t], tok0, p0 + q0 + 16 * t + c, scale_log2, m[t], l[t], o[t], hi[t], lo[t], lane);
+#pragma unroll
+    for (int t = 0; t < CT; ++t) group_values(v, hi[t], lo[t], o[t]);
+  };
+  int tok0 = 0;
+  for (; tok0 + 32 <= last; tok0 += 32) {
+    const int after = pt[min(tok0 + 64, last) / T];
+    scores();
+    load_keys(page_block(a, page, kvh, tok0 + 32, 0), k, lane);
+    rest(tok0);
+    load_values(page_block(a, page, kvh, tok0 + 32, 1), v, lane);
+    page = after;
+  }
+  scores();
+  rest(tok0);
+#pragma unroll
+  for (int t = 0; t < CT; ++t) {
+    const int qi = q0 + 16 * t + c;
+    const float inv = 1.0f / column_sum(l[t]);
+    if (qi >= len) continue;
     uint16_t* dst = a.out + plane_offset(row0 + qi, head * DH + 4 * g, a.n_q_heads * DH);
-    const float inv = 1.0f / (l * P_SCALE);
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-      store4_split(dst + plane_offset(0, 16 * j, 0), a.out_lo_offset, o[j][0] * inv, o[j][1] * inv, o[j][2] * inv, o[j][3] * inv);
+      store4_split(dst + plane_offset(0, 16 * j, 0), a.out_lo_offset, o[t][j][0] * inv, o[t][j][1] * inv, o[t][j][2] * inv,
+                   o[t][j][3] * inv);
   }
 }
 
+// Two tiles to a wavefront from 2048 wavefronts (two per SIMD) on; with fewer, CUs would idle.  One tile / two: 72
+// wavefronts of two tiles 7.5 / 11.2 us, 1224 14.8 / 16.0, 3840 30.7 / 30.7, 6144 73 / 66.
+static bool prefill_pairs(const AttnArgs& a) {
+  return (long long)ceil_div(a.max_seq_len, 32) * a.n_q_heads * a.n_seqs >= 2048;
+}
+const char* attention_prefill_name(const AttnArgs& a) {
+  return prefill_pairs(a) ? "attn_prefill_kernel<2>" : "attn_prefill_kernel<1>";
+}
 void launch_attention_prefill(const AttnArgs& a, hipStream_t s) {
   if (!a.n_seqs) return;
-  attn_prefill_kernel<<<dim3(ceil_div(a.max_seq_len, 64), a.n_q_heads, a.n_seqs), 256, 0, s>>>(a);
+  if (prefill_pairs(a)) attn_prefill_kernel<2><<<dim3(ceil_div(a.max_seq_len, 32), a.n_q_heads, a.n_seqs), 64, 0, s>>>(a);
+  else attn_prefill_kernel<1><<<dim3(ceil_div(a.max_seq_len, 16), a.n_q_heads, a.n_seqs), 64, 0, s>>>(a);
 }

@@ -251,6 +251,7 @@ struct AttnArgs {
   int n_seqs, max_seq_len;
 };
 void launch_attention_prefill(const AttnArgs& a, hipStream_t s);
+const char* attention_prefill_name(const AttnArgs& a);  // the kernel it launches, as a profiler shows it
 // Decode attention: partial results per (row, KV head, slot) when a.n_splits > 1 or the launch is
 // the grouped one - launch_attention_merge then joins the slots; with one split the result is final.
 void launch_attention_decode_fused(const AttnArgs& a, hipStream_t s);

@@ -112,3 +112,52 @@ def test_attention_splits_fill_the_chip_once(rows):
     print(f"{rows} rows: max |dlogits| = {worst:.3e}, max |dlogp| = {worst_lp:.3e}")
     assert worst <= TOL and worst_lp <= TOL
     eng.close()
+
+
+EDGE_LENS = [1, 15, 16, 17, 31, 32, 33, 47, 63, 64, 65, 95, 96, 97, 127, 129]
+
+
+@pytest.mark.parametrize("copies", [1, 4])
+def test_packed_attention_tiles(copies):
+    """Sequences around the edges of 16- and 32-position tiles and 32-position key groups: 16 of them take one
+    tile to a wavefront, 64 of them (5 blocks of 32 x 8 heads x 64) two."""
+    shape = dataclasses.replace(workloads.SMALL_BF16, n_layers=1)
+    w = scaled_weights(shape, seed=1)
+    model = oracle_model(shape, w)
+    lens = EDGE_LENS * copies
+    eng = make_engine(shape, w, max_live_samples=80, max_batch_tokens=8192)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    toks = np.random.default_rng(copies).integers(0, shape.vocab, int(cu[-1])).astype(np.int32)
+    got = eng.rollout_logprobs(toks, cu, temperature=1.0)
+    err = float(np.max(np.abs(got - T.packed_log_probs(model, toks, cu))))
+    print(f"{len(lens)} sequences: max |dlogp| = {err:.3e}")
+    assert err <= TOL
+    eng.close()
+
+
+def test_appended_rows_attention_tiles():
+    """The same edges as appended tokens behind a cached context that is no multiple of 32, enough of them for two
+    tiles to a wavefront: the logits after the last appended token against the oracle."""
+    shape = dataclasses.replace(workloads.SMALL_BF16, n_layers=1)
+    w = scaled_weights(shape, seed=1)
+    model = oracle_model(shape, w)
+    n = 64
+    lens = np.array([max(1, x - 1) for x in EDGE_LENS * 4])  # a sequence is the last response token and these
+    eng = make_engine(shape, w, max_live_samples=80, max_batch_tokens=8192)
+    toks, offs = workloads.make_prompts(1, 45, 45, shape.vocab, seed=4)
+    rng = np.random.default_rng(5)
+    first = rng.integers(0, shape.vocab, n).astype(np.int32)
+    ids, *_ = eng.rollout_prefill(toks, offs, n, np.full(n, 4, np.int32), forced_first=first)
+    aoffs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    app = rng.integers(0, shape.vocab, int(aoffs[-1])).astype(np.int32)
+    eng.rollout_extend(ids, app, aoffs, forced_next=rng.integers(0, shape.vocab, n).astype(np.int32))
+    gpu = eng.rollout_debug_logits()
+    fwd = T.KVForward(model)
+    prefix = fwd.new_cache()
+    fwd.extend([prefix], [toks])
+    caches = [prefix.fork() for _ in range(n)]
+    ref = fwd.extend(caches, [[int(first[i])] + [int(t) for t in app[aoffs[i]:aoffs[i + 1]]] for i in range(n)])
+    worst = max(float(np.max(np.abs(gpu[i] - ref[i][-1]))) for i in range(n))
+    print(f"max |dlogits| = {worst:.3e}")
+    assert worst <= TOL
+    eng.close()

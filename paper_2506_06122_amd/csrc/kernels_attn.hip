@@ -191,14 +191,17 @@ __device__ inline long long out_offset(const AttnArgs& a, int b, int k) {
 // they go to attn_merge_fused_kernel.
 // EXTRA: the model adds a bias to q, k, v and / or normalises q and k heads (a.extra).
 struct DecodeSmem {
-  uint16_t* q;   // [2][q_cols][DH] hi parts, lo parts
+  uint16_t* q;   // [2][q_cols][Q_LD] hi parts, lo parts
   int q_cols;
   uint16_t* kv;  // [2][DH]
   float* m;      // [NW][ml_cols], NW = wavefronts of the workgroup
   float* l;      // [NW][ml_cols]
   int ml_cols;
-  float* o;      // [NW][16 * DH]
+  float* o;      // [NW][16][O_LD]
 };
+// Row pitches in LDS of the queries and of the wavefronts' outputs: 16 bytes past a multiple of the 64 banks, so that the
+// 16 columns' 16-byte reads and stores go to different banks.
+constexpr int Q_LD = DH + 8, O_LD = DH + 4;
 
 // elements p[0] and p[64] summed over the split-K planes in ascending order, eight planes'
 // loads in flight together
@@ -284,8 +287,8 @@ __device__ __forceinline__ void rotate_and_stage(const AttnArgs& a, const Decode
       u = x0[n] * cc - x1[n] * sn;
       w = x1[n] * cc + x0[n] * sn;
     }
-    uint16_t* hi = sm.q + (long long)col * DH;
-    uint16_t* lo = hi + (long long)sm.q_cols * DH;
+    uint16_t* hi = sm.q + col * Q_LD;
+    uint16_t* lo = hi + sm.q_cols * Q_LD;
     split_f16(u, hi[i], lo[i]);
     split_f16(w, hi[i + 64], lo[i + 64]);
   }
@@ -327,7 +330,7 @@ __device__ __forceinline__ float merged_sum(const DecodeSmem& sm, int col) {
 }
 template <int NW>
 __device__ __forceinline__ void merge_wavefronts(const DecodeSmem& sm, int ml0, float m, float l, const f32x4 (&o)[8],
-                                                 int wave, int c, int g) {
+                                                 int wave, int c, int g, int cols) {
   l = column_sum(l);
   if (g == 0) sm.m[wave * sm.ml_cols + ml0 + c] = m;
   __syncthreads();
@@ -335,18 +338,26 @@ __device__ __forceinline__ void merge_wavefronts(const DecodeSmem& sm, int ml0, 
   const float M_use = (M == -INFINITY) ? 0.f : M;
   const float w = exp2f(m - M_use);
   if (g == 0) sm.l[wave * sm.ml_cols + ml0 + c] = l * w;
+  if (c < cols) {  // the columns in use
 #pragma unroll
-  for (int j = 0; j < 8; ++j)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) sm.o[wave * (16 * DH) + c * DH + 16 * j + 4 * g + i] = o[j][i] * w;
+    for (int j = 0; j < 8; ++j)
+      *(float4*)&sm.o[(wave * 16 + c) * O_LD + 16 * j + 4 * g] = make_float4(o[j][0] * w, o[j][1] * w, o[j][2] * w, o[j][3] * w);
+  }
   __syncthreads();
 }
-// element e of the merged, unnormalised output: the wavefronts' parts in ascending order
+// elements e .. e + 3 (e = column * DH + k) of the merged, unnormalised output: the wavefronts' parts in ascending order
 template <int NW>
-__device__ __forceinline__ float merged_out(const DecodeSmem& sm, int e) {
-  float v = sm.o[e];
+__device__ __forceinline__ float4 merged_out(const DecodeSmem& sm, int e) {
+  const float4* at = (const float4*)&sm.o[(e >> 7) * O_LD + (e & 127)];
+  float4 v = *at;
 #pragma unroll
-  for (int w = 1; w < NW; ++w) v += sm.o[w * (16 * DH) + e];
+  for (int w = 1; w < NW; ++w) {
+    const float4 u = at[w * (16 * O_LD / 4)];
+    v.x += u.x;
+    v.y += u.y;
+    v.z += u.z;
+    v.w += u.w;
+  }
   return v;
 }
 
@@ -433,8 +444,8 @@ __device__ __forceinline__ void decode_own_range(const AttnArgs& a, const Decode
   Frag q[8];
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
-    q[ks].u = *(const uint4*)&sm.q[c * DH + ks * 32 + g * 8];
-    q[4 + ks].u = *(const uint4*)&sm.q[(sm.q_cols + c) * DH + ks * 32 + g * 8];
+    q[ks].u = *(const uint4*)&sm.q[c * Q_LD + ks * 32 + g * 8];
+    q[4 + ks].u = *(const uint4*)&sm.q[(sm.q_cols + c) * Q_LD + ks * 32 + g * 8];
   }
   float m = -INFINITY, l = 0.f;
   f32x4 o[8];
@@ -472,14 +483,17 @@ __device__ __forceinline__ void decode_own_range(const AttnArgs& a, const Decode
     attend_frags(k, v, q, pos, pos, scale_log2, m, l, o, lane);
   }
 
-  merge_wavefronts<NW>(sm, 0, m, l, o, wave, c, g);
+  merge_wavefronts<NW>(sm, 0, m, l, o, wave, c, g, G);
   const int n_slots = a.n_slots ? a.n_slots : a.n_splits;
   const long long part = ((long long)b * n_kv + kvh) * n_slots + a.slot0 + split;
-  for (int e = tid; e < G * DH; e += 64 * NW) {
-    const int col = e >> 7;
-    const float acc = merged_out<NW>(sm, e);
-    if (direct) store1_split(a.out + out_offset(a, b, kvh * G * DH + e), a.out_lo_offset, acc / merged_sum<NW>(sm, col));
-    else a.part_o[part * (16 * DH) + e] = acc;
+  for (int e = 4 * tid; e < G * DH; e += 256 * NW) {
+    const float4 acc = merged_out<NW>(sm, e);
+    if (direct) {
+      const float inv = 1.0f / merged_sum<NW>(sm, e >> 7);
+      store4_split(a.out + out_offset(a, b, kvh * G * DH + e), a.out_lo_offset, acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
+    } else {
+      *(float4*)(a.part_o + part * (16 * DH) + e) = acc;
+    }
   }
   if (!direct && tid < 16) {
     a.part_ml[part * 32 + tid] = merged_max<NW>(sm, tid);
@@ -492,10 +506,10 @@ __device__ __forceinline__ void decode_own_range(const AttnArgs& a, const Decode
 // pairs are fewer than the CUs.
 template <bool EXTRA, int NW>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void attn_decode_fused_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t q_s[2 * 16 * DH];
+  __shared__ __attribute__((aligned(16))) uint16_t q_s[2 * 16 * Q_LD];
   __shared__ __attribute__((aligned(16))) uint16_t kv_s[2 * DH];
   __shared__ float m_s[NW * 16], l_s[NW * 16];
-  __shared__ float o_s[NW * 16 * DH];
+  __shared__ __attribute__((aligned(16))) float o_s[NW * 16 * O_LD];
   decode_own_range<EXTRA, NW>(a, DecodeSmem{q_s, 16, kv_s, m_s, l_s, 16, o_s}, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
@@ -542,8 +556,8 @@ __device__ __forceinline__ void decode_shared_range(const AttnArgs& a, const Dec
     Frag q[8];
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-      q[ks].u = *(const uint4*)&sm.q[(ct * 16 + c) * DH + ks * 32 + g * 8];
-      q[4 + ks].u = *(const uint4*)&sm.q[(sm.q_cols + ct * 16 + c) * DH + ks * 32 + g * 8];
+      q[ks].u = *(const uint4*)&sm.q[(ct * 16 + c) * Q_LD + ks * 32 + g * 8];
+      q[4 + ks].u = *(const uint4*)&sm.q[(sm.q_cols + ct * 16 + c) * Q_LD + ks * 32 + g * 8];
     }
     float m = -INFINITY, l = 0.f;
     f32x4 o[8];
@@ -552,15 +566,14 @@ __device__ __forceinline__ void decode_shared_range(const AttnArgs& a, const Dec
     for (int tok0 = t_begin + wave * 32; tok0 < t_end; tok0 += 128)
       attend_group(group_block(a, slot, kvh, tok0, 0), group_block(a, slot, kvh, tok0, 1), q, tok0, 0x7fffffff,
                    scale_log2, m, l, o, lane);
-    merge_wavefronts<4>(sm, ct * 16, m, l, o, wave, c, g);
-    for (int e = tid; e < 16 * DH; e += 256) {
+    merge_wavefronts<4>(sm, ct * 16, m, l, o, wave, c, g, 16);
+    for (int e = 4 * tid; e < 16 * DH; e += 4 * 256) {
       const int col = ct * 16 + (e >> 7);
       const int j = col / G, hc = col % G;
       const int b = j < GROUP_MEMBERS ? members[j] : -1;
       if (b < 0) continue;
       const long long part = ((long long)b * n_kv + kvh) * n_slots + split;
-      a.part_o[part * (16 * DH) + hc * DH + (e & 127)] =
-          sm.o[e] + sm.o[16 * DH + e] + sm.o[2 * 16 * DH + e] + sm.o[3 * 16 * DH + e];
+      *(float4*)(a.part_o + part * (16 * DH) + hc * DH + (e & 127)) = merged_out<4>(sm, e);
     }
     if (tid < 16) {
       const int col = ct * 16 + tid;
@@ -579,10 +592,10 @@ __device__ __forceinline__ void decode_shared_range(const AttnArgs& a, const Dec
 // workgroups [0, n_groups * n_kv * n_splits_a) take the shared ranges, the rest the own ranges
 template <int NCT, bool EXTRA>
 __global__ __launch_bounds__(256, 3) void attn_decode_grouped_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t q_s[2 * NCT * 16 * DH];
+  __shared__ __attribute__((aligned(16))) uint16_t q_s[2 * NCT * 16 * Q_LD];
   __shared__ __attribute__((aligned(16))) uint16_t kv_s[2 * DH];
   __shared__ float m_s[4 * NCT * 16], l_s[4 * NCT * 16];
-  __shared__ float o_s[4 * 16 * DH];
+  __shared__ __attribute__((aligned(16))) float o_s[4 * 16 * O_LD];
   const DecodeSmem sm{q_s, NCT * 16, kv_s, m_s, l_s, NCT * 16, o_s};
   const int n_kv = a.geom.n_kv_heads;
   const int n_shared = a.n_groups * n_kv * a.n_splits_a;

@@ -1,13 +1,17 @@
 // Fused per-row kernels of the matrix-core path: residual add + RMSNorm + bf16 cast (with
 // optional embedding gather), and split-K reduction + rotary embedding + KV-page write.
 // The residual stream stays fp32; only projection inputs and the KV cache are bf16.
+#include <type_traits>
+
 #include "kernels_fast.h"
 
-#define ROW_T 256
-
-// One workgroup per row; thread t holds the row's float4 chunks t, t + 256, ... (V of them) in
-// registers, so every load of the row is in flight before the first use (hidden <= 1024 V).
-template <int V>
+// One workgroup of ROW_T threads per row; thread t holds the row's float4 chunks t, t + ROW_T, ... (V of them) in
+// registers, so every load of the row is in flight before the first use (hidden <= 4 ROW_T V).
+// What bounds it in a decode step: latency.  A launch has as many workgroups as rows, each makes a few round trips to
+// memory, so as many threads as the row has chunks, and up to 16 split planes requested together (64 rows x 1536, 8 and 10
+// planes: 5.5 -> 4.8 us; 64 x 3584, 8 planes 6.9 -> 5.8; both with 2 us of launch).  With more rows than the chip
+// holds at once it is the bytes, and small workgroups that come and go keep more of them in flight.
+template <int ROW_T, int V>
 __global__ __launch_bounds__(ROW_T) void row_norm_kernel(RowNormArgs a) {
   __shared__ float partial[ROW_T / WAVE];
   const int r = blockIdx.x, t = threadIdx.x;
@@ -39,29 +43,36 @@ __global__ __launch_bounds__(ROW_T) void row_norm_kernel(RowNormArgs a) {
     const int c = t + ROW_T * v;
     gn[v] = c < n4 ? ((const float4*)a.gain)[c] : make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  // split planes, added in ascending order; the loads of four planes are issued together (a
-  // projection with a deep K leaves up to 16 planes: two at a time were eight round trips)
-  for (int z = 0; z < a.splits; z += 4) {
-    float4 u[4][V];
+  // split planes, added in ascending order; the loads of a batch of planes are issued together (a projection with a
+  // deep K leaves up to 16 planes)
+  auto add_planes = [&](auto batch) {
+    constexpr int Z = decltype(batch)::value;
+    for (int z = 0; z < a.splits; z += Z) {
+      float4 u[Z][V];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float4* pz = (const float4*)(a.partial + (long long)(z + q) * a.split_stride + (long long)r * a.hidden);
+      for (int q = 0; q < Z; ++q) {
+        const float4* pz = (const float4*)(a.partial + (long long)(z + q) * a.split_stride + (long long)r * a.hidden);
 #pragma unroll
-      for (int v = 0; v < V; ++v) {
-        const int c = t + ROW_T * v;
-        u[q][v] = (z + q < a.splits && c < n4) ? pz[c] : make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int v = 0; v < V; ++v) {
+          const int c = t + ROW_T * v;
+          u[q][v] = (z + q < a.splits && c < n4) ? pz[c] : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
       }
+#pragma unroll
+      for (int q = 0; q < Z; ++q)
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          x[v].x += u[q][v].x;
+          x[v].y += u[q][v].y;
+          x[v].z += u[q][v].z;
+          x[v].w += u[q][v].w;
+        }
     }
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int v = 0; v < V; ++v) {
-        x[v].x += u[q][v].x;
-        x[v].y += u[q][v].y;
-        x[v].z += u[q][v].z;
-        x[v].w += u[q][v].w;
-      }
-  }
+  };
+  constexpr int MOST = V == 1 ? 16 : 4;
+  if (a.splits <= 4) add_planes(std::integral_constant<int, 4>{});
+  else if (a.splits <= 8) add_planes(std::integral_constant<int, MOST < 8 ? MOST : 8>{});
+  else add_planes(std::integral_constant<int, MOST>{});
   // the row's expert picks, in pick order: slots and weights of a batch first, then all its rows at once
   constexpr int MB = V <= 2 ? 8 : 4;
   for (int j0 = 0; j0 < a.moe_k; j0 += MB) {
@@ -118,11 +129,16 @@ __global__ __launch_bounds__(ROW_T) void row_norm_kernel(RowNormArgs a) {
 }
 void launch_row_norm(const RowNormArgs& a, hipStream_t s) {
   if (!a.rows) return;
-  const int chunks = ceil_div(a.hidden >> 2, ROW_T);  // hidden is a multiple of 32 and at most 8192
-  if (chunks <= 1) row_norm_kernel<1><<<a.rows, ROW_T, 0, s>>>(a);
-  else if (chunks <= 2) row_norm_kernel<2><<<a.rows, ROW_T, 0, s>>>(a);
-  else if (chunks <= 4) row_norm_kernel<4><<<a.rows, ROW_T, 0, s>>>(a);
-  else row_norm_kernel<8><<<a.rows, ROW_T, 0, s>>>(a);
+  const int n4 = a.hidden >> 2;  // hidden is a multiple of 32 and at most 8192
+  // A thread per chunk where the chip's 512 Ki threads hold all rows at once; 256 threads beyond that (10568 rows x
+  // 3584: 134 us with 1024 threads to a row, 94 with 256) and where a row has no more chunks.
+  const bool at_once = (long long)a.rows * n4 <= 512 * 1024;
+  if (n4 <= 256) row_norm_kernel<256, 1><<<a.rows, 256, 0, s>>>(a);
+  else if (n4 <= 512 && at_once) row_norm_kernel<512, 1><<<a.rows, 512, 0, s>>>(a);
+  else if (n4 <= 512) row_norm_kernel<256, 2><<<a.rows, 256, 0, s>>>(a);
+  else if (n4 <= 1024 && at_once) row_norm_kernel<1024, 1><<<a.rows, 1024, 0, s>>>(a);
+  else if (n4 <= 1024) row_norm_kernel<256, 4><<<a.rows, 256, 0, s>>>(a);
+  else row_norm_kernel<256, 8><<<a.rows, 256, 0, s>>>(a);
 }
 
 // One thread per rotary pair (head, i): grid (rows, heads / 4), 4 heads of 64 pairs per block.

@@ -161,3 +161,21 @@ def test_appended_rows_attention_tiles():
     print(f"max |dlogits| = {worst:.3e}")
     assert worst <= TOL
     eng.close()
+
+
+@pytest.mark.parametrize("hidden,rows", [(96, 1), (1024, 40), (1056, 1985), (1056, 1986), (2048, 40), (2080, 1008), (2080, 1009), (4128, 40)])
+def test_norm_threads_lines(hidden, rows):
+    """Norm launches around the lines of their workgroups: a row of one chunk per thread and one more, and as many rows as
+    the chip holds at once with a thread per chunk (hidden 1056 and 2080: 1985 and 1008) and one more."""
+    shape = dataclasses.replace(workloads.SMALL_BF16, n_layers=1, hidden=hidden, ffn_dim=544)
+    w = scaled_weights(shape, seed=1, scale=0.7 if hidden > 1024 else 1.0)
+    model = oracle_model(shape, w)
+    eng = make_engine(shape, w, max_live_samples=40, max_context=600, max_batch_tokens=2048)
+    lens = [rows % 500] * bool(rows % 500) + [500] * (rows // 500)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    toks = np.random.default_rng(rows).integers(0, shape.vocab, rows).astype(np.int32)
+    got = eng.rollout_logprobs(toks, cu, temperature=1.0)
+    err = float(np.max(np.abs(got - T.packed_log_probs(model, toks, cu))))
+    print(f"hidden {hidden}, {rows} rows: max |dlogp| = {err:.3e}")
+    assert err <= TOL
+    eng.close()

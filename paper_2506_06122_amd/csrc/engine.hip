@@ -563,7 +563,7 @@ static void moe_block(rollout_ctx& c, LayerWeights& L, int layer, int R, RowNorm
   // Expected number of experts with at least one pick under uniform routing: the weight bytes
   // of the timing records (the true count stays on the device).
   const double touched = E * (1.0 - std::pow(1.0 - 1.0 / E, (double)picks));
-  GemmPlan pl = gemm_plan_grouped(EPI_SWIGLU_BF16, pa.block_rows);
+  GemmPlan pl = gemm_plan_grouped(EPI_SWIGLU_BF16, picks, E);
   GemmArgs gu{};
   gu.a = c.h_bf16.p;
   gu.a_lo = c.h_bf16.p + kPlaneLo;
@@ -599,7 +599,7 @@ static void moe_block(rollout_ctx& c, LayerWeights& L, int layer, int R, RowNorm
   dn.block_row_end = pa.block_row_end;
   dn.group_stride16 = (long long)d * fe * 2 / 16;
   dn.n_row_blocks = pa.max_blocks;
-  pl = gemm_plan_grouped(EPI_F32, pa.block_rows);
+  pl = gemm_plan_grouped(EPI_F32, picks, E);
   c.timer.begin(pl.name, touched * 2.0 * d * fe + 4.0 * picks * fe + 4.0 * picks * d, 2.0 * picks * d * fe, s);
   launch_gemm_bf16(dn, EPI_F32, pl, s);
   c.timer.end(s);

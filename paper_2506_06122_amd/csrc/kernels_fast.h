@@ -124,7 +124,7 @@ struct GemmPlan {
 };
 GemmPlan gemm_plan(int M, int N, int K, int epi, int max_splits);
 GemmPlan gemm_plan_stream(int M, int N, int K, int epi, int max_splits);  // the stream kernel for M <= 32
-GemmPlan gemm_plan_grouped(int epi, int block_rows);                     // experts' row blocks of moe_block_rows
+GemmPlan gemm_plan_grouped(int epi, long long picks, int n_experts);      // experts' row blocks of moe_block_rows
 // column parts per row that an EPI_LSE launch with this plan writes, and the most any plan writes
 inline int lse_parts(const GemmPlan& pl, int N) { return ceil_div(N >> 4, pl.nt); }
 inline int lse_parts_max(int N) { return ceil_div(N >> 4, 8); }
@@ -311,16 +311,7 @@ struct MoePlanArgs {
   int* block_row_end;       // [max_blocks]; unused blocks get begin = end = 0
 };
 void launch_moe_plan(const MoePlanArgs& a, hipStream_t s);
-// Rows per block of the grouped projections, by the picks an expert gets on average: few rows leave
-// more of the chip's loads in flight to the weights (the launch is a stream over the touched experts'
-// weights then), many rows use every weight fragment for a whole block (it is bound by the matrix
-// instructions and the operand traffic).  The lines are where the blocks' times cross for whole packed passes of the
-// 30B-A3B shape, 12 layers, 128 experts (ms with 32 / 64 / 128 rows; one block size of 64 rows with the kernel
-// before: last):
-//   picks  14.9:  2.70  2.78  3.14  ( 3.48)     27.9:  4.13  4.15  4.73  ( 5.04)     30.8:  4.33  4.23  4.80  ( 5.15)
-//          57.3:  6.82  6.82  7.04  ( 7.42)     99.0:  10.15 9.78  9.95  (11.31)     142:  13.48 12.88 12.93 (14.72)
-//          154:  14.57 13.81 13.76 (15.56)      185:  16.86 16.27 15.81 (17.75)      500:  42.99 40.14 39.30 (42.60)
+// Rows per block of the grouped projections, by the picks an expert gets on average; the columns go with them
+// (gemm_plan_grouped).
 constexpr int kMoeMinBlockRows = 32;
-inline int moe_block_rows(long long picks, int n_experts) {
-  return picks <= 28ll * n_experts ? 32 : picks <= 150ll * n_experts ? 64 : 128;
-}
+inline int moe_block_rows(long long picks, int n_experts) { return picks <= 14ll * n_experts ? 32 : 64; }

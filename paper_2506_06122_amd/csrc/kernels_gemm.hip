@@ -61,6 +61,7 @@ __device__ inline void store_tile_f32(const GemmArgs& p, int m, int nt, const f3
 // wavefront call it; `valid`: row m is stored.
 // What bounds it: instructions of a wavefront that has its SIMD to itself.  With exchanges through LDS, an IEEE division
 // and the rounding in integers the epilogue was 4.5 us of the 55 us that 33 rows x 37888 x 3584 take.
+template <bool TILE>  // the tile kernel's results are never in fragment order
 __device__ inline void store_swiglu(const GemmArgs& p, bool valid, int m, int nt, const f32x4& t0, const f32x4& t1,
                                     int g, bool two) {
   float v[4];
@@ -75,7 +76,7 @@ __device__ inline void store_swiglu(const GemmArgs& p, bool valid, int m, int nt
   const auto y = __builtin_amdgcn_permlane16_swap(hi.y, lo.y, false, false);
   if (valid && (two || g < 2)) {
     const int f = (nt + (g >> 1)) * 8;
-    uint16_t* out = (uint16_t*)p.out + (p.frag ? frag_offset(m, f, p.ldo >> 5) : plane_offset(m, f, p.ldo));
+    uint16_t* out = (uint16_t*)p.out + (!TILE && p.frag ? frag_offset(m, f, p.ldo >> 5) : plane_offset(m, f, p.ldo));
     *(uint4*)(out + (g & 1 ? p.out_lo_offset : 0)) = make_uint4(x[0], y[0], x[1], y[1]);
   }
 }
@@ -288,7 +289,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
     ss += __shfl_xor(ss, 32, WAVE);
     if (g == 0 && valid) p.ssq_out[(long long)blockIdx.x * p.ssq_stride + m] = ss;
   } else if (EPI == EPI_SWIGLU_BF16) {
-    store_swiglu(p, valid, m, nt0, t[0], t[1], g, NT == 2 && nt0 + 1 < n_tiles);
+    store_swiglu<false>(p, valid, m, nt0, t[0], t[1], g, NT == 2 && nt0 + 1 < n_tiles);
   } else if (valid) {
 #pragma unroll
     for (int q = 0; q < NT; ++q)
@@ -302,30 +303,32 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
 // alternate k-tiles and join their sums through LDS at the end (twice the wavefronts on a tile
 // whose size the chip's 256 CUs ask for).
 //
-// What bounds it: with many rows the matrix instructions (two per weight fragment and row tile,
-// hi and lo plane); with a few hundred rows or fewer the path from L2 into the CUs, measured at
-// 40-70 GB/s per CU in this kernel whatever the pipeline depth.  Per k-tile a workgroup moves
-// 128 BM + 64 BN bytes for BM BN / 256 tiles, so wide tiles win, and one round of workgroups that
-// fills all CUs wins over a second, mostly empty one: the plan below weighs the two.
+// What bounds it.  Long launches with many rows: the power limit.  The matrix units are busy 71 % of the cycles at a
+// clock that falls to 1.8 GHz; products from registers alone, on the same data, run at 2.0 PFLOP/s (2.4 on zeros), so
+// what a tile shape costs in data movement is what it loses.  A few hundred rows: wavefronts that have their SIMD
+// almost to themselves, where every wait shows.  Decode steps: the weights, and besides them, per k-tile, 128 BM +
+// 64 BN bytes through the CU for BM BN / 256 tiles, so wide tiles win, and one round of workgroups that fills all CUs wins
+// over a second, mostly empty one: the plan below weighs the two.
 //
-// Both operands go from memory straight into LDS (global_load_lds_dwordx4, 1 KiB per instruction),
-// S - 1 stages ahead of the stage that is multiplied, with one barrier per stage:
-//   - A wavefront waits until its own loads of stage s have arrived (s_waitcnt vmcnt counts in
-//     order: the loads of the S - 2 later stages may be outstanding), then the barrier says the
-//     same of every wavefront's loads.
-//   - It also waits for its LDS reads of stage s - 1 (lgkmcnt) before that barrier, so the loads of
-//     stage s + S - 1, issued after it, can overwrite that buffer.
-//   - Past the end of the K range the last k-tile is loaded again (never multiplied), so that every
-//     stage counts the same number of loads.
+// Both operands go from memory straight into LDS (global_load_lds_dwordx4, 1 KiB per instruction), S stages ahead, with
+// one barrier per stage.  The fragments of stage s + 1 are read between the products of stage s, and the copies of
+// stage s + S are issued there too:
+//   - A wavefront waits until its own copies of stage s + 1 have arrived (s_waitcnt vmcnt counts in
+//     order: the copies of the S - 2 later stages may be outstanding) and its fragments of stage s are in registers
+//     (lgkmcnt); then the barrier says the same of every wavefront.  So after it stage s + 1 can be read and the
+//     buffer of stage s be overwritten.
+//   - The last stage's products stand outside the loop, which therefore has no branch.  Past the end of the K range
+//     the last k-tile is copied and read again (never multiplied), so that every stage counts the same number of copies.
 // Activations: one instruction brings 8 rows x 128 bytes, a line holding both planes of 32 elements
 // (plane_offset).  The 16-byte chunk c of row r lands in slot c ^ (r % 8) of its row, by choosing
 // each lane's source address, which makes the fragment reads conflict-free.  Weights: a fragment is
 // one instruction and is read back as it lies.  Rows and column tiles past the end read the last
 // valid one; their results are not stored.
 //
-// Measured against the kernel it replaced (register-staged, 64 x 256 and 64 x 128 tiles), random
-// operands: 12000 rows x 37888 x 3584 5.53 -> 4.52 ms (720 TFLOP/s, 1440 issued), 1700 x 17920 x
-// 1536 192 -> 157 us, 187 x 17920 x 1536 33 -> 27 us, 64 x 37888 x 3584 70 -> 57 us.
+// Measured against the kernel before, which read a stage's fragments after its barrier (back to back, weights from
+// HBM, splits' planes included): 24 rows x 37888 x 3584 64 -> 48 us, 24 x 3584 x 18944 34 -> 26, 64 x 1536 x 8960 10.9 ->
+// 10.1, 256 x 37888 x 3584 125 -> 105, 512 x 37888 x 3584 229 -> 206, 1700 x 3584 x 18944 373 -> 336, 6000 x 37888 x 3584
+// 2.35 -> 2.18 ms (1.5 PFLOP/s issued).
 // 16 bytes per lane from base + voff to LDS byte `lds` + 16 * lane.  (The compiler keeps nothing in m0: it sets it
 // right before each instruction of its own that reads it.)  As inline assembly, because the compiler makes every
 // LDS read wait for all copies into LDS that it knows of.
@@ -344,14 +347,14 @@ __device__ __forceinline__ void wait_and_barrier() {
 }
 
 // GATHER: the rows of `a` come through row_map (experts' grouped projections)
-template <int WM, int WN, int MT, int NT, int KG, int S, int MINB, int EPI, bool GATHER>
-__global__ __launch_bounds__(WM* WN* KG * 64, MINB) void gemm_tile_kernel(GemmArgs p) {
+template <int WM, int WN, int MT, int NT, int KG, int S, int EPI, bool GATHER>
+__global__ __launch_bounds__(WM* WN* KG * 64, 2) void gemm_tile_kernel(GemmArgs p) {
   constexpr int NW = WM * WN * KG, BM = WM * MT * 16, BN = WN * NT * 16;
   constexpr int UA = BM / 8, UW = BN / 16, U1 = UA + UW;  // load instructions per k-tile
   constexpr int L = (U1 * KG + NW - 1) / NW;              // per wavefront and stage
   constexpr int RED = KG > 1 ? (KG - 1) * WM * WN * MT * NT : 0;
   constexpr int LDS_KB = S * U1 * KG > RED ? S * U1 * KG : RED;
-  static_assert(LDS_KB <= 160 && S >= 2 && KG <= 2, "fits the CU");
+  static_assert(LDS_KB <= 160 && S >= 2 && KG <= 2 && (S - 1) * L < 64, "fits the CU and the load counter");
   __shared__ __attribute__((aligned(1024))) char lds[LDS_KB * 1024];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, g = lane >> 4;
@@ -378,7 +381,8 @@ __global__ __launch_bounds__(WM* WN* KG * 64, MINB) void gemm_tile_kernel(GemmAr
   const char* ap = (const char*)p.a + (GATHER ? 0 : m0 * row_bytes);
 
   const int kg = wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
-  // this wavefront's loads of a stage: instruction u of the stage's U1 * KG
+  // this wavefront's loads of a stage: instruction u of the stage's U1 * KG.  An address moves on by a stage's k-tiles
+  // as long as there is one to load; then it stays.
   unsigned voff[L], step[L], dst[L];
   int k_of[L];
   const char* base[L];
@@ -388,69 +392,96 @@ __global__ __launch_bounds__(WM* WN* KG * 64, MINB) void gemm_tile_kernel(GemmAr
     const int uu = min(s * NW + wave, U1 * KG - 1);  // an uneven last round loads the last one again
     const int u = __builtin_amdgcn_readfirstlane(uu % U1);
     k_of[s] = __builtin_amdgcn_readfirstlane(uu / U1);
-    dst[s] = uu * 1024;
+    dst[s] = __builtin_amdgcn_readfirstlane(uu * 1024);
+    const unsigned k0 = min(kt_begin + k_of[s], kt_end - 1);
     if (u < UA) {
       const int m = min(m0 + u * 8 + (lane >> 3), m_limit - 1);
       const unsigned chunk = ((lane & 7) ^ (lane >> 3)) * 16;
-      if (GATHER) row_addr[s] = ap + p.row_map[m] * row_bytes + chunk;
-      else voff[s] = (unsigned)((m - m0) * row_bytes) + chunk;
+      if (GATHER) row_addr[s] = ap + p.row_map[m] * row_bytes + chunk + k0 * 128;
+      else voff[s] = (unsigned)((m - m0) * row_bytes) + chunk + k0 * 128;
       step[s] = 128;
       base[s] = ap;
     } else {
-      voff[s] = (unsigned)(min(nt0 + u - UA, n_tiles - 1) - nt0) * (unsigned)k_tiles * 1024u + lane * 16;
+      voff[s] = (unsigned)(min(nt0 + u - UA, n_tiles - 1) - nt0) * (unsigned)k_tiles * 1024u + lane * 16 + k0 * 1024;
       step[s] = 1024;
       base[s] = wp;
     }
   }
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)lds;
-  auto issue = [&](int kt, int buf) {
-#pragma unroll
-    for (int s = 0; s < L; ++s) {
-      const int k = min(kt + k_of[s], kt_end - 1);
-      const unsigned to = lds0 + buf * (U1 * KG * 1024) + dst[s];
-      if (GATHER && step[s] == 128) load_to_lds(to, row_addr[s] + (long long)k * 128);
-      else load_to_lds(to, voff[s], base[s] + (long long)k * step[s]);
+  auto issue = [&](int s, int kt, int buf) {  // load s of the stage that starts at k-tile kt
+    const unsigned to = __builtin_amdgcn_readfirstlane(lds0 + buf * (U1 * KG * 1024) + dst[s]);
+    const unsigned move = kt + KG + k_of[s] < kt_end ? KG * step[s] : 0u;
+    if (GATHER && step[s] == 128) {
+      load_to_lds(to, row_addr[s]);
+      row_addr[s] += move;
+    } else {
+      load_to_lds(to, voff[s], base[s]);
+      voff[s] += move;
     }
   };
-
   f32x4 acc[MT][NT];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int s = 0; s < S - 1; ++s) issue(kt_begin + s * KG, s);
+  for (int q = 0; q < S; ++q)
+#pragma unroll
+    for (int s = 0; s < L; ++s) issue(s, kt_begin + q * KG, q);
 
   // fragment reads: row tile i of this wavefront is row groups 2 i and 2 i + 1 (8 rows, 1 KiB each)
   const int a_row = kg * U1 * 1024 + (wm * MT * 2 + (r >> 3)) * 1024 + (r & 7) * 128;
   const int a_hi = a_row + (g ^ (r & 7)) * 16, a_lo = a_row + ((4 + g) ^ (r & 7)) * 16;
   const int w_at = kg * U1 * 1024 + (UA + wn * NT) * 1024 + lane * 16;
+  u32x4 w[2][NT], a[2][MT][2];
+  constexpr int NR = NT + 2 * MT, NM = MT * NT * 2, NS = NR + L;
+  auto read = [&](int x, const char* b, int f) {  // fragment f of a stage, in the order in which they are multiplied
+    if (f < 2) a[x][0][1 - f] = *(const u32x4*)(b + (f ? a_hi : a_lo));
+    else if (f < 2 + NT) w[x][f - 2] = *(const u32x4*)(b + w_at + (f - 2) * 1024);
+    else a[x][(f - NT) >> 1][1 - ((f - NT) & 1)] = *(const u32x4*)(b + ((f - NT) & 1 ? a_hi : a_lo) + ((f - NT) >> 1) * 2048);
+  };
+  auto mul = [&](int x, int q) {  // row tile by row tile, lo part first, then hi
+    const int i = q / (2 * NT), plane = 1 - q / NT % 2, j = q % NT;
+    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[x][j]),
+                                                        __builtin_bit_cast(bf16x8, a[x][i][plane]), acc[i][j], 0, 0, 0);
+  };
+  wait_and_barrier<(S - 1) * L>();
+#pragma unroll
+  for (int f = 0; f < NR; ++f) read(0, lds, f);
   int buf = 0;
-  for (int kt = kt_begin; kt < kt_end; kt += KG) {
+  auto stage = [&](int x, int kt) {
     wait_and_barrier<(S - 2) * L>();
-    const char* b = lds + buf * (U1 * KG * 1024);
-    u32x4 w[NT], a[MT][2];
+    const int next = buf == S - 1 ? 0 : buf + 1;
+    const char* b = lds + next * (U1 * KG * 1024);
 #pragma unroll
-    for (int j = 0; j < NT; ++j) w[j] = *(const u32x4*)(b + w_at + j * 1024);
+    for (int q = 0; q < NM; ++q) {
+      mul(x, q);
 #pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      a[i][1] = *(const u32x4*)(b + a_lo + i * 2048);
-      a[i][0] = *(const u32x4*)(b + a_hi + i * 2048);
+      for (int u = 0; u < NS; ++u)
+        if (u * NM / NS == q) {
+          if (u < NR) read(x ^ 1, b, u);
+          else issue(u - NR, kt + S * KG, buf);
+        }
+      __builtin_amdgcn_sched_barrier(0);
     }
-    issue(kt + (S - 1) * KG, buf == 0 ? S - 1 : buf - 1);
-    if (KG == 1 || kt + kg < kt_end) {  // an odd last k-tile belongs to the first group
-      __builtin_amdgcn_s_setprio(1);
+    buf = next;
+  };
+  auto last = [&](int x, int kt) {
+    if (KG > 1 && kt + kg >= kt_end) return;  // an odd last k-tile belongs to the first group
 #pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int plane = 1; plane >= 0; --plane)  // lo part first, then hi
-#pragma unroll
-          for (int j = 0; j < NT; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[j]),
-                                                                __builtin_bit_cast(bf16x8, a[i][plane]), acc[i][j], 0, 0, 0);
-      __builtin_amdgcn_s_setprio(0);
-    }
-    buf = buf == S - 1 ? 0 : buf + 1;
+    for (int q = 0; q < NM; ++q) mul(x, q);
+  };
+  int kt = kt_begin, left = (kt_end - kt_begin + KG - 1) / KG;
+  for (; left > 2; left -= 2) {
+    stage(0, kt);
+    stage(1, kt + KG);
+    kt += 2 * KG;
+  }
+  if (left == 2) {
+    stage(0, kt);
+    last(1, kt + KG);
+  } else {
+    last(0, kt);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may still be on its way into LDS
   if constexpr (KG > 1) {
@@ -539,7 +570,7 @@ __global__ __launch_bounds__(WM* WN* KG * 64, MINB) void gemm_tile_kernel(GemmAr
 #pragma unroll
         for (int j = 0; j < NT; j += 2)
           if (wt0 + j < n_tiles)
-            store_swiglu(p, m < m_limit, m, wt0 + j, acc[i][j], acc[i][j + 1 < NT ? j + 1 : j], g,
+            store_swiglu<true>(p, m < m_limit, m, wt0 + j, acc[i][j], acc[i][j + 1 < NT ? j + 1 : j], g,
                          j + 1 < NT && wt0 + j + 1 < n_tiles);
       } else {
 #pragma unroll
@@ -575,33 +606,41 @@ static const StreamShape kStreamShapes[] = {
 // The tile kernel's shapes.  per_kt, per_kt_alone: microseconds per k-tile of one workgroup's share
 // of a CU that holds its full number of workgroups (per_cu), or only one; fixed: what a workgroup
 // costs besides (first loads' latency, result), not hidden by a next round when it has the CU to
-// itself; start: the launch.  Fitted to 2000 timed launches (40 to 9200 rows, eleven (N, K) pairs of
-// the 1.5B, 7B and 30B-A3B shapes, one to sixteen splits; rms error of the log 0.08-0.15).
+// itself; start: the launch.  Fitted to 6500 timed launches (17 to 6000 rows, twelve (N, K) pairs of
+// the 1.5B, 7B and 30B-A3B shapes, one to sixteen splits; rms error of the log 0.09-0.14); the plans it picks are 3 %
+// slower than the best of all shapes and splits, where the nine shapes before lost 9 % with the best picks.
 struct TileShape {
-  int wm, wn, mt, nt, kg, s, minb;
+  int wm, wn, mt, nt, kg, s, per_cu;
   float per_kt, per_kt_alone, start, fixed;
   const char* name[4];  // by epilogue: F32, SWIGLU, LSE, SWIGLU with gathered rows
 };
 #define TILE_NAME(a) \
   {"gemm_tile_kernel<" a ",0,false>", "gemm_tile_kernel<" a ",1,false>", "gemm_tile_kernel<" a ",3,false>", "gemm_tile_kernel<" a ",1,true>"}
-// x-macro: index, template arguments, model
-#define TILE_SHAPES(X)                                        \
-  X(0, 2, 2, 1, 4, 1, 4, 3, 0.151f, 0.179f, 2.1f, 1.4f)   /*  32 x 128 */ \
-  X(1, 2, 2, 2, 4, 1, 4, 2, 0.224f, 0.253f, 0.8f, 3.4f)   /*  64 x 128 */ \
-  X(2, 2, 2, 3, 2, 2, 4, 1, 0.187f, 0.187f, 0.0f, 4.3f)   /*  96 x  64 */ \
-  X(3, 2, 2, 2, 5, 2, 3, 1, 0.271f, 0.271f, 0.0f, 5.4f)   /*  64 x 160 */ \
-  X(4, 2, 2, 3, 5, 2, 3, 1, 0.348f, 0.348f, 0.0f, 7.0f)   /*  96 x 160 */ \
-  X(5, 4, 2, 2, 5, 1, 5, 1, 0.478f, 0.478f, 0.0f, 7.3f)   /* 128 x 160 */ \
-  X(6, 4, 2, 2, 10, 1, 4, 1, 0.827f, 0.827f, 0.0f, 10.0f) /* 128 x 320 */ \
-  X(7, 2, 2, 4, 4, 1, 2, 3, 0.391f, 0.556f, 3.5f, 2.5f)   /* 128 x 128 */ \
-  X(8, 2, 2, 4, 8, 1, 2, 2, 0.623f, 0.781f, 0.2f, 8.2f)   /* 128 x 256 */
+// x-macro: index, template arguments, workgroups per CU, model
+#define TILE_SHAPES(X) \
+  X(0, 1, 4, 2, 1, 1, 8, 2, 0.121f, 0.128f, 2.11f, 0.91f) /* 32 x 64 */      \
+  X(1, 1, 4, 2, 2, 1, 6, 2, 0.200f, 0.205f, 2.22f, 1.12f) /* 32 x 128 */     \
+  X(2, 1, 4, 2, 3, 1, 5, 2, 0.277f, 0.282f, 2.86f, 1.15f) /* 32 x 192 */     \
+  X(3, 2, 2, 2, 2, 1, 6, 2, 0.175f, 0.175f, 2.86f, 0.88f) /* 64 x 64 */      \
+  X(4, 2, 2, 2, 3, 1, 5, 2, 0.226f, 0.231f, 2.61f, 1.21f) /* 64 x 96 */      \
+  X(5, 2, 2, 2, 4, 1, 5, 2, 0.261f, 0.258f, 2.84f, 1.64f) /* 64 x 128 */     \
+  X(6, 2, 2, 2, 5, 1, 4, 2, 0.304f, 0.310f, 2.72f, 1.91f) /* 64 x 160 */     \
+  X(7, 2, 2, 2, 6, 1, 4, 2, 0.335f, 0.341f, 2.84f, 2.26f) /* 64 x 192 */     \
+  X(8, 2, 2, 2, 8, 1, 3, 2, 0.399f, 0.500f, 1.85f, 3.66f) /* 64 x 256 */     \
+  X(9, 2, 2, 3, 4, 1, 4, 2, 0.326f, 0.329f, 2.71f, 2.31f) /* 96 x 128 */     \
+  X(10, 2, 2, 3, 6, 2, 3, 1, 0.406f, 0.406f, 1.11f, 6.42f) /* 96 x 192 */    \
+  X(11, 4, 2, 2, 4, 1, 6, 1, 0.403f, 0.403f, 0.40f, 5.54f) /* 128 x 128 */   \
+  X(12, 4, 2, 2, 5, 1, 5, 1, 0.468f, 0.468f, 0.18f, 6.44f) /* 128 x 160 */   \
+  X(13, 4, 2, 2, 8, 1, 5, 1, 0.621f, 0.621f, 0.20f, 9.09f) /* 128 x 256 */   \
+  X(14, 4, 2, 2, 10, 1, 4, 1, 0.751f, 0.751f, 0.31f, 9.98f) /* 128 x 320 */  \
+  X(15, 4, 2, 3, 8, 1, 3, 1, 0.876f, 0.876f, 0.03f, 11.38f) /* 192 x 256 */
 static const TileShape kTileShapes[] = {
-#define X(id, wm, wn, mt, nt, kg, s, minb, a, b, c, d) \
-  {wm, wn, mt, nt, kg, s, minb, a, b, c, d, TILE_NAME(#wm "," #wn "," #mt "," #nt "," #kg "," #s "," #minb)},
+#define X(id, wm, wn, mt, nt, kg, s, per_cu, a, b, c, d) \
+  {wm, wn, mt, nt, kg, s, per_cu, a, b, c, d, TILE_NAME(#wm "," #wn "," #mt "," #nt "," #kg "," #s)},
     TILE_SHAPES(X)
 #undef X
 };
-constexpr bool grouped_shape(int id) { return id == 0 || id == 1 || id == 7; }  // row blocks of moe_block_rows
+constexpr bool grouped_shape(int id) { return id <= 2 || id == 7 || id == 8; }  // the experts' launches (gemm_plan_grouped)
 constexpr int kLseMinTile = 8;    // column tiles per workgroup an EPI_LSE launch has at least (sizes the parts' buffers)
 
 // Microseconds one projection is expected to take: the busiest CU's rounds of workgroups, not less
@@ -609,10 +648,7 @@ constexpr int kLseMinTile = 8;    // column tiles per workgroup an EPI_LSE launc
 static double tile_cost(const TileShape& t, int M, int n_tiles, int k_tiles, int z) {
   TileGrid g{ceil_div(n_tiles, t.wn * t.nt), ceil_div(M, t.wm * t.mt * 16), z};
   const int n = tile_groups(g);
-  // one workgroup per CU: nothing hides its first loads and its result from the next round, and over many
-  // rounds the model flatters it by up to a fifth
-  if (t.minb == 1 && n > 2) return 1e30;
-  const int kt = ceil_div(k_tiles, z), per_cu = t.minb, rest = n % per_cu;
+  const int kt = ceil_div(k_tiles, z), per_cu = t.per_cu, rest = n % per_cu;
   double us = t.start + (double)(n - rest) * (kt * t.per_kt + t.fixed);
   if (rest)
     us += kt * (t.per_kt_alone + (per_cu * t.per_kt - t.per_kt_alone) * (rest - 1) / std::max(1, per_cu - 1)) + t.fixed;
@@ -654,11 +690,23 @@ static GemmPlan gemm_plan_tiled(int M, int N, int K, int epi, int max_splits) {
   return pl;
 }
 
-// the grouped (per-expert) launches: row blocks of 32, 64 or 128 rows (moe_block_rows), all with 128 columns
-GemmPlan gemm_plan_grouped(int epi, int block_rows) {
+// The grouped (per-expert) launches.  Few picks: the launch is a stream over the touched experts' weights, and more,
+// narrower workgroups have more of it in flight; many picks: wide tiles, which use every fragment for more products.
+// Whole decode steps (s) and packed passes of the 30B-A3B shape, 12 layers, 128 experts, by picks per expert; ms with
+// 32 x 64 / 32 x 128 / 32 x 192 / 64 x 128 / 64 x 192 / 64 x 256 / 128 x 128 / 128 x 256:
+//   s  0.5:  1.07  1.18  1.17  1.25  1.27  1.36                 s  4.0:  1.57  1.45  1.57  1.60  1.57  1.60
+//   s  2.0:  1.26  1.36  1.33  1.40  1.42  1.47                    3.8:  1.60  1.59  1.66  1.67  1.75  1.85
+//   s  6.0:  1.65  1.54  1.65  1.65  1.74  1.81  1.74  1.86        7.5:  2.06  1.95  1.90  1.96  1.98  2.05  2.36  2.21
+//   s  8.0:  1.79  1.79  1.73  1.75  1.87  2.02  1.84  1.96       11.7:  2.41  2.25  2.24  2.34  2.27  2.29  2.85  2.75
+//   s   16:  2.65  2.41  2.43  2.42  2.29  2.38  2.68  2.47       21.9:  3.74  3.33  3.26  3.26  3.25  3.21  3.75  3.74
+//       31:  4.74  4.24  4.13  4.07  3.96  3.97  4.87  4.62       62.5:  8.18  6.96  6.67  6.77  6.35  6.13  7.23  6.69
+//      188:  21.1  17.1  16.2  16.1  14.8  14.0  16.0  14.4        562:                    45.0  41.3  40.0  44.3  40.1
+// (before, blocks of 32, 64 or 128 rows x 128 columns and the kernel before: s 0.5 1.23, s 2.0 1.51, s 16 2.67, 31 4.31,
+// 188 16.2, 562 45.0)
+GemmPlan gemm_plan_grouped(int epi, long long picks, int n_experts) {
   GemmPlan pl{};
   pl.kind = 1;
-  pl.shape = block_rows == 32 ? 0 : block_rows == 64 ? 1 : 7;
+  pl.shape = picks <= 3ll * n_experts ? 0 : picks <= 7ll * n_experts ? 1 : picks <= 14ll * n_experts ? 2 : picks <= 20ll * n_experts ? 7 : 8;
   const TileShape& t = kTileShapes[pl.shape];
   pl.nt = t.wn * t.nt;
   pl.splits = 1;
@@ -678,14 +726,14 @@ static int launch_tile(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s) {
   const dim3 grid((unsigned)tile_workgroups(a.grid));
   const bool gather = a.row_map != nullptr;
   switch (pl.shape) {
-#define X(id, wm, wn, mt, nt, kg, st, minb, ...)                                                                    \
+#define X(id, wm, wn, mt, nt, kg, st, ...)                                                                          \
   case id:                                                                                                           \
-    if (epi == EPI_F32) gemm_tile_kernel<wm, wn, mt, nt, kg, st, minb, EPI_F32, false><<<grid, wm * wn * kg * 64, 0, s>>>(a); \
+    if (epi == EPI_F32) gemm_tile_kernel<wm, wn, mt, nt, kg, st, EPI_F32, false><<<grid, wm * wn * kg * 64, 0, s>>>(a); \
     else if (epi == EPI_LSE) /* never planned with fewer than kLseMinTile column tiles */                             \
-      gemm_tile_kernel<wm, wn, mt, nt, kg, st, minb, wn * nt >= kLseMinTile ? EPI_LSE : EPI_F32, false><<<grid, wm * wn * kg * 64, 0, s>>>(a); \
+      gemm_tile_kernel<wm, wn, mt, nt, kg, st, wn * nt >= kLseMinTile ? EPI_LSE : EPI_F32, false><<<grid, wm * wn * kg * 64, 0, s>>>(a); \
     else if (grouped_shape(id) && gather)                                                                             \
-      gemm_tile_kernel<wm, wn, mt, nt, kg, st, minb, EPI_SWIGLU_BF16, grouped_shape(id)><<<grid, wm * wn * kg * 64, 0, s>>>(a); \
-    else gemm_tile_kernel<wm, wn, mt, nt, kg, st, minb, EPI_SWIGLU_BF16, false><<<grid, wm * wn * kg * 64, 0, s>>>(a); \
+      gemm_tile_kernel<wm, wn, mt, nt, kg, st, EPI_SWIGLU_BF16, grouped_shape(id)><<<grid, wm * wn * kg * 64, 0, s>>>(a); \
+    else gemm_tile_kernel<wm, wn, mt, nt, kg, st, EPI_SWIGLU_BF16, false><<<grid, wm * wn * kg * 64, 0, s>>>(a); \
     break;
     TILE_SHAPES(X)
 #undef X

@@ -5,6 +5,9 @@
 struct TileGrid {
   int nx = 0, ny = 0, nz = 0;        // column blocks, row blocks, K splits
   int group_m = 1, group_n = 1;      // row and column blocks an XCD takes side by side
+  int gy = 1;                        // row groups
+  unsigned by_per = 0, by_nz = 0, by_gy = 0, by_m = 0;  // tile_by of group_m * group_n, nz, gy and group_m (tile_divisors)
+  bool divide = false;               // too large for them
 };
 struct TileBlock {
   int x, y, z;
@@ -13,19 +16,44 @@ struct TileBlock {
 
 constexpr long long tile_ceil(long long a, long long b) { return (a + b - 1) / b; }
 
+// x / d as one multiplication: the high word of x m, m = ceil(2^32 / d), is the quotient for x d < 2^32.  0 stands for
+// d = 1.  (A division of two runtime integers is some 30 instructions, and the kernel needs four quotients before its
+// first load: 0.3 us of a launch.)
+constexpr unsigned tile_by(long long d) { return d == 1 ? 0u : (unsigned)(((1ll << 32) + d - 1) / d); }
+constexpr unsigned tile_div(unsigned x, unsigned by) {
+  const unsigned q = (unsigned)(((unsigned long long)x * by) >> 32);
+  return by ? q : x;
+}
+
 // Workgroup -> block.  The launch is one-dimensional and workgroups go to the 8 XCDs (each with its own L2)
 // round-robin by index, so index % 8 is the XCD and index / 8 the order inside it.  An XCD takes groups of
 // group_m row blocks x group_n column blocks, whose workgroups run side by side and share the operands' lines in
 // its L2; groups go round the XCDs with the split varying fastest, then the row blocks.
 constexpr TileBlock tile_block(const TileGrid& g, unsigned index) {
-  const int xcd = index & 7, idx = index >> 3, per = g.group_m * g.group_n;
-  const int unit = (idx / per) * 8 + xcd, in = idx % per;
-  const int gy = (g.ny + g.group_m - 1) / g.group_m, q = unit / g.nz;
-  const int x = (q / gy) * g.group_n + in / g.group_m, y = (q % gy) * g.group_m + in % g.group_m;
-  return TileBlock{x, y, unit % g.nz, y < g.ny && x < g.nx};
+  const unsigned xcd = index & 7, idx = index >> 3, per = g.group_m * g.group_n, nz = g.nz, gy = g.gy, gm = g.group_m;
+  unsigned run = tile_div(idx, g.by_per), unit = run * 8 + xcd, in = idx - run * per;
+  unsigned q = tile_div(unit, g.by_nz), xg = tile_div(q, g.by_gy), xi = tile_div(in, g.by_m);
+  if (g.divide) {
+    run = idx / per, unit = run * 8 + xcd, in = idx % per;
+    q = unit / nz, xg = q / gy, xi = in / gm;
+  }
+  const int x = (int)(xg * g.group_n + xi), y = (int)((q - xg * gy) * gm + in - xi * gm);
+  return TileBlock{x, y, (int)(unit - q * nz), y < g.ny && x < g.nx};
 }
 constexpr long long tile_units(const TileGrid& g) { return tile_ceil(g.ny, g.group_m) * tile_ceil(g.nx, g.group_n) * g.nz; }
 constexpr long long tile_workgroups(const TileGrid& g) { return tile_ceil(tile_units(g), 8) * 8 * g.group_m * g.group_n; }
+
+// what tile_block divides by, once the launch's counts and groups are set
+constexpr void tile_divisors(TileGrid& g) {
+  g.gy = (int)tile_ceil(g.ny, g.group_m);
+  const long long per = g.group_m * g.group_n;
+  g.by_per = tile_by(per);
+  g.by_nz = tile_by(g.nz);
+  g.by_gy = tile_by(g.gy);
+  g.by_m = tile_by(g.group_m);
+  const long long most = per > g.nz ? (per > g.gy ? per : g.gy) : (g.nz > g.gy ? g.nz : g.gy);
+  g.divide = tile_workgroups(g) * most >= 1ll << 32;  // no dividend is larger than the number of workgroups
+}
 
 // Sets group_m and group_n and returns the workgroups the busiest CU gets (32 CUs to an XCD).
 // Groups go to the XCDs whole, so a group that is large against the launch leaves XCDs idle: of the
@@ -45,6 +73,7 @@ constexpr int tile_groups(TileGrid& g) {
     }
   }
   g.group_m = best_m;
+  tile_divisors(g);
   return best;
 }
 
@@ -62,6 +91,7 @@ constexpr void tile_groups_experts(TileGrid& g) {
   const int most = g.ny < 16 ? g.ny : 16;
   g.group_n = 1;
   g.group_m = most;
-  while (g.group_m > most / 2 && groups_share_xcds(tile_ceil(g.ny, g.group_m))) --g.group_m;
-  if (g.group_m <= most / 2) g.group_m = most;
+  while (2 * g.group_m >= most && groups_share_xcds(tile_ceil(g.ny, g.group_m))) --g.group_m;
+  if (2 * g.group_m < most) g.group_m = most;
+  tile_divisors(g);
 }

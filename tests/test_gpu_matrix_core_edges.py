@@ -64,6 +64,44 @@ def test_moe_block_rows_lines(rows):
     eng.close()
 
 
+@pytest.mark.parametrize("rows", [12, 13, 28, 29, 56, 57, 80, 81])
+def test_moe_tile_shape_lines(rows):
+    """On either side of the lines between the experts' tile shapes (3, 7, 14 and 20 picks per expert: 16 experts, 4 picks a
+    row), with column counts that none of the shapes divides (gate/up 2 x 96, hidden 544)."""
+    shape = dataclasses.replace(workloads.SMALL_MOE_BF16, hidden=544, expert_ffn_dim=96)
+    w = scaled_weights(shape, seed=1, scale=1.5)
+    model = oracle_model(shape, w)
+    eng = make_engine(shape, w, flags=2)
+    toks = np.random.default_rng(rows).integers(0, shape.vocab, rows).astype(np.int32)
+    got = eng.rollout_logprobs(toks, [0, rows], temperature=1.0)
+    picks = eng.rollout_debug_routing(rows)
+    model.routing_override = {l: picks[l] for l in range(shape.n_layers)}
+    err = float(np.max(np.abs(got - T.packed_log_probs(model, toks, [0, rows]))))
+    below, outside = (max(g[i] for g in model.routing_regret) for i in (0, 1))
+    print(f"{rows} rows: max |dlogp| = {err:.3e}, routing gaps {below:.3e} {outside:.3e}")
+    assert err <= TOL and below <= TOL and outside <= TOL
+    eng.close()
+
+
+@pytest.mark.parametrize("rows,hidden,ffn", [(1, 512, 544), (17, 544, 1056), (40, 2080, 4000), (65, 544, 9000 // 32 * 32), (97, 1056, 2016),
+                                             (129, 2080, 1056), (193, 544, 5024), (300, 1056, 544), (700, 2080, 2016), (1985, 544, 1056)])
+def test_tile_plans_remainders(rows, hidden, ffn):
+    """Packed passes whose rows, columns and k-tiles leave remainders in whatever tile shape and number of splits the
+    planner picks (17 and 33 k-tiles among them: odd, and no more than a few per split)."""
+    shape = dataclasses.replace(workloads.SMALL_BF16, n_layers=1, hidden=hidden, ffn_dim=ffn)
+    w = scaled_weights(shape, seed=1, scale=0.7 if hidden > 1024 else 1.0)
+    model = oracle_model(shape, w)
+    eng = make_engine(shape, w, max_context=600, max_batch_tokens=2048)
+    lens = [rows % 500] * bool(rows % 500) + [500] * (rows // 500)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    toks = np.random.default_rng(rows).integers(0, shape.vocab, rows).astype(np.int32)
+    got = eng.rollout_logprobs(toks, cu, temperature=1.0)
+    err = float(np.max(np.abs(got - T.packed_log_probs(model, toks, cu))))
+    print(f"{rows} rows, hidden {hidden}, ffn {ffn}: max |dlogp| = {err:.3e}")
+    assert err <= TOL
+    eng.close()
+
+
 @pytest.mark.parametrize("rows", [15, 16, 17, 31, 32, 33])
 @pytest.mark.parametrize("hidden", [512, 2080])
 def test_streamed_rows_lines(rows, hidden):

@@ -116,7 +116,10 @@ constexpr int kSampleParts = 64, kSampleSegments = 1024;
 constexpr int kNucleusBins0 = 41 * 16;                           // exponents 0..40 x 4 mantissa bits
 constexpr int kNucleusHist = kNucleusBins0 + 1024 + 512;         // the three histograms of a row
 constexpr int kNucleusFound = kNucleusHist + kSampleSegments / 2;  // behind 1024 32-bit counts: what the search found
-constexpr int kNucleusScratch = kNucleusFound + 32;              // 64-bit words
+constexpr int kNucleusCounts = kNucleusFound + 32;               // per part the ids it listed, 32 bits each
+constexpr int kNucleusList = kNucleusCounts + kSampleParts / 2;  // the listed ids, shared out among the parts
+constexpr int kNucleusListed = 8192;
+constexpr int kNucleusScratch = kNucleusList + kNucleusListed;   // 64-bit words
 void launch_sample(SampleRows r, int rows, int vocab, hipStream_t s);
 void launch_philox_words(unsigned long long seed, const long long* ids, const unsigned* steps, unsigned* out,
                          int n, hipStream_t s);

@@ -15,10 +15,12 @@
 // significant bits, so as a float it is exact and its bits order like its value: 6 bits of
 // exponent and 23 of mantissa.  Histogram 0 bins by exponent and 4 mantissa bits (656 bins), the next
 // two by the following 10 and the last 9 bits among the ids of the bin found before; a bin is
-// found from the top by a prefix sum.  A fifth sweep leaves, per segment of 256 ids, the weight
-// above tau and the number of ids at tau, from which the draw needs no further sweep.  What bounds it:
-// the arithmetic of the weights (about 60 instructions per id and sweep), so the sweeps of a row
-// run on several workgroups, like the first two.  64 rows x 151936 ids, top_p 0.9: see launch_sample.
+// found from the top by a prefix sum.  What bounds it: the arithmetic of the weights, 60 instructions per id and
+// sweep, so the sweeps of a row run on several workgroups, like the first two, and the sweep that fills
+// histogram 1 is the last one as a rule: it leaves, per segment of 256 ids, the weight of the bins above the one found,
+// and lists the ids of that bin (some 500 of 151936 where logits spread like N(0, 2.5)); the draw finds the
+// rest from the list.  Rows so flat that the list overflows take two more sweeps instead: histogram 2, then
+// per segment the weight above tau and the number of ids at tau.  64 rows x 151936 ids, top_p 0.9: see launch_sample.
 #include <algorithm>
 
 #include "kernels.h"
@@ -27,12 +29,15 @@
 
 #define SAMP_T 1024
 
-// P(frac(t)) of t = d * log2(e), as bits; n = floor(t).  false: the weight is 0.
-__device__ inline bool fixexp_bits(float d, unsigned& bits, int& n_out) {
+// The weight as a float, exact (24 significant bits at most): P(frac(t)) with its exponent raised by 40 + floor(t),
+// t = d * log2(e), less what is worth less than 1; 0 for t below -40.  No branch, so that the arithmetic of a
+// thread's ids interleaves.
+__device__ inline float fixexp_value(float d) {
 #pragma clang fp contract(off)
   const float log2e = 0x1.715476p+0f;
   float t = d * log2e;
-  if (!(t >= -40.0f)) return false;
+  const bool any = t >= -40.0f;  // not so where d is no number
+  t = any ? t : -40.0f;
   float n = floorf(t);
   float f = t - n;
   float y = 0x1.5bd2aep-16f;
@@ -50,37 +55,23 @@ __device__ inline bool fixexp_bits(float d, unsigned& bits, int& n_out) {
   y = y + 0x1.62e430p-1f;
   y = y * f;
   y = y + 0x1.000000p+0f;
-  bits = __float_as_uint(y);
-  n_out = (int)n;
-  return true;
+  // y is about 1 to 2, so nothing leaves the exponent's 8 bits
+  const float v = truncf(__uint_as_float(__float_as_uint(y) + ((unsigned)((int)n + 40) << 23)));
+  return any ? v : 0.f;
 }
-// The weight as the bits of a float, exact (24 significant bits at most); 0 for weight 0.
-__device__ inline unsigned fixexp_key(float d) {
-  unsigned bits;
-  int n;
-  if (!fixexp_bits(d, bits, n)) return 0u;
-  // floor(y * 2^(40 + n)): the exponent grows by 40 + n, mantissa bits worth less than 1 go
-  const int e = (int)((bits >> 23) & 0xffu) - 127 + 40 + n;
-  if (e < 0) return 0u;
-  const unsigned below_one = e < 23 ? (1u << (23 - e)) - 1u : 0u;
-  return (((unsigned)(e + 127) << 23) | (bits & 0x7fffffu)) & ~below_one;
+// its bits: they order like the weights
+__device__ inline unsigned fixexp_key(float d) { return __float_as_uint(fixexp_value(d)); }
+// A weight, at most 2^41, as hi 2^22 + lo, lo below 2^22: a few instructions where 64-bit shifts take several times as
+// many cycles, and 256 ids' parts add up in 32 bits.
+struct WeightParts {
+  unsigned hi, lo;
+};
+__device__ inline WeightParts weight_parts(float v) {
+  const unsigned hi = (unsigned)(v * 0x1p-22f);
+  return WeightParts{hi, (unsigned)fmaf(-0x1p22f, (float)hi, v)};
 }
-__device__ inline unsigned long long key_weight(unsigned key) {
-  if (!key) return 0ull;
-  const int e = (int)(key >> 23) - 127;
-  const unsigned mant = (key & 0x7fffffu) | 0x800000u;
-  return e >= 23 ? (unsigned long long)mant << (e - 23) : (unsigned long long)(mant >> (23 - e));
-}
-
-// The weight itself, for the sweeps that only add weights up.
-__device__ inline unsigned long long fixexp_weight(float d) {
-  unsigned bits;
-  int n;
-  if (!fixexp_bits(d, bits, n)) return 0ull;
-  // y's 24 bits times 2^(e + 40 + n - 23), at most 2^17 (d <= 0): one 64-bit shift, to the right
-  const int e = (int)((bits >> 23) & 0xffu) - 127;
-  return ((unsigned long long)((bits & 0x7fffffu) | 0x800000u) << 17) >> (-e - n);
-}
+__device__ inline unsigned long long parts_sum(const WeightParts& w) { return ((unsigned long long)w.hi << 22) + w.lo; }
+__device__ inline unsigned long long key_weight(unsigned key) { return parts_sum(weight_parts(__uint_as_float(key))); }
 
 __device__ inline float scaled_logit(float logit, float inv_t) {
 #pragma clang fp contract(off)
@@ -99,23 +90,27 @@ __device__ inline unsigned long long dpp_add_u64(unsigned long long v) {
   const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(v >> 32), CTRL, ROWS, 0xf, false);
   return v + (((unsigned long long)hi << 32) | lo);
 }
-__device__ inline unsigned long long wave_scan_u64(unsigned long long v) {
+__device__ inline unsigned long long row_scan_u64(unsigned long long v) {  // over each 16 lanes
   v = dpp_add_u64<0x111, 0xf>(v);
   v = dpp_add_u64<0x112, 0xf>(v);
   v = dpp_add_u64<0x114, 0xf>(v);
-  v = dpp_add_u64<0x118, 0xf>(v);
+  return dpp_add_u64<0x118, 0xf>(v);
+}
+__device__ inline unsigned long long read_lane_u64(unsigned long long v, int lane) {  // lane: uniform
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, lane);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), lane);
+  return ((unsigned long long)hi << 32) | lo;
+}
+__device__ inline unsigned long long wave_scan_u64(unsigned long long v) {
+  v = row_scan_u64(v);
   v = dpp_add_u64<0x142, 0xa>(v);
   return dpp_add_u64<0x143, 0xc>(v);
 }
 __device__ inline unsigned long long wave_total_u64(unsigned long long v) {
-  v = wave_scan_u64(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, 63);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), 63);
-  return ((unsigned long long)hi << 32) | lo;
+  return read_lane_u64(wave_scan_u64(v), 63);
 }
 
-// Sum over the wavefront of values below 2^43 (the weights of four ids), in every lane: as two sums of 32 bits,
-// whose steps are one instruction each.
+// Sum over the wavefront, in every lane.
 __device__ inline unsigned wave_total_u32(unsigned v) {
   v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);
   v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
@@ -125,9 +120,8 @@ __device__ inline unsigned wave_total_u32(unsigned v) {
   v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);
   return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
-__device__ inline unsigned long long wave_total_weights(unsigned long long v) {
-  const unsigned lo = wave_total_u32((unsigned)v & 0x3fffffu), hi = wave_total_u32((unsigned)(v >> 22));
-  return ((unsigned long long)hi << 22) + lo;
+__device__ inline unsigned long long wave_total_weights(const WeightParts& w) {
+  return parts_sum(WeightParts{wave_total_u32(w.hi), wave_total_u32(w.lo)});
 }
 
 struct SampShared {
@@ -159,13 +153,16 @@ __device__ inline unsigned long long block_sum_u64(unsigned long long v, SampSha
   return s;
 }
 
-// Inclusive prefix sum over the threads of the workgroup.
-__device__ inline unsigned long long block_scan_u64(unsigned long long v, SampShared& sh) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// Inclusive prefix sum over the threads of the workgroup, and the sum over all of them.
+__device__ inline unsigned long long block_scan_u64(unsigned long long v, SampShared& sh, unsigned long long& total) {
+  static_assert(SAMP_T / WAVE == 16, "a wavefront's sum to each lane of a row");
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   v = wave_scan_u64(v);
   if (lane == 63) sh.wave_part[wave] = v;
   __syncthreads();
-  for (int w = 0; w < wave; ++w) v += sh.wave_part[w];
+  const unsigned long long waves = row_scan_u64(sh.wave_part[lane & 15]);
+  total = read_lane_u64(waves, 15);
+  if (wave > 0) v += read_lane_u64(waves, wave - 1);
   __syncthreads();
   return v;
 }
@@ -207,9 +204,6 @@ void launch_philox_words(unsigned long long seed, const long long* ids, const un
 // 16 segments per 4096-id tile of the block.  Every pass is a coalesced sweep that leaves one
 // value per segment in LDS; a prefix search over at most 1024 segment values then names the
 // segment that holds the id in question, and one wavefront resolves it inside the segment.
-struct Seg4 {
-  unsigned long long w[4];
-};
 struct Key4 {
   unsigned k[4];
 };
@@ -218,38 +212,78 @@ struct Logit4 {
   float v[4];
 };
 
-// logits of ids i0 .. i0 + 3, -inf past the end
-__device__ inline Logit4 load_logits4(const float* __restrict__ row, int i0, int vocab, bool vec_ok) {
-  Logit4 out = {{-INFINITY, -INFINITY, -INFINITY, -INFINITY}};
-  float(&v)[4] = out.v;
-  if (vec_ok && i0 + 3 < vocab) {
-    const float4 t = *(const float4*)(row + i0);
-    v[0] = t.x;
-    v[1] = t.y;
-    v[2] = t.z;
-    v[3] = t.w;
+// logits of ids i0 .. i0 + 3 for i0 <= vocab - 4, of the row's last four for more (logits4 puts those right).  One
+// 16-byte load whatever the row's alignment (the chip asks for that of a dword), and no branch: a load behind one
+// waits for the loads before it.
+typedef float quad_any __attribute__((ext_vector_type(4), aligned(4)));
+template <bool ANY_VOCAB>
+__device__ inline Logit4 request4(const float* __restrict__ row, int i0, int vocab) {
+  Logit4 out;
+  if (!ANY_VOCAB || vocab >= 4) {
+    const quad_any t = *(const quad_any*)(row + min(i0, vocab - 4));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) out.v[e] = t[e];
   } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (i0 + e < vocab) v[e] = row[i0 + e];
+    for (int e = 0; e < 4; ++e) out.v[e] = row[min(e, vocab - 1)];
   }
   return out;
 }
-__device__ inline Key4 load_keys4(const float* __restrict__ row, int i0, int vocab, bool vec_ok, float inv_t, float m) {
-  const Logit4 z = load_logits4(row, i0, vocab, vec_ok);
+// ids past the end hold one of the row's last logits, for the caller to leave out
+__device__ inline Logit4 logits4(Logit4 z, int i0, int vocab) {
+  if (i0 > vocab - 4 && vocab >= 4 && (vocab & 3)) {
+    const int by = min(i0 - (vocab - 4), 3);
+    if (by & 1) z = Logit4{{z.v[1], z.v[2], z.v[3], z.v[3]}};
+    if (by & 2) z = Logit4{{z.v[2], z.v[3], z.v[3], z.v[3]}};
+  }
+  return z;
+}
+__device__ inline Key4 keys4(const Logit4& z, int i0, int vocab, float inv_t, float m) {
   Key4 out;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) out.k[e] = i0 + e < vocab ? fixexp_key(shifted(scaled_logit(z.v[e], inv_t), m)) : 0u;
+  for (int e = 0; e < 4; ++e) {
+    const unsigned key = fixexp_key(shifted(scaled_logit(z.v[e], inv_t), m));
+    out.k[e] = i0 + e < vocab ? key : 0u;
+  }
   return out;
 }
-__device__ inline Seg4 load_weights4(const float* __restrict__ row, int i0, int vocab, bool vec_ok, float inv_t,
-                                     float m) {
-  const Logit4 z = load_logits4(row, i0, vocab, vec_ok);
-  Seg4 out;
+__device__ inline WeightParts weight4(const Logit4& z, int i0, int vocab, float inv_t, float m) {  // of the four together
+  const Key4 q = keys4(z, i0, vocab, inv_t, m);
+  WeightParts sum{0u, 0u};
 #pragma unroll
-  for (int e = 0; e < 4; ++e) out.w[e] = i0 + e < vocab ? fixexp_weight(shifted(scaled_logit(z.v[e], inv_t), m)) : 0ull;
-  return out;
+  for (int e = 0; e < 4; ++e) {
+    const WeightParts w = weight_parts(__uint_as_float(q.k[e]));
+    sum.hi += w.hi;
+    sum.lo += w.lo;
+  }
+  return sum;
 }
+
+// This thread's four logits of tiles t0, t0 + step, ... of a row.  The first AHEAD tiles are requested where the object
+// is made, so that they are under way while a sweep finds out what it needs to know of the sweeps before (those
+// sweeps have vocabularies of several tiles).
+template <int AHEAD>
+struct RowTiles {
+  const float* row;
+  int vocab, t0, step;
+  Logit4 ahead[AHEAD > 0 ? AHEAD : 1];
+  __device__ inline RowTiles(const float* row, int vocab, int t0, int step)
+      : row(row), vocab(vocab), t0(t0), step(step) {
+#pragma unroll
+    for (int q = 0; q < AHEAD; ++q) ahead[q] = request4<false>(row, (t0 + q * step) * 4096 + (int)threadIdx.x * 4, vocab);
+    if (AHEAD > 0) __builtin_amdgcn_sched_barrier(0);
+  }
+  // f(first id, logits) of every tile
+  template <typename F>
+  __device__ inline void each(F&& f) const {
+    const int n_tiles = (vocab + 4095) >> 12, i0 = (int)threadIdx.x * 4;
+#pragma unroll
+    for (int q = 0; q < AHEAD; ++q)
+      if (t0 + q * step < n_tiles) f((t0 + q * step) * 4096 + i0, logits4(ahead[q], (t0 + q * step) * 4096 + i0, vocab));
+    for (int t = t0 + AHEAD * step; t < n_tiles; t += step)
+      f(t * 4096 + i0, logits4(request4<AHEAD == 0>(row, t * 4096 + i0, vocab), t * 4096 + i0, vocab));
+  }
+};
 
 __device__ inline float row_inv_temp(const SampleRows& a, int r) { return a.inv_temp ? a.inv_temp[r] : a.inv_temp_all; }
 __device__ inline float row_top_p(const SampleRows& a, int r) { return a.top_p ? a.top_p[r] : a.top_p_all; }
@@ -266,16 +300,26 @@ __device__ inline unsigned nucleus_bin(unsigned key, int level) {
 }
 __device__ inline int nucleus_bins(int level) { return level == 0 ? kNucleusBins0 : level == 1 ? 1024 : 512; }
 
+__device__ inline unsigned long long nucleus_theta(unsigned long long S, float top_p) {
+  const unsigned long long p24 = (unsigned long long)floorf(fmaxf(top_p, 0.f) * 16777216.0f);
+  const unsigned long long theta = (S >> 24) * p24 + (((S & 0xffffffull) * p24) >> 24);
+  return theta < 1 ? 1 : theta;
+}
 struct NucleusState {
-  unsigned long long theta, above;  // weight to reach; weight of the bins above the ones found
-  unsigned prefix;                  // key bits found so far (nucleus_prefix of the next level; the key of tau after level 2)
+  unsigned long long sum, theta, above;  // all weight; weight to reach; weight of the bins above the ones found
+  unsigned prefix;                       // key bits found so far (nucleus_prefix of the next level; the key of tau after level 2)
 };
-// One more level: hist (n bins) names the highest bin at which the weight from the top reaches theta.
-__device__ inline void nucleus_descend(const unsigned long long* hist, int level, NucleusState& st, SampShared& sh) {
+// One more level.  The histogram's bins, counted from the top, lie one per thread (v); the first at which the weight
+// from the top reaches theta is found.
+__device__ inline void nucleus_descend(unsigned long long v, int level, float top_p, NucleusState& st, SampShared& sh) {
   const int n = nucleus_bins(level), t = threadIdx.x;
   if (t == 0) sh.bcast[0] = sh.bcast[1] = 0ull;  // a row without weights (no finite maximum) finds no bin
-  const unsigned long long v = t < n ? hist[n - 1 - t] : 0ull;
-  const unsigned long long inc = block_scan_u64(v, sh) + st.above;
+  unsigned long long total;
+  const unsigned long long inc = block_scan_u64(v, sh, total) + st.above;
+  if (level == 0) {
+    st.sum = total;
+    st.theta = nucleus_theta(total, top_p);
+  }
   if (t < n && inc >= st.theta && inc - v < st.theta) {  // exactly one thread: the sums only grow, and all of them reach theta
     sh.bcast[0] = (unsigned long long)(n - 1 - t);
     sh.bcast[1] = inc - v;
@@ -286,74 +330,63 @@ __device__ inline void nucleus_descend(const unsigned long long* hist, int level
   st.prefix = level == 0 ? bin + (127u << 4) : level == 1 ? (st.prefix << 10) | bin : (st.prefix << 9) | bin;
   __syncthreads();
 }
-__device__ inline unsigned long long nucleus_theta(unsigned long long S, float top_p) {
-  const unsigned long long p24 = (unsigned long long)floorf(fmaxf(top_p, 0.f) * 16777216.0f);
-  const unsigned long long theta = (S >> 24) * p24 + (((S & 0xffffffull) * p24) >> 24);
-  return theta < 1 ? 1 : theta;
+// this thread's bin of a histogram, counted from the top
+__device__ inline unsigned long long nucleus_bin_from_top(const unsigned long long* hist, int level) {
+  const int at = nucleus_bins(level) - 1 - (int)threadIdx.x;
+  return at >= 0 ? hist[at] : 0ull;
 }
-// State after the first `levels` histograms of row r (global scratch); S = sum of all weights.
-__device__ inline NucleusState nucleus_from_scratch(const SampleRows& a, int r, int levels, unsigned long long& S,
-                                                    SampShared& sh) {
-  const unsigned long long* h = a.nucleus + (long long)r * kNucleusScratch;
-  S = block_sum_u64(threadIdx.x < kNucleusBins0 ? h[threadIdx.x] : 0ull, sh);
-  NucleusState st{nucleus_theta(S, row_top_p(a, r)), 0ull, 0u};
-  nucleus_descend(h, 0, st, sh);
-  if (levels > 1) nucleus_descend(h + kNucleusBins0, 1, st, sh);
-  if (levels > 2) nucleus_descend(h + kNucleusBins0 + 1024, 2, st, sh);
-  return st;
-}
-// Tiles t0, t0 + step, ... of the row into the LDS histogram of `level` (zeroed here).  From level 1 on only the ids
+// The tiles into the LDS histogram of `level` (zeroed here).  From level 1 on only the ids
 // of one narrow bin count, so an id whose exponent t lies outside the bin's range is passed over before its
 // weight is computed: a weight w in the bin [lo, hi) comes from a value in [w, w + 1) that is 2^(40 + t) within
 // a few 2^-23, so t + 40 lies between log2(lo) and log2(hi + 1), each widened by 0.01.
-__device__ inline void nucleus_histogram(const float* row, int vocab, bool vec_ok, float inv_t, float m, int t0, int step,
-                                         int level, unsigned prefix, SampShared& sh) {
-  const int tid = threadIdx.x, n_tiles = (vocab + 4095) >> 12;
-  sh.hist[tid] = 0ull;
+template <int AHEAD>
+__device__ inline void nucleus_histogram(const RowTiles<AHEAD>& tiles, float inv_t, float m, int level, unsigned prefix,
+                                         SampShared& sh) {
+  sh.hist[threadIdx.x] = 0ull;
   __syncthreads();
-  float t_lo = 0.f, t_hi = 0.f;
   if (level > 0) {
     const int shift = level == 1 ? 19 : 9;
-    t_lo = log2f(__uint_as_float(prefix << shift)) - 40.01f;
-    t_hi = log2f(__uint_as_float((prefix + 1u) << shift) + 1.f) - 39.99f;
-  }
-  for (int t = t0; t < n_tiles; t += step) {
-    if (level > 0) {
-      const Logit4 z = load_logits4(row, t * 4096 + tid * 4, vocab, vec_ok);
+    const float t_lo = log2f(__uint_as_float(prefix << shift)) - 40.01f;
+    const float t_hi = log2f(__uint_as_float((prefix + 1u) << shift) + 1.f) - 39.99f;
+    tiles.each([&](int i0, const Logit4& z) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float d = shifted(scaled_logit(z.v[e], inv_t), m), x = d * 0x1.715476p+0f;
-        if (x >= t_lo && x <= t_hi) {  // (not so where d is no number)
+        if (x >= t_lo && x <= t_hi && i0 + e < tiles.vocab) {  // (not so where d is no number)
           const unsigned key = fixexp_key(d);
           if (key && nucleus_prefix(key, level) == prefix) atomicAdd(&sh.hist[nucleus_bin(key, level)], key_weight(key));
         }
       }
-      continue;
-    }
-    const Key4 q = load_keys4(row, t * 4096 + tid * 4, vocab, vec_ok, inv_t, m);
+    });
+  } else {
+    tiles.each([&](int i0, const Logit4& z) {
+      const Key4 q = keys4(z, i0, tiles.vocab, inv_t, m);
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (q.k[e]) atomicAdd(&sh.hist[nucleus_bin(q.k[e], level)], key_weight(q.k[e]));
+      for (int e = 0; e < 4; ++e)
+        if (q.k[e]) atomicAdd(&sh.hist[nucleus_bin(q.k[e], 0)], key_weight(q.k[e]));
+    });
   }
   __syncthreads();
 }
-// Tiles t0, t0 + step, ...: per segment the weight above tau and the number of ids at tau
-template <typename F>
-__device__ inline void nucleus_segments(const float* row, int vocab, bool vec_ok, float inv_t, float m, int t0, int step,
-                                        unsigned tau_key, F&& put) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int n_tiles = (vocab + 4095) >> 12, n_seg = (vocab + 255) >> 8;
-  for (int t = t0; t < n_tiles; t += step) {
-    const Key4 q = load_keys4(row, t * 4096 + tid * 4, vocab, vec_ok, inv_t, m);
-    unsigned long long v = 0;  // the weight (at most 256 x 2^40 per segment), the count from bit 52 on
+// Per segment the weight above tau and the number of ids at tau
+template <int AHEAD, typename F>
+__device__ inline void nucleus_segments(const RowTiles<AHEAD>& tiles, float inv_t, float m, unsigned tau_key, F&& put) {
+  const int n_seg = (tiles.vocab + 255) >> 8;
+  tiles.each([&](int i0, const Logit4& z) {
+    const Key4 q = keys4(z, i0, tiles.vocab, inv_t, m);
+    WeightParts above{0u, 0u};
+    unsigned at = 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      if (q.k[e] > tau_key) v += key_weight(q.k[e]);
-      if (q.k[e] == tau_key) v += 1ull << 52;
+      const WeightParts w = weight_parts(__uint_as_float(q.k[e]));
+      above.hi += q.k[e] > tau_key ? w.hi : 0u;
+      above.lo += q.k[e] > tau_key ? w.lo : 0u;
+      at += (unsigned)__popcll(__ballot(q.k[e] == tau_key));
     }
-    v = wave_total_u64(v);
-    if (lane == 0 && t * 16 + wave < n_seg) put(t * 16 + wave, v & ((1ull << 52) - 1ull), (unsigned)(v >> 52));
-  }
+    const unsigned long long sum = wave_total_weights(above);
+    const int seg = i0 >> 8;
+    if ((threadIdx.x & 63) == 0 && seg < n_seg) put(seg, sum, at);
+  });
 }
 
 // Smallest segment whose inclusive prefix of sh.vals[0..n_seg) exceeds target, and the
@@ -413,25 +446,16 @@ __device__ inline int resolve_in_segment(const unsigned long long (&v)[4], unsig
 
 // First sweep on `parts` workgroups per row: maximum of the scaled logits over tiles
 // blockIdx.x, blockIdx.x + parts, ...
-__global__ __launch_bounds__(SAMP_T) void sample_max_kernel(SampleRows a, int vocab, int parts) {
+__global__ __launch_bounds__(SAMP_T, 8) void sample_max_kernel(SampleRows a, int vocab, int parts) {
   __shared__ SampShared sh;
   const int tid = threadIdx.x, r = blockIdx.y;
   const float* row = a.logits + (long long)(a.logits_row ? a.logits_row[r] : r) * vocab;
   const float inv_t = row_inv_temp(a, r);
-  const bool vec_ok = (vocab & 3) == 0 && (((unsigned long long)row) & 15ull) == 0;
-  const int n_tiles = (vocab + 4095) >> 12;
   float m = -INFINITY;
-  for (int t = blockIdx.x; t < n_tiles; t += parts) {
-    const int i0 = t * 4096 + tid * 4;
-    if (vec_ok && i0 + 3 < vocab) {
-      const float4 v = *(const float4*)(row + i0);
-      m = fmaxf(fmaxf(m, fmaxf(scaled_logit(v.x, inv_t), scaled_logit(v.y, inv_t))),
-                fmaxf(scaled_logit(v.z, inv_t), scaled_logit(v.w, inv_t)));
-    } else {
-      for (int e = 0; e < 4; ++e)
-        if (i0 + e < vocab) m = fmaxf(m, scaled_logit(row[i0 + e], inv_t));
-    }
-  }
+  RowTiles<4>(row, vocab, blockIdx.x, parts).each([&](int, const Logit4& z) {  // an id taken twice changes no maximum
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m = fmaxf(m, scaled_logit(z.v[e], inv_t));
+  });
   m = block_max(m, sh);
   if (tid == 0) a.part_max[(long long)r * kSampleParts + blockIdx.x] = m;
   if (a.nucleus && row_has_nucleus(a, r, vocab))
@@ -439,70 +463,148 @@ __global__ __launch_bounds__(SAMP_T) void sample_max_kernel(SampleRows a, int vo
       a.nucleus[(long long)r * kNucleusScratch + i] = 0ull;
 }
 
-// one part per lane: their loads go out together
-__device__ inline float row_max(const SampleRows& a, int r, int parts) {
+// one part per lane: their loads go out together, and wave_max joins them
+__device__ inline float row_part_max(const SampleRows& a, int r, int parts) {
   static_assert(kSampleParts <= WAVE, "one part per lane");
-  const int lane = threadIdx.x & 63;
-  return wave_max(lane < parts ? a.part_max[(long long)r * kSampleParts + lane] : -INFINITY);
+  return a.part_max[(long long)r * kSampleParts + min((int)threadIdx.x & 63, parts - 1)];
 }
 
 // Second sweep on `parts` workgroups per row: the weights of the same tiles, one sum per
-// 256-id segment; rows with a nucleus: histogram 0.  Bound by the arithmetic: 256 rows x 151936 ids without a
-// nucleus 40.0 us (64 rows 13.3), where weights by way of keys and 64-bit wavefront sums took 58.6 (18.0) and
-// a weight from two 64-bit shifts with sums by exchanges through LDS 45.4 (16.0).
-__global__ __launch_bounds__(SAMP_T) void sample_segments_kernel(SampleRows a, int vocab, int parts) {
+// 256-id segment; rows with a nucleus: histogram 0.  Bound by the arithmetic, some 35 instructions per id; the first
+// tiles are requested before the maximum is known.
+__global__ __launch_bounds__(SAMP_T, 8) void sample_segments_kernel(SampleRows a, int vocab, int parts) {
   __shared__ SampShared sh;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = blockIdx.y;
+  const int tid = threadIdx.x, r = blockIdx.y;
   const float* row = a.logits + (long long)(a.logits_row ? a.logits_row[r] : r) * vocab;
   const float inv_t = row_inv_temp(a, r);
-  const bool vec_ok = (vocab & 3) == 0 && (((unsigned long long)row) & 15ull) == 0;
   const int n_seg = (vocab + 255) >> 8;
-  const int n_tiles = (vocab + 4095) >> 12;
-  const float m = row_max(a, r, parts);
+  const float part = row_part_max(a, r, parts);
+  const RowTiles<4> tiles(row, vocab, blockIdx.x, parts);
+  const float m = wave_max(part);
   if (a.nucleus && row_has_nucleus(a, r, vocab)) {
-    nucleus_histogram(row, vocab, vec_ok, inv_t, m, blockIdx.x, parts, 0, 0u, sh);
+    nucleus_histogram(tiles, inv_t, m, 0, 0u, sh);
     if (tid < kNucleusBins0 && sh.hist[tid]) atomicAdd(a.nucleus + (long long)r * kNucleusScratch + tid, sh.hist[tid]);
     return;
   }
-  for (int t = blockIdx.x; t < n_tiles; t += parts) {
-    const Seg4 q = load_weights4(row, t * 4096 + tid * 4, vocab, vec_ok, inv_t, m);
-    const unsigned long long ws = wave_total_weights(q.w[0] + q.w[1] + q.w[2] + q.w[3]);
-    if (lane == 0 && t * 16 + wave < n_seg) a.seg_sums[(long long)r * kSampleSegments + t * 16 + wave] = ws;
-  }
+  tiles.each([&](int i0, const Logit4& z) {
+    const unsigned long long ws = wave_total_weights(weight4(z, i0, vocab, inv_t, m));
+    if ((tid & 63) == 0 && i0 >> 8 < n_seg) a.seg_sums[(long long)r * kSampleSegments + (i0 >> 8)] = ws;
+  });
 }
 
-// The sweeps that only rows with a nucleus need, `parts` workgroups per row: histogram 1, histogram 2 (every
-// workgroup finds the bins of the histograms before it again, from a few KiB), then the segments.
-template <int LEVEL>
-__global__ __launch_bounds__(SAMP_T) void sample_nucleus_kernel(SampleRows a, int vocab, int parts) {
+// ids a part can list
+__device__ inline int nucleus_listed(int parts) { return min(2048, kNucleusListed / parts); }
+// Did a part of row r find more ids in its bin than it could list?  Every lane takes a part's count.
+__device__ inline bool nucleus_overflow(const unsigned long long* scratch, int parts) {
+  const unsigned n = ((const unsigned*)(scratch + kNucleusCounts))[min((int)threadIdx.x & 63, parts - 1)];
+  return __any(n > (unsigned)nucleus_listed(parts));
+}
+
+// The third sweep, only for rows with a nucleus: histogram 1, the segments' weights above the bin that histogram 0
+// names, and the list of its ids.  What a workgroup needs is requested at once, the histogram before the logits since
+// loads return in order.  One id in eight or so can be at or above the bin: a wavefront queues those in LDS
+// and computes their weights 64 at a time.  64 rows x 151936 ids: see launch_sample.
+__global__ __launch_bounds__(SAMP_T, 8) void sample_list_kernel(SampleRows a, int vocab, int parts) {
   __shared__ SampShared sh;
-  const int tid = threadIdx.x, r = blockIdx.y;
+  __shared__ uint2 queue[SAMP_T / WAVE][256 + WAVE];  // (logit, id)
+  __shared__ uint2 list[2048];  // (key, id)
+  __shared__ unsigned listed;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = blockIdx.y;
   if (!row_has_nucleus(a, r, vocab)) return;  // uniform
   const float* row = a.logits + (long long)(a.logits_row ? a.logits_row[r] : r) * vocab;
-  const float inv_t = row_inv_temp(a, r);
-  const bool vec_ok = (vocab & 3) == 0 && (((unsigned long long)row) & 15ull) == 0;
-  const float m = row_max(a, r, parts);
-  unsigned long long S;
-  const NucleusState st = nucleus_from_scratch(a, r, LEVEL, S, sh);
+  const float inv_t = row_inv_temp(a, r), top_p = row_top_p(a, r);
   unsigned long long* scratch = a.nucleus + (long long)r * kNucleusScratch;
-  if constexpr (LEVEL < 3) {
-    nucleus_histogram(row, vocab, vec_ok, inv_t, m, blockIdx.x, parts, LEVEL, st.prefix, sh);
-    unsigned long long* h = scratch + (LEVEL == 1 ? kNucleusBins0 : kNucleusBins0 + 1024);
-    if (tid < nucleus_bins(LEVEL) && sh.hist[tid]) atomicAdd(h + tid, sh.hist[tid]);
+  const float part = row_part_max(a, r, parts);
+  const unsigned long long h0 = nucleus_bin_from_top(scratch, 0);
+  const RowTiles<4> tiles(row, vocab, blockIdx.x, parts);
+  const float m = wave_max(part);
+  sh.hist[tid] = sh.vals[tid] = 0ull;
+  if (tid == 0) listed = 0u;
+  NucleusState st{};
+  nucleus_descend(h0, 0, top_p, st, sh);  // (its barriers stand between the two lines above and the sweep)
+
+  const unsigned room = (unsigned)nucleus_listed(parts);
+  const int n_seg = (vocab + 255) >> 8;
+  // As in nucleus_histogram no weight of the bin is found below some t, and so below some logit: t's d + m over
+  // 1 / T, lowered by more than the four roundings between a logit and its t add up to.  (No number where there is no
+  // finite maximum: no id passes, and none has a weight.)
+  const float d_lo = (log2f(__uint_as_float(st.prefix << 19)) - 40.02f) * 0.6931472f;
+  const float z_lo = (m + d_lo - 0x1p-19f * (fabsf(m) + fabsf(d_lo))) / inv_t;
+  const float lowest = z_lo - 0x1p-19f * fabsf(z_lo);
+  uint2* mine = queue[wave];
+  int queued = 0;
+  auto weigh = [&](const uint2& u) {
+    const unsigned key = fixexp_key(shifted(scaled_logit(__uint_as_float(u.x), inv_t), m)), prefix = key >> 19;
+    const unsigned long long w = key_weight(key);
+    if (prefix > st.prefix) {
+      atomicAdd(&sh.vals[u.y >> 8], w);
+    } else if (prefix == st.prefix) {
+      atomicAdd(&sh.hist[nucleus_bin(key, 1)], w);
+      const unsigned to = atomicAdd(&listed, 1u);
+      if (to < room) list[to] = make_uint2(key, u.y);
+    }
+  };
+  tiles.each([&](int i0, const Logit4& z) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool in = z.v[e] >= lowest && i0 + e < vocab;
+      const unsigned long long lanes = __ballot(in);
+      const int to = queued + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)lanes, 0u));
+      if (in) mine[to] = make_uint2(__float_as_uint(z.v[e]), (unsigned)(i0 + e));
+      queued += __popcll(lanes);
+    }
+    __builtin_amdgcn_wave_barrier();  // a wavefront's LDS accesses stay in order
+    while (queued >= WAVE) {
+      queued -= WAVE;
+      weigh(mine[queued + lane]);
+    }
+    __builtin_amdgcn_wave_barrier();
+  });
+  if (lane < queued) weigh(mine[lane]);
+  __syncthreads();
+  if (tid < n_seg && (tid >> 4) % parts == (int)blockIdx.x) a.seg_sums[(long long)r * kSampleSegments + tid] = sh.vals[tid];
+  if (sh.hist[tid]) atomicAdd(scratch + kNucleusBins0 + tid, sh.hist[tid]);
+  if (tid == 0) ((unsigned*)(scratch + kNucleusCounts))[blockIdx.x] = listed;
+  uint2* out = (uint2*)(scratch + kNucleusList) + blockIdx.x * room;
+  for (unsigned q = tid; q < min(listed, room); q += SAMP_T) out[q] = list[q];
+}
+
+// The sweeps of rows whose list overflowed, `parts` workgroups per row: histogram 2 (every workgroup finds the
+// bins of the histograms before it again, from a few KiB), then the segments.
+template <int LEVEL>
+__global__ __launch_bounds__(SAMP_T, 8) void sample_nucleus_kernel(SampleRows a, int vocab, int parts) {
+  __shared__ SampShared sh;
+  const int tid = threadIdx.x, r = blockIdx.y;
+  unsigned long long* scratch = a.nucleus + (long long)r * kNucleusScratch;
+  if (!row_has_nucleus(a, r, vocab) || !nucleus_overflow(scratch, parts)) return;  // uniform
+  const float* row = a.logits + (long long)(a.logits_row ? a.logits_row[r] : r) * vocab;
+  const float inv_t = row_inv_temp(a, r), top_p = row_top_p(a, r);
+  const float part = row_part_max(a, r, parts);
+  const unsigned long long h0 = nucleus_bin_from_top(scratch, 0);
+  const unsigned long long h1 = nucleus_bin_from_top(scratch + kNucleusBins0, 1);
+  const unsigned long long h2 = LEVEL > 2 ? nucleus_bin_from_top(scratch + kNucleusBins0 + 1024, 2) : 0ull;
+  const RowTiles<4> tiles(row, vocab, blockIdx.x, parts);
+  const float m = wave_max(part);
+  NucleusState st{};
+  nucleus_descend(h0, 0, top_p, st, sh);
+  nucleus_descend(h1, 1, top_p, st, sh);
+  if constexpr (LEVEL == 2) {
+    nucleus_histogram(tiles, inv_t, m, 2, st.prefix, sh);
+    if (tid < nucleus_bins(2) && sh.hist[tid]) atomicAdd(scratch + kNucleusBins0 + 1024 + tid, sh.hist[tid]);
   } else {
+    nucleus_descend(h2, 2, top_p, st, sh);
     unsigned* ties = (unsigned*)(scratch + kNucleusHist);
     if (blockIdx.x == 0 && tid == 0) {  // for the selection
       unsigned long long* found = scratch + kNucleusFound;
-      found[0] = S;
+      found[0] = st.sum;
       found[1] = st.theta;
       found[2] = st.above;
       found[3] = st.prefix;
     }
-    nucleus_segments(row, vocab, vec_ok, inv_t, m, blockIdx.x, parts, st.prefix,
-                     [&](int seg, unsigned long long above, unsigned n) {
-                       a.seg_sums[(long long)r * kSampleSegments + seg] = above;
-                       ties[seg] = n;
-                     });
+    nucleus_segments(tiles, inv_t, m, st.prefix, [&](int seg, unsigned long long above, unsigned n) {
+      a.seg_sums[(long long)r * kSampleSegments + seg] = above;
+      ties[seg] = n;
+    });
   }
 }
 
@@ -512,24 +614,56 @@ __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab,
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = blockIdx.x;
   const float* row = a.logits + (long long)(a.logits_row ? a.logits_row[r] : r) * vocab;
   const float inv_t = row_inv_temp(a, r);
-  const bool vec_ok = (vocab & 3) == 0 && (((unsigned long long)row) & 15ull) == 0;
   const int n_seg = (vocab + 255) >> 8;
-  const int n_tiles = (vocab + 4095) >> 12;
   const bool nucleus = row_has_nucleus(a, r, vocab);
 
   float m = -INFINITY;
   unsigned long long S = 0;
-  NucleusState st{0ull, 0ull, 0u};
+  NucleusState st{};
   if (parts) {
-    m = row_max(a, r, parts);
+    m = wave_max(row_part_max(a, r, parts));
     if (nucleus) {
       const unsigned long long* scratch = a.nucleus + (long long)r * kNucleusScratch;
-      S = scratch[kNucleusFound];
-      st = NucleusState{scratch[kNucleusFound + 1], scratch[kNucleusFound + 2], (unsigned)scratch[kNucleusFound + 3]};
-      const unsigned* ties = (const unsigned*)(scratch + kNucleusHist);
-      if (tid < n_seg) {
-        sh.hist[tid] = a.seg_sums[(long long)r * kSampleSegments + tid];
-        sh.ties[tid] = ties[tid];
+      const unsigned* counts = (const unsigned*)(scratch + kNucleusCounts);
+      const uint2* list = (const uint2*)(scratch + kNucleusList);
+      const int room = nucleus_listed(parts);
+      const float top_p = row_top_p(a, r);
+      // all that is needed as a rule, requested at once: the first 64 ids of this wavefront's part come before their number
+      const unsigned long long h0 = nucleus_bin_from_top(scratch, 0), h1 = nucleus_bin_from_top(scratch + kNucleusBins0, 1);
+      const unsigned long long sum = a.seg_sums[(long long)r * kSampleSegments + min(tid, n_seg - 1)];
+      const int n_part = wave < parts ? (int)counts[wave] : 0;
+      static_assert(kNucleusListed / kSampleParts >= WAVE, "a part has room for 64 ids");
+      const uint2 first = list[min(wave, parts - 1) * room + lane];
+      if (!nucleus_overflow(scratch, parts)) {
+        sh.hist[tid] = tid < n_seg ? sum : 0ull;
+        sh.vals[tid] = 0ull;
+        sh.ties[tid] = 0u;
+        nucleus_descend(h0, 0, top_p, st, sh);
+        nucleus_descend(h1, 1, top_p, st, sh);
+        auto each_listed = [&](auto&& f) {  // a wavefront takes the parts wave, wave + 16, ...
+          if (lane < n_part) f(first);
+          for (int i = WAVE + lane; i < n_part; i += WAVE) f(list[wave * room + i]);
+          for (int q = wave + SAMP_T / WAVE; q < parts; q += SAMP_T / WAVE)
+            for (int i = lane; i < (int)counts[q]; i += WAVE) f(list[q * room + i]);
+        };
+        each_listed([&](const uint2& u) {
+          if (nucleus_prefix(u.x, 2) == st.prefix) atomicAdd(&sh.vals[nucleus_bin(u.x, 2)], key_weight(u.x));
+        });
+        __syncthreads();
+        nucleus_descend(nucleus_bin_from_top(sh.vals, 2), 2, top_p, st, sh);
+        S = st.sum;
+        each_listed([&](const uint2& u) {
+          if (u.x > st.prefix) atomicAdd(&sh.hist[u.y >> 8], key_weight(u.x));
+          else if (u.x == st.prefix) atomicAdd(&sh.ties[u.y >> 8], 1u);
+        });
+      } else {
+        S = scratch[kNucleusFound];
+        st = NucleusState{S, scratch[kNucleusFound + 1], scratch[kNucleusFound + 2], (unsigned)scratch[kNucleusFound + 3]};
+        const unsigned* ties = (const unsigned*)(scratch + kNucleusHist);
+        if (tid < n_seg) {
+          sh.hist[tid] = sum;
+          sh.ties[tid] = ties[tid];
+        }
       }
     } else {
       unsigned long long local = 0;
@@ -540,42 +674,32 @@ __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab,
       S = block_sum_u64(local, sh);
     }
   } else {
-    for (int t = 0; t < n_tiles; ++t) {
-      const int i0 = t * 4096 + tid * 4;
-      if (vec_ok && i0 + 3 < vocab) {
-        const float4 v = *(const float4*)(row + i0);
-        m = fmaxf(fmaxf(m, fmaxf(scaled_logit(v.x, inv_t), scaled_logit(v.y, inv_t))),
-                  fmaxf(scaled_logit(v.z, inv_t), scaled_logit(v.w, inv_t)));
-      } else {
-        for (int e = 0; e < 4; ++e)
-          if (i0 + e < vocab) m = fmaxf(m, scaled_logit(row[i0 + e], inv_t));
-      }
-    }
+    const RowTiles<0> tiles(row, vocab, 0, 1);
+    tiles.each([&](int, const Logit4& z) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) m = fmaxf(m, scaled_logit(z.v[e], inv_t));
+    });
     m = block_max(m, sh);
     if (nucleus) {
-      nucleus_histogram(row, vocab, vec_ok, inv_t, m, 0, 1, 0, 0u, sh);
-      S = block_sum_u64(sh.hist[tid], sh);
-      st.theta = nucleus_theta(S, row_top_p(a, r));
-      nucleus_descend(sh.hist, 0, st, sh);
-      for (int level = 1; level < 3; ++level) {
-        nucleus_histogram(row, vocab, vec_ok, inv_t, m, 0, 1, level, st.prefix, sh);
-        nucleus_descend(sh.hist, level, st, sh);
+      const float top_p = row_top_p(a, r);
+      for (int level = 0; level < 3; ++level) {
+        nucleus_histogram(tiles, inv_t, m, level, st.prefix, sh);
+        nucleus_descend(nucleus_bin_from_top(sh.hist, level), level, top_p, st, sh);
       }
-      nucleus_segments(row, vocab, vec_ok, inv_t, m, 0, 1, st.prefix,
-                       [&](int seg, unsigned long long above, unsigned n) {
-                         sh.hist[seg] = above;
-                         sh.ties[seg] = n;
-                       });
+      S = st.sum;
+      nucleus_segments(tiles, inv_t, m, st.prefix, [&](int seg, unsigned long long above, unsigned n) {
+        sh.hist[seg] = above;
+        sh.ties[seg] = n;
+      });
     } else {
       // all weights, one sum per segment
       unsigned long long local = 0;
-      for (int t = 0; t < n_tiles; ++t) {
-        const Seg4 q = load_weights4(row, t * 4096 + tid * 4, vocab, vec_ok, inv_t, m);
-        const unsigned long long mine = q.w[0] + q.w[1] + q.w[2] + q.w[3];
-        local += mine;
+      tiles.each([&](int i0, const Logit4& z) {
+        const WeightParts mine = weight4(z, i0, vocab, inv_t, m);
+        local += parts_sum(mine);
         const unsigned long long ws = wave_total_weights(mine);
-        if (lane == 0 && t * 16 + wave < n_seg) sh.vals[t * 16 + wave] = ws;
-      }
+        if (lane == 0 && i0 >> 8 < n_seg) sh.vals[i0 >> 8] = ws;
+      });
       S = block_sum_u64(local, sh);  // also orders the writes to sh.vals
     }
   }
@@ -592,7 +716,8 @@ __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab,
       k_ties = tau ? (unsigned)((st.theta - st.above + tau - 1) / tau) : 0u;  // theta > above: tau's bin was needed to reach it
       s_n = st.above + k_ties * tau;
       const unsigned mine = tid < n_seg ? sh.ties[tid] : 0u;
-      const unsigned before = (unsigned)block_scan_u64(mine, sh) - mine;
+      unsigned long long all;
+      const unsigned before = (unsigned)block_scan_u64(mine, sh, all) - mine;
       const unsigned in = before < k_ties ? min(mine, k_ties - before) : 0u;
       if (tid < n_seg) {
         sh.vals[tid] = sh.hist[tid] + in * tau;
@@ -608,7 +733,8 @@ __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab,
     unsigned long long before;
     find_segment(sh, n_seg, R, seg, before);
     if (wave == 0) {
-      const Key4 q = load_keys4(row, seg * 256 + lane * 4, vocab, vec_ok, inv_t, m);
+      const int i0 = seg * 256 + lane * 4;
+      const Key4 q = keys4(logits4(request4<true>(row, i0, vocab), i0, vocab), i0, vocab, inv_t, m);
       unsigned long long v[4];
       if (nucleus) {
         unsigned at_tau = 0;
@@ -660,11 +786,11 @@ __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab,
 
 // Large vocabularies with scratch at hand: the sweeps of a row on several workgroups (about 512 in all),
 // then the selection; else everything in one workgroup per row.
-// 64 rows x 151936 ids, top_p 0.9: 8.1 + 16.3 us for maximum and histogram 0, 12.9 + 12.5 + 24.7 us for the other
-// histograms and the segments above tau, 9.1 us for the selection: 95 us per call of rollout_sample, where
-// one workgroup per row that searched tau bit by bit took 1809 us.  (111 us with the parts' maxima read one
-// after the other, scans through LDS and every id's weight computed in histograms 1 and 2.)  The sweeps'
-// arithmetic takes the time: 39 MB of logits pass in 8 us.
+// 64 rows x 151936 ids, top_p 0.9, with 2 us of launch each: 8.8 + 14.2 us for maximum and histogram 0, 14.9 us for
+// the sweep that lists, 4.3 + 3.3 us for the two that find nothing to do, 12.2 us for the selection: 67 us per
+// call of rollout_sample.  With histograms 1 and 2 and the segments above tau in three full sweeps and weights by
+// 64-bit shifts 94 us (8.1 + 16.3 + 12.9 + 12.5 + 24.7 + 9.1); one workgroup per row that searched tau bit by bit 1809 us.
+// The sweeps' arithmetic takes the time: 39 MB of logits pass in 8 us.
 static void launch_sample_rows(const SampleRows& r, int rows, int vocab, hipStream_t s) {
   const int n_tiles = (vocab + 4095) >> 12;
   int parts = 0;
@@ -678,7 +804,7 @@ static void launch_sample_rows(const SampleRows& r, int rows, int vocab, hipStre
   sample_max_kernel<<<grid, SAMP_T, 0, s>>>(r, vocab, parts);
   sample_segments_kernel<<<grid, SAMP_T, 0, s>>>(r, vocab, parts);
   if (r.any_nucleus) {
-    sample_nucleus_kernel<1><<<grid, SAMP_T, 0, s>>>(r, vocab, parts);
+    sample_list_kernel<<<grid, SAMP_T, 0, s>>>(r, vocab, parts);
     sample_nucleus_kernel<2><<<grid, SAMP_T, 0, s>>>(r, vocab, parts);
     sample_nucleus_kernel<3><<<grid, SAMP_T, 0, s>>>(r, vocab, parts);
   }

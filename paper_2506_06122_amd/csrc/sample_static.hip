@@ -22,7 +22,7 @@ constexpr size_t kOffNucleus = kOffSegSums + sizeof(unsigned long long) * kMaxRo
 constexpr size_t kScratchBytes = kOffNucleus + sizeof(unsigned long long) * kMaxRows * kNucleusScratch;
 static_assert(kOffSegSums % 256 == 0 && kOffNucleus % 256 == 0, "256-byte aligned parts");
 
-// One copy per GPU the library runs on, held until the process ends (about 7.7 MB).  In host
+// One copy per GPU the library runs on, held until the process ends (about 25 MB).  In host
 // code this name is only a handle for hipGetSymbolAddress: the address a kernel can use is
 // looked up once per device and kept in g_scratch_ptr.
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];

@@ -54,6 +54,22 @@ def test_more_rows_than_the_nucleus_scratch_holds():
         assert int(toks[r]) == sampler.sample(z[r], np.float32(1.0), 0.9, int(x[r]))[0], f"row {r}"
 
 
+@pytest.mark.parametrize("rows,vocab", [(1, 151936), (40, 65536 + 3), (300, 28676)])
+def test_rows_from_flat_to_spread(rows, vocab):
+    """The bin that ends the nucleus holds from all ids down to a few: on either side of what a workgroup can list,
+    with 38, 12 and 2 workgroups to a row."""
+    import torch
+    import paper_2506_06122_amd as R
+    for scale in np.geomspace(0.01, 4.0, 9):
+        z = workloads.random_logits(rows, vocab, seed=11, scale=float(scale))
+        x = workloads.uniform_words(rows, seed=12)
+        toks, _, sums = R.rollout_sample(torch.from_numpy(z).cuda(), 1.0, 0.9, x)
+        for r in {0, rows - 1}:
+            w = sampler.fixexp_weights(z[r], sampler.inv_temperature(1.0))
+            assert int(sums[r]) == int(np.sum(w, dtype=np.uint64)), f"scale {scale} row {r}"
+            assert int(toks[r]) == sampler.draw(w, sampler.nucleus(w, 0.9), int(x[r])), f"scale {scale} row {r}"
+
+
 @pytest.mark.parametrize("vocab", [1, 255, 4097, 28672, 28673, 65536 + 3, 262144])
 def test_whole_vocabulary_matches_oracle(vocab):
     """top_p = 1 on the same rows: every weight counts, from 2^40 (equal maxima: the largest sums of a segment) down

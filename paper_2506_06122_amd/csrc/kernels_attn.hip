@@ -69,9 +69,14 @@ __device__ __forceinline__ void group_scores(const Frag (&k)[2][4], const Frag (
     s1 = MFMA16(k[1][i & 3].v, q[(i + 4) & 7].v, s1);
   }
 }
-//   softmax: probabilities as hi + lo half-precision parts.  limit = last visible position of the column; m in log2
-//   units; l = this lane's share of the column's sum (column_sum at the end); o = unnormalised output^T fragments,
-//   rescaled only where the maximum of a column has moved.
+//   softmax: probabilities as hi + lo half-precision parts.  limit = last visible position of the column; m = the
+//   column's maximum in log2 units less P_SCALE_LOG2; l = this lane's share of the column's sum (column_sum at the end);
+//   o = unnormalised output^T fragments, rescaled only where the maximum of a column has moved.
+//   m carries the scale of the probabilities because what is subtracted from the scores has to be the very number that
+//   the sums and partial results go by: its own rounding then cancels, and a probability's exponent is rounded once.
+//   The exponentials are bare instructions, which return 0 for results below 2^-126.  Nothing is lost by that: as a
+//   half-precision operand such a probability is 0 anyway, and beside the maximum's own 2^10 neither it nor a sum
+//   that is rescaled by so little (at most 2^27 terms of 2^10 before) reaches the last bit.
 __device__ __forceinline__ void group_softmax(f32x4 s0, f32x4 s1, int tok0, int limit, float scale_log2, float& m,
                                               float& l, f32x4 (&o)[8], Frag& hi, Frag& lo, int lane) {
   if (!__all(tok0 + 31 <= limit)) {
@@ -83,7 +88,7 @@ __device__ __forceinline__ void group_softmax(f32x4 s0, f32x4 s1, int tok0, int 
     }
   }
   float mx = fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])), fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3])));
-  mx = column_max(mx) * scale_log2;
+  mx = fmaf(column_max(mx), scale_log2, -P_SCALE_LOG2);
   if (__any(mx > m)) {
     const float m_new = fmaxf(m, mx);
     const float alpha = __builtin_amdgcn_exp2f(m - (m_new == -INFINITY ? 0.f : m_new));
@@ -97,7 +102,7 @@ __device__ __forceinline__ void group_softmax(f32x4 s0, f32x4 s1, int tok0, int 
       o[j][3] *= alpha;
     }
   }
-  const float shift = P_SCALE_LOG2 - (m == -INFINITY ? 0.f : m);
+  const float shift = m == -INFINITY ? 0.f : -m;
   float p[8];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -489,8 +494,8 @@ __device__ __forceinline__ void decode_own_range(const AttnArgs& a, const Decode
   for (int e = 4 * tid; e < G * DH; e += 256 * NW) {
     const float4 acc = merged_out<NW>(sm, e);
     if (direct) {
-      const float inv = 1.0f / merged_sum<NW>(sm, e >> 7);
-      store4_split(a.out + out_offset(a, b, kvh * G * DH + e), a.out_lo_offset, acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
+      const float sum = merged_sum<NW>(sm, e >> 7);
+      store4_split(a.out + out_offset(a, b, kvh * G * DH + e), a.out_lo_offset, acc.x / sum, acc.y / sum, acc.z / sum, acc.w / sum);
     } else {
       *(float4*)(a.part_o + part * (16 * DH) + e) = acc;
     }

@@ -46,9 +46,13 @@
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
-// __expf carries a few ulp; the reciprocal's one ulp is below that, and both are far below the 2^-17 of the result's
-// two parts.  An exponential that overflows gives 1 / inf = 0.
-__device__ inline float silu_f(float a) { return a * __builtin_amdgcn_rcpf(1.0f + __expf(-a)); }
+// a / (1 + e^-a).  The quotient from the reciprocal (1 ulp) is put right by its remainder: over all 2^32 operands the
+// bits are those of the IEEE division, in half its instructions; only for a < -87.3, where the reciprocal of more than
+// 2^126 is flushed, 0 stands for results below 6e-37.  div_fixup is for infinite operands.
+__device__ inline float silu_f(float a) {
+  const float d = 1.0f + __expf(-a), r = __builtin_amdgcn_rcpf(d), q = a * r;
+  return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-d, q, a), r, q), d, a);
+}
 
 // D[n][m] tile of fp32 results -> memory.  lane (r, g) holds rows n = 4g..4g+3 of the tile at column m = r.
 __device__ inline void store_tile_f32(const GemmArgs& p, int m, int nt, const f32x4& t, int g, int z) {

@@ -54,6 +54,23 @@ def test_more_rows_than_the_nucleus_scratch_holds():
         assert int(toks[r]) == sampler.sample(z[r], np.float32(1.0), 0.9, int(x[r]))[0], f"row {r}"
 
 
+@pytest.mark.parametrize("vocab", [256, 257, 1024, 4352, 4353])
+@pytest.mark.parametrize("top_p", [0.9, 1.0])
+def test_wavefronts_without_ids(vocab, top_p):
+    """One workgroup per row skips the wavefronts whose 256 ids lie past the end: none, one id or all of the last ones."""
+    import torch
+    import paper_2506_06122_amd as R
+    z = hard_rows(vocab, seed=vocab)
+    x = workloads.uniform_words(len(z), seed=5)
+    x[::2] = 2 ** 32 - 1
+    toks, _, sums = R.rollout_sample(torch.from_numpy(z).cuda(), 0.8, top_p, x)
+    inv_t = sampler.inv_temperature(0.8)
+    for r in range(len(z)):
+        w = sampler.fixexp_weights(z[r], inv_t)
+        assert int(sums[r]) == int(np.sum(w, dtype=np.uint64)), f"row {r}"
+        assert int(toks[r]) == sampler.draw(w, sampler.nucleus(w, top_p), int(x[r])), f"row {r}"
+
+
 @pytest.mark.parametrize("rows,vocab", [(1, 151936), (40, 65536 + 3), (300, 28676)])
 def test_rows_from_flat_to_spread(rows, vocab):
     """The bin that ends the nucleus holds from all ids down to a few: on either side of what a workgroup can list,

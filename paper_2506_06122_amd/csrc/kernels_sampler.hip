@@ -19,8 +19,9 @@
 // sweep, so the sweeps of a row run on several workgroups, like the first two, and the sweep that fills
 // histogram 1 is the last one as a rule: it leaves, per segment of 256 ids, the weight of the bins above the one found,
 // and lists the ids of that bin (some 500 of 151936 where logits spread like N(0, 2.5)); the draw finds the
-// rest from the list.  Rows so flat that the list overflows take two more sweeps instead: histogram 2, then
-// per segment the weight above tau and the number of ids at tau.  64 rows x 151936 ids, top_p 0.9: see launch_sample.
+// rest from the list.  Rows so flat that the list would overflow (nucleus_is_flat) take full sweeps instead:
+// histogram 1, histogram 2, then per segment the weight above tau and the number of ids at tau.  64 rows x 151936 ids,
+// top_p 0.9: see launch_sample.
 #include <algorithm>
 
 #include "kernels.h"
@@ -129,7 +130,7 @@ struct SampShared {
   unsigned long long hist[SAMP_T];   // a histogram, or the nucleus' weight above tau per segment
   unsigned ties[SAMP_T];             // ids at tau per segment
   unsigned long long wave_part[SAMP_T / WAVE];
-  unsigned long long bcast[2];
+  unsigned long long bcast[3];
   float fwave[SAMP_T / WAVE];
 };
 
@@ -311,12 +312,13 @@ __device__ inline unsigned long long nucleus_theta(unsigned long long S, float t
 struct NucleusState {
   unsigned long long sum, theta, above;  // all weight; weight to reach; weight of the bins above the ones found
   unsigned prefix;                       // key bits found so far (nucleus_prefix of the next level; the key of tau after level 2)
+  unsigned long long here;               // weight of the bin found last
 };
 // One more level.  The histogram's bins, counted from the top, lie one per thread (v); the first at which the weight
 // from the top reaches theta is found.
 __device__ inline void nucleus_descend(unsigned long long v, int level, float top_p, NucleusState& st, SampShared& sh) {
   const int n = nucleus_bins(level), t = threadIdx.x;
-  if (t == 0) sh.bcast[0] = sh.bcast[1] = 0ull;  // a row without weights (no finite maximum) finds no bin
+  if (t == 0) sh.bcast[0] = sh.bcast[1] = sh.bcast[2] = 0ull;  // a row without weights (no finite maximum) finds no bin
   unsigned long long total;
   const unsigned long long inc = block_scan_u64(v, sh, total) + st.above;
   if (level == 0) {
@@ -326,10 +328,12 @@ __device__ inline void nucleus_descend(unsigned long long v, int level, float to
   if (t < n && inc >= st.theta && inc - v < st.theta) {  // exactly one thread: the sums only grow, and all of them reach theta
     sh.bcast[0] = (unsigned long long)(n - 1 - t);
     sh.bcast[1] = inc - v;
+    sh.bcast[2] = v;
   }
   __syncthreads();
   const unsigned bin = (unsigned)sh.bcast[0];
   st.above = sh.bcast[1];
+  st.here = sh.bcast[2];
   st.prefix = level == 0 ? bin + (127u << 4) : level == 1 ? (st.prefix << 10) | bin : (st.prefix << 9) | bin;
   __syncthreads();
 }
@@ -503,10 +507,23 @@ __device__ inline bool nucleus_overflow(const unsigned long long* scratch, int p
   return __any(n > (unsigned)nucleus_listed(parts));
 }
 
+// Will the ids of the bin that histogram 0 names overflow the list?  Its weight over the power of two below it is their number, or
+// what it would be at the foot of that power of two, where bins are twice as wide as at its end: whatever the phase,
+// rows of one spread decide alike.  (A call whose rows go both ways pays for both: 64 rows of N(0, 0.2) by the true
+// number 99 us.)  They fall to the parts within some three standard deviations.  64 rows x 151936 ids of N(0, s), top_p
+// 0.9, us a call with the list / with full sweeps throughout: s 0.05 99 / 86, 0.2 101 / 80 (some 7500 ids: the
+// list overflows), 0.35 74 / 80, 0.7 65 / 79, 1.5 58 / 78; 256 rows: 0.2 261 / 208, 0.7 252 / 205 (2 x 2048 places),
+// 1.0 168 / 205.  The same in every workgroup of a row.
+__device__ inline bool nucleus_is_flat(const NucleusState& st, int parts) {
+  const float room = __builtin_amdgcn_sqrtf((float)nucleus_listed(parts) + 2.25f) - 1.5f;  // x^2 + 3 x = places
+  return (float)st.here > __uint_as_float((st.prefix << 19) & 0x7f800000u) * ((float)parts * room * room);
+}
+
 // The third sweep, only for rows with a nucleus: histogram 1, the segments' weights above the bin that histogram 0
-// names, and the list of its ids.  What a workgroup needs is requested at once, the histogram before the logits since
-// loads return in order.  One id in eight or so can be at or above the bin: a wavefront queues those in LDS
-// and computes their weights 64 at a time.  64 rows x 151936 ids: see launch_sample.
+// names, and the list of its ids; of flat rows histogram 1 alone, and every part says that its list overflowed.  What a
+// workgroup needs is requested at once, the histogram before the logits since loads return in order.  One id in eight
+// or so can be at or above the bin: a wavefront queues those in LDS and computes their weights 64 at a time.
+// 64 rows x 151936 ids: see launch_sample.
 __global__ __launch_bounds__(SAMP_T, 8) void sample_list_kernel(SampleRows a, int vocab, int parts) {
   __shared__ SampShared sh;
   __shared__ uint2 queue[SAMP_T / WAVE][256 + WAVE];  // (logit, id)
@@ -527,6 +544,12 @@ __global__ __launch_bounds__(SAMP_T, 8) void sample_list_kernel(SampleRows a, in
   nucleus_descend(h0, 0, top_p, st, sh);  // (its barriers stand between the two lines above and the sweep)
 
   const unsigned room = (unsigned)nucleus_listed(parts);
+  if (nucleus_is_flat(st, parts)) {
+    nucleus_histogram(tiles, inv_t, m, 1, st.prefix, sh);
+    if (sh.hist[tid]) atomicAdd(scratch + kNucleusBins0 + tid, sh.hist[tid]);
+    if (tid == 0) ((unsigned*)(scratch + kNucleusCounts))[blockIdx.x] = room + 1u;
+    return;
+  }
   const int n_seg = (vocab + 255) >> 8;
   // As in nucleus_histogram no weight of the bin is found below some t, and so below some logit: t's d + m over
   // 1 / T, lowered by more than the four roundings between a logit and its t add up to.  (No number where there is no
@@ -536,13 +559,19 @@ __global__ __launch_bounds__(SAMP_T, 8) void sample_list_kernel(SampleRows a, in
   const float lowest = z_lo - 0x1p-19f * fabsf(z_lo);
   uint2* mine = queue[wave];
   int queued = 0;
-  auto weigh = [&](const uint2& u) {
-    const unsigned key = fixexp_key(shifted(scaled_logit(__uint_as_float(u.x), inv_t), m)), prefix = key >> 19;
-    const unsigned long long w = key_weight(key);
-    if (prefix > st.prefix) {
-      atomicAdd(&sh.vals[u.y >> 8], w);
-    } else if (prefix == st.prefix) {
-      atomicAdd(&sh.hist[nucleus_bin(key, 1)], w);
+  auto weigh = [&](const uint2& u, bool full) {
+    const unsigned key = fixexp_key(shifted(scaled_logit(__uint_as_float(u.x), inv_t), m)), prefix = key >> 19, seg = u.y >> 8;
+    const WeightParts w = weight_parts(__uint_as_float(key));
+    const bool above = prefix > st.prefix;
+    if (full && __all(seg == (unsigned)__builtin_amdgcn_readfirstlane((int)seg))) {
+      // ids of one segment, as in flat rows: 64 atomics on one word are one after the other
+      const unsigned long long sum = wave_total_weights(WeightParts{above ? w.hi : 0u, above ? w.lo : 0u});
+      if (lane == 0) atomicAdd(&sh.vals[seg], sum);
+    } else if (above) {
+      atomicAdd(&sh.vals[seg], parts_sum(w));
+    }
+    if (prefix == st.prefix) {
+      atomicAdd(&sh.hist[nucleus_bin(key, 1)], parts_sum(w));
       const unsigned to = atomicAdd(&listed, 1u);
       if (to < room) list[to] = make_uint2(key, u.y);
     }
@@ -559,11 +588,11 @@ __global__ __launch_bounds__(SAMP_T, 8) void sample_list_kernel(SampleRows a, in
     __builtin_amdgcn_wave_barrier();  // a wavefront's LDS accesses stay in order
     while (queued >= WAVE) {
       queued -= WAVE;
-      weigh(mine[queued + lane]);
+      weigh(mine[queued + lane], true);
     }
     __builtin_amdgcn_wave_barrier();
   });
-  if (lane < queued) weigh(mine[lane]);
+  if (lane < queued) weigh(mine[lane], false);
   __syncthreads();
   if (tid < n_seg && (tid >> 4) % parts == (int)blockIdx.x) a.seg_sums[(long long)r * kSampleSegments + tid] = sh.vals[tid];
   if (sh.hist[tid]) atomicAdd(scratch + kNucleusBins0 + tid, sh.hist[tid]);

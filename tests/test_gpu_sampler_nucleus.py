@@ -87,6 +87,23 @@ def test_rows_from_flat_to_spread(rows, vocab):
             assert int(toks[r]) == sampler.draw(w, sampler.nucleus(w, 0.9), int(x[r])), f"scale {scale} row {r}"
 
 
+@pytest.mark.parametrize("rows,vocab", [(64, 151936), (64, 32001), (256, 32001)])
+@pytest.mark.parametrize("top_p", [0.5, 0.9, 0.99])
+def test_flat_rows_lines(rows, vocab, top_p):
+    """Rows on either side of the line between the list and full sweeps (8 workgroups to a row with five tiles or one, 2 with
+    four), flat and spread ones in one call."""
+    import torch
+    import paper_2506_06122_amd as R
+    scales = np.array([0.03, 0.1, 0.2, 0.35, 0.5, 0.6, 0.7, 0.8, 1.0, 1.5], np.float32)
+    z = workloads.random_logits(rows, vocab, seed=21, scale=1.0) * scales[np.arange(rows) % 10, None]
+    x = workloads.uniform_words(rows, seed=22)
+    toks, _, sums = R.rollout_sample(torch.from_numpy(z).cuda(), 1.0, top_p, x)
+    for r in range(20, 30):
+        w = sampler.fixexp_weights(z[r], sampler.inv_temperature(1.0))
+        assert int(sums[r]) == int(np.sum(w, dtype=np.uint64)), f"scale {scales[r % 10]}"
+        assert int(toks[r]) == sampler.draw(w, sampler.nucleus(w, top_p), int(x[r])), f"scale {scales[r % 10]}"
+
+
 @pytest.mark.parametrize("vocab", [1, 255, 4097, 28672, 28673, 65536 + 3, 262144])
 def test_whole_vocabulary_matches_oracle(vocab):
     """top_p = 1 on the same rows: every weight counts, from 2^40 (equal maxima: the largest sums of a segment) down

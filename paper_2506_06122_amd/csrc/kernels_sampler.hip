@@ -499,6 +499,14 @@ __global__ __launch_bounds__(SAMP_T, 8) void sample_segments_kernel(SampleRows a
   });
 }
 
+// What lanes of a wavefront wrote to LDS before it, others read after it.  (Its LDS accesses are carried out in order, so
+// this is an order for the compiler and no instruction.)
+__device__ inline void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ids a part can list
 __device__ inline int nucleus_listed(int parts) { return min(2048, kNucleusListed / parts); }
 // Did a part of row r find more ids in its bin than it could list?  Every lane takes a part's count.
@@ -585,12 +593,12 @@ __global__ __launch_bounds__(SAMP_T, 8) void sample_list_kernel(SampleRows a, in
       if (in) mine[to] = make_uint2(__float_as_uint(z.v[e]), (unsigned)(i0 + e));
       queued += __popcll(lanes);
     }
-    __builtin_amdgcn_wave_barrier();  // a wavefront's LDS accesses stay in order
+    wave_lds_fence();
     while (queued >= WAVE) {
       queued -= WAVE;
       weigh(mine[queued + lane], true);
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_fence();
   });
   if (lane < queued) weigh(mine[lane], false);
   __syncthreads();

@@ -43,9 +43,8 @@ constexpr TileBlock tile_block(const TileGrid& g, unsigned index) {
 constexpr long long tile_units(const TileGrid& g) { return tile_ceil(g.ny, g.group_m) * tile_ceil(g.nx, g.group_n) * g.nz; }
 constexpr long long tile_workgroups(const TileGrid& g) { return tile_ceil(tile_units(g), 8) * 8 * g.group_m * g.group_n; }
 
-// what tile_block divides by, once the launch's counts and groups are set
+// what tile_block divides by, once the launch's groups are set (the planner's search does without)
 constexpr void tile_divisors(TileGrid& g) {
-  g.gy = (int)tile_ceil(g.ny, g.group_m);
   const long long per = g.group_m * g.group_n;
   g.by_per = tile_by(per);
   g.by_nz = tile_by(g.nz);
@@ -73,7 +72,7 @@ constexpr int tile_groups(TileGrid& g) {
     }
   }
   g.group_m = best_m;
-  tile_divisors(g);
+  g.gy = (int)tile_ceil(g.ny, best_m);
   return best;
 }
 
@@ -93,5 +92,5 @@ constexpr void tile_groups_experts(TileGrid& g) {
   g.group_m = most;
   while (2 * g.group_m >= most && groups_share_xcds(tile_ceil(g.ny, g.group_m))) --g.group_m;
   if (2 * g.group_m < most) g.group_m = most;
-  tile_divisors(g);
+  g.gy = (int)tile_ceil(g.ny, g.group_m);
 }

@@ -34,11 +34,13 @@ int main() {
         TileGrid g;
         g.nx = nx, g.ny = ny, g.nz = nz;
         const int per_cu = tile_groups(g);
+        tile_divisors(g);
         check(g, "dense");
         // the busiest XCD's workgroups, shared by its 32 CUs
         if ((long long)per_cu * 256 < (long long)nx * ny * nz || g.group_m < 1 || g.group_m > 16) return 2;
         if (nz == 1) {  // the experts' launches
           tile_groups_experts(g);
+          tile_divisors(g);
           check(g, "grouped");
         }
         ++n;
@@ -51,6 +53,7 @@ int main() {
         TileGrid g;
         g.nx = nx, g.ny = ny, g.nz = 1;
         tile_groups_experts(g);
+        tile_divisors(g);
         int load[8] = {};
         for (long long i = 0; i < tile_workgroups(g); ++i) {
           const TileBlock b = tile_block(g, (unsigned)i);

@@ -1,4 +1,5 @@
-"""The tile launch's mapping of workgroups to blocks (csrc/tile_grid.h, plain integers) on the CPU."""
+"""The tile launch's mapping of workgroups to blocks (csrc/tile_grid.h) and the choice of tile shapes (csrc/tile_plan.h),
+plain integers and floats, on the CPU."""
 import os
 import shutil
 import subprocess
@@ -8,14 +9,22 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def test_every_block_is_visited_once(tmp_path):
+def run_driver(name, tmp_path):
     cxx = shutil.which("g++")
     if not cxx:
         pytest.skip("no host C++ compiler")
-    out = str(tmp_path / "tile_grid_driver")
+    out = str(tmp_path / name)
     res = subprocess.run([cxx, "-std=c++17", "-O2", "-Wall", "-Wextra", "-Werror",
-                          os.path.join(ROOT, "tests", "host", "tile_grid_driver.cpp"), "-o", out], capture_output=True, text=True)
+                          os.path.join(ROOT, "tests", "host", name + ".cpp"), "-o", out], capture_output=True, text=True)
     assert res.returncode == 0, res.stderr
     res = subprocess.run([out], capture_output=True, text=True, timeout=300)
     assert res.returncode == 0, res.stderr
-    assert int(res.stdout.split()[0]) > 1000
+    return res.stdout
+
+
+def test_every_block_is_visited_once(tmp_path):
+    assert int(run_driver("tile_grid_driver", tmp_path).split()[0]) > 1000
+
+
+def test_a_plan_is_evaluated_once(tmp_path):
+    assert run_driver("tile_plan_driver", tmp_path).count("plans") == 4

@@ -52,6 +52,13 @@ __device__ inline void split4_bf16(float a, float b, float c, float d, uint2& hi
   split2_bf16(c, d, hi.y, lo.y);
 }
 
+// a / d from r, the hardware's reciprocal of d (1 ulp): put right by the remainder, rounded as the IEEE division but for
+// neighbours of a tie, in a third of its instructions.  For finite a and normal r.
+__device__ inline float quotient(float a, float d, float r) {
+  const float q = a * r;
+  return fmaf(fmaf(-d, q, a), r, q);
+}
+
 // IEEE half: the 16-bit format of the KV cache of bf16 models.  Keys and values are of order
 // one, so the three extra mantissa bits over bf16 are what keeps 28-layer logits within
 // tolerance of the unrounded reference at the same bytes per cached token.  Values saturate

@@ -494,8 +494,9 @@ __device__ __forceinline__ void decode_own_range(const AttnArgs& a, const Decode
   for (int e = 4 * tid; e < G * DH; e += 256 * NW) {
     const float4 acc = merged_out<NW>(sm, e);
     if (direct) {
-      const float sum = merged_sum<NW>(sm, e >> 7);
-      store4_split(a.out + out_offset(a, b, kvh * G * DH + e), a.out_lo_offset, acc.x / sum, acc.y / sum, acc.z / sum, acc.w / sum);
+      const float sum = merged_sum<NW>(sm, e >> 7), r = __builtin_amdgcn_rcpf(sum);
+      store4_split(a.out + out_offset(a, b, kvh * G * DH + e), a.out_lo_offset, quotient(acc.x, sum, r),
+                   quotient(acc.y, sum, r), quotient(acc.z, sum, r), quotient(acc.w, sum, r));
     } else {
       *(float4*)(a.part_o + part * (16 * DH) + e) = acc;
     }

@@ -46,12 +46,11 @@
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
-// a / (1 + e^-a).  The quotient from the reciprocal (1 ulp) is put right by its remainder: over all 2^32 operands the
-// bits are those of the IEEE division, in half its instructions; only for a < -87.3, where the reciprocal of more than
-// 2^126 is flushed, 0 stands for results below 6e-37.  div_fixup is for infinite operands.
+// a / (1 + e^-a).  Over all 2^32 operands the bits are those of the IEEE division; only for a < -87.3, where the
+// reciprocal of more than 2^126 is flushed, 0 stands for results below 6e-37.  div_fixup is for infinite operands.
 __device__ inline float silu_f(float a) {
-  const float d = 1.0f + __expf(-a), r = __builtin_amdgcn_rcpf(d), q = a * r;
-  return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-d, q, a), r, q), d, a);
+  const float d = 1.0f + __expf(-a);
+  return __builtin_amdgcn_div_fixupf(quotient(a, d, __builtin_amdgcn_rcpf(d)), d, a);
 }
 
 // D[n][m] tile of fp32 results -> memory.  lane (r, g) holds rows n = 4g..4g+3 of the tile at column m = r.

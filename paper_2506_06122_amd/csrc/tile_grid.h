@@ -7,7 +7,6 @@ struct TileGrid {
   int group_m = 1, group_n = 1;      // row and column blocks an XCD takes side by side
   int gy = 1;                        // row groups
   unsigned by_per = 0, by_nz = 0, by_gy = 0, by_m = 0;  // tile_by of group_m * group_n, nz, gy and group_m (tile_divisors)
-  bool divide = false;               // too large for them
 };
 struct TileBlock {
   int x, y, z;
@@ -16,13 +15,14 @@ struct TileBlock {
 
 constexpr long long tile_ceil(long long a, long long b) { return (a + b - 1) / b; }
 
-// x / d as one multiplication: the high word of x m, m = ceil(2^32 / d), is the quotient for x d < 2^32.  0 stands for
-// d = 1.  (A division of two runtime integers is some 30 instructions, and the kernel needs four quotients before its
-// first load: 0.3 us of a launch.)
+// x / d as one multiplication by m = ceil(2^32 / d), whose high word is the quotient or one more: m is less than 1
+// above 2^32 / d, so x m / 2^32 is less than x / 2^32 < 1 above x / d.  For d >= 1 and x + d < 2^32 (a launch has fewer than
+// 2^31 workgroups); m = 0 stands for d = 1.  (A division of two runtime integers is some 30 instructions, and the
+// kernel needs four quotients before its first load: 0.3 us of a launch.)
 constexpr unsigned tile_by(long long d) { return d == 1 ? 0u : (unsigned)(((1ll << 32) + d - 1) / d); }
-constexpr unsigned tile_div(unsigned x, unsigned by) {
+constexpr unsigned tile_div(unsigned x, unsigned d, unsigned by) {
   const unsigned q = (unsigned)(((unsigned long long)x * by) >> 32);
-  return by ? q : x;
+  return by ? q - (q * d > x) : x;
 }
 
 // Workgroup -> block.  The launch is one-dimensional and workgroups go to the 8 XCDs (each with its own L2)
@@ -31,12 +31,8 @@ constexpr unsigned tile_div(unsigned x, unsigned by) {
 // its L2; groups go round the XCDs with the split varying fastest, then the row blocks.
 constexpr TileBlock tile_block(const TileGrid& g, unsigned index) {
   const unsigned xcd = index & 7, idx = index >> 3, per = g.group_m * g.group_n, nz = g.nz, gy = g.gy, gm = g.group_m;
-  unsigned run = tile_div(idx, g.by_per), unit = run * 8 + xcd, in = idx - run * per;
-  unsigned q = tile_div(unit, g.by_nz), xg = tile_div(q, g.by_gy), xi = tile_div(in, g.by_m);
-  if (g.divide) {
-    run = idx / per, unit = run * 8 + xcd, in = idx % per;
-    q = unit / nz, xg = q / gy, xi = in / gm;
-  }
+  const unsigned run = tile_div(idx, per, g.by_per), unit = run * 8 + xcd, in = idx - run * per;
+  const unsigned q = tile_div(unit, nz, g.by_nz), xg = tile_div(q, gy, g.by_gy), xi = tile_div(in, gm, g.by_m);
   const int x = (int)(xg * g.group_n + xi), y = (int)((q - xg * gy) * gm + in - xi * gm);
   return TileBlock{x, y, (int)(unit - q * nz), y < g.ny && x < g.nx};
 }
@@ -45,13 +41,10 @@ constexpr long long tile_workgroups(const TileGrid& g) { return tile_ceil(tile_u
 
 // what tile_block divides by, once the launch's groups are set (the planner's search does without)
 constexpr void tile_divisors(TileGrid& g) {
-  const long long per = g.group_m * g.group_n;
-  g.by_per = tile_by(per);
+  g.by_per = tile_by(g.group_m * g.group_n);
   g.by_nz = tile_by(g.nz);
   g.by_gy = tile_by(g.gy);
   g.by_m = tile_by(g.group_m);
-  const long long most = per > g.nz ? (per > g.gy ? per : g.gy) : (g.nz > g.gy ? g.nz : g.gy);
-  g.divide = tile_workgroups(g) * most >= 1ll << 32;  // no dividend is larger than the number of workgroups
 }
 
 // Sets group_m and group_n and returns the workgroups the busiest CU gets (32 CUs to an XCD).

@@ -24,8 +24,37 @@ static void check(const TileGrid& g, const char* what) {
     }
 }
 
+// tile_div against the division, around multiples of the divisor up to the last index a launch can have
+static bool quotients() {
+  for (long long d : {1ll, 2ll, 3ll, 5ll, 7ll, 12ll, 16ll, 61ll, 64ll, 641ll, 1000ll, 4095ll, 4883ll, 65535ll, 65537ll, 1000003ll, 0x7fffffffll})
+    for (long long step : {1ll, 3ll, 1009ll, 65537ll, 1000003ll})
+      for (long long k = 0; k < 2000; ++k)
+        for (long long at : {k * step * d, 0x80000000ll - k * step * d, 0x80000000ll - k * step})
+          for (long long x = at - 2; x <= at + 2; ++x)
+            if (x >= 0 && x < 0x80000000ll && tile_div((unsigned)x, (unsigned)d, tile_by(d)) != (unsigned)(x / d)) {
+              std::fprintf(stderr, "%lld / %lld\n", x, d);
+              return false;
+            }
+  return true;
+}
+
 int main() {
   int n = 0;
+  if (!quotients()) return 4;
+  // the last workgroups of a launch far larger than any this library makes
+  {
+    TileGrid g;
+    g.nx = 4099, g.ny = 200003, g.nz = 1;
+    tile_groups(g);
+    tile_divisors(g);
+    const long long last = tile_workgroups(g);
+    for (long long i = last > 3000000 ? last - 3000000 : 0; i < last; ++i) {
+      const long long idx = i >> 3, per = (long long)g.group_m * g.group_n, unit = idx / per * 8 + (i & 7), in = idx % per;
+      const long long gy = tile_ceil(g.ny, g.group_m), x = unit / gy * g.group_n + in / g.group_m, y = unit % gy * g.group_m + in % g.group_m;
+      const TileBlock b = tile_block(g, (unsigned)i);
+      if (b.x != x || b.y != y || b.z != 0) return 5;
+    }
+  }
   const int wide[] = {1, 2, 3, 5, 8, 12, 13, 28, 36, 112, 140, 148, 297, 594, 1187, 1188};
   for (int nx : wide)
     for (int ny : {1, 2, 3, 4, 5, 6, 7, 15, 16, 17, 31, 33, 64, 100, 129, 289, 513})

@@ -363,6 +363,35 @@ int rollout_debug_logits(rollout_ctx *ctx, int32_t *rows, float *out);
  * rows: in capacity, out count.  Errors: E_INVAL, E_STATE (not recording / nothing yet). */
 int rollout_debug_routing(rollout_ctx *ctx, int32_t *rows, int32_t *out);
 
+/* Parity hook: one launch of the projection kernel with a tile shape of the caller's choice, which the planner would take
+ * for large problems only.  All arrays DEVICE memory; the call enqueues one kernel on hip_stream.
+ *   a        activations, bf16 [rows][k / 32][2][32]: 32 hi parts, then their lo parts
+ *   w        weights in fragment order, bf16 [groups][n / 16][k / 32][k % 32 / 8][n % 16][8]; with epilogue 1 a tile of 16
+ *            columns is 8 gates, then their 8 ups
+ *   epilogue 0: out float [planes][m][n], one plane per K split (at most `splits`; planes returns their number)
+ *            1: out bf16 [m][n / 64][2][32], silu(gate) * up; n a multiple of 64
+ *            3: log-sum-exp parts of scale * result per block of the shape's columns, float [blocks][m] each, and for rows
+ *               with target[row] >= 0 that column's value
+ *   row_map .. n_blocks: NULL and 0, or a grouped launch: row block y holds rows [block_begin[y], block_end[y]), none
+ *            longer than the shape's rows, with the weights of group_of_block[y]; row_map (epilogue 1, shapes with
+ *            `grouped`) names the row of `a` that each takes
+ * Errors: E_INVAL (a shape, size or combination that no launch has; array contents are not checked), E_HIP. */
+typedef struct {
+  int32_t shape, epilogue, splits, m, n, k;
+  const void *a, *w;
+  void *out;
+  const int32_t *row_map, *group_of_block, *block_begin, *block_end;
+  int32_t n_blocks;
+  const int32_t *target;
+  float scale;
+  float *part_max, *part_sum, *target_value;
+} rollout_tile_product;
+int rollout_debug_tile_product(const rollout_tile_product *p, void *hip_stream, int32_t *planes);
+/* Returns the number of tile shapes; describes shape `index` where there is one (any pointer may be NULL): rows and
+ * columns of its tile, K groups of wavefronts, stages of its ring, whether row_map can be used. */
+int32_t rollout_debug_tile_shape(int32_t index, int32_t *rows, int32_t *columns, int32_t *k_groups, int32_t *stages,
+                                 int32_t *grouped);
+
 int rollout_get_stats(rollout_ctx *ctx, rollout_stats *out);
 /* Per-kernel timings gathered under ROLLOUT_RT_KERNEL_TIMING.  n: in capacity of `out`, out
  * number of entries written (kernels with at least one timed launch).  The entry named
@@ -393,7 +422,7 @@ int rollout_sample(const float *logits, int32_t rows, int32_t vocab, float tempe
  * float [rows], weight_sums uint64 [rows] or NULL - and the call only enqueues kernels on
  * hip_stream: no allocation, no host-device copy, no synchronisation; outputs are valid once the
  * stream has reached that point.  The kernels' scratch (the partial maxima, segment
- * sums and histograms of the sweeps, about 30 KB per row) is a fixed device array inside the
+ * sums, histograms and listed ids of the sweeps, about 96 KB per row) is a fixed device array inside the
  * library, one copy per GPU, kept until the process ends: rows <= ROLLOUT_SAMPLE_STATIC_MAX_ROWS,
  * else E_INVAL.  Every call on a GPU uses that one array, which keeps the last call's contents
  * (nothing in it has to start at zero: each call writes what it reads): calls that overlap on one

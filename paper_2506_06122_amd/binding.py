@@ -84,6 +84,13 @@ class rollout_kernel_stat(C.Structure):
                 ("flops", C.c_double)]
 
 
+class rollout_tile_product(C.Structure):
+    _fields_ = ([(n, C.c_int32) for n in ("shape", "epilogue", "splits", "m", "n", "k")] +
+                [(n, C.c_void_p) for n in ("a", "w", "out", "row_map", "group_of_block", "block_begin", "block_end")] +
+                [("n_blocks", C.c_int32), ("target", C.c_void_p), ("scale", C.c_float)] +
+                [(n, C.c_void_p) for n in ("part_max", "part_sum", "target_value")])
+
+
 # every symbol include/rollout.h declares: name -> (restype, argtypes)
 _P = C.c_void_p
 SIGNATURES = {
@@ -104,6 +111,8 @@ SIGNATURES = {
     "rollout_queue_get_stats": (C.c_int, [_P, C.POINTER(rollout_queue_stats)]),
     "rollout_debug_logits": (C.c_int, [_P, C.POINTER(C.c_int32), _P]),
     "rollout_debug_routing": (C.c_int, [_P, C.POINTER(C.c_int32), _P]),
+    "rollout_debug_tile_product": (C.c_int, [C.POINTER(rollout_tile_product), _P, C.POINTER(C.c_int32)]),
+    "rollout_debug_tile_shape": (C.c_int32, [C.c_int32] + [C.POINTER(C.c_int32)] * 5),
     "rollout_get_stats": (C.c_int, [_P, C.POINTER(rollout_stats)]),
     "rollout_kernel_stats": (C.c_int, [_P, C.POINTER(C.c_int32), C.POINTER(rollout_kernel_stat)]),
     "rollout_last_error": (C.c_char_p, [_P]),
@@ -377,6 +386,28 @@ def _kernel_stats(self) -> list:
 
 
 Rollout.rollout_kernel_stats = _kernel_stats
+
+
+def rollout_debug_tile_shapes() -> list:
+    """(rows, columns, K groups, stages, takes row_map) of every tile shape of the projection kernel."""
+    lib = load_library()
+    out = []
+    for i in range(lib.rollout_debug_tile_shape(-1, None, None, None, None, None)):
+        v = [C.c_int32() for _ in range(5)]
+        lib.rollout_debug_tile_shape(i, *[C.byref(x) for x in v])
+        out.append(tuple(x.value for x in v))
+    return out
+
+
+def rollout_debug_tile_product(stream=None, **fields) -> int:
+    """Fields of rollout_tile_product, arrays as CUDA tensors.  Returns the number of planes written."""
+    lib = load_library()
+    p = rollout_tile_product(**{k: v.data_ptr() if hasattr(v, "data_ptr") else v for k, v in fields.items()})
+    planes = C.c_int32()
+    rc = lib.rollout_debug_tile_product(C.byref(p), stream, C.byref(planes))
+    if rc != OK:
+        raise RolloutError(rc, lib.rollout_last_error(None).decode())
+    return planes.value
 
 
 def rollout_sample(logits, temperature, top_p, uniforms, forced=None, stream=None):

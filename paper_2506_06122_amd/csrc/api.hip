@@ -10,6 +10,7 @@
 #include <thread>
 
 #include "engine.h"
+#include "tile_plan.h"
 
 static thread_local std::string g_init_error;
 
@@ -1280,6 +1281,66 @@ int rollout_debug_routing(rollout_ctx* ctx, int32_t* rows, int32_t* out) {
                              (size_t)n * k * sizeof(int), c.md.n_layers, hipMemcpyDeviceToHost, c.stream));
     HIP_TRY(hipStreamSynchronize(c.stream));
     *rows = n;
+  });
+}
+
+int32_t rollout_debug_tile_shape(int32_t index, int32_t* rows, int32_t* columns, int32_t* k_groups, int32_t* stages,
+                                 int32_t* grouped) {
+  constexpr int n = sizeof(kTileShapes) / sizeof(kTileShapes[0]);
+  if (index < 0 || index >= n) return n;
+  const TileShape& t = kTileShapes[index];
+  if (rows) *rows = t.wm * t.mt * 16;
+  if (columns) *columns = t.wn * t.nt * 16;
+  if (k_groups) *k_groups = t.kg;
+  if (stages) *stages = t.s;
+  if (grouped) *grouped = grouped_shape(index);
+  return n;
+}
+
+int rollout_debug_tile_product(const rollout_tile_product* p, void* hip_stream, int32_t* planes) {
+  return guarded(nullptr, [&] {
+    if (!p || !planes) fail(ROLLOUT_E_INVAL, "null argument");
+    const bool grouped = p->group_of_block != nullptr;
+    const int epi = p->epilogue;
+    if (p->shape < 0 || p->shape >= rollout_debug_tile_shape(-1, nullptr, nullptr, nullptr, nullptr, nullptr) || p->m < 1 ||
+        p->n < 16 || p->n % 16 || p->k < 32 || p->k % 32 || p->splits < 1 || p->splits > p->k / 32 || !p->a || !p->w)
+      fail(ROLLOUT_E_INVAL, "bad shape or size");
+    const TileShape& t = kTileShapes[p->shape];
+    if (epi != EPI_F32 && epi != EPI_SWIGLU_BF16 && epi != EPI_LSE) fail(ROLLOUT_E_INVAL, "no such epilogue");
+    if ((epi != EPI_F32 || grouped) && p->splits != 1) fail(ROLLOUT_E_INVAL, "only plain fp32 results have K splits");
+    if (epi == EPI_SWIGLU_BF16 && p->n % 64) fail(ROLLOUT_E_INVAL, "gates and ups come in 64 columns");
+    if (epi == EPI_LSE ? grouped || t.wn * t.nt < kLseMinTile || !p->target || !p->part_max || !p->part_sum || !p->target_value
+                       : !p->out)
+      fail(ROLLOUT_E_INVAL, "bad log-sum-exp launch or null output");
+    if (grouped ? !p->block_begin || !p->block_end || p->n_blocks < 1 : p->row_map != nullptr)
+      fail(ROLLOUT_E_INVAL, "bad groups");
+    if (p->row_map && (epi != EPI_SWIGLU_BF16 || !grouped_shape(p->shape))) fail(ROLLOUT_E_INVAL, "no such gathering launch");
+    GemmArgs g{};
+    g.a = p->a;
+    g.a_lo = (const uint16_t*)p->a + kPlaneLo;
+    g.w = p->w;
+    g.out = p->out;
+    g.out_lo_offset = kPlaneLo;
+    g.M = p->m;
+    g.N = p->n;
+    g.K = p->k;
+    g.ldo = epi == EPI_SWIGLU_BF16 ? p->n / 2 : p->n;
+    g.split_stride = grouped ? 0 : (long long)p->m * p->n;
+    g.row_map = p->row_map;
+    g.group_of_block = p->group_of_block;
+    g.block_row_begin = p->block_begin;
+    g.block_row_end = p->block_end;
+    g.group_stride16 = (long long)p->n * p->k * 2 / 16;
+    g.n_row_blocks = p->n_blocks;
+    g.lse_target = p->target;
+    g.lse_scale = p->scale;
+    g.lse_max = p->part_max;
+    g.lse_sum = p->part_sum;
+    g.lse_tgt = p->target_value;
+    g.lse_stride = p->m;
+    const GemmPlan pl{1, p->shape, t.wn * t.nt, p->splits, ""};
+    *planes = launch_gemm_bf16(g, epi, pl, (hipStream_t)hip_stream);
+    HIP_TRY(hipGetLastError());
   });
 }
 

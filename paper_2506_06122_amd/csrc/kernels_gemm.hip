@@ -607,8 +607,6 @@ static const StreamShape kStreamShapes[] = {
 #undef X
 };
 
-constexpr bool grouped_shape(int id) { return id <= 2 || id == 7 || id == 8; }  // the experts' launches (gemm_plan_grouped)
-constexpr int kLseMinTile = 8;    // column tiles per workgroup an EPI_LSE launch has at least (sizes the parts' buffers)
 
 static GemmPlan gemm_plan_tiled(int M, int N, int K, int epi, int max_splits) {
   static thread_local TilePlans plans;

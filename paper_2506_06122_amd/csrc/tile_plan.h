@@ -43,6 +43,9 @@ constexpr TileShape kTileShapes[] = {
     TILE_SHAPES(X)
 #undef X
 };
+constexpr bool grouped_shape(int id) { return id <= 2 || id == 7 || id == 8; }  // the experts' launches (gemm_plan_grouped)
+constexpr int kLseMinTile = 8;  // column tiles per workgroup an EPI_LSE launch has at least (sizes the parts' buffers)
+
 // Microseconds one projection is expected to take: the busiest CU's rounds of workgroups, and what comes from beyond the
 // L2s - the weights once, the activations once per XCD that works on them (a K split's and row group's share goes to
 // one XCD in gcd(splits x row groups, 8) of 8: with 7 or 10 splits every L2 fetches what it would share with 8) -

@@ -15,14 +15,14 @@ struct TileBlock {
 
 constexpr long long tile_ceil(long long a, long long b) { return (a + b - 1) / b; }
 
-// x / d as one multiplication by m = ceil(2^32 / d), whose high word is the quotient or one more: m is less than 1
-// above 2^32 / d, so x m / 2^32 is less than x / 2^32 < 1 above x / d.  For d >= 1 and x + d < 2^32 (a launch has fewer than
-// 2^31 workgroups); m = 0 stands for d = 1.  (A division of two runtime integers is some 30 instructions, and the
-// kernel needs four quotients before its first load: 0.3 us of a launch.)
-constexpr unsigned tile_by(long long d) { return d == 1 ? 0u : (unsigned)(((1ll << 32) + d - 1) / d); }
+// x / d for any x and d >= 1, as one multiplication by m = floor(2^32 / d) (2^32 - 1 for d = 1), whose high word is the
+// quotient or one less: m is at most 1 below 2^32 / d, so x m / 2^32 is at most x / 2^32 < 1 below x / d.  (A division of
+// two runtime integers is some 30 instructions, and the kernel needs four quotients before its first load: 0.3 us of
+// a launch.)
+constexpr unsigned tile_by(long long d) { return d == 1 ? 0xffffffffu : (unsigned)((1ll << 32) / d); }
 constexpr unsigned tile_div(unsigned x, unsigned d, unsigned by) {
   const unsigned q = (unsigned)(((unsigned long long)x * by) >> 32);
-  return by ? q - (q * d > x) : x;
+  return q + (x - q * d >= d);
 }
 
 // Workgroup -> block.  The launch is one-dimensional and workgroups go to the 8 XCDs (each with its own L2)

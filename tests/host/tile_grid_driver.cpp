@@ -24,14 +24,14 @@ static void check(const TileGrid& g, const char* what) {
     }
 }
 
-// tile_div against the division, around multiples of the divisor up to the last index a launch can have
+// tile_div against the division, around multiples of the divisor up to the last 32-bit number
 static bool quotients() {
   for (long long d : {1ll, 2ll, 3ll, 5ll, 7ll, 12ll, 16ll, 61ll, 64ll, 641ll, 1000ll, 4095ll, 4883ll, 65535ll, 65537ll, 1000003ll, 0x7fffffffll})
     for (long long step : {1ll, 3ll, 1009ll, 65537ll, 1000003ll})
       for (long long k = 0; k < 2000; ++k)
-        for (long long at : {k * step * d, 0x80000000ll - k * step * d, 0x80000000ll - k * step})
+        for (long long at : {k * step * d, 0x80000000ll - k * step * d, 0x100000000ll - k * step * d, 0x100000000ll - k * step})
           for (long long x = at - 2; x <= at + 2; ++x)
-            if (x >= 0 && x < 0x80000000ll && tile_div((unsigned)x, (unsigned)d, tile_by(d)) != (unsigned)(x / d)) {
+            if (x >= 0 && x < 0x100000000ll && tile_div((unsigned)x, (unsigned)d, tile_by(d)) != (unsigned)(x / d)) {
               std::fprintf(stderr, "%lld / %lld\n", x, d);
               return false;
             }

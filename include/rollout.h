@@ -425,7 +425,7 @@ int rollout_sample(const float *logits, int32_t rows, int32_t vocab, float tempe
  * sums, histograms and listed ids of the sweeps, about 96 KB per row) is a fixed device array inside the
  * library, one copy per GPU, kept until the process ends: rows <= ROLLOUT_SAMPLE_STATIC_MAX_ROWS,
  * else E_INVAL.  Every call on a GPU uses that one array, which keeps the last call's contents
- * (nothing in it has to start at zero: each call writes what it reads): calls that overlap on one
+ * (nothing in it has to start at zero: each call writes what it uses): calls that overlap on one
  * GPU - two streams, two threads - race; serialise them.  The array's address is looked up on
  * the first call on a device (rollout_init does it too); make that first call, or
  * rollout_sample_static_prepare(), outside graph capture.  Errors: E_INVAL, E_HIP;

@@ -36,7 +36,7 @@
 //       Workgroups past the last column block, if the launcher adds any, walk a later
 //       projection's weights into the memory-side cache (TouchRange, kernels_fast.h).
 //   gemm_tile_kernel    (more rows: larger decode steps, prefill, the teacher-forced
-//       pass, the experts' grouped projections): output tiles of 32 x 128 up to 128 x 320, both
+//       pass, the experts' grouped projections): output tiles of 32 x 64 up to 192 x 256, both
 //       operands copied straight from memory into a ring of LDS stages.
 #include <cstdio>
 

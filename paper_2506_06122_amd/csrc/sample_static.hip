@@ -80,8 +80,9 @@ int rollout_sample_static(const float* logits, int32_t rows, int32_t vocab, floa
   const int rc = scratch_for_current_device(&base);
   if (rc != ROLLOUT_OK) return rc;
   hipStream_t s = (hipStream_t)hip_stream;
-  // nothing in the array has to start at zero: every element a kernel reads was written earlier in
-  // the same call, by the sweeps before it
+  // nothing in the array has to start at zero: every element a kernel uses was written earlier in
+  // the same call, by the sweeps before it (places of the lists are loaded before their number is known: what
+  // was not written there is not used)
   SampleRows sr{};
   sr.logits = logits;
   sr.inv_temp_all = 1.0f / temperature;

@@ -19,7 +19,8 @@ struct TileShape {
 };
 #define TILE_NAME(a) \
   {"gemm_tile_kernel<" a ",0,false>", "gemm_tile_kernel<" a ",1,false>", "gemm_tile_kernel<" a ",3,false>", "gemm_tile_kernel<" a ",1,true>"}
-// x-macro: index, template arguments, workgroups per CU, model
+// x-macro: index, template arguments, workgroups per CU, model.  (192 x 256 keeps 192 accumulators a lane and spills some ten
+// registers, in its epilogue only.)
 #define TILE_SHAPES(X) \
   X(0, 1, 4, 2, 1, 1, 8, 2, 0.113f, 0.123f, 0.82f, 1.15f) /* 32 x 64 */       \
   X(1, 1, 4, 2, 2, 1, 6, 2, 0.185f, 0.191f, 0.91f, 1.49f) /* 32 x 128 */      \

@@ -40,15 +40,15 @@ def test_moe_routing_edges(n_experts, top_k, n_samples):
     eng.close()
 
 
-@pytest.mark.parametrize("rows", [112, 113, 184, 264, 600, 601])
+@pytest.mark.parametrize("rows", [56, 57, 80, 81, 264, 600])
 def test_moe_block_rows_lines(rows):
-    """Packed passes on either side of the lines between the experts' block sizes (28 and 150 picks per
-    expert: 16 experts, 4 picks a row) and between them, two sequences, against the oracle with the GPU's expert sets."""
+    """Packed passes on either side of the line between the experts' block sizes (32 and 64 rows: 14 picks per
+    expert, 16 experts, 4 picks a row) and beyond it, two sequences, against the oracle with the GPU's expert sets."""
     shape = workloads.SMALL_MOE_BF16
     w = scaled_weights(shape, seed=1, scale=1.5)
     model = oracle_model(shape, w)
     eng = make_engine(shape, w, max_context=700, max_batch_tokens=1024, flags=2)
-    cu = [0, rows - 61, rows]
+    cu = [0, rows - 21, rows]
     toks = np.random.default_rng(rows).integers(0, shape.vocab, rows).astype(np.int32)
     got = eng.rollout_logprobs(toks, cu, temperature=1.0)
     picks = eng.rollout_debug_routing(rows)
@@ -67,8 +67,9 @@ def test_moe_block_rows_lines(rows):
 @pytest.mark.parametrize("rows", [12, 13, 28, 29, 56, 57, 80, 81])
 def test_moe_tile_shape_lines(rows):
     """On either side of the lines between the experts' tile shapes (3, 7, 14 and 20 picks per expert: 16 experts, 4 picks a
-    row), with column counts that none of the shapes divides (gate/up 2 x 96, hidden 544)."""
-    shape = dataclasses.replace(workloads.SMALL_MOE_BF16, hidden=544, expert_ffn_dim=96)
+    row), with column counts that leave remainders in tiles of 128, 192 and 256 columns (gate/up 2 x 160, hidden 544; only the
+    latter in tiles of 64, which divide every gate/up projection)."""
+    shape = dataclasses.replace(workloads.SMALL_MOE_BF16, hidden=544, expert_ffn_dim=160)
     w = scaled_weights(shape, seed=1, scale=1.5)
     model = oracle_model(shape, w)
     eng = make_engine(shape, w, flags=2)
@@ -86,8 +87,9 @@ def test_moe_tile_shape_lines(rows):
 @pytest.mark.parametrize("rows,hidden,ffn", [(1, 512, 544), (17, 544, 1056), (40, 2080, 4000), (65, 544, 9000 // 32 * 32), (97, 1056, 2016),
                                              (129, 2080, 1056), (193, 544, 5024), (300, 1056, 544), (700, 2080, 2016), (1985, 544, 1056)])
 def test_tile_plans_remainders(rows, hidden, ffn):
-    """Packed passes whose rows, columns and k-tiles leave remainders in whatever tile shape and number of splits the
-    planner picks (17 and 33 k-tiles among them: odd, and no more than a few per split)."""
+    """Whole packed passes whose rows, columns and k-tiles leave remainders in the tile shapes and numbers of splits that the
+    planner picks for them (17 and 33 k-tiles among them: odd, and no more than a few per split).  These are tiles of up to 96 rows;
+    test_gpu_tile_shapes launches every shape by itself."""
     shape = dataclasses.replace(workloads.SMALL_BF16, n_layers=1, hidden=hidden, ffn_dim=ffn)
     w = scaled_weights(shape, seed=1, scale=0.7 if hidden > 1024 else 1.0)
     model = oracle_model(shape, w)

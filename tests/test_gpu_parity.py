@@ -227,7 +227,7 @@ def full_batch_case(shape, load, picks, max_batch_tokens=16384):
 
 def test_c2_full_batch_sampled_rows_and_row_invariance():
     """The headline job as it is launched in the benchmark - the full 1.5B-shaped model, all 32
-    prompts x 8 samples (256 live rows: packed prefill of about 9k prompt tokens, 64 x 128 tile
+    prompts x 8 samples (256 live rows: packed prefill of about 9k prompt tokens, tile
     projections, one-split attention); the oracle takes the shortest and the longest prompt."""
     load = workloads.load_c2()
     lens = np.diff(load.prompt_offsets)
@@ -513,8 +513,8 @@ def test_teacher_forced_logprob_pass_matches_oracle():
 
 def test_logprob_pass_at_config5_logits_shape():
     """The teacher-forced pass as config 5 runs it - the 7B matrix shapes, hidden 3584, the full
-    152064-entry vocabulary (1188 column parts per row in the fused log-sum-exp), chunks of more
-    than 512 packed rows (the 64 x 256 tile plan) - with the layer count cut to 2 so that the
+    152064-entry vocabulary (594 column parts per row in the fused log-sum-exp), chunks of more
+    than 512 packed rows (tiles of 128 rows for most projections) - with the layer count cut to 2 so that the
     fp64 oracle fits: 8 sequences of 1 to 320 tokens in three chunks of up to 640 rows."""
     import dataclasses
     shape = dataclasses.replace(workloads.C3_7B, n_layers=2, name="qwen2.5-7b-shape-2-layers")
@@ -533,7 +533,7 @@ def test_logprob_pass_at_config5_logits_shape():
           f"mean log-prob {want[want != 0].mean():.3f}")
     assert err <= TOL["bf16"]
     assert all(got[a] == 0.0 for a in cu[:-1])
-    # the same sequence alone (300 rows: the 64 x 128 tile plan and other split-K counts) agrees with
+    # the same sequence alone (300 rows: other tile shapes and split-K counts) agrees with
     # its rows inside the 620-row chunk far inside the tolerance: what differs is summation order
     eng = make_engine(shape, w, kv_pool_bytes=64 << 20, max_live_samples=8, max_context=512, max_batch_tokens=640)
     alone = eng.rollout_logprobs(toks[cu[3]:cu[4]], [0, lens[3]], temperature=1.0)

@@ -74,7 +74,7 @@ def test_wavefronts_without_ids(vocab, top_p):
 @pytest.mark.parametrize("rows,vocab", [(1, 151936), (40, 65536 + 3), (300, 28676)])
 def test_rows_from_flat_to_spread(rows, vocab):
     """The bin that ends the nucleus holds from all ids down to a few: on either side of what a workgroup can list,
-    with 38, 12 and 2 workgroups to a row."""
+    with 38, 12 and 2 workgroups to a row (the scratch of a call holds 512 rows, so 300 are one batch)."""
     import torch
     import paper_2506_06122_amd as R
     for scale in np.geomspace(0.01, 4.0, 9):

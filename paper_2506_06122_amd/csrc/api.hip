@@ -1339,6 +1339,7 @@ int rollout_debug_tile_product(const rollout_tile_product* p, void* hip_stream, 
     g.lse_tgt = p->target_value;
     g.lse_stride = p->m;
     const GemmPlan pl{1, p->shape, t.wn * t.nt, p->splits, ""};
+    (void)hipGetLastError();  // an older error of the thread is not this launch's
     *planes = launch_gemm_bf16(g, epi, pl, (hipStream_t)hip_stream);
     HIP_TRY(hipGetLastError());
   });

@@ -41,3 +41,14 @@ def test_policy_loss_after_a_stale_error():
     leave_an_error()
     got = R.rollout_policy_loss(*args)
     assert got[0] == want[0] and torch.equal(got[1], want[1]) and torch.equal(got[2], want[2])
+
+
+def test_tile_product_after_a_stale_error():
+    import torch
+    from paper_2506_06122_amd import binding as B
+    a, w = torch.ones(1, 1, 2, 32, dtype=torch.bfloat16, device="cuda"), torch.ones(16 * 32, dtype=torch.bfloat16, device="cuda")
+    out = torch.zeros(16, device="cuda")
+    torch.cuda.synchronize()
+    leave_an_error()
+    assert B.rollout_debug_tile_product(shape=0, epilogue=0, splits=1, m=1, n=16, k=32, a=a, w=w, out=out) == 1
+    assert out.tolist() == [64.0] * 16

@@ -306,6 +306,9 @@ void engine_init(rollout_ctx& c, const rollout_weights& w) {
     c.attn_part_o.alloc((size_t)c.attn_max_parts * 16 * 128);
     c.attn_part_ml.alloc((size_t)c.attn_max_parts * 32);
     c.ssq.alloc((size_t)(d / 16 + 1) * 256);
+    c.join_parts.alloc(kJoinTiles * kJoinParts * 256);
+    c.join_tickets.alloc(kJoinTiles * kTicketStride);
+    HIP_TRY(hipMemsetAsync(c.join_tickets.p, 0, c.join_tickets.n * sizeof(unsigned), c.stream));
     {
       const size_t parts = lse_parts_max(m.vocab);
       c.lse_max.alloc(parts * R);
@@ -768,11 +771,13 @@ static void forward_rows_tiled(rollout_ctx& c, int R, const SeqBatch* seqs) {
 // partial sums of squares, the consuming projection scales its output rows by
 // rsqrt(mean + eps).  The last down projection uses the final norm's gain, so the logits
 // projection reads its operand directly.
-static void stream_project(rollout_ctx& c, const DevBuf<uint16_t>& a, const void* w, int M, int N, int K,
-                           int epi, bool normalise_input, void* out, int ldo, long long out_lo_offset,
-                           const float* resid_gain, const TouchRange& touch = TouchRange{}) {
+static int stream_project(rollout_ctx& c, const DevBuf<uint16_t>& a, const void* w, int M, int N, int K,
+                          int epi, bool normalise_input, void* out, int ldo, long long out_lo_offset,
+                          const float* resid_gain, int max_splits = 1) {
   GemmArgs g{};
-  g.touch = touch;
+  g.join = c.join_parts.p;
+  g.tickets = c.join_tickets.p;
+  g.split_stride = (long long)M * N;
   g.a = a.p;
   g.a_lo = a.p + a.n / 2;
   g.w = w;
@@ -789,7 +794,7 @@ static void stream_project(rollout_ctx& c, const DevBuf<uint16_t>& a, const void
     g.rinv_ssq = c.ssq.p;
     g.rinv_partials = c.ssq_partials;
   }
-  const GemmPlan pl = gemm_plan_stream(M, N, K, epi, 1);
+  const GemmPlan pl = gemm_plan_stream(M, N, K, epi, max_splits);
   double bytes = 2.0 * N * K + 2.0 * 2 * M * K;  // weights once, both activation planes once
   if (epi == EPI_RESID) {
     g.x = c.x.p;
@@ -804,9 +809,10 @@ static void stream_project(rollout_ctx& c, const DevBuf<uint16_t>& a, const void
     bytes += 4.0 * M * N;
   }
   c.timer.begin(pl.name, bytes, 2.0 * M * N * K, c.stream);
-  launch_gemm_bf16(g, epi, pl, c.stream);
+  const int z = launch_gemm_bf16(g, epi, pl, c.stream);
   c.timer.end(c.stream);
   if (epi == EPI_RESID) c.ssq_partials = ceil_div(N >> 4, pl.nt);
+  return z;
 }
 
 static void forward_rows_decode(rollout_ctx& c, int R) {
@@ -833,19 +839,7 @@ static void forward_rows_decode(rollout_ctx& c, int R) {
   }
   for (int l = 0; l < m.n_layers; ++l) {
     LayerWeights& L = c.layers[l];
-    // The down projection has only hidden/16 workgroups, each streaming a deep slice: it is the
-    // one projection here that gains more from finding its weights in the memory-side cache
-    // (11 -> 7 us at config 2's shape) than walking them costs the launch that hosts the walk
-    // (the QKV projection, which leaves half the CUs idle: +1.6 us).  Hosted by the attention
-    // or O-projection launch, or done for the gate/up weights, the walk cost what it gained.
-    TouchRange down_touch;
-    if (L.w_down_p.n <= ((size_t)64 << 20)) {
-      down_touch.p = L.w_down_p.p;
-      down_touch.lines = (long long)(L.w_down_p.n / 128);
-      down_touch.wgs = 128;
-    }
-    stream_project(c, c.h_bf16, L.wqkv_p.p, R, c.qkv_dim, d, EPI_F32, true, c.partial.p, c.qkv_dim, 0, nullptr,
-                   down_touch);
+    const int z = stream_project(c, c.h_bf16, L.wqkv_p.p, R, c.qkv_dim, d, EPI_F32, true, c.partial.p, c.qkv_dim, 0, nullptr, 4);
 
     AttnArgs at{};
     at.out = c.attn_bf16.p;
@@ -862,7 +856,8 @@ static void forward_rows_decode(rollout_ctx& c, int R) {
     at.row_slot = c.row_slot.p;
     at.rows = R;
     at.qkv_raw = c.partial.p;
-    at.qkv_planes = 1;
+    at.qkv_planes = z;
+    at.qkv_plane_stride = (long long)R * c.qkv_dim;
     at.cos_sin = c.cos_sin.p;
     at.extra = QkvExtras{L.qkv_bias.p, L.q_gain.p, L.k_gain.p, m.rms_eps};
     plan_decode_attention(c, R, at);

@@ -39,33 +39,10 @@ __host__ __device__ inline long long plane_offset(int m, int k, int K) {
   return 2 * (long long)m * K + ((k >> 5) << 6) + (k & 31);
 }
 
-// A read-only range that spare workgroups of a launch walk, one dword per 128-byte line, while
-// the launch's own workgroups wait on memory latency: the projection that streams these weights
-// next then finds them in the memory-side cache (256 MiB) instead of HBM.
-struct TouchRange {
-  const void* p = nullptr;
-  long long lines = 0;  // 128-byte lines
-  int wgs = 0;          // workgroups that share the walk (0 = none)
-};
-#ifdef __HIPCC__
-// Workgroup `wg` of t.wgs reads one dword of every 128-byte line of its share of the range,
-// up to 8 loads in flight per lane; the values go nowhere.
-__device__ inline void touch_range(const TouchRange& t, int wg) {
-  const long long stride = (long long)t.wgs * blockDim.x;
-  const char* p = (const char*)t.p;
-  unsigned acc = 0;
-  long long i = (long long)wg * blockDim.x + threadIdx.x;
-  for (; i + 7 * stride < t.lines; i += 8 * stride) {
-    unsigned v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = *(const unsigned*)(p + (i + u * stride) * 128);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) acc ^= v[u];
-  }
-  for (; i < t.lines; i += stride) acc ^= *(const unsigned*)(p + i * 128);
-  asm volatile("" ::"v"(acc));  // keeps the loads
-}
-#endif
+// Scratch of the K splits that meet in their launch (join_splits): at most kJoinTiles joined tiles, each of at most
+// kJoinParts KiB, and as many tickets.
+constexpr int kTicketStride = 32;  // a ticket has its 128-byte line to itself
+constexpr size_t kJoinTiles = 512, kJoinParts = 16;
 
 struct GemmArgs {
   const void* a;     // activations as bf16 hi and lo parts: interleaved rows (plane_offset), or with `frag` two
@@ -78,13 +55,14 @@ struct GemmArgs {
   long long split_stride;  // floats between split planes (EPI_F32)
   int k_tiles_per_split;   // filled by the launcher
   TileGrid grid;           // tile kernel: the launch's blocks (launcher)
+  // EPI_RESID with K splits: they meet in the launch (join_splits)
+  float* join = nullptr;         // [joined tiles][splits] parts of a wavefront
+  unsigned* tickets = nullptr;   // one per joined tile, kTicketStride apart, 0 between launches
   // input normalisation (stream kernel)
   const float* rinv_ssq = nullptr;  // [rinv_partials][ssq_stride] partial sums of squares of the input rows
   int rinv_partials = 0;
   int ssq_stride = 0;
   float eps = 0.f;
-  TouchRange touch;   // stream kernel: walked by the workgroups with blockIdx.x >= touch_x0
-  int touch_x0 = 0;   // filled by the launcher
   // EPI_RESID
   float* x = nullptr;            // [M][N] residual stream, updated in place
   const float* gain = nullptr;   // [N] gain of the RMSNorm that follows
@@ -117,7 +95,7 @@ struct GemmArgs {
 inline int stream_rows(int hidden) { return hidden <= 2048 ? 32 : 16; }
 
 // How one projection is launched: kind 0 = gemm_stream_kernel, 1 = gemm_tile_kernel; shape = which of the
-// kernel's configurations, nt = column tiles per workgroup.
+// kernel's configurations, nt = column tiles per workgroup, splits = K splits (planes, or joined with EPI_RESID).
 struct GemmPlan {
   int kind, shape, nt, splits;
   const char* name;  // kernel name as a profiler shows it (without the argument list)

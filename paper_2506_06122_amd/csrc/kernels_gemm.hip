@@ -23,9 +23,9 @@
 //       partial accumulators meet in LDS.  Activations come straight from L2, stored in
 //       fragment order by their producers (frag_offset, kernels_fast.h) so that an operand
 //       fragment, like a weight fragment, is whole cache lines.  Narrow outputs (few column
-//       tiles) use wide workgroups (16 wavefronts) rather than split-K planes, so every output
-//       element is complete inside one workgroup and the epilogue can carry the neighbouring
-//       element-wise work:
+//       tiles) use wide workgroups (16 wavefronts) or, where K is deep, splits that join in the launch
+//       (join_splits), so every output element is complete inside one wavefront and the epilogue can
+//       carry the neighbouring element-wise work:
 //         - RMSNorm is split in two.  The producer of the residual stream (EPI_RESID) adds
 //           its result to x, stores x * gain as the next projection's operand and one
 //           partial sum of squares per (workgroup, row); the consumer sums those partials
@@ -33,8 +33,6 @@
 //           by rsqrt(mean + eps) - a row scale commutes with the projection.  No workgroup
 //           ever waits for another.
 //         - SwiGLU on column tiles of 8 gates and their 8 ups (EPI_SWIGLU_BF16).
-//       Workgroups past the last column block, if the launcher adds any, walk a later
-//       projection's weights into the memory-side cache (TouchRange, kernels_fast.h).
 //   gemm_tile_kernel    (more rows: larger decode steps, prefill, the teacher-forced
 //       pass, the experts' grouped projections): output tiles of 32 x 64 up to 192 x 256, both
 //       operands copied straight from memory into a ring of LDS stages.
@@ -87,6 +85,58 @@ __device__ inline void store_swiglu(const GemmArgs& p, bool valid, int m, int nt
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
+// K splits joined inside their launch.  Every split's wavefront stores its partial tile, takes a ticket, and the one that
+// takes the last ticket adds the others' parts to its own - in the order of the splits, so that the sum does not
+// depend on who came last - and goes on with the epilogue; the others are done.
+//   What makes the parts visible, since each XCD has its own L2: they are stored and loaded at the scope of the device (sc1:
+//   through to the memory side, and past the L2), and the ticket is drawn only when the stores have been acknowledged.
+//   No fence is needed, whose write-back of a whole L2 is what makes a join expensive: 96 column tiles x 8960, 6
+//   rows, two halves 7.8 us as two planes, 8.8 joined, where a second launch takes 4.
+//   The last one sets the ticket back to 0 for the next launch.
+constexpr int kDeviceScope = 16;  // cache policy of a buffer access: sc1
+// One wavefront's N quads per lane; `tile`: its index among the launch's joined tiles.  True in the last wavefront of
+// the `splits`, whose t then holds the sum.
+template <int N>
+__device__ __forceinline__ bool join_splits(const GemmArgs& p, int tile, int split, int splits, f32x4 (&t)[N], int lane) {
+  float* base = p.join + (long long)tile * splits * (N * 256);
+  const __amdgpu_buffer_rsrc_t parts = __builtin_amdgcn_make_buffer_rsrc(base, 0, splits * N * 1024, 0x00027000);
+#pragma unroll
+  for (int q = 0; q < N; ++q)
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, t[q]), parts, lane * 16, (split * N + q) * 1024, kDeviceScope);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  unsigned* ticket = p.tickets + tile * kTicketStride;
+  unsigned drawn = 0;
+  if (lane == 0) drawn = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  drawn = __builtin_amdgcn_readfirstlane(drawn);
+  if ((int)drawn != splits - 1) return false;
+  asm volatile("" ::: "memory");  // the loads stay behind the ticket
+  if (lane == 0) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+  for (int q = 0; q < N; ++q) t[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  constexpr int ZB = N >= 4 ? 2 : 4;  // splits whose loads are in flight together
+  for (int z = 0; z < splits; z += ZB) {
+    u32x4 u[ZB][N];
+#pragma unroll
+    for (int i = 0; i < ZB; ++i)
+#pragma unroll
+      for (int q = 0; q < N; ++q)
+        u[i][q] = __builtin_amdgcn_raw_buffer_load_b128(parts, lane * 16, (min(z + i, splits - 1) * N + q) * 1024, kDeviceScope);
+#pragma unroll
+    for (int i = 0; i < ZB; ++i)
+      if (z + i < splits) {
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+          const f32x4 v = __builtin_bit_cast(f32x4, u[i][q]);
+          t[q][0] += v[0];
+          t[q][1] += v[1];
+          t[q][2] += v[2];
+          t[q][3] += v[3];
+        }
+      }
+  }
+  return true;
+}
+
 // What bounds it: the weight stream from HBM (6.0 TB/s on this chip for one large read), plus about 3 us of
 // launch and latency, plus the activations, which every workgroup reads in full through its CU's
 // L2 path (about 60 GB/s): 64 K bytes of hi and lo parts beside 32 NT K bytes of weights.
@@ -96,16 +146,12 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 //   - Loads are not predicated: k-tiles, rows and columns past the end read the last valid one and are not
 //     multiplied or stored.
 // Measured (4 rows, weights from HBM): gate/up 7B shape (272 MB) 49.3 -> 43.1 us, down 7B (136 MB) 38.3 -> 26.8,
-// gate/up 1.5B (55 MB) 14.1 -> 12.7, down 1.5B (27.5 MB, only 96 column tiles) 13.1 -> 12.0.
+// gate/up 1.5B (55 MB) 14.1 -> 12.7.  Narrow outputs in K splits: beside gemm_plan_stream.
 template <int MT, int NT, int KU, int NW, bool KEEP, int EPI>
 __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
-  static_assert(NT <= 2 && MT <= 2 && NT <= NW, "one epilogue unit covers a workgroup's columns");
+  static_assert(MT <= 2 && MT <= NW && (NT % 2 == 0 || EPI != EPI_SWIGLU_BF16), "a wavefront finishes a row tile, SwiGLU in pairs of column tiles");
   __shared__ float4 red[NW * MT * NT * 64];
   __shared__ float rs_part[MT * NW * 64];
-  if (p.touch.wgs > 0 && (int)blockIdx.x >= p.touch_x0) {  // uniform over the workgroup
-    if (blockIdx.z == 0) touch_range(p.touch, blockIdx.x - p.touch_x0);
-    return;
-  }
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, g = lane >> 4;
   const int n_tiles = p.N >> 4, k_tiles = p.K >> 5;
@@ -242,7 +288,9 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
   __syncthreads();
   if (wave >= MT) return;
   const bool valid = m < p.M;
-  f32x4 t[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+  f32x4 t[NT];
+#pragma unroll
+  for (int q = 0; q < NT; ++q) t[q] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int q = 0; q < NT; ++q)
 #pragma unroll
@@ -253,6 +301,9 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
       t[q][2] += v.z;
       t[q][3] += v.w;
     }
+  if constexpr (EPI == EPI_RESID) {
+    if (gridDim.y > 1 && !join_splits(p, (blockIdx.z * MT + own) * gridDim.x + blockIdx.x, blockIdx.y, gridDim.y, t, lane)) return;
+  }
   if (RS > 0 && p.rinv_ssq) {
     // second half of the RMSNorm of this projection's input: scale row m by
     // rsqrt(mean(x^2) + eps); the 4 lanes of a row share the partial sums
@@ -292,8 +343,10 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
     ss += __shfl_xor(ss, 16, WAVE);
     ss += __shfl_xor(ss, 32, WAVE);
     if (g == 0 && valid) p.ssq_out[(long long)blockIdx.x * p.ssq_stride + m] = ss;
-  } else if (EPI == EPI_SWIGLU_BF16) {
-    store_swiglu<false>(p, valid, m, nt0, t[0], t[1], g, NT == 2 && nt0 + 1 < n_tiles);
+  } else if constexpr (EPI == EPI_SWIGLU_BF16) {
+#pragma unroll
+    for (int q = 0; q < NT; q += 2)
+      if (nt0 + q < n_tiles) store_swiglu<false>(p, valid, m, nt0 + q, t[q], t[q + 1], g, nt0 + q + 1 < n_tiles);
   } else if (valid) {
 #pragma unroll
     for (int q = 0; q < NT; ++q)
@@ -588,12 +641,16 @@ __global__ __launch_bounds__(WM* WN* KG * 64, 2) void gemm_tile_kernel(GemmArgs 
 // ------------------------------------------------------------------------------------------
 // The stream kernel's shapes, with the epilogues each is planned with.
 //     MT NT KU NW KEEP
-#define STREAM_SHAPES(X)                                                                  \
-  X(0, 1, 2, 2, 8, false, EPI_F32, EPI_SWIGLU_BF16)  /* up to 16 rows, wide outputs */     \
-  X(1, 1, 2, 2, 16, false, EPI_F32, EPI_F32)         /* narrow, at least 192 tiles */      \
-  X(2, 1, 1, 3, 16, false, EPI_F32, EPI_RESID)       /* narrow */                          \
-  X(3, 2, 2, 2, 4, false, EPI_F32, EPI_SWIGLU_BF16)  /* up to 32 rows, from 192 tiles on */ \
-  X(4, 1, 1, 3, 16, true, EPI_F32, EPI_RESID)        /* narrow, a row block per 16 rows */
+#define STREAM_SHAPES(X)                                                                                     \
+  X(0, 1, 2, 2, 8, false, EPI_F32, EPI_SWIGLU_BF16)  /* up to 16 rows, wide outputs */                       \
+  X(1, 1, 4, 1, 8, false, EPI_F32, EPI_F32)          /* the same from 9 rows on, without SwiGLU */           \
+  X(2, 1, 1, 3, 16, false, EPI_F32, EPI_RESID)       /* narrow outputs in one piece */                       \
+  X(3, 1, 2, 3, 8, false, EPI_F32, EPI_RESID)        /* narrow outputs in K splits: planes, or joined */     \
+  X(4, 1, 4, 2, 8, false, EPI_RESID, EPI_RESID)      /* the same, deep and wider */                          \
+  X(5, 2, 2, 2, 4, false, EPI_F32, EPI_SWIGLU_BF16)  /* up to 32 rows, wide outputs */                       \
+  X(6, 2, 4, 1, 4, false, EPI_F32, EPI_F32)          /* the logits */                                        \
+  X(7, 1, 1, 3, 16, true, EPI_F32, EPI_RESID)        /* narrow outputs in one piece, a row block per 16 rows */ \
+  X(8, 2, 2, 2, 8, false, EPI_F32, EPI_RESID)        /* narrow outputs in K splits */
 struct StreamShape {
   int mt, nt;
   const char* name[3];  // by epilogue: F32, SWIGLU, RESID
@@ -673,28 +730,53 @@ static int launch_tile(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s) {
   return a.grid.nz;
 }
 
-// Up to 16 rows: wide outputs with two column tiles and 8 wavefronts per workgroup, narrow ones with 16
-// wavefronts, so that the K range, not the column count, fills the CUs - one column tile, or two where that still
-// leaves more than a hundred workgroups (the fused QKV projection of 7B-class models: it halves the
-// activation re-reads; the residual epilogue's projections run better with one).
-// 17 to 32 rows (the callers ask for them up to stream_rows): the wider outputs with two row tiles per workgroup, so
-// that the weights are read once; the narrow ones as two workgroups of 16 rows, the second one's weights from L2 (KEEP:
-// their loads leave them there), twice the workgroups on CUs that are idle otherwise.  Decode step of the 1.5B
-// shape at 24 rows: 1.74 ms; two row tiles everywhere 1.80, non-temporal weights in both row blocks 1.87.
+// Wide outputs (SwiGLU, the logits): no split, workgroups enough without.  Two column tiles to a workgroup; the logits
+// four as soon as the activations weigh as much as the weights (a fragment of up to 8 rows is half as many lines):
+// 151936 x 1536, 6 rows 68.6 / 72.4 us with two / four, 16 rows 82.8 / 77.7, 32 rows 112 / 95.
+//
+// Narrow outputs are bound by what one CU can fetch, about 65 GB/s: (64 MT + 32 NT) K bytes per workgroup, and as many
+// workgroups as there are column blocks.  So the K range is cut until the CUs are full: where the splits' planes are
+// summed by the next launch anyway (max_splits > 1: attention sums those of q, k, v), or joined in the launch
+// (EPI_RESID), which costs about 2 us (3 with four column tiles).  us with weights from HBM, 6 / 16 / 32 rows, in one
+// piece and in splits:
+//   1536 x 8960    13.3 / 16.8 / 16.3  ->   9.3 / 10.0 / 11.7  (two column tiles, 5 splits)
+//   1536 x 1536     5.1 /  5.8 /  6.0  ->   5.6 /  6.1 /  6.7  (4 splits): left in one piece
+//   2048 x 1536     5.2 /  5.7 /  5.9  ->   4.2 /  4.3 /  5.3  (4 planes)
+//   3584 x 18944   27.4 / 35.0 (4 / 12 rows) -> 26.3 / 27.5 with four column tiles and 4 splits, 25.5 / 29.0 with two and 2
+//   3584 x 3584     8.0 /  9.6 (4 / 12 rows) ->  8.6 /  9.3: left in one piece
+//   4608 x 3584    10.1 / 11.8 (4 / 12 rows, 16 wavefronts) -> 9.8 / 10.6 (3 planes)
 GemmPlan gemm_plan_stream(int M, int N, int K, int epi, int max_splits) {
   GemmPlan pl{};
-  const int n_tiles = N >> 4, k_tiles = K >> 5;
-  const bool wide = n_tiles / 2 >= 512 || epi == EPI_SWIGLU_BF16, wider = wide || (epi == EPI_F32 && n_tiles >= 192);
+  const int n_tiles = N >> 4, k_tiles = K >> 5, mt = M > 16 ? 2 : 1;
   pl.kind = 0;
-  if (M > 16) pl.shape = wider ? 3 : 4;
-  else pl.shape = wide ? 0 : wider ? 1 : 2;
-  pl.nt = kStreamShapes[pl.shape].nt;
   pl.splits = 1;
-  if (epi == EPI_F32 && !wide && max_splits > 1) {
-    int z = (256 + n_tiles - 1) / n_tiles;
-    z = std::min(z, std::max(1, k_tiles / 64));
-    pl.splits = std::max(1, std::min({z, max_splits, 4}));
+  if (epi == EPI_SWIGLU_BF16) {
+    pl.shape = mt == 2 ? 5 : 0;
+  } else if (epi == EPI_F32 && n_tiles >= 1024) {
+    pl.shape = mt == 2 ? 6 : M > 8 ? 1 : 0;
+  } else if (epi == EPI_F32) {
+    const int blocks = ceil_div(n_tiles, 2);
+    pl.splits = std::max(1, std::min({ceil_div(384, blocks), max_splits, 4, k_tiles / 8}));
+    pl.shape = pl.splits > 1 ? (mt == 2 ? 8 : 3) : mt == 2 ? 7 : 2;
+  } else {
+    // us of one CU's fetches with nt column tiles per workgroup and z splits
+    auto fetch = [&](int nt, int z, int rows64) {
+      const double us = (double)K / z * (rows64 * 64 + 32 * nt) / 65e3;
+      return us * std::max(1.0, (double)ceil_div(n_tiles, nt) * z / 256) + (z > 1 ? 1.0 + 0.5 * nt : 0.0);
+    };
+    auto splits = [&](int nt) { return std::max(1, std::min({256 / ceil_div(n_tiles, nt), nt == 2 ? 5 : 4, k_tiles / 8})); };
+    const int z2 = splits(2), z4 = splits(4);
+    const double one = fetch(1, 1, 1), two = fetch(2, z2, mt), four = fetch(4, z4, mt);
+    pl.shape = mt == 2 ? 7 : 2;
+    if (z2 > 1 && two < one && (mt == 2 || two <= four)) {
+      pl.shape = mt == 2 ? 8 : 3;
+      pl.splits = z2;
+    } else if (z4 > 1 && four < one && mt == 1) {
+      pl.shape = 4;
+      pl.splits = z4;
+    }
   }
+  pl.nt = kStreamShapes[pl.shape].nt;
   pl.name = kStreamShapes[pl.shape].name[epi];
   return pl;
 }
@@ -706,14 +788,10 @@ GemmPlan gemm_plan(int M, int N, int K, int epi, int max_splits) {
 static int launch_stream(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s) {
   const StreamShape& t = kStreamShapes[pl.shape];
   const int n_tiles = a.N >> 4, k_tiles = a.K >> 5;
-  a.k_tiles_per_split = ceil_div(k_tiles, epi == EPI_F32 ? pl.splits : 1);
-  dim3 grid(ceil_div(n_tiles, t.nt), ceil_div(k_tiles, a.k_tiles_per_split), ceil_div(a.M, 16 * t.mt));
-  if (a.touch.wgs > 0 && grid.y == 1) {
-    a.touch_x0 = (int)grid.x;
-    grid.x += (unsigned)a.touch.wgs;
-  } else {
-    a.touch.wgs = 0;
-  }
+  a.k_tiles_per_split = ceil_div(k_tiles, pl.splits);
+  const dim3 grid(ceil_div(n_tiles, t.nt), ceil_div(k_tiles, a.k_tiles_per_split), ceil_div(a.M, 16 * t.mt));
+  if (epi == EPI_RESID && grid.y > 1 && (!a.join || (size_t)grid.x * grid.z * t.mt > kJoinTiles || grid.y * t.nt > kJoinParts))
+    throw HipError(hipErrorInvalidValue, "joined projection", __FILE__, __LINE__);
   switch (pl.shape) {
 #define X(id, mt, nt, ku, nw, keep, e0, e1)                                                        \
   case id:                                                                                         \

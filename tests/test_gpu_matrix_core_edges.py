@@ -138,6 +138,40 @@ def test_streamed_rows_lines(rows, hidden):
     eng.close()
 
 
+@pytest.mark.parametrize("rows,hidden,ffn", [(1, 512, 8960), (9, 544, 9024), (16, 1056, 4992), (17, 544, 9024), (32, 1056, 6016),
+                                             (8, 3072, 5024), (16, 3104, 8032)])
+def test_streamed_splits_join(rows, hidden, ffn):
+    """Down projections deep enough for K splits that join inside their launch: two and four column tiles to a workgroup, one
+    and two row tiles, column blocks and splits with remainders.  Several steps and layers, so that every ticket is drawn
+    again; the same job a second time gives the same bits, whichever split came last."""
+    shape = dataclasses.replace(workloads.SMALL_BF16, n_layers=2, hidden=hidden, ffn_dim=ffn)
+    w = scaled_weights(shape, seed=1, scale=0.7 if hidden > 1024 else 1.0)
+    model = oracle_model(shape, w)
+    toks, offs = workloads.make_prompts(1, 20, 20, shape.vocab, seed=4)
+    forced = np.random.default_rng(6).integers(0, shape.vocab, (rows, 4)).astype(np.int32)
+    runs = []
+    for _ in range(2):
+        eng = make_engine(shape, w, max_live_samples=40)
+        eng.rollout_prefill(toks, offs, rows, np.full(rows, 4, np.int32), forced_first=forced[:, 0])
+        got = []
+        for t in range(1, 4):
+            eng.rollout_decode_step(forced_tokens=forced[:, t])
+            got.append(eng.rollout_debug_logits())
+        runs.append(got)
+        eng.close()
+    fwd = T.KVForward(model)
+    prefix = fwd.new_cache()
+    fwd.extend([prefix], [toks])
+    caches = [prefix.fork() for _ in range(rows)]
+    worst = 0.0
+    for t in range(1, 4):
+        ref = fwd.extend(caches, [[int(forced[i, t - 1])] for i in range(rows)])
+        worst = max(worst, max(float(np.max(np.abs(runs[0][t - 1][k] - ref[k][0]))) for k in range(rows)))
+    print(f"{rows} rows, hidden {hidden}, ffn {ffn}: max |dlogits| = {worst:.3e}")
+    assert worst <= TOL
+    assert all(np.array_equal(a, b) for a, b in zip(*runs))
+
+
 @pytest.mark.parametrize("rows", [7, 20, 43, 127, 129])
 def test_attention_splits_fill_the_chip_once(rows):
     """Row counts that do not divide the 256 CUs, with contexts long enough to be cut: 16, 6, 2 and 1 splits per

@@ -37,6 +37,7 @@
 //       pass, the experts' grouped projections): output tiles of 32 x 64 up to 192 x 256, both
 //       operands copied straight from memory into a ring of LDS stages.
 #include <cstdio>
+#include <utility>
 
 #include "kernels_fast.h"
 #include "tile_plan.h"
@@ -360,9 +361,14 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
 // alternate k-tiles and join their sums through LDS at the end (twice the wavefronts on a tile
 // whose size the chip's 256 CUs ask for).
 //
-// What bounds it.  Long launches with many rows: the power limit.  The matrix units are busy 71 % of the cycles at a
-// clock that falls to 1.8 GHz; products from registers alone, on the same data, run at 2.0 PFLOP/s (2.4 on zeros), so
-// what a tile shape costs in data movement is what it loses.  A few hundred rows: wavefronts that have their SIMD
+// What bounds it.  Long launches with many rows: the power limit.  On zeros the 192 x 256 tiles issue 1.9 PFLOP/s, on
+// real data 1.4 to 1.6 (box to box), whatever the tile's shape; so what counts is what a product costs beside itself:
+//   - Of each product the lo and the hi part run one after the other, on the same sums: from registers alone 2.0 -> 2.2
+//     PFLOP/s, here 1 to 2.5 %.  (32 x 32 products: 1.75 from registers.)
+//   - Wide wavefronts: 96 x 128 of a 192 x 256 tile in each of four wavefronts, with a SIMD's registers to itself, instead of 48 x 128
+//     in eight reads 20 KB from LDS for 96 products instead of 28.  10568 rows x 3584 x 18944 2.35 -> 2.23 ms (128 x 320 and
+//     160 x 256), 2600 x 3584 x 18944 577 -> 540 us, 4600 x 2048 x 1536 53 -> 48; 10568 x 37888 x 3584 4.02 -> 3.94 ms.
+// A few hundred rows: wavefronts that have their SIMD
 // almost to themselves, where every wait shows.  Decode steps: the weights, and besides them, per k-tile, 128 BM +
 // 64 BN bytes through the CU for BM BN / 256 tiles, so wide tiles win, and one round of workgroups that fills all CUs wins
 // over a second, mostly empty one: the plan below weighs the two.
@@ -403,9 +409,16 @@ __device__ __forceinline__ void wait_and_barrier() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
+// f(0), ..., f(N - 1) with the index as a constant
+template <class F, int... I>
+__device__ __forceinline__ void unrolled(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+
 // GATHER: the rows of `a` come through row_map (experts' grouped projections)
 template <int WM, int WN, int MT, int NT, int KG, int S, int EPI, bool GATHER>
-__global__ __launch_bounds__(WM* WN* KG * 64, 2) void gemm_tile_kernel(GemmArgs p) {
+__global__ __launch_bounds__(WM* WN* KG * 64, wide_wavefronts(WM, WN, MT, NT, KG, S) ? 1 : 2) void gemm_tile_kernel(GemmArgs p) {
+  constexpr bool WIDE = wide_wavefronts(WM, WN, MT, NT, KG, S);
   constexpr int NW = WM * WN * KG, BM = WM * MT * 16, BN = WN * NT * 16;
   constexpr int UA = BM / 8, UW = BN / 16, U1 = UA + UW;  // load instructions per k-tile
   constexpr int L = (U1 * KG + NW - 1) / NW;              // per wavefront and stage
@@ -465,7 +478,7 @@ __global__ __launch_bounds__(WM* WN* KG * 64, 2) void gemm_tile_kernel(GemmArgs 
     }
   }
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)lds;
-  auto issue = [&](int s, int kt, int buf) {  // load s of the stage that starts at k-tile kt
+  auto issue = [&](int s, int kt, int buf) __attribute__((always_inline)) {  // load s of the stage that starts at k-tile kt
     const unsigned to = __builtin_amdgcn_readfirstlane(lds0 + buf * (U1 * KG * 1024) + dst[s]);
     const unsigned move = kt + KG + k_of[s] < kt_end ? KG * step[s] : 0u;
     if (GATHER && step[s] == 128) {
@@ -492,41 +505,53 @@ __global__ __launch_bounds__(WM* WN* KG * 64, 2) void gemm_tile_kernel(GemmArgs 
   const int w_at = kg * U1 * 1024 + (UA + wn * NT) * 1024 + lane * 16;
   u32x4 w[2][NT], a[2][MT][2];
   constexpr int NR = NT + 2 * MT, NM = MT * NT * 2, NS = NR + L;
-  auto read = [&](int x, const char* b, int f) {  // fragment f of a stage, in the order in which they are multiplied
+  auto read = [&](int x, const char* b, int f) __attribute__((always_inline)) {  // fragment f of a stage, in the order in which they are multiplied
     if (f < 2) a[x][0][1 - f] = *(const u32x4*)(b + (f ? a_hi : a_lo));
     else if (f < 2 + NT) w[x][f - 2] = *(const u32x4*)(b + w_at + (f - 2) * 1024);
     else a[x][(f - NT) >> 1][1 - ((f - NT) & 1)] = *(const u32x4*)(b + ((f - NT) & 1 ? a_hi : a_lo) + ((f - NT) >> 1) * 2048);
   };
-  auto mul = [&](int x, int q) {  // row tile by row tile, lo part first, then hi
-    const int i = q / (2 * NT), plane = 1 - q / NT % 2, j = q % NT;
+  auto mul = [&](int x, int q) __attribute__((always_inline)) {  // row tile by row tile; of each product the lo part, then the hi part
+    const int i = q / (2 * NT), plane = 1 - q % 2, j = q / 2 % NT;
     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[x][j]),
                                                         __builtin_bit_cast(bf16x8, a[x][i][plane]), acc[i][j], 0, 0, 0);
   };
+  // With a SIMD's registers to itself a wavefront keeps its sums in the accumulation registers.  Left alone, the compiler
+  // moves them back and forth between the stages (90 moves each way in two stages of 96 products): it has to
+  // have them there at the end of each.
+  auto keep_sums = [&]() __attribute__((always_inline)) {
+    if constexpr (WIDE) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) asm volatile("" : "+a"(acc[i][j]));
+    }
+  };
+  keep_sums();
   wait_and_barrier<(S - 1) * L>();
 #pragma unroll
   for (int f = 0; f < NR; ++f) read(0, lds, f);
   int buf = 0;
-  auto stage = [&](int x, int kt) {
+  auto stage = [&](int x, int kt) __attribute__((always_inline)) {
     wait_and_barrier<(S - 2) * L>();
     const int next = buf == S - 1 ? 0 : buf + 1;
     const char* b = lds + next * (U1 * KG * 1024);
-#pragma unroll
-    for (int q = 0; q < NM; ++q) {
+    unrolled([&](auto qc) __attribute__((always_inline)) {
+      constexpr int q = decltype(qc)::value, u0 = (q * NS + NM - 1) / NM, u1 = ((q + 1) * NS + NM - 1) / NM;
       mul(x, q);
 #pragma unroll
-      for (int u = 0; u < NS; ++u)
-        if (u * NM / NS == q) {
-          if (u < NR) read(x ^ 1, b, u);
-          else issue(u - NR, kt + S * KG, buf);
-        }
+      for (int u = u0; u < u1; ++u) {
+        if (u < NR) read(x ^ 1, b, u);
+        else issue(u - NR, kt + S * KG, buf);
+      }
       __builtin_amdgcn_sched_barrier(0);
-    }
+    }, std::make_integer_sequence<int, NM>{});
+    keep_sums();
     buf = next;
   };
-  auto last = [&](int x, int kt) {
+  auto last = [&](int x, int kt) __attribute__((always_inline)) {
     if (KG > 1 && kt + kg >= kt_end) return;  // an odd last k-tile belongs to the first group
-#pragma unroll
-    for (int q = 0; q < NM; ++q) mul(x, q);
+    unrolled([&](auto qc) __attribute__((always_inline)) { mul(x, decltype(qc)::value); }, std::make_integer_sequence<int, NM>{});
+    keep_sums();
   };
   int kt = kt_begin, left = (kt_end - kt_begin + KG - 1) / KG;
   for (; left > 2; left -= 2) {

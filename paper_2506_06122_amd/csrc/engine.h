@@ -220,7 +220,7 @@ struct rollout_ctx : HostState {
   DevBuf<int> chunk_ints;        // [3 r_max]: rows whose logits are wanted, then (source, destination) page pairs
   double chunk_kv_tokens = 0, chunk_attn_flops = 0;  // the chunk's share of the attention, for the timing records
   DevBuf<float> join_parts;     // parts of K splits that meet in their launch, and their tickets
-  DevBuf<unsigned> join_tickets;
+  DevBuf<unsigned> join_tickets, attn_tickets;
   DevBuf<float> ssq;            // [partials][256] partial sums of squares of the residual rows (decode path)
   int ssq_partials = 0;
   bool h_is_final = false;      // the last forward left x * final gain in h_bf16 (decode path)

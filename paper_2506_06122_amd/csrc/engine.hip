@@ -305,6 +305,8 @@ void engine_init(rollout_ctx& c, const rollout_weights& w) {
     c.row_t0.alloc(r.max_live_samples);
     c.attn_part_o.alloc((size_t)c.attn_max_parts * 16 * 128);
     c.attn_part_ml.alloc((size_t)c.attn_max_parts * 32);
+    c.attn_tickets.alloc((size_t)r.max_live_samples * m.n_kv_heads * kTicketStride);
+    HIP_TRY(hipMemsetAsync(c.attn_tickets.p, 0, c.attn_tickets.n * sizeof(unsigned), c.stream));
     c.ssq.alloc((size_t)(d / 16 + 1) * 256);
     c.join_parts.alloc(kJoinTiles * kJoinParts * 256);
     c.join_tickets.alloc(kJoinTiles * kTicketStride);
@@ -486,8 +488,7 @@ static void embed_and_norm(rollout_ctx& c, int R) {
   c.timer.end(c.stream);
 }
 
-// The second launch of a decode attention whose rows have several partial results: joins the
-// slots of every (row, KV head).  Timed under its own name; bytes = the slots read (output
+// The second launch of a decode attention with shared prompts: joins the slots of every (row, KV head).  Timed under its own name; bytes = the slots read (output
 // fragments, maxima and sums) and the rows written as two bf16 planes.
 static void merge_attention_slots(rollout_ctx& c, const AttnArgs& at, int rows) {
   const int slots = at.n_slots ? at.n_slots : at.n_splits;
@@ -498,9 +499,10 @@ static void merge_attention_slots(rollout_ctx& c, const AttnArgs& at, int rows) 
 }
 
 // How the cached positions of a decode step's `rows` rows are cut: wavefronts per workgroup and KV splits
-// per (row, KV head), at most the 16 the merge kernel takes.  A round of a workgroup (32 positions per
-// wavefront) takes about 1.5 us, a merge launch as much as three rounds, so a split has to save more
-// rounds than that.  A workgroup of eight wavefronts has its CU to itself, so the splits stop where the
+// per (row, KV head), at most the 16 whose results are joined at once.  A round of a workgroup (32 positions per
+// wavefront) takes about 1.5 us, the join of the splits about as much, and a split whose rounds are uneven more, so it
+// has to save more than two rounds (saved rounds 2: 16 rows of the 7B shape 3.297 ms a step in one piece or cut, 20 of the 1.5B
+// shape 1.530; 3: 3.351 -> 3.298 and 1.588 -> 1.538).  While a second launch of 4.9 us joined them it was three.  A workgroup of eight wavefronts has its CU to itself, so the splits stop where the
 // workgroups still fit the 256 CUs at once: with one split more a second, nearly empty set of them
 // doubled the launch (1.5B shape, 20 rows at 16000 positions: 2.98 ms a step, 2.39 now).
 static void plan_decode_attention(const rollout_ctx& c, int rows, AttnArgs& at) {
@@ -509,7 +511,7 @@ static void plan_decode_attention(const rollout_ctx& c, int rows, AttnArgs& at) 
   const int round = at.wide ? 256 : 128;
   const int most = std::max(1, std::min({256 / base, ceil_div(c.decode_max_ctx, 256), c.attn_max_parts / base, 16}));
   const int whole = ceil_div(c.decode_max_ctx, round), cut = ceil_div(c.decode_max_ctx, round * most);
-  const int n = whole - cut > 3 ? most : 1;
+  const int n = whole - cut > 2 ? most : 1;
   at.split_tokens = ceil_div(ceil_div(c.decode_max_ctx, n), 128) * 128;
   at.n_splits = ceil_div(c.decode_max_ctx, at.split_tokens);
 }
@@ -729,11 +731,11 @@ static void forward_rows_tiled(rollout_ctx& c, int R, const SeqBatch* seqs) {
         c.timer.end(s);
         merge_attention_slots(c, at, Bd);
       } else {
+        at.tickets = c.attn_tickets.p;
         plan_decode_attention(c, Bd, at);
         c.timer.begin(decode_attention_name(at), kv_bytes + qo_bytes, c.attn_flops_this_call, s);
         launch_attention_decode_fused(at, s);
         c.timer.end(s);
-        if (at.n_splits > 1) merge_attention_slots(c, at, Bd);
       }
     }
 
@@ -861,6 +863,7 @@ static void forward_rows_decode(rollout_ctx& c, int R) {
     at.cos_sin = c.cos_sin.p;
     at.extra = QkvExtras{L.qkv_bias.p, L.q_gain.p, L.k_gain.p, m.rms_eps};
     plan_decode_attention(c, R, at);
+    at.tickets = c.attn_tickets.p;
     at.part_o = c.attn_part_o.p;
     at.part_ml = c.attn_part_ml.p;
     // every cached key and value once (a shared prompt once for all its samples), q in, out
@@ -869,7 +872,6 @@ static void forward_rows_decode(rollout_ctx& c, int R) {
                   c.attn_flops_this_call, s);
     launch_attention_decode_fused(at, s);
     c.timer.end(s);
-    if (at.n_splits > 1) merge_attention_slots(c, at, R);
 
     stream_project(c, c.attn_bf16, L.wo_p.p, R, d, c.q_dim, EPI_RESID, false, nullptr, d, 0, L.norm2.p);
     stream_project(c, c.h_bf16, L.w_gate_up_p.p, R, 2 * f, d, EPI_SWIGLU_BF16, true, c.act_bf16.p, f,

@@ -16,7 +16,7 @@
 //   decode  : one workgroup per (KV split, KV head, sample); columns = the G query heads;
 //             the rotary embedding of the new query and key and the KV-page write ride in
 //             the prologue; its 4 or 8 wavefronts interleave over the split's 32-position groups
-//             and merge through LDS; several splits per sample merge in a second small kernel.
+//             and merge through LDS; of several splits per sample the last to finish joins the results.
 //   decode, shared prompts (optional): in the same launch, workgroups of (split, KV head, up
 //             to 4 samples of one prompt) take the prompt's shared pages with the members'
 //             query heads as columns, and the per-sample workgroups start after those pages.
@@ -27,6 +27,7 @@
 
 typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 union Frag {
   uint4 u;
   f16x8 v;
@@ -193,7 +194,7 @@ __device__ inline long long out_offset(const AttnArgs& a, int b, int k) {
 // t0..pos-1 from the pages (t0 = 0 unless the sample's prompt is attended by its group, below).
 // The new position itself is attended from LDS as a one-token group, so nothing written in
 // this launch is read back from memory.  With several partial results per (sample, KV head)
-// they go to attn_merge_fused_kernel.
+// the split that finishes last joins them (with shared prompts attn_merge_fused_kernel does).
 // EXTRA: the model adds a bias to q, k, v and / or normalises q and k heads (a.extra).
 struct DecodeSmem {
   uint16_t* q;   // [2][q_cols][Q_LD] hi parts, lo parts
@@ -490,7 +491,11 @@ __device__ __forceinline__ void decode_own_range(const AttnArgs& a, const Decode
 
   merge_wavefronts<NW>(sm, 0, m, l, o, wave, c, g, G);
   const int n_slots = a.n_slots ? a.n_slots : a.n_splits;
-  const long long part = ((long long)b * n_kv + kvh) * n_slots + a.slot0 + split;
+  const long long slots0 = ((long long)b * n_kv + kvh) * n_slots;
+  // the slots of this (sample, KV head); stored and loaded at the scope of the device where they meet in this launch
+  const __amdgpu_buffer_rsrc_t part_o = __builtin_amdgcn_make_buffer_rsrc(a.part_o + slots0 * (16 * DH), 0, n_slots * 16 * DH * 4, 0x00027000);
+  const __amdgpu_buffer_rsrc_t part_ml = __builtin_amdgcn_make_buffer_rsrc(a.part_ml + slots0 * 32, 0, n_slots * 32 * 4, 0x00027000);
+  const int slot_here = a.slot0 + split;
   for (int e = 4 * tid; e < G * DH; e += 256 * NW) {
     const float4 acc = merged_out<NW>(sm, e);
     if (direct) {
@@ -498,12 +503,68 @@ __device__ __forceinline__ void decode_own_range(const AttnArgs& a, const Decode
       store4_split(a.out + out_offset(a, b, kvh * G * DH + e), a.out_lo_offset, quotient(acc.x, sum, r),
                    quotient(acc.y, sum, r), quotient(acc.z, sum, r), quotient(acc.w, sum, r));
     } else {
-      *(float4*)(a.part_o + part * (16 * DH) + e) = acc;
+      __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(acc.x), __float_as_uint(acc.y), __float_as_uint(acc.z), __float_as_uint(acc.w)},
+                                             part_o, e * 4, slot_here * (16 * DH * 4), kDeviceScope);
     }
   }
-  if (!direct && tid < 16) {
-    a.part_ml[part * 32 + tid] = merged_max<NW>(sm, tid);
-    a.part_ml[part * 32 + 16 + tid] = merged_sum<NW>(sm, tid);
+  if (direct) return;
+  if (tid < 16) {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(merged_max<NW>(sm, tid)), part_ml, tid * 4, slot_here * 128, kDeviceScope);
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(merged_sum<NW>(sm, tid)), part_ml, 64 + tid * 4, slot_here * 128, kDeviceScope);
+  }
+  if (!a.tickets) return;  // (uniform) a second launch joins the slots
+  // The split that draws the last ticket joins the slots, in their order; as the joined projections do (join_splits):
+  // the parts are there when their ticket is drawn, and no fence is needed.
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) {
+    unsigned* ticket = a.tickets + (b * n_kv + kvh) * kTicketStride;
+    const unsigned drawn = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool last = (int)drawn == used - 1;
+    if (last) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sm.m[0] = last ? 1.f : 0.f;
+  }
+  __syncthreads();
+  if (sm.m[0] == 0.f) return;
+  for (int e = 4 * tid; e < G * DH; e += 256 * NW) {
+    const int col = e >> 7;
+    float ms[16], ls[16];
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+      const int at = min(s, used - 1) * 128;
+      ms[s] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(part_ml, col * 4, at, kDeviceScope));
+      ls[s] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(part_ml, 64 + col * 4, at, kDeviceScope));
+    }
+    u32x4 v[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) v[s] = __builtin_amdgcn_raw_buffer_load_b128(part_o, e * 4, min(s, used - 1) * (16 * DH * 4), kDeviceScope);
+    float M = -INFINITY, L = 0.f;
+#pragma unroll
+    for (int s = 0; s < 16; ++s) M = s < used ? fmaxf(M, ms[s]) : M;
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+      ms[s] = s < used ? exp2f(ms[s] - M) : 0.f;
+      L += s < used ? ls[s] * ms[s] : 0.f;
+    }
+    f32x4 acc{0.f, 0.f, 0.f, 0.f};
+    auto add = [&](const u32x4& u, float w) {
+      const f32x4 f = __builtin_bit_cast(f32x4, u);
+      acc[0] += f[0] * w;
+      acc[1] += f[1] * w;
+      acc[2] += f[2] * w;
+      acc[3] += f[3] * w;
+    };
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+      if (s < used) add(v[s], ms[s] / L);
+    if (used > 8) {
+#pragma unroll
+      for (int s = 0; s < 8; ++s) v[s] = __builtin_amdgcn_raw_buffer_load_b128(part_o, e * 4, min(8 + s, used - 1) * (16 * DH * 4), kDeviceScope);
+#pragma unroll
+      for (int s = 0; s < 8; ++s)
+        if (8 + s < used) add(v[s], ms[8 + s] / L);
+    }
+    store4_split(a.out + out_offset(a, b, kvh * G * DH + e), a.out_lo_offset, acc[0], acc[1], acc[2], acc[3]);
   }
 }
 
@@ -614,8 +675,8 @@ __global__ __launch_bounds__(256, 3) void attn_decode_grouped_kernel(AttnArgs a)
   }
 }
 
-// Merge of the partial results of one (sample, KV head), at most 16 slots: a launch of its
-// own, because a launch boundary is the cheapest way to publish results between workgroups here.
+// Merge of the partial results of one (sample, KV head), at most 16 slots, where samples of a prompt have
+// attended to its shared pages together.
 __global__ __launch_bounds__(256) void attn_merge_fused_kernel(AttnArgs a) {
   __shared__ float w_s[16][16];  // [slot][column] weight 2^(m_s - M) / L
   const int tid = threadIdx.x, kvh = blockIdx.x, b = blockIdx.y;

@@ -42,6 +42,7 @@ __host__ __device__ inline long long plane_offset(int m, int k, int K) {
 // Scratch of the K splits that meet in their launch (join_splits): at most kJoinTiles joined tiles, each of at most
 // kJoinParts KiB, and as many tickets.
 constexpr int kTicketStride = 32;  // a ticket has its 128-byte line to itself
+constexpr int kDeviceScope = 16;   // cache policy of a buffer access at the scope of the device: sc1
 constexpr size_t kJoinTiles = 512, kJoinParts = 16;
 
 struct GemmArgs {
@@ -204,6 +205,7 @@ struct AttnArgs {
   bool wide = false;               // decode: workgroups of 8 wavefronts instead of 4
   float* part_o;                   // [rows][n_kv_heads][n_slots][16][128]
   float* part_ml;                  // [rows][n_kv_heads][n_slots][2][16]
+  unsigned* tickets = nullptr;     // decode, plain: one per (row, KV head), kTicketStride apart, 0 between launches
   int n_slots = 0;                 // partial results per (row, KV head); the launcher sets n_splits when 0
   // decode with shared prompts (launch_attention_decode_grouped): the samples of one prompt
   // attend to the prompt's shared pages together - each key and value fragment is read once
@@ -230,10 +232,10 @@ struct AttnArgs {
 };
 void launch_attention_prefill(const AttnArgs& a, hipStream_t s);
 const char* attention_prefill_name(const AttnArgs& a);  // the kernel it launches, as a profiler shows it
-// Decode attention: partial results per (row, KV head, slot) when a.n_splits > 1 or the launch is
-// the grouped one - launch_attention_merge then joins the slots; with one split the result is final.
+// Decode attention: the result is final; with several splits (a.n_splits > 1) it goes through the
+// partial results and a.tickets.
 void launch_attention_decode_fused(const AttnArgs& a, hipStream_t s);
-// the same with shared prompts; needs n_q_heads / n_kv_heads <= 8 (4 members x heads <= 32 columns)
+// the same with shared prompts, partial results per (row, KV head, slot) for launch_attention_merge; needs n_q_heads / n_kv_heads <= 8 (4 members x heads <= 32 columns)
 void launch_attention_decode_grouped(const AttnArgs& a, hipStream_t s);
 void launch_attention_merge(const AttnArgs& a, hipStream_t s);
 

@@ -94,7 +94,6 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 //   No fence is needed, whose write-back of a whole L2 is what makes a join expensive: 96 column tiles x 8960, 6
 //   rows, two halves 7.8 us as two planes, 8.8 joined, where a second launch takes 4.
 //   The last one sets the ticket back to 0 for the next launch.
-constexpr int kDeviceScope = 16;  // cache policy of a buffer access: sc1
 // One wavefront's N quads per lane; `tile`: its index among the launch's joined tiles.  True in the last wavefront of
 // the `splits`, whose t then holds the sum.
 template <int N>

@@ -191,6 +191,38 @@ def test_attention_splits_fill_the_chip_once(rows):
 EDGE_LENS = [1, 15, 16, 17, 31, 32, 33, 47, 63, 64, 65, 95, 96, 97, 127, 129]
 
 
+@pytest.mark.parametrize("rows,context", [(1, 4100), (3, 1100), (20, 1000), (33, 1500)])
+def test_attention_splits_join_in_any_order(rows, context):
+    """Contexts cut over several workgroups, whose last one to finish joins the results: the oracle's logits, and the same
+    bits in a second context, whichever was last (up to 16 splits; eight and four wavefronts; rows of the tile path)."""
+    shape = dataclasses.replace(workloads.SMALL_BF16, hidden=512, ffn_dim=544)
+    w = scaled_weights(shape, seed=1)
+    model = oracle_model(shape, w)
+    toks, offs = workloads.make_prompts(1, context, context, shape.vocab, seed=4)
+    forced = np.random.default_rng(6).integers(0, shape.vocab, (rows, 4)).astype(np.int32)
+    runs = []
+    for _ in range(2):
+        eng = make_engine(shape, w, max_live_samples=40, max_context=4200, max_batch_tokens=4200)
+        eng.rollout_prefill(toks, offs, rows, np.full(rows, 4, np.int32), forced_first=forced[:, 0])
+        got = []
+        for t in range(1, 4):
+            eng.rollout_decode_step(forced_tokens=forced[:, t])
+            got.append(eng.rollout_debug_logits())
+        runs.append(got)
+        eng.close()
+    fwd = T.KVForward(model)
+    prefix = fwd.new_cache()
+    fwd.extend([prefix], [toks])
+    caches = [prefix.fork() for _ in range(min(rows, 2))]
+    worst = 0.0
+    for t in range(1, 4):
+        ref = fwd.extend(caches, [[int(forced[i, t - 1])] for i in range(len(caches))])
+        worst = max(worst, max(float(np.max(np.abs(runs[0][t - 1][k] - ref[k][0]))) for k in range(len(caches))))
+    print(f"{rows} rows at {context}: max |dlogits| = {worst:.3e}")
+    assert worst <= TOL
+    assert all(np.array_equal(a, b) for a, b in zip(*runs))
+
+
 @pytest.mark.parametrize("copies", [1, 4])
 def test_packed_attention_tiles(copies):
     """Sequences around the edges of 16- and 32-position tiles and 32-position key groups: 16 of them take one

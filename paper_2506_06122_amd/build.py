@@ -14,6 +14,8 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # a kernel's first scalar arguments are in registers when its wavefronts start (kernels_fast.h)
+         "-mllvm", "-amdgpu-kernarg-preload-count=16",
          "-Wall", "-Wno-unused-result", "-Wno-unused-command-line-argument",
          "-I" + os.path.join(HERE, "..", "include")]
 # every floating-point step of the sampler is a single rounded operation

@@ -572,7 +572,22 @@ __device__ __forceinline__ void decode_own_range(const AttnArgs& a, const Decode
 // workgroup has a CU to itself and covers 256 positions per round, for the steps whose (sample, KV head)
 // pairs are fewer than the CUs.
 template <bool EXTRA, int NW>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void attn_decode_fused_kernel(AttnArgs a) {
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void attn_decode_fused_kernel(
+    const float* qkv_raw, const int* row_pos, const int* row_slot, const int* page_table, int n_q_heads, int n_kv_heads,
+    int qkv_planes, int max_pages, int page_tokens, int split_tokens, AttnArgs a) {
+  a.qkv_raw = qkv_raw;
+  a.row_pos = row_pos;
+  a.row_slot = row_slot;
+  a.page_table = page_table;
+  a.n_q_heads = n_q_heads;
+  a.geom.n_kv_heads = n_kv_heads;
+  a.qkv_planes = qkv_planes;
+  a.max_pages = max_pages;
+  a.geom.page_tokens = page_tokens;
+  a.split_tokens = split_tokens;
+  a.row_t0 = nullptr;  // no prompt is attended by its group here
+  a.slot0 = 0;
+  a.n_slots = 0;
   __shared__ __attribute__((aligned(16))) uint16_t q_s[2 * 16 * Q_LD];
   __shared__ __attribute__((aligned(16))) uint16_t kv_s[2 * DH];
   __shared__ float m_s[NW * 16], l_s[NW * 16];
@@ -757,16 +772,18 @@ __global__ __launch_bounds__(256) void attn_merge_fused_kernel(AttnArgs a) {
   }
 }
 
+#define DECODE_ARGS a.qkv_raw, a.row_pos, a.row_slot, a.page_table, a.n_q_heads, a.geom.n_kv_heads, a.qkv_planes, a.max_pages, \
+                    a.geom.page_tokens, a.split_tokens, a
 void launch_attention_decode_fused(const AttnArgs& a, hipStream_t s) {
   if (!a.rows) return;
   const dim3 grid(a.n_splits, a.geom.n_kv_heads, a.rows);
   const bool extra = a.extra.bias || a.extra.q_gain;
   if (a.wide) {
-    if (extra) attn_decode_fused_kernel<true, 8><<<grid, 512, 0, s>>>(a);
-    else attn_decode_fused_kernel<false, 8><<<grid, 512, 0, s>>>(a);
+    if (extra) attn_decode_fused_kernel<true, 8><<<grid, 512, 0, s>>>(DECODE_ARGS);
+    else attn_decode_fused_kernel<false, 8><<<grid, 512, 0, s>>>(DECODE_ARGS);
   } else {
-    if (extra) attn_decode_fused_kernel<true, 4><<<grid, 256, 0, s>>>(a);
-    else attn_decode_fused_kernel<false, 4><<<grid, 256, 0, s>>>(a);
+    if (extra) attn_decode_fused_kernel<true, 4><<<grid, 256, 0, s>>>(DECODE_ARGS);
+    else attn_decode_fused_kernel<false, 4><<<grid, 256, 0, s>>>(DECODE_ARGS);
   }
 }
 void launch_attention_merge(const AttnArgs& a, hipStream_t s) {

@@ -6,6 +6,10 @@
 #include "common.h"
 #include "tile_grid.h"
 
+// Kernels of a decode step take what their first loads need as leading scalar arguments, at most 14 dwords, and the rest
+// as a struct behind them: the build asks for leading scalars to be preloaded into registers, where the struct is a read
+// from memory away (streamed projections, 16 rows: 1536 x 1536 5.5 -> 5.2 us, 1536 x 8960 in 5 splits 9.9 -> 9.3).
+
 // Epilogues of the projection kernels:
 //   EPI_F32          out[m][n] fp32 (split-K planes allowed)
 //   EPI_SWIGLU_BF16  every column tile holds 8 gates, then their 8 ups: act[m][f] = silu(gate) * up as bf16 hi/lo

@@ -148,32 +148,33 @@ __device__ __forceinline__ bool join_splits(const GemmArgs& p, int tile, int spl
 // Measured (4 rows, weights from HBM): gate/up 7B shape (272 MB) 49.3 -> 43.1 us, down 7B (136 MB) 38.3 -> 26.8,
 // gate/up 1.5B (55 MB) 14.1 -> 12.7.  Narrow outputs in K splits: beside gemm_plan_stream.
 template <int MT, int NT, int KU, int NW, bool KEEP, int EPI>
-__global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
+__global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(const void* pw, const void* pa, long long lo_off, const float* rinv_ssq,
+                                                              int M, int N, int K, int k_tiles_per_split, int frag,
+                                                              int rinv_partials, GemmArgs p) {
   static_assert(MT <= 2 && MT <= NW && (NT % 2 == 0 || EPI != EPI_SWIGLU_BF16), "a wavefront finishes a row tile, SwiGLU in pairs of column tiles");
   __shared__ float4 red[NW * MT * NT * 64];
   __shared__ float rs_part[MT * NW * 64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, g = lane >> 4;
-  const int n_tiles = p.N >> 4, k_tiles = p.K >> 5;
+  const int n_tiles = N >> 4, k_tiles = K >> 5;
   const int nt0 = blockIdx.x * NT;
-  const int kt_begin = blockIdx.y * p.k_tiles_per_split;
-  const int kt_end = min(k_tiles, kt_begin + p.k_tiles_per_split);
+  const int kt_begin = blockIdx.y * k_tiles_per_split;
+  const int kt_end = min(k_tiles, kt_begin + k_tiles_per_split);
 
   const u32x4* w_src[NT];
 #pragma unroll
-  for (int j = 0; j < NT; ++j) w_src[j] = (const u32x4*)p.w + (long long)min(nt0 + j, n_tiles - 1) * k_tiles * 64 + lane;
+  for (int j = 0; j < NT; ++j) w_src[j] = (const u32x4*)pw + (long long)min(nt0 + j, n_tiles - 1) * k_tiles * 64 + lane;
   // activation fragments of this lane: row m of each row tile, k = 8 g .. 8 g + 7 of k-tile 0; a k-tile further on is
   // a_step away
   const u32x4* a_src[MT];
   int rows[MT];
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
-    rows[i] = min((int)(blockIdx.z * MT + i) * 16 + r, p.M - 1);
-    a_src[i] = (const u32x4*)((const uint16_t*)p.a +
-                              (p.frag ? frag_offset(rows[i], g * 8, k_tiles) : plane_offset(rows[i], g * 8, p.K)));
+    rows[i] = min((int)(blockIdx.z * MT + i) * 16 + r, M - 1);
+    a_src[i] = (const u32x4*)((const uint16_t*)pa +
+                              (frag ? frag_offset(rows[i], g * 8, k_tiles) : plane_offset(rows[i], g * 8, K)));
   }
-  const int a_step = p.frag ? 64 : 8;
-  const long long lo_off = ((const uint16_t*)p.a_lo - (const uint16_t*)p.a) >> 3;
+  const int a_step = frag ? 64 : 8;
 
   f32x4 acc[MT][NT];
 #pragma unroll
@@ -231,22 +232,22 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
   // row r - so that no wavefront has more than a few of them; the shares meet in LDS with the
   // accumulators.
   constexpr int RS = EPI == EPI_RESID ? 0 : 8;  // the projections that add to the residual read no norm's input
-  const int n_rs = p.rinv_ssq ? p.rinv_partials : 0;
-  const float* rs_src = p.rinv_ssq ? p.rinv_ssq : (const float*)p.a;
+  const int n_rs = rinv_ssq ? rinv_partials : 0;
+  const float* rs_src = rinv_ssq ? rinv_ssq : (const float*)pa;
   float rs_of[MT][RS + 1];
 #pragma unroll
   for (int q = 0; q < MT; ++q)
 #pragma unroll
     for (int i = 0; i < RS; ++i)  // clamped here, masked where they are summed
-      rs_of[q][i] = rs_src[(long long)max(min((i * NW + wave) * 4 + g, n_rs - 1), 0) * p.ssq_stride + (p.rinv_ssq ? rows[q] : 0)];
+      rs_of[q][i] = rs_src[(long long)max(min((i * NW + wave) * 4 + g, n_rs - 1), 0) * p.ssq_stride + (rinv_ssq ? rows[q] : 0)];
   const int own = MT > 1 ? min(wave, MT - 1) : 0;  // wavefront i < MT finishes row tile i
-  const int m = (blockIdx.z * MT + own) * 16 + r, row = min(m, p.M - 1);
+  const int m = (blockIdx.z * MT + own) * 16 + r, row = min(m, M - 1);
   float4 xv[NT], gn[NT];
   if (EPI == EPI_RESID) {
 #pragma unroll
     for (int q = 0; q < NT; ++q) {
       const int n = min(nt0 + q, n_tiles - 1) * 16 + g * 4;
-      xv[q] = *(const float4*)(p.x + (long long)row * p.N + n);
+      xv[q] = *(const float4*)(p.x + (long long)row * N + n);
       gn[q] = *(const float4*)(p.gain + n);
     }
   }
@@ -287,7 +288,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
   }
   __syncthreads();
   if (wave >= MT) return;
-  const bool valid = m < p.M;
+  const bool valid = m < M;
   f32x4 t[NT];
 #pragma unroll
   for (int q = 0; q < NT; ++q) t[q] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -304,7 +305,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
   if constexpr (EPI == EPI_RESID) {
     if (gridDim.y > 1 && !join_splits(p, (blockIdx.z * MT + own) * gridDim.x + blockIdx.x, blockIdx.y, gridDim.y, t, lane)) return;
   }
-  if (RS > 0 && p.rinv_ssq) {
+  if (RS > 0 && rinv_ssq) {
     // second half of the RMSNorm of this projection's input: scale row m by
     // rsqrt(mean(x^2) + eps); the 4 lanes of a row share the partial sums
     float rs = 0.f;
@@ -312,7 +313,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
     for (int w = 0; w < NW; ++w) rs += rs_part[(own * NW + w) * 64 + lane];
     rs += __shfl_xor(rs, 16, WAVE);
     rs += __shfl_xor(rs, 32, WAVE);
-    const float rinv = 1.0f / sqrtf(rs / (float)p.K + p.eps);
+    const float rinv = 1.0f / sqrtf(rs / (float)K + p.eps);
 #pragma unroll
     for (int q = 0; q < NT; ++q) {
       t[q][0] *= rinv;
@@ -332,11 +333,11 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(GemmArgs p) {
         x4.y += t[q][1];
         x4.z += t[q][2];
         x4.w += t[q][3];
-        *(float4*)(p.x + (long long)m * p.N + n) = x4;
+        *(float4*)(p.x + (long long)m * N + n) = x4;
         ss += x4.x * x4.x + x4.y * x4.y + x4.z * x4.z + x4.w * x4.w;
         uint2 hi, lo;
         split4_bf16(x4.x * gn[q].x, x4.y * gn[q].y, x4.z * gn[q].z, x4.w * gn[q].w, hi, lo);
-        uint16_t* hp = p.h + (p.frag ? frag_offset(m, n, n_tiles >> 1) : plane_offset(m, n, p.N));
+        uint16_t* hp = p.h + (frag ? frag_offset(m, n, n_tiles >> 1) : plane_offset(m, n, N));
         *(uint2*)hp = hi;
         *(uint2*)(hp + p.h_lo_offset) = lo;
       }
@@ -416,7 +417,9 @@ __device__ __forceinline__ void unrolled(F&& f, std::integer_sequence<int, I...>
 
 // GATHER: the rows of `a` come through row_map (experts' grouped projections)
 template <int WM, int WN, int MT, int NT, int KG, int S, int EPI, bool GATHER>
-__global__ __launch_bounds__(WM* WN* KG * 64, wide_wavefronts(WM, WN, MT, NT, KG, S) ? 1 : 2) void gemm_tile_kernel(GemmArgs p) {
+__global__ __launch_bounds__(WM* WN* KG * 64, wide_wavefronts(WM, WN, MT, NT, KG, S) ? 1 : 2) void gemm_tile_kernel(
+    const void* pw, const void* pa, int M, int N, int K, int k_tiles_per_split, unsigned group, int gy, unsigned by_per,
+    unsigned by_nz, unsigned by_gy, unsigned by_m, GemmArgs p) {
   constexpr bool WIDE = wide_wavefronts(WM, WN, MT, NT, KG, S);
   constexpr int NW = WM * WN * KG, BM = WM * MT * 16, BN = WN * NT * 16;
   constexpr int UA = BM / 8, UW = BN / 16, U1 = UA + UW;  // load instructions per k-tile
@@ -427,27 +430,39 @@ __global__ __launch_bounds__(WM* WN* KG * 64, wide_wavefronts(WM, WN, MT, NT, KG
   __shared__ __attribute__((aligned(1024))) char lds[LDS_KB * 1024];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, g = lane >> 4;
-  const int n_tiles = p.N >> 4, k_tiles = p.K >> 5;
-  const TileBlock block = tile_block(p.grid, blockIdx.x);
+  const int n_tiles = N >> 4, k_tiles = K >> 5;
+  TileGrid grid;
+  grid.nx = (n_tiles + WN * NT - 1) / (WN * NT);
+  grid.nz = (int)(group >> 16);
+  grid.group_m = (int)(group & 255);
+  grid.group_n = (int)(group >> 8 & 127);
+  const bool grouped = group >> 15 & 1;
+  grid.ny = grouped ? p.grid.ny : (M + BM - 1) / BM;
+  grid.gy = gy;
+  grid.by_per = by_per;
+  grid.by_nz = by_nz;
+  grid.by_gy = by_gy;
+  grid.by_m = by_m;
+  const TileBlock block = tile_block(grid, blockIdx.x);
   if (!block.inside) return;  // uniform
   const int bx = block.x, by = block.y, bz = block.z;
   const int nt0 = bx * (BN / 16);
   int m0 = by * BM;
-  const int kt_begin = bz * p.k_tiles_per_split;
-  const int kt_end = min(k_tiles, kt_begin + p.k_tiles_per_split);
+  const int kt_begin = bz * k_tiles_per_split;
+  const int kt_end = min(k_tiles, kt_begin + k_tiles_per_split);
 
   // grouped (per-expert) launches: this row block belongs to one group with its own weights
-  const char* wp = (const char*)p.w;
-  int m_limit = p.M;
-  if (p.group_of_block) {
+  const char* wp = (const char*)pw;
+  int m_limit = M;
+  if (grouped) {
     wp += (long long)p.group_of_block[by] * p.group_stride16 * 16;
     m0 = p.block_row_begin[by];
     m_limit = p.block_row_end[by];
     if (m0 >= m_limit) return;  // unused block of the plan (uniform over the workgroup)
   }
   wp += (long long)nt0 * k_tiles * 1024;
-  const long long row_bytes = (long long)p.K * 4;
-  const char* ap = (const char*)p.a + (GATHER ? 0 : m0 * row_bytes);
+  const long long row_bytes = (long long)K * 4;
+  const char* ap = (const char*)pa + (GATHER ? 0 : m0 * row_bytes);
 
   const int kg = wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
   // this wavefront's loads of a stage: instruction u of the stage's U1 * KG.  An address moves on by a stage's k-tiles
@@ -726,6 +741,7 @@ GemmPlan gemm_plan_grouped(int epi, long long picks, int n_experts) {
   return pl;
 }
 
+#define TILE_ARGS a.w, a.a, a.M, a.N, a.K, a.k_tiles_per_split, group, a.grid.gy, a.grid.by_per, a.grid.by_nz, a.grid.by_gy, a.grid.by_m, a
 static int launch_tile(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s) {
   const TileShape& t = kTileShapes[pl.shape];
   const int n_tiles = a.N >> 4, k_tiles = a.K >> 5, bm = t.wm * t.mt * 16;
@@ -737,16 +753,17 @@ static int launch_tile(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s) {
   else tile_groups(a.grid);
   tile_divisors(a.grid);
   const dim3 grid((unsigned)tile_workgroups(a.grid));
+  const unsigned group = (unsigned)a.grid.group_m | (unsigned)a.grid.group_n << 8 | (a.group_of_block ? 1u << 15 : 0u) | (unsigned)a.grid.nz << 16;
   const bool gather = a.row_map != nullptr;
   switch (pl.shape) {
 #define X(id, wm, wn, mt, nt, kg, st, ...)                                                                          \
   case id:                                                                                                           \
-    if (epi == EPI_F32) gemm_tile_kernel<wm, wn, mt, nt, kg, st, EPI_F32, false><<<grid, wm * wn * kg * 64, 0, s>>>(a); \
+    if (epi == EPI_F32) gemm_tile_kernel<wm, wn, mt, nt, kg, st, EPI_F32, false><<<grid, wm * wn * kg * 64, 0, s>>>(TILE_ARGS); \
     else if (epi == EPI_LSE) /* never planned with fewer than kLseMinTile column tiles */                             \
-      gemm_tile_kernel<wm, wn, mt, nt, kg, st, wn * nt >= kLseMinTile ? EPI_LSE : EPI_F32, false><<<grid, wm * wn * kg * 64, 0, s>>>(a); \
+      gemm_tile_kernel<wm, wn, mt, nt, kg, st, wn * nt >= kLseMinTile ? EPI_LSE : EPI_F32, false><<<grid, wm * wn * kg * 64, 0, s>>>(TILE_ARGS); \
     else if (grouped_shape(id) && gather)                                                                             \
-      gemm_tile_kernel<wm, wn, mt, nt, kg, st, EPI_SWIGLU_BF16, grouped_shape(id)><<<grid, wm * wn * kg * 64, 0, s>>>(a); \
-    else gemm_tile_kernel<wm, wn, mt, nt, kg, st, EPI_SWIGLU_BF16, false><<<grid, wm * wn * kg * 64, 0, s>>>(a); \
+      gemm_tile_kernel<wm, wn, mt, nt, kg, st, EPI_SWIGLU_BF16, grouped_shape(id)><<<grid, wm * wn * kg * 64, 0, s>>>(TILE_ARGS); \
+    else gemm_tile_kernel<wm, wn, mt, nt, kg, st, EPI_SWIGLU_BF16, false><<<grid, wm * wn * kg * 64, 0, s>>>(TILE_ARGS); \
     break;
     TILE_SHAPES(X)
 #undef X
@@ -809,9 +826,11 @@ GemmPlan gemm_plan(int M, int N, int K, int epi, int max_splits) {
   return M > 16 || epi == EPI_LSE ? gemm_plan_tiled(M, N, K, epi, max_splits) : gemm_plan_stream(M, N, K, epi, max_splits);
 }
 
+#define STREAM_ARGS a.w, a.a, lo_off, a.rinv_ssq, a.M, a.N, a.K, a.k_tiles_per_split, (int)a.frag, a.rinv_partials, a
 static int launch_stream(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s) {
   const StreamShape& t = kStreamShapes[pl.shape];
   const int n_tiles = a.N >> 4, k_tiles = a.K >> 5;
+  const long long lo_off = ((const uint16_t*)a.a_lo - (const uint16_t*)a.a) >> 3;  // 16-byte pieces
   a.k_tiles_per_split = ceil_div(k_tiles, pl.splits);
   const dim3 grid(ceil_div(n_tiles, t.nt), ceil_div(k_tiles, a.k_tiles_per_split), ceil_div(a.M, 16 * t.mt));
   if (epi == EPI_RESID && grid.y > 1 && (!a.join || (size_t)grid.x * grid.z * t.mt > kJoinTiles || grid.y * t.nt > kJoinParts))
@@ -819,8 +838,8 @@ static int launch_stream(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s)
   switch (pl.shape) {
 #define X(id, mt, nt, ku, nw, keep, e0, e1)                                                        \
   case id:                                                                                         \
-    if (epi == e0) gemm_stream_kernel<mt, nt, ku, nw, keep, e0><<<grid, nw * 64, 0, s>>>(a);        \
-    else if (epi == e1) gemm_stream_kernel<mt, nt, ku, nw, keep, e1><<<grid, nw * 64, 0, s>>>(a);   \
+    if (epi == e0) gemm_stream_kernel<mt, nt, ku, nw, keep, e0><<<grid, nw * 64, 0, s>>>(STREAM_ARGS);        \
+    else if (epi == e1) gemm_stream_kernel<mt, nt, ku, nw, keep, e1><<<grid, nw * 64, 0, s>>>(STREAM_ARGS);   \
     else throw HipError(hipErrorInvalidValue, "streamed projection", __FILE__, __LINE__);              \
     break;
     STREAM_SHAPES(X)

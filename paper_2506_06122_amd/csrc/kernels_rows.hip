@@ -12,7 +12,16 @@
 // planes: 5.5 -> 4.8 us; 64 x 3584, 8 planes 6.9 -> 5.8; both with 2 us of launch).  With more rows than the chip
 // holds at once it is the bytes, and small workgroups that come and go keep more of them in flight.
 template <int ROW_T, int V>
-__global__ __launch_bounds__(ROW_T) void row_norm_kernel(RowNormArgs a) {
+__global__ __launch_bounds__(ROW_T) void row_norm_kernel(float* x_rows, const float* partial_rows, const float* gain, long long split_stride,
+                                                         const int* tokens, int hidden, int splits, int moe_k, RowNormArgs a) {
+  a.x = x_rows;
+  a.partial = partial_rows;
+  a.gain = gain;
+  a.split_stride = split_stride;
+  a.tokens = tokens;
+  a.hidden = hidden;
+  a.splits = splits;
+  a.moe_k = moe_k;
   __shared__ float partial[ROW_T / WAVE];
   const int r = blockIdx.x, t = threadIdx.x;
   const int n4 = a.hidden >> 2;
@@ -127,18 +136,19 @@ __global__ __launch_bounds__(ROW_T) void row_norm_kernel(RowNormArgs a) {
     *(uint2*)(hp + a.h_lo_offset) = lo;
   }
 }
+#define ROW_ARGS a.x, a.partial, a.gain, a.split_stride, a.tokens, a.hidden, a.splits, a.moe_k, a
 void launch_row_norm(const RowNormArgs& a, hipStream_t s) {
   if (!a.rows) return;
   const int n4 = a.hidden >> 2;  // hidden is a multiple of 32 and at most 8192
   // A thread per chunk where the chip's 512 Ki threads hold all rows at once; 256 threads beyond that (10568 rows x
   // 3584: 134 us with 1024 threads to a row, 94 with 256) and where a row has no more chunks.
   const bool at_once = (long long)a.rows * n4 <= 512 * 1024;
-  if (n4 <= 256) row_norm_kernel<256, 1><<<a.rows, 256, 0, s>>>(a);
-  else if (n4 <= 512 && at_once) row_norm_kernel<512, 1><<<a.rows, 512, 0, s>>>(a);
-  else if (n4 <= 512) row_norm_kernel<256, 2><<<a.rows, 256, 0, s>>>(a);
-  else if (n4 <= 1024 && at_once) row_norm_kernel<1024, 1><<<a.rows, 1024, 0, s>>>(a);
-  else if (n4 <= 1024) row_norm_kernel<256, 4><<<a.rows, 256, 0, s>>>(a);
-  else row_norm_kernel<256, 8><<<a.rows, 256, 0, s>>>(a);
+  if (n4 <= 256) row_norm_kernel<256, 1><<<a.rows, 256, 0, s>>>(ROW_ARGS);
+  else if (n4 <= 512 && at_once) row_norm_kernel<512, 1><<<a.rows, 512, 0, s>>>(ROW_ARGS);
+  else if (n4 <= 512) row_norm_kernel<256, 2><<<a.rows, 256, 0, s>>>(ROW_ARGS);
+  else if (n4 <= 1024 && at_once) row_norm_kernel<1024, 1><<<a.rows, 1024, 0, s>>>(ROW_ARGS);
+  else if (n4 <= 1024) row_norm_kernel<256, 4><<<a.rows, 256, 0, s>>>(ROW_ARGS);
+  else row_norm_kernel<256, 8><<<a.rows, 256, 0, s>>>(ROW_ARGS);
 }
 
 // One thread per rotary pair (head, i): grid (rows, heads / 4), 4 heads of 64 pairs per block.

@@ -93,7 +93,15 @@ __device__ inline float fold_rows(const float (&v)[LIN_ROWS], int lane) {
 }
 
 template <typename T, bool NORM, bool GLU, bool VEC>
-__global__ __launch_bounds__(256) void linear_simple_kernel(LinearArgs p, const T* __restrict__ w) {
+__global__ __launch_bounds__(256) void linear_simple_kernel(const T* __restrict__ w, const float* a, const float* gain, const int* rows_index,
+                                                            int lda, int M, int N, int K, LinearArgs p) {
+  p.a = a;
+  p.gain = gain;
+  p.rows_index = rows_index;
+  p.lda = lda;
+  p.M = M;
+  p.N = N;
+  p.K = K;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int n = blockIdx.x * 4 + wave, m0 = blockIdx.y * LIN_ROWS;
   if (n >= p.N) return;
@@ -143,7 +151,7 @@ void launch_linear_simple(const LinearArgs& p, const T* w, bool glu, hipStream_t
       glu      ? (vec ? linear_simple_kernel<T, true, true, true> : linear_simple_kernel<T, true, true, false>)
       : p.gain ? (vec ? linear_simple_kernel<T, true, false, true> : linear_simple_kernel<T, true, false, false>)
                : (vec ? linear_simple_kernel<T, false, false, true> : linear_simple_kernel<T, false, false, false>);
-  kernel<<<grid, 256, 0, s>>>(p, w);
+  kernel<<<grid, 256, 0, s>>>(w, p.a, p.gain, p.rows_index, p.lda, p.M, p.N, p.K, p);
 }
 template void launch_linear_simple<float>(const LinearArgs&, const float*, bool, hipStream_t);
 template void launch_linear_simple<bf16_t>(const LinearArgs&, const bf16_t*, bool, hipStream_t);

@@ -414,6 +414,11 @@ int rollout_abi_version(void);
 int rollout_sample(const float *logits, int32_t rows, int32_t vocab, float temperature, float top_p,
                    const uint32_t *uniforms, const int32_t *forced, void *hip_stream, int32_t *tokens,
                    float *logprobs, uint64_t *weight_sums);
+/* Test hook: the same draw, but no part of a row waits for the others, so that whichever finishes a phase last does all
+ * shares that are left (what happens when the parts' workgroups do not run together). */
+int rollout_debug_sample_impatient(const float *logits, int32_t rows, int32_t vocab, float temperature, float top_p,
+                                   const uint32_t *uniforms, void *hip_stream, int32_t *tokens, float *logprobs,
+                                   uint64_t *weight_sums);
 
 /* rollout_sample for callers that cannot allocate device memory or wait: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same kernels and results as

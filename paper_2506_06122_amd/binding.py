@@ -119,6 +119,7 @@ SIGNATURES = {
     "rollout_destroy": (None, [_P]),
     "rollout_abi_version": (C.c_int, []),
     "rollout_sample": (C.c_int, [_P, C.c_int32, C.c_int32, C.c_float, C.c_float, _P, _P, _P, _P, _P, _P]),
+    "rollout_debug_sample_impatient": (C.c_int, [_P, C.c_int32, C.c_int32, C.c_float, C.c_float, _P, _P, _P, _P, _P]),
     "rollout_sample_static": (C.c_int, [_P, C.c_int32, C.c_int32, C.c_float, C.c_float, _P, _P, _P, _P, _P, _P]),
     "rollout_sample_static_prepare": (C.c_int, []),
     "rollout_sample_static_error": (C.c_char_p, []),
@@ -408,6 +409,20 @@ def rollout_debug_tile_product(stream=None, **fields) -> int:
     if rc != OK:
         raise RolloutError(rc, lib.rollout_last_error(None).decode())
     return planes.value
+
+
+def rollout_debug_sample_impatient(logits, temperature, top_p, uniforms, stream=None):
+    """rollout_sample whose workgroups do not wait for each other (test hook)."""
+    lib = load_library()
+    assert logits.is_cuda and logits.is_contiguous() and logits.dtype.is_floating_point and logits.element_size() == 4
+    rows, vocab = logits.shape
+    uni = _arr(uniforms, np.uint32)
+    toks, lps, sums = np.empty(rows, np.int32), np.empty(rows, np.float32), np.empty(rows, np.uint64)
+    rc = lib.rollout_debug_sample_impatient(logits.data_ptr(), rows, vocab, temperature, top_p, _ptr(uni), stream,
+                                            _ptr(toks), _ptr(lps), _ptr(sums))
+    if rc != OK:
+        raise RolloutError(rc, lib.rollout_last_error(None).decode())
+    return toks, lps, sums
 
 
 def rollout_sample(logits, temperature, top_p, uniforms, forced=None, stream=None):

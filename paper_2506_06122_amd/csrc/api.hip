@@ -1511,9 +1511,9 @@ struct EnqueuedCall {
 
 extern "C" {
 
-int rollout_sample(const float* logits, int32_t rows, int32_t vocab, float temperature, float top_p,
-                   const uint32_t* uniforms, const int32_t* forced, void* hip_stream, int32_t* tokens,
-                   float* logprobs, uint64_t* weight_sums) {
+static int sample_call(const float* logits, int32_t rows, int32_t vocab, float temperature, float top_p,
+                       const uint32_t* uniforms, const int32_t* forced, void* hip_stream, int32_t* tokens,
+                       float* logprobs, uint64_t* weight_sums, int patience) {
   return guarded(nullptr, [&] {
     if (!logits || rows < 0 || vocab < 1 || vocab > 262144 || !uniforms || !tokens || !logprobs)
       fail(ROLLOUT_E_INVAL, "bad argument");
@@ -1528,7 +1528,7 @@ int rollout_sample(const float* logits, int32_t rows, int32_t vocab, float tempe
     const size_t R = rows;
     const bool nucleus = top_p < 1.f && !(forced && *std::min_element(forced, forced + rows) >= 0);
     const size_t nucleus_rows = nucleus ? std::min<size_t>(R, 512) : 0;
-    cs.begin(CallScratch::piece(R * 4) + CallScratch::piece(R * kSampleParts * 4) + CallScratch::piece(R * kSampleSegments * 8) +
+    cs.begin(CallScratch::piece(R * 4) + CallScratch::piece(R * kSampleHead * 4) + CallScratch::piece(R * kSampleSegments * 8) +
                  CallScratch::piece(nucleus_rows * kNucleusScratch * 8),
              4 * CallScratch::piece(R * 4) + CallScratch::piece(R * 8));
     EnqueuedCall call(s);
@@ -1552,17 +1552,30 @@ int rollout_sample(const float* logits, int32_t rows, int32_t vocab, float tempe
     sr.tokens = tok;
     sr.logprobs = lp;
     sr.weight_sums = ws;
-    sr.part_max = cs.take<float>(R * kSampleParts);
+    sr.part_max = cs.take<float>(R * kSampleHead);
     sr.seg_sums = cs.take<unsigned long long>(R * kSampleSegments);
     sr.any_nucleus = nucleus;
     if (nucleus) sr.nucleus = cs.take<unsigned long long>(nucleus_rows * kNucleusScratch);
     sr.nucleus_rows = (int)nucleus_rows;
+    sr.patience = patience;
     launch_sample(sr, rows, vocab, s);
     call.finish();
     std::memcpy(tokens, tok, R * sizeof(int));
     std::memcpy(logprobs, lp, R * sizeof(float));
     if (weight_sums) std::memcpy(weight_sums, ws, R * sizeof(unsigned long long));
   });
+}
+
+int rollout_sample(const float* logits, int32_t rows, int32_t vocab, float temperature, float top_p,
+                   const uint32_t* uniforms, const int32_t* forced, void* hip_stream, int32_t* tokens,
+                   float* logprobs, uint64_t* weight_sums) {
+  return sample_call(logits, rows, vocab, temperature, top_p, uniforms, forced, hip_stream, tokens, logprobs, weight_sums,
+                     kMeetSpins);
+}
+int rollout_debug_sample_impatient(const float* logits, int32_t rows, int32_t vocab, float temperature, float top_p,
+                                   const uint32_t* uniforms, void* hip_stream, int32_t* tokens, float* logprobs,
+                                   uint64_t* weight_sums) {
+  return sample_call(logits, rows, vocab, temperature, top_p, uniforms, nullptr, hip_stream, tokens, logprobs, weight_sums, 0);
 }
 
 int rollout_policy_loss(int32_t n_seqs, const int32_t* cu_seqlens, const float* logp_new, const float* logp_old,

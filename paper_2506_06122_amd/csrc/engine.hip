@@ -352,7 +352,7 @@ void engine_init(rollout_ctx& c, const rollout_weights& w) {
   c.samp_rows = (int)std::min<size_t>(R, 4096);
   c.samp_nucleus_rows = std::min(c.samp_rows, 512);
   const size_t seg_words = (size_t)c.samp_rows * kSampleSegments, nucleus_words = (size_t)c.samp_nucleus_rows * kNucleusScratch;
-  c.samp_scratch.alloc(seg_words + nucleus_words + (size_t)c.samp_rows * (kSampleParts / 2));
+  c.samp_scratch.alloc(seg_words + nucleus_words + (size_t)c.samp_rows * (kSampleHead / 2));
   c.samp_seg_sums.p = c.samp_scratch.p;
   c.samp_nucleus.p = c.samp_seg_sums.p + seg_words;
   c.samp_part_max.p = (float*)(c.samp_nucleus.p + nucleus_words);

@@ -79,6 +79,7 @@ struct SlotState {
 };
 
 // ---- sampling ---------------------------------------------------------------------------
+constexpr int kMeetSpins = 128;  // looks of about 0.5 us; the parts of a row finish a phase within a few us of each other
 struct SampleRows {
   const float* logits;      // [*][vocab]
   const int* logits_row;    // [rows] row of `logits` each draw reads, or NULL (identity)
@@ -95,13 +96,14 @@ struct SampleRows {
   unsigned long long* weight_sums;  // out [rows] or NULL
   // Scratch that lets a row's two sweeps over the vocabulary run on several workgroups (the
   // sums are integers, so the split changes nothing): both or neither.
-  float* part_max = nullptr;               // [rows][kSampleParts]
+  float* part_max = nullptr;               // [rows][kSampleHead]: maxima of the parts, then the words they meet at
   unsigned long long* seg_sums = nullptr;  // [rows][kSampleSegments]
   // any_nucleus = false promises that no row draws with top_p < 1; with it, `nucleus` is the scratch of
   // nucleus_rows rows that lets those rows' sweeps run on several workgroups too.
   bool any_nucleus = true;
   unsigned long long* nucleus = nullptr;   // [nucleus_rows][kNucleusScratch]
   int nucleus_rows = 0;
+  int patience = kMeetSpins;               // looks of a part at the others' progress before it leaves its share to them
   // What the draw ends with, where asked for: the token and log-prob in host memory mapped for the
   // device, and the state of slot row_slot[r] (a negative one has none): its next position is
   // row_pos[r] + pos_step, the other fields follow from the row's own.
@@ -113,10 +115,10 @@ struct SampleRows {
   SlotState slots{};
 };
 constexpr int kSampleParts = 64, kSampleSegments = 1024;
+constexpr int kMeetWords = 16, kSampleHead = kSampleParts + kMeetWords + 2;  // 32-bit words: what the parts meet at, the random word
 constexpr int kNucleusBins0 = 41 * 16;                           // exponents 0..40 x 4 mantissa bits
 constexpr int kNucleusHist = kNucleusBins0 + 1024 + 512;         // the three histograms of a row
-constexpr int kNucleusFound = kNucleusHist + kSampleSegments / 2;  // behind 1024 32-bit counts: what the search found
-constexpr int kNucleusCounts = kNucleusFound + 32;               // per part the ids it listed, 32 bits each
+constexpr int kNucleusCounts = kNucleusHist + kSampleSegments / 2;  // behind 1024 32-bit counts: per part the ids it listed, 32 bits each
 constexpr int kNucleusList = kNucleusCounts + kSampleParts / 2;  // the listed ids, shared out among the parts
 constexpr int kNucleusListed = 8192;
 constexpr int kNucleusScratch = kNucleusList + kNucleusListed;   // 64-bit words

@@ -16,7 +16,7 @@
 // exponent and 23 of mantissa.  Histogram 0 bins by exponent and 4 mantissa bits (656 bins), the next
 // two by the following 10 and the last 9 bits among the ids of the bin found before; a bin is
 // found from the top by a prefix sum.  What bounds it: the arithmetic of the weights, 60 instructions per id and
-// sweep, so the sweeps of a row run on several workgroups, like the first two, and the sweep that fills
+// sweep, so the sweeps of a row run on several workgroups, and the sweep that fills
 // histogram 1 is the last one as a rule: it leaves, per segment of 256 ids, the weight of the bins above the one found,
 // and lists the ids of that bin (some 500 of 151936 where logits spread like N(0, 2.5)); the draw finds the
 // rest from the list.  Rows so flat that the list would overflow (nucleus_is_flat) take full sweeps instead:
@@ -32,33 +32,32 @@
 
 // The weight as a float, exact (24 significant bits at most): P(frac(t)) with its exponent raised by 40 + floor(t),
 // t = d * log2(e), less what is worth less than 1; 0 for t below -40.  No branch, so that the arithmetic of a
-// thread's ids interleaves.
+// thread's ids interleaves.  The coefficients carry the 2^40 (a power of two scales every product and sum exactly), and a t below -40,
+// or one that is no number, becomes one whose weight is below 1.
 __device__ inline float fixexp_value(float d) {
 #pragma clang fp contract(off)
   const float log2e = 0x1.715476p+0f;
   float t = d * log2e;
-  const bool any = t >= -40.0f;  // not so where d is no number
-  t = any ? t : -40.0f;
+  t = t >= -40.0f ? t : -50.0f;
   float n = floorf(t);
   float f = t - n;
-  float y = 0x1.5bd2aep-16f;
+  float y = 0x1.5bd2aep+24f;
   y = y * f;
-  y = y + 0x1.3262dep-13f;
+  y = y + 0x1.3262dep+27f;
   y = y * f;
-  y = y + 0x1.5efc6ap-10f;
+  y = y + 0x1.5efc6ap+30f;
   y = y * f;
-  y = y + 0x1.3b1a32p-7f;
+  y = y + 0x1.3b1a32p+33f;
   y = y * f;
-  y = y + 0x1.c6b140p-5f;
+  y = y + 0x1.c6b140p+35f;
   y = y * f;
-  y = y + 0x1.ebfbdep-3f;
+  y = y + 0x1.ebfbdep+37f;
   y = y * f;
-  y = y + 0x1.62e430p-1f;
+  y = y + 0x1.62e430p+39f;
   y = y * f;
-  y = y + 0x1.000000p+0f;
-  // y is about 1 to 2, so nothing leaves the exponent's 8 bits
-  const float v = truncf(__uint_as_float(__float_as_uint(y) + ((unsigned)((int)n + 40) << 23)));
-  return any ? v : 0.f;
+  y = y + 0x1.000000p+40f;
+  // y is about 2^40 to 2^41, so nothing leaves the exponent's 8 bits
+  return truncf(__uint_as_float(__float_as_uint(y) + ((unsigned)(int)n << 23)));
 }
 // its bits: they order like the weights
 __device__ inline unsigned fixexp_key(float d) { return __float_as_uint(fixexp_value(d)); }
@@ -132,6 +131,7 @@ struct SampShared {
   unsigned long long wave_part[SAMP_T / WAVE];
   unsigned long long bcast[3];
   float fwave[SAMP_T / WAVE];
+  float log_sum, logit;
 };
 
 __device__ inline float block_max(float v, SampShared& sh) {
@@ -260,32 +260,55 @@ __device__ inline WeightParts weight4(const Logit4& z, int i0, int vocab, float 
   return sum;
 }
 
-// This thread's four logits of tiles t0, t0 + step, ... of a row.  The first AHEAD tiles are requested where the object
+// How `parts` workgroups share a row: whole rounds of tiles go round by tile, and what is left by segments, the same
+// number to each, so that the last round does not leave some of them idle (38 tiles, 8 parts: 75 segments each instead of 64
+// or 80).  The last round's segments of a part are one wavefront's each, as in a tile.
+struct RowShares {
+  int parts, rounds, per;  // whole rounds; ids of the rest per part
+  __host__ __device__ RowShares(int vocab, int parts) : parts(parts), rounds((vocab >> 12) / parts) {
+    per = (((vocab - rest0() + 255) >> 8) + parts - 1) / parts << 8;
+  }
+  __host__ __device__ inline int rest0() const { return rounds * parts << 12; }  // the first id behind the rounds
+  __device__ inline int part_of_segment(int seg) const {
+    const int rest = seg - (rest0() >> 8);
+    return rest < 0 ? (seg >> 4) % parts : rest / (per >> 8);
+  }
+};
+
+// This thread's four logits of a part's share of a row, round by round.  The first AHEAD rounds are requested where the object
 // is made, so that they are under way while a sweep finds out what it needs to know of the sweeps before (those
 // sweeps have vocabularies of several tiles).
 template <int AHEAD>
 struct RowTiles {
   const float* row;
-  int vocab, t0, step;
+  int vocab, part;
+  RowShares in;
   Logit4 ahead[AHEAD > 0 ? AHEAD : 1];
-  __device__ inline RowTiles(const float* row, int vocab, int t0, int step)
-      : row(row), vocab(vocab), t0(t0), step(step) {
+  __device__ inline int first_id(int q) const {  // of round q
+    const int i0 = (int)threadIdx.x * 4;
+    if (q < in.rounds) return ((part + q * in.parts) << 12) + i0;
+    const int at = (q - in.rounds) * 4096 + i0;  // (a rest of more than a tile per part is none: it would be a round)
+    return at < in.per ? in.rest0() + part * in.per + at : 0x7ffffff0;
+  }
+  __device__ inline RowTiles(const float* row, int vocab, int part, const RowShares& in) : row(row), vocab(vocab), part(part), in(in) {
 #pragma unroll
-    for (int q = 0; q < AHEAD; ++q) ahead[q] = request4<false>(row, (t0 + q * step) * 4096 + (int)threadIdx.x * 4, vocab);
+    for (int q = 0; q < AHEAD; ++q) ahead[q] = request4<false>(row, first_id(q), vocab);
     if (AHEAD > 0) __builtin_amdgcn_sched_barrier(0);
   }
-  // f(first id, logits) of every tile.  With one workgroup per row a wavefront whose ids all lie past the end passes: a
+  // f(first id, logits) of every round; a wavefront whose ids all lie past the end passes.  (With one workgroup per row a
   // small vocabulary leaves most wavefronts of its one tile without any, and their arithmetic took as long again as the
-  // others' (1024 ids, top_p 1 / 0.9: 6.0 -> 5.4, 13.3 -> 11.9 us a call).
+  // others': 1024 ids, top_p 1 / 0.9 6.0 -> 5.4, 13.3 -> 11.9 us a call.)
   template <typename F>
   __device__ inline void each(F&& f) const {
-    const int n_tiles = (vocab + 4095) >> 12, i0 = (int)threadIdx.x * 4;
 #pragma unroll
-    for (int q = 0; q < AHEAD; ++q)
-      if (t0 + q * step < n_tiles) f((t0 + q * step) * 4096 + i0, logits4(ahead[q], (t0 + q * step) * 4096 + i0, vocab));
-    for (int t = t0 + AHEAD * step; t < n_tiles; t += step)
-      if (AHEAD > 0 || t * 4096 + (i0 & ~255) < vocab)  // (uniform: a wavefront's 256 ids are one segment)
-        f(t * 4096 + i0, logits4(request4<AHEAD == 0>(row, t * 4096 + i0, vocab), t * 4096 + i0, vocab));
+    for (int q = 0; q < AHEAD; ++q) {
+      const int i0 = first_id(q);
+      if ((i0 & ~255) < vocab) f(i0, logits4(ahead[q], i0, vocab));  // (uniform: a wavefront's 256 ids are one segment)
+    }
+    for (int q = AHEAD; q <= in.rounds; ++q) {
+      const int i0 = first_id(q);
+      if ((i0 & ~255) < vocab) f(i0, logits4(request4<AHEAD == 0>(row, i0, vocab), i0, vocab));
+    }
   }
 };
 
@@ -337,10 +360,21 @@ __device__ inline void nucleus_descend(unsigned long long v, int level, float to
   st.prefix = level == 0 ? bin + (127u << 4) : level == 1 ? (st.prefix << 10) | bin : (st.prefix << 9) | bin;
   __syncthreads();
 }
-// this thread's bin of a histogram, counted from the top
+// Loads and stores at the scope of the device: what parts of a row, on different XCDs, leave for each other in one launch.
+template <typename T>
+__device__ inline T load_device(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ inline void store_device(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// this thread's bin of a histogram (in LDS, or DEVICE: in the scratch), counted from the top
+template <bool DEVICE>
 __device__ inline unsigned long long nucleus_bin_from_top(const unsigned long long* hist, int level) {
   const int at = nucleus_bins(level) - 1 - (int)threadIdx.x;
-  return at >= 0 ? hist[at] : 0ull;
+  if (at < 0) return 0ull;
+  return DEVICE ? load_device(hist + at) : hist[at];
 }
 // The tiles into the LDS histogram of `level` (zeroed here).  From level 1 on only the ids
 // of one narrow bin count, so an id whose exponent t lies outside the bin's range is passed over before its
@@ -396,38 +430,20 @@ __device__ inline void nucleus_segments(const RowTiles<AHEAD>& tiles, float inv_
   });
 }
 
-// Smallest segment whose inclusive prefix of sh.vals[0..n_seg) exceeds target, and the
+// Smallest segment whose inclusive prefix of the segments' values (one per thread) exceeds target, and the
 // exclusive prefix before it.  Requires the total to exceed target.
-__device__ inline void find_segment(SampShared& sh, int n_seg, unsigned long long target, int& seg,
+__device__ inline void find_segment(SampShared& sh, unsigned long long mine, unsigned long long target, int& seg,
                                     unsigned long long& before) {
-  const int tid = threadIdx.x;
-  if (tid == 0) {
-    sh.bcast[0] = 0;
-    sh.bcast[1] = 0;
-  }
-  __syncthreads();
-  if (tid < WAVE) {
-    const int per = SAMP_T / WAVE;
-    unsigned long long mine = 0;
-    for (int j = 0; j < per; ++j) mine += tid * per + j < n_seg ? sh.vals[tid * per + j] : 0ull;
-    const unsigned long long inc = wave_scan_u64(mine);
-    unsigned long long exc = inc - mine;
-    if (exc <= target && target < inc) {
-      unsigned long long acc = exc;
-      int j = 0;
-      for (; j < per - 1; ++j) {
-        unsigned long long v = tid * per + j < n_seg ? sh.vals[tid * per + j] : 0ull;
-        if (acc + v > target) break;
-        acc += v;
-      }
-      sh.bcast[0] = (unsigned long long)(tid * per + j);
-      sh.bcast[1] = acc;
-    }
+  if (threadIdx.x == 0) sh.bcast[0] = sh.bcast[1] = 0ull;
+  unsigned long long total;
+  const unsigned long long inc = block_scan_u64(mine, sh, total);  // (its barriers stand between the two writes)
+  if (inc > target && inc - mine <= target) {
+    sh.bcast[0] = threadIdx.x;
+    sh.bcast[1] = inc - mine;
   }
   __syncthreads();
   seg = (int)sh.bcast[0];
   before = sh.bcast[1];
-  __syncthreads();
 }
 
 // One wavefront: index of the element of its 4-per-lane values whose running sum first exceeds
@@ -451,20 +467,28 @@ __device__ inline int resolve_in_segment(const unsigned long long (&v)[4], unsig
   return found;
 }
 
-// First sweep on `parts` workgroups per row: maximum of the scaled logits over tiles
+// The parts' common words of a row (SampleRows::part_max)
+__device__ inline unsigned* meeting_words(const SampleRows& a, int r) {
+  return (unsigned*)a.part_max + (long long)r * kSampleHead + kSampleParts;
+}
+
+// First launch, `parts` workgroups per row: maximum of the scaled logits over tiles
 // blockIdx.x, blockIdx.x + parts, ...
-__global__ __launch_bounds__(SAMP_T, 8) void sample_max_kernel(SampleRows a, int vocab, int parts) {
+__global__ __launch_bounds__(SAMP_T, 8) void sample_max_kernel(SampleRows a, int vocab, RowShares in) {
+  const int parts = in.parts;
   __shared__ SampShared sh;
   const int tid = threadIdx.x, r = blockIdx.y;
   const float* row = a.logits + (long long)(a.logits_row ? a.logits_row[r] : r) * vocab;
   const float inv_t = row_inv_temp(a, r);
   float m = -INFINITY;
-  RowTiles<4>(row, vocab, blockIdx.x, parts).each([&](int, const Logit4& z) {  // an id taken twice changes no maximum
+  RowTiles<4>(row, vocab, blockIdx.x, in).each([&](int, const Logit4& z) {  // an id taken twice changes no maximum
 #pragma unroll
     for (int e = 0; e < 4; ++e) m = fmaxf(m, scaled_logit(z.v[e], inv_t));
   });
   m = block_max(m, sh);
-  if (tid == 0) a.part_max[(long long)r * kSampleParts + blockIdx.x] = m;
+  if (tid == 0) a.part_max[(long long)r * kSampleHead + blockIdx.x] = m;
+  // the words the parts meet at, and behind them the row's random word: from host memory it takes the draw 2 us
+  if (blockIdx.x == 0 && tid < kSampleHead - kSampleParts) meeting_words(a, r)[tid] = tid < kMeetWords || !a.uniforms ? 0u : a.uniforms[r];
   if (a.nucleus && row_has_nucleus(a, r, vocab))
     for (int i = blockIdx.x * SAMP_T + tid; i < kNucleusHist; i += parts * SAMP_T)
       a.nucleus[(long long)r * kNucleusScratch + i] = 0ull;
@@ -473,30 +497,7 @@ __global__ __launch_bounds__(SAMP_T, 8) void sample_max_kernel(SampleRows a, int
 // one part per lane: their loads go out together, and wave_max joins them
 __device__ inline float row_part_max(const SampleRows& a, int r, int parts) {
   static_assert(kSampleParts <= WAVE, "one part per lane");
-  return a.part_max[(long long)r * kSampleParts + min((int)threadIdx.x & 63, parts - 1)];
-}
-
-// Second sweep on `parts` workgroups per row: the weights of the same tiles, one sum per
-// 256-id segment; rows with a nucleus: histogram 0.  Bound by the arithmetic, some 35 instructions per id; the first
-// tiles are requested before the maximum is known.
-__global__ __launch_bounds__(SAMP_T, 8) void sample_segments_kernel(SampleRows a, int vocab, int parts) {
-  __shared__ SampShared sh;
-  const int tid = threadIdx.x, r = blockIdx.y;
-  const float* row = a.logits + (long long)(a.logits_row ? a.logits_row[r] : r) * vocab;
-  const float inv_t = row_inv_temp(a, r);
-  const int n_seg = (vocab + 255) >> 8;
-  const float part = row_part_max(a, r, parts);
-  const RowTiles<4> tiles(row, vocab, blockIdx.x, parts);
-  const float m = wave_max(part);
-  if (a.nucleus && row_has_nucleus(a, r, vocab)) {
-    nucleus_histogram(tiles, inv_t, m, 0, 0u, sh);
-    if (tid < kNucleusBins0 && sh.hist[tid]) atomicAdd(a.nucleus + (long long)r * kNucleusScratch + tid, sh.hist[tid]);
-    return;
-  }
-  tiles.each([&](int i0, const Logit4& z) {
-    const unsigned long long ws = wave_total_weights(weight4(z, i0, vocab, inv_t, m));
-    if ((tid & 63) == 0 && i0 >> 8 < n_seg) a.seg_sums[(long long)r * kSampleSegments + (i0 >> 8)] = ws;
-  });
+  return a.part_max[(long long)r * kSampleHead + min((int)threadIdx.x & 63, parts - 1)];
 }
 
 // What lanes of a wavefront wrote to LDS before it, others read after it.  (Its LDS accesses are carried out in order, so
@@ -511,7 +512,7 @@ __device__ inline void wave_lds_fence() {
 __device__ inline int nucleus_listed(int parts) { return min(2048, kNucleusListed / parts); }
 // Did a part of row r find more ids in its bin than it could list?  Every lane takes a part's count.
 __device__ inline bool nucleus_overflow(const unsigned long long* scratch, int parts) {
-  const unsigned n = ((const unsigned*)(scratch + kNucleusCounts))[min((int)threadIdx.x & 63, parts - 1)];
+  const unsigned n = load_device((const unsigned*)(scratch + kNucleusCounts) + min((int)threadIdx.x & 63, parts - 1));
   return __any(n > (unsigned)nucleus_listed(parts));
 }
 
@@ -527,231 +528,30 @@ __device__ inline bool nucleus_is_flat(const NucleusState& st, int parts) {
   return (float)st.here > __uint_as_float((st.prefix << 19) & 0x7f800000u) * ((float)parts * room * room);
 }
 
-// The third sweep, only for rows with a nucleus: histogram 1, the segments' weights above the bin that histogram 0
-// names, and the list of its ids; of flat rows histogram 1 alone, and every part says that its list overflowed.  What a
-// workgroup needs is requested at once, the histogram before the logits since loads return in order.  One id in eight
-// or so can be at or above the bin: a wavefront queues those in LDS and computes their weights 64 at a time.
-// 64 rows x 151936 ids: see launch_sample.
-__global__ __launch_bounds__(SAMP_T, 8) void sample_list_kernel(SampleRows a, int vocab, int parts) {
-  __shared__ SampShared sh;
-  __shared__ uint2 queue[SAMP_T / WAVE][256 + WAVE];  // (logit, id)
-  __shared__ uint2 list[2048];  // (key, id)
-  __shared__ unsigned listed;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = blockIdx.y;
-  if (!row_has_nucleus(a, r, vocab)) return;  // uniform
-  const float* row = a.logits + (long long)(a.logits_row ? a.logits_row[r] : r) * vocab;
-  const float inv_t = row_inv_temp(a, r), top_p = row_top_p(a, r);
-  unsigned long long* scratch = a.nucleus + (long long)r * kNucleusScratch;
-  const float part = row_part_max(a, r, parts);
-  const unsigned long long h0 = nucleus_bin_from_top(scratch, 0);
-  const RowTiles<4> tiles(row, vocab, blockIdx.x, parts);
-  const float m = wave_max(part);
-  sh.hist[tid] = sh.vals[tid] = 0ull;
-  if (tid == 0) listed = 0u;
-  NucleusState st{};
-  nucleus_descend(h0, 0, top_p, st, sh);  // (its barriers stand between the two lines above and the sweep)
-
-  const unsigned room = (unsigned)nucleus_listed(parts);
-  if (nucleus_is_flat(st, parts)) {
-    nucleus_histogram(tiles, inv_t, m, 1, st.prefix, sh);
-    if (sh.hist[tid]) atomicAdd(scratch + kNucleusBins0 + tid, sh.hist[tid]);
-    if (tid == 0) ((unsigned*)(scratch + kNucleusCounts))[blockIdx.x] = room + 1u;
-    return;
-  }
-  const int n_seg = (vocab + 255) >> 8;
-  // As in nucleus_histogram no weight of the bin is found below some t, and so below some logit: t's d + m over
-  // 1 / T, lowered by more than the four roundings between a logit and its t add up to.  (No number where there is no
-  // finite maximum: no id passes, and none has a weight.)
-  const float d_lo = (log2f(__uint_as_float(st.prefix << 19)) - 40.02f) * 0.6931472f;
-  const float z_lo = (m + d_lo - 0x1p-19f * (fabsf(m) + fabsf(d_lo))) / inv_t;
-  const float lowest = z_lo - 0x1p-19f * fabsf(z_lo);
-  uint2* mine = queue[wave];
-  int queued = 0;
-  auto weigh = [&](const uint2& u, bool full) {
-    const unsigned key = fixexp_key(shifted(scaled_logit(__uint_as_float(u.x), inv_t), m)), prefix = key >> 19, seg = u.y >> 8;
-    const WeightParts w = weight_parts(__uint_as_float(key));
-    const bool above = prefix > st.prefix;
-    if (full && __all(seg == (unsigned)__builtin_amdgcn_readfirstlane((int)seg))) {
-      // ids of one segment, as in flat rows: 64 atomics on one word are one after the other
-      const unsigned long long sum = wave_total_weights(WeightParts{above ? w.hi : 0u, above ? w.lo : 0u});
-      if (lane == 0) atomicAdd(&sh.vals[seg], sum);
-    } else if (above) {
-      atomicAdd(&sh.vals[seg], parts_sum(w));
-    }
-    if (prefix == st.prefix) {
-      atomicAdd(&sh.hist[nucleus_bin(key, 1)], parts_sum(w));
-      const unsigned to = atomicAdd(&listed, 1u);
-      if (to < room) list[to] = make_uint2(key, u.y);
-    }
-  };
-  tiles.each([&](int i0, const Logit4& z) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const bool in = z.v[e] >= lowest && i0 + e < vocab;
-      const unsigned long long lanes = __ballot(in);
-      const int to = queued + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)lanes, 0u));
-      if (in) mine[to] = make_uint2(__float_as_uint(z.v[e]), (unsigned)(i0 + e));
-      queued += __popcll(lanes);
-    }
-    wave_lds_fence();
-    while (queued >= WAVE) {
-      queued -= WAVE;
-      weigh(mine[queued + lane], true);
-    }
-    wave_lds_fence();
-  });
-  if (lane < queued) weigh(mine[lane], false);
-  __syncthreads();
-  if (tid < n_seg && (tid >> 4) % parts == (int)blockIdx.x) a.seg_sums[(long long)r * kSampleSegments + tid] = sh.vals[tid];
-  if (sh.hist[tid]) atomicAdd(scratch + kNucleusBins0 + tid, sh.hist[tid]);
-  if (tid == 0) ((unsigned*)(scratch + kNucleusCounts))[blockIdx.x] = listed;
-  uint2* out = (uint2*)(scratch + kNucleusList) + blockIdx.x * room;
-  for (unsigned q = tid; q < min(listed, room); q += SAMP_T) out[q] = list[q];
-}
-
-// The sweeps of rows whose list overflowed, `parts` workgroups per row: histogram 2 (every workgroup finds the
-// bins of the histograms before it again, from a few KiB), then the segments.
-template <int LEVEL>
-__global__ __launch_bounds__(SAMP_T, 8) void sample_nucleus_kernel(SampleRows a, int vocab, int parts) {
-  __shared__ SampShared sh;
-  const int tid = threadIdx.x, r = blockIdx.y;
-  unsigned long long* scratch = a.nucleus + (long long)r * kNucleusScratch;
-  if (!row_has_nucleus(a, r, vocab) || !nucleus_overflow(scratch, parts)) return;  // uniform
-  const float* row = a.logits + (long long)(a.logits_row ? a.logits_row[r] : r) * vocab;
-  const float inv_t = row_inv_temp(a, r), top_p = row_top_p(a, r);
-  const float part = row_part_max(a, r, parts);
-  const unsigned long long h0 = nucleus_bin_from_top(scratch, 0);
-  const unsigned long long h1 = nucleus_bin_from_top(scratch + kNucleusBins0, 1);
-  const unsigned long long h2 = LEVEL > 2 ? nucleus_bin_from_top(scratch + kNucleusBins0 + 1024, 2) : 0ull;
-  const RowTiles<4> tiles(row, vocab, blockIdx.x, parts);
-  const float m = wave_max(part);
-  NucleusState st{};
-  nucleus_descend(h0, 0, top_p, st, sh);
-  nucleus_descend(h1, 1, top_p, st, sh);
-  if constexpr (LEVEL == 2) {
-    nucleus_histogram(tiles, inv_t, m, 2, st.prefix, sh);
-    if (tid < nucleus_bins(2) && sh.hist[tid]) atomicAdd(scratch + kNucleusBins0 + 1024 + tid, sh.hist[tid]);
-  } else {
-    nucleus_descend(h2, 2, top_p, st, sh);
-    unsigned* ties = (unsigned*)(scratch + kNucleusHist);
-    if (blockIdx.x == 0 && tid == 0) {  // for the selection
-      unsigned long long* found = scratch + kNucleusFound;
-      found[0] = st.sum;
-      found[1] = st.theta;
-      found[2] = st.above;
-      found[3] = st.prefix;
-    }
-    nucleus_segments(tiles, inv_t, m, st.prefix, [&](int seg, unsigned long long above, unsigned n) {
-      a.seg_sums[(long long)r * kSampleSegments + seg] = above;
-      ties[seg] = n;
-    });
-  }
-}
-
-// parts = 0: this kernel sweeps the row itself; else it starts from what the kernels above left
-__global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab, int parts) {
-  __shared__ SampShared sh;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = blockIdx.x;
-  const float* row = a.logits + (long long)(a.logits_row ? a.logits_row[r] : r) * vocab;
-  const float inv_t = row_inv_temp(a, r);
-  const int n_seg = (vocab + 255) >> 8;
-  const bool nucleus = row_has_nucleus(a, r, vocab);
-
-  float m = -INFINITY;
-  unsigned long long S = 0;
-  NucleusState st{};
-  if (parts) {
-    m = wave_max(row_part_max(a, r, parts));
-    if (nucleus) {
-      const unsigned long long* scratch = a.nucleus + (long long)r * kNucleusScratch;
-      const unsigned* counts = (const unsigned*)(scratch + kNucleusCounts);
-      const uint2* list = (const uint2*)(scratch + kNucleusList);
-      const int room = nucleus_listed(parts);
-      const float top_p = row_top_p(a, r);
-      // all that is needed as a rule, requested at once: the first 64 ids of this wavefront's part come before their number
-      const unsigned long long h0 = nucleus_bin_from_top(scratch, 0), h1 = nucleus_bin_from_top(scratch + kNucleusBins0, 1);
-      const unsigned long long sum = a.seg_sums[(long long)r * kSampleSegments + min(tid, n_seg - 1)];
-      const int n_part = wave < parts ? (int)counts[wave] : 0;
-      static_assert(kNucleusListed / kSampleParts >= WAVE, "a part has room for 64 ids");
-      const uint2 first = list[min(wave, parts - 1) * room + lane];
-      if (!nucleus_overflow(scratch, parts)) {
-        sh.hist[tid] = tid < n_seg ? sum : 0ull;
-        sh.vals[tid] = 0ull;
-        sh.ties[tid] = 0u;
-        nucleus_descend(h0, 0, top_p, st, sh);
-        nucleus_descend(h1, 1, top_p, st, sh);
-        auto each_listed = [&](auto&& f) {  // a wavefront takes the parts wave, wave + 16, ...
-          if (lane < n_part) f(first);
-          for (int i = WAVE + lane; i < n_part; i += WAVE) f(list[wave * room + i]);
-          for (int q = wave + SAMP_T / WAVE; q < parts; q += SAMP_T / WAVE)
-            for (int i = lane; i < (int)counts[q]; i += WAVE) f(list[q * room + i]);
-        };
-        each_listed([&](const uint2& u) {
-          if (nucleus_prefix(u.x, 2) == st.prefix) atomicAdd(&sh.vals[nucleus_bin(u.x, 2)], key_weight(u.x));
-        });
-        __syncthreads();
-        nucleus_descend(nucleus_bin_from_top(sh.vals, 2), 2, top_p, st, sh);
-        S = st.sum;
-        each_listed([&](const uint2& u) {
-          if (u.x > st.prefix) atomicAdd(&sh.hist[u.y >> 8], key_weight(u.x));
-          else if (u.x == st.prefix) atomicAdd(&sh.ties[u.y >> 8], 1u);
-        });
-      } else {
-        S = scratch[kNucleusFound];
-        st = NucleusState{S, scratch[kNucleusFound + 1], scratch[kNucleusFound + 2], (unsigned)scratch[kNucleusFound + 3]};
-        const unsigned* ties = (const unsigned*)(scratch + kNucleusHist);
-        if (tid < n_seg) {
-          sh.hist[tid] = sum;
-          sh.ties[tid] = ties[tid];
-        }
-      }
-    } else {
-      unsigned long long local = 0;
-      if (tid < n_seg) {
-        local = a.seg_sums[(long long)r * kSampleSegments + tid];
-        sh.vals[tid] = local;
-      }
-      S = block_sum_u64(local, sh);
-    }
-  } else {
-    const RowTiles<0> tiles(row, vocab, 0, 1);
-    tiles.each([&](int, const Logit4& z) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) m = fmaxf(m, scaled_logit(z.v[e], inv_t));
-    });
-    m = block_max(m, sh);
-    if (nucleus) {
-      const float top_p = row_top_p(a, r);
-      for (int level = 0; level < 3; ++level) {
-        nucleus_histogram(tiles, inv_t, m, level, st.prefix, sh);
-        nucleus_descend(nucleus_bin_from_top(sh.hist, level), level, top_p, st, sh);
-      }
-      S = st.sum;
-      nucleus_segments(tiles, inv_t, m, st.prefix, [&](int seg, unsigned long long above, unsigned n) {
-        sh.hist[seg] = above;
-        sh.ties[seg] = n;
-      });
-    } else {
-      // all weights, one sum per segment
-      unsigned long long local = 0;
-      tiles.each([&](int i0, const Logit4& z) {
-        const WeightParts mine = weight4(z, i0, vocab, inv_t, m);
-        local += parts_sum(mine);
-        const unsigned long long ws = wave_total_weights(mine);
-        if (lane == 0 && i0 >> 8 < n_seg) sh.vals[i0 >> 8] = ws;
-      });
-      S = block_sum_u64(local, sh);  // also orders the writes to sh.vals
-    }
-  }
-
+// What the draw from a row starts with: weights, and with a nucleus its end (st) and, in sh.hist and sh.ties, per segment
+// the weight above tau and the ids at tau; without one the segments' weights in sh.vals.  word: the row's random word.
+// A chain of round trips and barriers: in a draw the logarithm of the sum is another wavefront's, and the token's logit comes
+// from the one that resolves it.
+__device__ inline void select_token(const SampleRows& a, int r, const float* row, int vocab, float inv_t, float m,
+                                    unsigned long long S, const NucleusState& st, bool nucleus, const unsigned* word, SampShared& sh) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n_seg = (vocab + 255) >> 8;
+  const unsigned x_given = word ? *word : 0u;
   int token = a.forced ? a.forced[r] : -1;
-  if ((unsigned)token >= (unsigned)vocab) {  // nothing forced (an id outside the vocabulary forces nothing)
+  const bool given = (unsigned)token < (unsigned)vocab;
+  const int who = given ? 0 : SAMP_T - 1;
+  float log_sum = 0.f, logit = 0.f;
+  if (tid == who) {
+    if (given) logit = row[token];
+    log_sum = (float)(log((double)S) - 40.0 * 0.693147180559945309417);
+    if (!given) sh.log_sum = log_sum;
+  }
+  if (!given) {  // nothing forced (an id outside the vocabulary forces nothing)
     // nucleus membership: key above tau's, or at tau among the first k_ties ids there
     const unsigned tau_key = st.prefix;
-    unsigned long long s_n = S;
+    unsigned long long s_n = S, of_segment;
     unsigned k_ties = 0;
+    __syncthreads();
     if (nucleus) {
-      __syncthreads();
       const unsigned long long tau = key_weight(tau_key);
       k_ties = tau ? (unsigned)((st.theta - st.above + tau - 1) / tau) : 0u;  // theta > above: tau's bin was needed to reach it
       s_n = st.above + k_ties * tau;
@@ -759,22 +559,21 @@ __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab,
       unsigned long long all;
       const unsigned before = (unsigned)block_scan_u64(mine, sh, all) - mine;
       const unsigned in = before < k_ties ? min(mine, k_ties - before) : 0u;
-      if (tid < n_seg) {
-        sh.vals[tid] = sh.hist[tid] + in * tau;
-        sh.ties[tid] = in;  // ids at tau that are in, per segment
-      }
-      __syncthreads();
+      of_segment = tid < n_seg ? sh.hist[tid] + in * tau : 0ull;
+      sh.ties[tid] = in;  // ids at tau that are in, per segment
+    } else {
+      of_segment = tid < n_seg ? sh.vals[tid] : 0ull;
     }
     // inverse CDF in ascending id order over the nucleus
-    const unsigned x = a.uniforms ? a.uniforms[r]
-                                  : philox_word0(a.seed, (unsigned long long)a.sample_id[r], (unsigned)a.step[r]);
+    const unsigned x = word ? x_given : philox_word0(a.seed, (unsigned long long)a.sample_id[r], (unsigned)a.step[r]);
     const unsigned long long R = (s_n >> 32) * x + (((s_n & 0xffffffffull) * x) >> 32);
     int seg;
     unsigned long long before;
-    find_segment(sh, n_seg, R, seg, before);
+    find_segment(sh, of_segment, R, seg, before);
     if (wave == 0) {
       const int i0 = seg * 256 + lane * 4;
-      const Key4 q = keys4(logits4(request4<true>(row, i0, vocab), i0, vocab), i0, vocab, inv_t, m);
+      const Logit4 z = logits4(request4<true>(row, i0, vocab), i0, vocab);
+      const Key4 q = keys4(z, i0, vocab, inv_t, m);
       unsigned long long v[4];
       if (nucleus) {
         unsigned at_tau = 0;
@@ -798,19 +597,23 @@ __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab,
         for (int e = 0; e < 4; ++e) v[e] = key_weight(q.k[e]);
       }
       const int idx = resolve_in_segment(v, R - before, lane);
-      if (lane == 0) sh.bcast[0] = (unsigned long long)(seg * 256 + idx);
+      if (idx >= 0 && lane == idx >> 2) sh.logit = (idx & 3) == 0 ? z.v[0] : (idx & 3) == 1 ? z.v[1] : (idx & 3) == 2 ? z.v[2] : z.v[3];
+      token = min(max(seg * 256 + idx, 0), vocab - 1);  // (no id is found in a row without weights)
+      if (lane == 0 && idx < 0) sh.logit = row[token];
     }
     __syncthreads();
-    token = min(max((int)sh.bcast[0], 0), vocab - 1);  // (no id is found in a row without weights)
+    logit = sh.logit;
+    log_sum = sh.log_sum;
   }
   if (tid == 0) {
-    float d = shifted(scaled_logit(row[token], inv_t), m);
+    const float d = shifted(scaled_logit(logit, inv_t), m);
     a.tokens[r] = token;
-    a.logprobs[r] = d - (float)(log((double)S) - 40.0 * 0.693147180559945309417);
+    const float logprob = d - log_sum;
+    a.logprobs[r] = logprob;
     if (a.weight_sums) a.weight_sums[r] = S;
     if (a.host_tokens) {
       a.host_tokens[r] = token;
-      a.host_logprobs[r] = a.logprobs[r];
+      a.host_logprobs[r] = logprob;
     }
     const int sl = a.row_slot ? a.row_slot[r] : -1;
     if (sl >= 0) {
@@ -824,31 +627,330 @@ __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab,
   }
 }
 
-// Large vocabularies with scratch at hand: the sweeps of a row on several workgroups (about 512 in all),
-// then the selection; else everything in one workgroup per row.
-// 64 rows x 151936 ids, top_p 0.9, with 2 us of launch each: 8.8 + 14.2 us for maximum and histogram 0, 14.9 us for
-// the sweep that lists, 4.3 + 3.3 us for the two that find nothing to do, 12.2 us for the selection: 67 us per
-// call of rollout_sample.  With histograms 1 and 2 and the segments above tau in three full sweeps and weights by
-// 64-bit shifts 94 us (8.1 + 16.3 + 12.9 + 12.5 + 24.7 + 9.1); one workgroup per row that searched tau bit by bit 1809 us.
+
+// Where the parts of a row meet between the phases of one launch: count (words 4 phase) and `left` (the 64 bits behind).
+// Every part does its share and reports, and the one that reports last is `last`; the others look up to `patience` times whether
+// all have reported (below 0: they end).  A part waits only so long: if the others have not reported by then - their workgroups may not even run, for all it
+// knows - it leaves its share of the phases to come to the last one and ends.  So no wait needs another workgroup
+// to make progress, and every share is done once: the last one closes `left` as it takes what is in it, and
+// a part that finds it closed keeps its own.  What the parts leave for each other goes by load_device, store_device
+// and atomics, and is there when they report.  Returns the shares to go on with; 0: this workgroup is done.
+constexpr unsigned long long kLeftClosed = 1ull << 63;
+__device__ inline unsigned long long meet(unsigned* words, int phase, int parts, unsigned long long shares, int patience, bool& last,
+                                          SampShared& sh) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned* count = words + 4 * phase;
+    unsigned long long* left = (unsigned long long*)(words + 4 * phase + 2);
+    const int n = __popcll(shares);
+    int seen = (int)__hip_atomic_fetch_add(count, (unsigned)n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + n;
+    const bool is_last = seen == parts;
+    if (is_last) {
+      shares |= __hip_atomic_exchange(left, kLeftClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else if (patience >= 0) {
+      for (int spin = 0; spin < patience && seen != parts; ++spin) {
+        __builtin_amdgcn_s_sleep(1);
+        seen = (int)load_device(count);
+      }
+      if (seen != parts && !(__hip_atomic_fetch_or(left, shares, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kLeftClosed)) shares = 0ull;
+    } else {
+      shares = 0ull;
+    }
+    sh.bcast[0] = shares;
+    sh.bcast[1] = is_last;
+  }
+  __syncthreads();
+  shares = read_lane_u64(sh.bcast[0], 0);
+  last = sh.bcast[1] != 0ull;
+  __syncthreads();
+  return shares;
+}
+
+// One part's share of the sweep that lists: histogram 1, the segments' weights above the bin that histogram 0
+// names, and the list of its ids; of flat rows histogram 1 alone, and the part says that its list overflowed.
+// One id in eight or so can be at or above the bin: a wavefront queues those in LDS and computes their
+// weights 64 at a time.  64 rows x 151936 ids: see launch_sample.
+struct ListShared {
+  uint2 queue[SAMP_T / WAVE][256 + WAVE];  // (logit, id)
+  uint2 list[2048];                        // (key, id)
+  unsigned listed;
+};
+__device__ inline void list_share(const SampleRows& a, int r, const RowTiles<4>& tiles, int part, int parts, bool flat, float inv_t,
+                                  float m, const NucleusState& st, unsigned long long* scratch, SampShared& sh, ListShared& ls) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, vocab = tiles.vocab;
+  const unsigned room = (unsigned)nucleus_listed(parts);
+  unsigned* counts = (unsigned*)(scratch + kNucleusCounts);
+  if (flat) {
+    nucleus_histogram(tiles, inv_t, m, 1, st.prefix, sh);
+    if (sh.hist[tid]) atomicAdd(scratch + kNucleusBins0 + tid, sh.hist[tid]);
+    if (tid == 0) store_device(counts + part, room + 1u);
+    return;
+  }
+  sh.hist[tid] = sh.vals[tid] = 0ull;
+  if (tid == 0) ls.listed = 0u;
+  __syncthreads();
+  const int n_seg = (vocab + 255) >> 8;
+  // As in nucleus_histogram no weight of the bin is found below some t, and so below some logit: t's d + m over
+  // 1 / T, lowered by more than the four roundings between a logit and its t add up to.  (No number where there is no
+  // finite maximum: no id passes, and none has a weight.)
+  const float d_lo = (log2f(__uint_as_float(st.prefix << 19)) - 40.02f) * 0.6931472f;
+  const float z_lo = (m + d_lo - 0x1p-19f * (fabsf(m) + fabsf(d_lo))) / inv_t;
+  const float lowest = z_lo - 0x1p-19f * fabsf(z_lo);
+  uint2* mine = ls.queue[wave];
+  int queued = 0;
+  auto weigh = [&](const uint2& u, bool full) {
+    const unsigned key = fixexp_key(shifted(scaled_logit(__uint_as_float(u.x), inv_t), m)), prefix = key >> 19, seg = u.y >> 8;
+    const WeightParts w = weight_parts(__uint_as_float(key));
+    const bool above = prefix > st.prefix;
+    if (full && __all(seg == (unsigned)__builtin_amdgcn_readfirstlane((int)seg))) {
+      // ids of one segment, as in flat rows: 64 atomics on one word are one after the other
+      const unsigned long long sum = wave_total_weights(WeightParts{above ? w.hi : 0u, above ? w.lo : 0u});
+      if (lane == 0) atomicAdd(&sh.vals[seg], sum);
+    } else if (above) {
+      atomicAdd(&sh.vals[seg], parts_sum(w));
+    }
+    if (prefix == st.prefix) {
+      atomicAdd(&sh.hist[nucleus_bin(key, 1)], parts_sum(w));
+      const unsigned to = atomicAdd(&ls.listed, 1u);
+      if (to < room) ls.list[to] = make_uint2(key, u.y);
+    }
+  };
+  tiles.each([&](int i0, const Logit4& z) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool in = z.v[e] >= lowest && i0 + e < vocab;
+      const unsigned long long lanes = __ballot(in);
+      const int to = queued + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)lanes, 0u));
+      if (in) mine[to] = make_uint2(__float_as_uint(z.v[e]), (unsigned)(i0 + e));
+      queued += __popcll(lanes);
+    }
+    wave_lds_fence();
+    while (queued >= WAVE) {
+      queued -= WAVE;
+      weigh(mine[queued + lane], true);
+    }
+    wave_lds_fence();
+  });
+  if (lane < queued) weigh(mine[lane], false);
+  __syncthreads();
+  if (tid < n_seg && tiles.in.part_of_segment(tid) == part) store_device(a.seg_sums + (long long)r * kSampleSegments + tid, sh.vals[tid]);
+  if (sh.hist[tid]) atomicAdd(scratch + kNucleusBins0 + tid, sh.hist[tid]);
+  if (tid == 0) store_device(counts + part, ls.listed);
+  unsigned long long* out = scratch + kNucleusList + part * room;
+  for (unsigned q = tid; q < min(ls.listed, room); q += SAMP_T) store_device(out + q, (unsigned long long)ls.list[q].y << 32 | ls.list[q].x);
+  __syncthreads();  // ls and sh are free again
+}
+
+// Second launch, `parts` workgroups per row: the sweeps behind the maximum and the draw, in phases between which the
+// parts meet.  Without a nucleus one sum per 256-id segment, and the last part draws.  With one: histogram 0; the sweep that lists;
+// then, unless a part found more ids than it could list, the last part draws, else histogram 2, the
+// segments, and the last part draws.  (In flat rows every part says so: nucleus_is_flat.)
+// What bounds it: the arithmetic of the weights, some 35 instructions per id and sweep.  A part's first tiles are requested before
+// it knows what it needs to know of the phase before.  As launches of their own the phases cost 2 us each to start, two of
+// them for nothing in ordinary rows, and their last workgroups' time: see launch_sample.
+// NUCLEUS: some rows may have one.
+template <bool NUCLEUS>
+__global__ __launch_bounds__(SAMP_T, 8) void sample_rest_kernel(SampleRows a, int vocab, RowShares in) {
+  const int parts = in.parts;
+  __shared__ SampShared sh;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = blockIdx.y;
+  const float* row = a.logits + (long long)(a.logits_row ? a.logits_row[r] : r) * vocab;
+  const float inv_t = row_inv_temp(a, r);
+  const int n_seg = (vocab + 255) >> 8;
+  const float part_max = row_part_max(a, r, parts);
+  unsigned long long shares = 1ull << blockIdx.x;
+  unsigned* words = meeting_words(a, r);
+  unsigned long long* seg_sums = a.seg_sums + (long long)r * kSampleSegments;
+  bool last;
+  float m;
+  NucleusState st{};
+  if (!NUCLEUS || !row_has_nucleus(a, r, vocab)) {  // uniform
+    {
+      const RowTiles<4> tiles(row, vocab, blockIdx.x, in);
+      m = wave_max(part_max);
+      tiles.each([&](int i0, const Logit4& z) {
+        const unsigned long long ws = wave_total_weights(weight4(z, i0, vocab, inv_t, m));
+        if (lane == 0 && i0 >> 8 < n_seg) store_device(seg_sums + (i0 >> 8), ws);
+      });
+    }
+    if (!meet(words, 0, parts, shares, -1, last, sh)) return;
+    unsigned long long local = 0;
+    if (tid < n_seg) {
+      local = load_device(seg_sums + tid);
+      sh.vals[tid] = local;
+    }
+    select_token(a, r, row, vocab, inv_t, m, block_sum_u64(local, sh), st, false, a.uniforms ? words + kMeetWords : nullptr, sh);
+    return;
+  }
+  if constexpr (NUCLEUS) {
+    __shared__ ListShared ls;
+    unsigned long long* scratch = a.nucleus + (long long)r * kNucleusScratch;
+    {
+      const RowTiles<4> tiles(row, vocab, blockIdx.x, in);
+      m = wave_max(part_max);
+      nucleus_histogram(tiles, inv_t, m, 0, 0u, sh);
+      if (tid < kNucleusBins0 && sh.hist[tid]) atomicAdd(scratch + tid, sh.hist[tid]);
+    }
+    const float top_p = row_top_p(a, r);
+    // f(part, its tiles) for every share; `before` while the first one's tiles are on their way
+    auto each_share = [&](auto&& before, auto&& f) {
+      int part = __ffsll((long long)shares) - 1;
+      bool first = true;
+      for (unsigned long long rest = shares; rest; rest &= rest - 1) {
+        part = __ffsll((long long)rest) - 1;
+        const RowTiles<4> tiles(row, vocab, part, in);
+        if (first) before();
+        first = false;
+        f(part, tiles);
+      }
+    };
+    shares = meet(words, 0, parts, shares, a.patience, last, sh);
+    if (!shares) return;
+    bool flat = false;
+    {
+      const unsigned long long h0 = nucleus_bin_from_top<true>(scratch, 0);
+      each_share(
+          [&] {
+            nucleus_descend(h0, 0, top_p, st, sh);
+            flat = nucleus_is_flat(st, parts);
+          },
+          [&](int part, const RowTiles<4>& tiles) { list_share(a, r, tiles, part, parts, flat, inv_t, m, st, scratch, sh, ls); });
+    }
+    shares = meet(words, 1, parts, shares, a.patience, last, sh);
+    if (!shares) return;
+    // all that is needed as a rule, requested at once: the first 64 ids of this wavefront's part come before their number
+    const unsigned long long h1 = nucleus_bin_from_top<true>(scratch + kNucleusBins0, 1);
+    const bool overflow = nucleus_overflow(scratch, parts);
+    if (!overflow && !last) return;
+    if (!overflow) {
+      const unsigned* counts = (const unsigned*)(scratch + kNucleusCounts);
+      const unsigned long long* list = scratch + kNucleusList;
+      const int room = nucleus_listed(parts);
+      const unsigned long long sum = load_device(seg_sums + min(tid, n_seg - 1));
+      const int n_part = wave < parts ? (int)load_device(counts + wave) : 0;
+      static_assert(kNucleusListed / kSampleParts >= WAVE, "a part has room for 64 ids");
+      const unsigned long long first = load_device(list + min(wave, parts - 1) * room + lane);
+      sh.hist[tid] = tid < n_seg ? sum : 0ull;
+      sh.vals[tid] = 0ull;
+      sh.ties[tid] = 0u;
+      nucleus_descend(h1, 1, top_p, st, sh);
+      auto each_listed = [&](auto&& f) {  // a wavefront takes the parts wave, wave + 16, ...
+        if (lane < n_part) f((unsigned)first, (unsigned)(first >> 32));
+        auto from = [&](int q, int i) {
+          const unsigned long long u = load_device(list + q * room + i);
+          f((unsigned)u, (unsigned)(u >> 32));
+        };
+        for (int i = WAVE + lane; i < n_part; i += WAVE) from(wave, i);
+        for (int q = wave + SAMP_T / WAVE; q < parts; q += SAMP_T / WAVE)
+          for (int i = lane, n = (int)load_device(counts + q); i < n; i += WAVE) from(q, i);
+      };
+      each_listed([&](unsigned key, unsigned) {
+        if (nucleus_prefix(key, 2) == st.prefix) atomicAdd(&sh.vals[nucleus_bin(key, 2)], key_weight(key));
+      });
+      __syncthreads();
+      nucleus_descend(nucleus_bin_from_top<false>(sh.vals, 2), 2, top_p, st, sh);
+      each_listed([&](unsigned key, unsigned id) {
+        if (key > st.prefix) atomicAdd(&sh.hist[id >> 8], key_weight(key));
+        else if (key == st.prefix) atomicAdd(&sh.ties[id >> 8], 1u);
+      });
+      select_token(a, r, row, vocab, inv_t, m, st.sum, st, true, a.uniforms ? words + kMeetWords : nullptr, sh);
+      return;
+    }
+    // the ids did not fit
+    {
+      each_share([&] { nucleus_descend(h1, 1, top_p, st, sh); },
+                 [&](int, const RowTiles<4>& tiles) {
+                   nucleus_histogram(tiles, inv_t, m, 2, st.prefix, sh);
+                   if (tid < nucleus_bins(2) && sh.hist[tid]) atomicAdd(scratch + kNucleusBins0 + 1024 + tid, sh.hist[tid]);
+                   __syncthreads();
+                 });
+    }
+    shares = meet(words, 2, parts, shares, a.patience, last, sh);
+    if (!shares) return;
+    unsigned* ties = (unsigned*)(scratch + kNucleusHist);
+    {
+      const unsigned long long h2 = nucleus_bin_from_top<true>(scratch + kNucleusBins0 + 1024, 2);
+      each_share([&] { nucleus_descend(h2, 2, top_p, st, sh); },
+                 [&](int, const RowTiles<4>& tiles) {
+                   nucleus_segments(tiles, inv_t, m, st.prefix, [&](int seg, unsigned long long above, unsigned n) {
+                     store_device(seg_sums + seg, above);
+                     store_device(ties + seg, n);
+                   });
+                 });
+    }
+    if (!meet(words, 3, parts, shares, -1, last, sh)) return;
+    if (tid < n_seg) {
+      sh.hist[tid] = load_device(seg_sums + tid);
+      sh.ties[tid] = load_device(ties + tid);
+    }
+    select_token(a, r, row, vocab, inv_t, m, st.sum, st, true, a.uniforms ? words + kMeetWords : nullptr, sh);
+  }
+}
+
+// One workgroup per row: small vocabularies, or no scratch.
+__global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab) {
+  __shared__ SampShared sh;
+  const int lane = threadIdx.x & 63, r = blockIdx.x;
+  const float* row = a.logits + (long long)(a.logits_row ? a.logits_row[r] : r) * vocab;
+  const float inv_t = row_inv_temp(a, r);
+  const int n_seg = (vocab + 255) >> 8;
+  const bool nucleus = row_has_nucleus(a, r, vocab);
+  const RowTiles<0> tiles(row, vocab, 0, RowShares(vocab, 1));
+  float m = -INFINITY;
+  tiles.each([&](int, const Logit4& z) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m = fmaxf(m, scaled_logit(z.v[e], inv_t));
+  });
+  m = block_max(m, sh);
+  unsigned long long S;
+  NucleusState st{};
+  if (nucleus) {
+    const float top_p = row_top_p(a, r);
+    for (int level = 0; level < 3; ++level) {
+      nucleus_histogram(tiles, inv_t, m, level, st.prefix, sh);
+      nucleus_descend(nucleus_bin_from_top<false>(sh.hist, level), level, top_p, st, sh);
+    }
+    S = st.sum;
+    nucleus_segments(tiles, inv_t, m, st.prefix, [&](int seg, unsigned long long above, unsigned n) {
+      sh.hist[seg] = above;
+      sh.ties[seg] = n;
+    });
+  } else {
+    // all weights, one sum per segment
+    unsigned long long local = 0;
+    tiles.each([&](int i0, const Logit4& z) {
+      const WeightParts mine = weight4(z, i0, vocab, inv_t, m);
+      local += parts_sum(mine);
+      const unsigned long long ws = wave_total_weights(mine);
+      if (lane == 0 && i0 >> 8 < n_seg) sh.vals[i0 >> 8] = ws;
+    });
+    S = block_sum_u64(local, sh);  // also orders the writes to sh.vals
+  }
+  select_token(a, r, row, vocab, inv_t, m, S, st, nucleus, a.uniforms ? a.uniforms + r : nullptr, sh);
+}
+
+// Large vocabularies with scratch at hand: the sweeps of a row on several workgroups (about 512 in all) and two launches,
+// the maximum and the rest; else everything in one workgroup per row.
+// 64 rows x 151936 ids, top_p 0.9: 9.0 us for the maximum, 41.4 for the rest, of which some 11 are histogram 0, 10 the sweep that
+// lists, 10 the draw and 3 each time the parts meet; 65 us per call of rollout_sample.  In six launches (9.5 + 14.2 + 15.3 +
+// 2.9 + 2.7 + 13.7, where two found nothing to do) 69 us; one row 53 -> 45, 16 rows x 32001 56 -> 44, 64 flat rows
+// (N(0, 0.2)) 100 -> 87, 64 rows without a nucleus 44.5 -> 41; one workgroup per row that searched tau bit by bit 1809 us.
 // The sweeps' arithmetic takes the time: 39 MB of logits pass in 8 us.
 static void launch_sample_rows(const SampleRows& r, int rows, int vocab, hipStream_t s) {
   const int n_tiles = (vocab + 4095) >> 12;
   int parts = 0;
   if (r.part_max && r.seg_sums && (r.nucleus || !r.any_nucleus) && n_tiles >= 8 && vocab <= 256 * kSampleSegments)
-    parts = std::max(2, std::min({n_tiles, kSampleParts, 512 / rows}));
+    parts = std::max(2, std::min({n_tiles, kSampleParts - 1, 512 / rows}));
   if (parts < 2) {
-    sample_kernel<<<rows, SAMP_T, 0, s>>>(r, vocab, 0);
+    sample_kernel<<<rows, SAMP_T, 0, s>>>(r, vocab);
     return;
   }
   const dim3 grid(parts, rows);
-  sample_max_kernel<<<grid, SAMP_T, 0, s>>>(r, vocab, parts);
-  sample_segments_kernel<<<grid, SAMP_T, 0, s>>>(r, vocab, parts);
-  if (r.any_nucleus) {
-    sample_list_kernel<<<grid, SAMP_T, 0, s>>>(r, vocab, parts);
-    sample_nucleus_kernel<2><<<grid, SAMP_T, 0, s>>>(r, vocab, parts);
-    sample_nucleus_kernel<3><<<grid, SAMP_T, 0, s>>>(r, vocab, parts);
-  }
-  sample_kernel<<<rows, SAMP_T, 0, s>>>(r, vocab, parts);
+  const RowShares in(vocab, parts);
+  sample_max_kernel<<<grid, SAMP_T, 0, s>>>(r, vocab, in);
+  if (r.any_nucleus) sample_rest_kernel<true><<<grid, SAMP_T, 0, s>>>(r, vocab, in);
+  else sample_rest_kernel<false><<<grid, SAMP_T, 0, s>>>(r, vocab, in);
 }
 
 void launch_sample(SampleRows r, int rows, int vocab, hipStream_t s) {

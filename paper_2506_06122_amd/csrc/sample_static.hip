@@ -16,8 +16,8 @@ constexpr int kMaxRows = ROLLOUT_SAMPLE_STATIC_MAX_ROWS;
 constexpr int kMaxDevices = 64;
 
 // layout of the scratch array (byte offsets, each a multiple of 256)
-constexpr size_t kOffPartMax = 0;                                                  // float [kMaxRows][kSampleParts]
-constexpr size_t kOffSegSums = kOffPartMax + sizeof(float) * kMaxRows * kSampleParts;  // u64 [kMaxRows][kSampleSegments]
+constexpr size_t kOffPartMax = 0;                                                  // float [kMaxRows][kSampleHead]
+constexpr size_t kOffSegSums = kOffPartMax + sizeof(float) * kMaxRows * kSampleHead;  // u64 [kMaxRows][kSampleSegments]
 constexpr size_t kOffNucleus = kOffSegSums + sizeof(unsigned long long) * kMaxRows * kSampleSegments;  // u64 [kMaxRows][kNucleusScratch]
 constexpr size_t kScratchBytes = kOffNucleus + sizeof(unsigned long long) * kMaxRows * kNucleusScratch;
 static_assert(kOffSegSums % 256 == 0 && kOffNucleus % 256 == 0, "256-byte aligned parts");

@@ -118,3 +118,26 @@ def test_whole_vocabulary_matches_oracle(vocab):
         w = sampler.fixexp_weights(z[r], inv_t)
         assert int(sums[r]) == int(np.sum(w, dtype=np.uint64)), f"row {r}"
         assert int(toks[r]) == sampler.draw(w, sampler.nucleus(w, 1.0), int(x[r])), f"row {r}"
+
+
+@pytest.mark.parametrize("vocab", [28673, 32001, 65536 + 3, 151936, 262144])
+@pytest.mark.parametrize("top_p", [0.5, 0.9, 1.0])
+def test_shares_left_to_the_last(vocab, top_p):
+    """Parts of a row that do not wait for each other leave their shares to the one that finishes last: every phase, with lists
+    and with full sweeps, by one workgroup or by some; and the calls that wait give the same bits, again and again."""
+    import torch
+    import paper_2506_06122_amd as R
+    from paper_2506_06122_amd import binding
+    z = hard_rows(vocab, seed=vocab)
+    z = torch.from_numpy(np.concatenate([z, z[:3]])).cuda()
+    x = workloads.uniform_words(len(z), seed=7)
+    toks, lps, sums = R.rollout_sample(z, 0.8, top_p, x)
+    inv_t = sampler.inv_temperature(0.8)
+    for r in range(len(z)):
+        w = sampler.fixexp_weights(z[r].cpu().numpy(), inv_t)
+        assert int(sums[r]) == int(np.sum(w, dtype=np.uint64)), f"row {r}"
+        assert int(toks[r]) == sampler.draw(w, sampler.nucleus(w, top_p), int(x[r])), f"row {r}"
+    for again in range(4):
+        for call in (binding.rollout_debug_sample_impatient, R.rollout_sample):
+            got = call(z, 0.8, top_p, x)
+            assert all(np.array_equal(a, b, equal_nan=True) for a, b in zip(got, (toks, lps, sums)))

@@ -606,7 +606,7 @@ static void decode_impl(rollout_ctx& c, const int32_t* forced_tokens, const uint
   ga.host_live = live_changed ? hi : nullptr;
   ga.host_forced = forced_tokens ? hi + R : nullptr;
   ga.host_uniform = uniform_override ? (const unsigned*)(hi + 2 * R) : nullptr;
-  launch_gather_decode_rows(ga, c.stream);
+  if (Rq) launch_gather_decode_rows(ga, c.stream);  // without one the embedding does it
   c.decode_max_ctx = 1;
   c.decode_max_own = 1;
   c.kv_tokens_this_call = 0;
@@ -632,7 +632,7 @@ static void decode_impl(rollout_ctx& c, const int32_t* forced_tokens, const uint
   int n_fin = 0;  // prompts that end in this step: their last rows' logits follow the decode rows'
   c.timer.start_call();
   if (!Rq) {
-    engine_forward_rows(c, B, nullptr);
+    engine_forward_rows(c, B, nullptr, &ga);
     c.timer.empty_bracket(c.stream);
     engine_logits(c, nullptr, 0, B, c.logits.p);
     c.last_logit_rows = B;

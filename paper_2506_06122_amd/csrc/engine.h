@@ -251,9 +251,9 @@ struct rollout_ctx : HostState {
 
 // engine.hip
 void engine_init(rollout_ctx& c, const rollout_weights& w);
-// uses c.row_token / row_pos / row_slot; result in c.x.  seqs describes packed sequences
+// uses c.row_token / row_pos / row_slot, which the first launch fills from `gather` where it is given; result in c.x.  seqs describes packed sequences
 // (prefill, log-probs) or is NULL when every row is one sample's next position (decode).
-void engine_forward_rows(rollout_ctx& c, int rows, const SeqBatch* seqs);
+void engine_forward_rows(rollout_ctx& c, int rows, const SeqBatch* seqs, const GatherRows* gather = nullptr);
 // logits of `n` rows of c.x selected by rows_index (device, or NULL for rows first..first+n) into out
 void engine_logits(rollout_ctx& c, const int* rows_index, int first, int n, float* out);
 // out[r] = log-softmax(logits of row r of c.x * inv_t)[target[r]] for rows 0..n-1 (0 where

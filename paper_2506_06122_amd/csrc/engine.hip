@@ -387,11 +387,11 @@ void engine_upload_page_rows(rollout_ctx& c) {
 // T = storage type of the weights; KT = storage type of the KV cache (fp32 models: fp32,
 // bf16 models: IEEE half, see common.h)
 template <typename T, typename KT>
-static void forward_rows_simple(rollout_ctx& c, int R, bool decode) {
+static void forward_rows_simple(rollout_ctx& c, int R, bool decode, const GatherRows* gather) {
   const rollout_model_desc& m = c.md;
   hipStream_t s = c.stream;
   const int d = m.hidden;
-  launch_embed<T>((const T*)c.embed.p, c.row_token.p, c.x.p, R, d, s);
+  launch_embed<T>((const T*)c.embed.p, c.row_token.p, gather, c.x.p, R, d, s);
   for (int l = 0; l < m.n_layers; ++l) {
     LayerWeights& L = c.layers[l];
     launch_linear_simple<T>({c.x.p, d, nullptr, L.norm1.p, m.rms_eps, c.qkv.p, c.qkv_dim, nullptr, R, c.qkv_dim, d},
@@ -472,7 +472,7 @@ static void gate_up(rollout_ctx& c, LayerWeights& L, int R) {
   c.timer.end(c.stream);
 }
 
-static void embed_and_norm(rollout_ctx& c, int R) {
+static void embed_and_norm(rollout_ctx& c, int R, const GatherRows* gather) {
   RowNormArgs rn{};
   rn.x = c.x.p;
   rn.h = c.h_bf16.p;
@@ -481,6 +481,7 @@ static void embed_and_norm(rollout_ctx& c, int R) {
   rn.hidden = c.md.hidden;
   rn.eps = c.md.rms_eps;
   rn.tokens = c.row_token.p;
+  if (gather) rn.gather = *gather;
   rn.embed = (const uint16_t*)c.embed.p;
   rn.gain = c.layers[0].norm1.p;
   c.timer.begin("row_norm_kernel", (double)R * c.md.hidden * (2 + 4 + 2), 0, c.stream);
@@ -620,13 +621,13 @@ static void moe_block(rollout_ctx& c, LayerWeights& L, int layer, int R, RowNorm
   c.timer.end(s);
 }
 
-static void forward_rows_tiled(rollout_ctx& c, int R, const SeqBatch* seqs) {
+static void forward_rows_tiled(rollout_ctx& c, int R, const SeqBatch* seqs, const GatherRows* gather) {
   const rollout_model_desc& m = c.md;
   hipStream_t s = c.stream;
   const int d = m.hidden, f = m.ffn_dim;
   if (m.n_experts > 0)  // the per-layer pick counters of the routing kernels start at zero
     HIP_TRY(hipMemsetAsync(c.moe_count.p, 0, c.moe_count.n * sizeof(int), s));
-  embed_and_norm(c, R);
+  embed_and_norm(c, R, gather);
   RowNormArgs rn{};
   rn.x = c.x.p;
   rn.h = c.h_bf16.p;
@@ -817,7 +818,7 @@ static int stream_project(rollout_ctx& c, const DevBuf<uint16_t>& a, const void*
   return z;
 }
 
-static void forward_rows_decode(rollout_ctx& c, int R) {
+static void forward_rows_decode(rollout_ctx& c, int R, const GatherRows* gather) {
   const rollout_model_desc& m = c.md;
   hipStream_t s = c.stream;
   const int d = m.hidden, f = m.ffn_dim;
@@ -830,6 +831,7 @@ static void forward_rows_decode(rollout_ctx& c, int R) {
     rn.hidden = d;
     rn.eps = m.rms_eps;
     rn.tokens = c.row_token.p;
+    if (gather) rn.gather = *gather;
     rn.embed = (const uint16_t*)c.embed.p;
     rn.gain = c.layers[0].norm1.p;
     rn.ssq_out = c.ssq.p;
@@ -882,18 +884,18 @@ static void forward_rows_decode(rollout_ctx& c, int R) {
   c.h_is_final = true;
 }
 
-void engine_forward_rows(rollout_ctx& c, int rows, const SeqBatch* seqs) {
+void engine_forward_rows(rollout_ctx& c, int rows, const SeqBatch* seqs, const GatherRows* gather) {
   if (rows < 1) return;
   c.last_route_rows = rows;
   if (!c.simple) {
     if (!seqs && rows <= stream_rows(c.md.hidden) && !c.md.n_experts)
-      forward_rows_decode(c, rows);
+      forward_rows_decode(c, rows, gather);
     else
-      forward_rows_tiled(c, rows, seqs);
+      forward_rows_tiled(c, rows, seqs, gather);
   } else if (c.md.dtype == ROLLOUT_DTYPE_F32) {
-    forward_rows_simple<float, float>(c, rows, !seqs);
+    forward_rows_simple<float, float>(c, rows, !seqs, gather);
   } else {
-    forward_rows_simple<bf16_t, f16_t>(c, rows, !seqs);
+    forward_rows_simple<bf16_t, f16_t>(c, rows, !seqs, gather);
   }
 }
 

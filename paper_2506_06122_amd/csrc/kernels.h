@@ -5,8 +5,10 @@
 
 // ---- plain one-op-per-kernel path (any storage type; used for fp32 models and as the
 // ---- cross-check path for bf16) -------------------------------------------------------
+struct GatherRows;
+// x[r] = the embedding of tokens[r]; with gather (a decode step) of the row gathered on the way
 template <typename T>
-void launch_embed(const T* table, const int* tokens, float* x, int rows, int hidden, hipStream_t s);
+void launch_embed(const T* table, const int* tokens, const GatherRows* gather, float* x, int rows, int hidden, hipStream_t s);
 
 // out[r] = x[r] * gain * rsqrt(mean(x[r]^2) + eps)
 void launch_rmsnorm_f32(const float* x, const float* gain, float* out, int rows, int hidden, float eps,
@@ -78,6 +80,42 @@ struct SlotState {
   float* top_p;          // [slots]
 };
 
+// row r <- slot live[r]: token, position, slot, sampling parameters.  What changed on the host comes along from
+// memory mapped for the device: the live list (host_live, kept in `live`), the step's forced tokens and
+// sampler words (each may be NULL).
+struct GatherRows {
+  SlotState st;
+  int rows;
+  int* live;
+  const int* host_live;
+  const int* host_forced;
+  const unsigned* host_uniform;
+  int *token, *pos, *slot, *step, *forced;
+  unsigned* uniform;
+  float *inv_temp, *top_p;
+  long long* sample_id;
+};
+// The token of row r.  One thread of a row stores; a kernel that reads the rows' tokens does this first, and saves a
+// launch.
+__device__ inline int gather_row(const GatherRows& a, int r, bool store) {
+  const int sl = a.host_live ? a.host_live[r] : a.live[r];
+  const int token = a.st.last_token[sl];
+  if (store) {
+    if (a.host_forced) a.forced[r] = a.host_forced[r];
+    if (a.host_uniform) a.uniform[r] = a.host_uniform[r];
+    if (a.host_live) a.live[r] = sl;
+    a.token[r] = token;
+    a.pos[r] = a.st.pos[sl];
+    a.slot[r] = sl;
+    a.inv_temp[r] = a.st.inv_temp[sl];
+    a.top_p[r] = a.st.top_p[sl];
+    a.sample_id[r] = a.st.sample_id[sl];
+    a.step[r] = a.st.step[sl];
+  }
+  return token;
+}
+void launch_gather_decode_rows(const GatherRows& a, hipStream_t s);
+
 // ---- sampling ---------------------------------------------------------------------------
 constexpr int kMeetSpins = 128;  // looks of about 0.5 us; the parts of a row finish a phase within a few us of each other
 struct SampleRows {
@@ -128,23 +166,6 @@ void launch_philox_words(unsigned long long seed, const long long* ids, const un
 // out[r] = log softmax(logits[r] * inv_temp)[target[r]]; target < 0 writes 0
 void launch_logprob_gather(const float* logits, const int* target, float inv_temp, float* out, int rows,
                            int vocab, hipStream_t s);
-
-// row r <- slot live[r]: token, position, slot, sampling parameters.  What changed on the host comes along from
-// memory mapped for the device: the live list (host_live, kept in `live`), the step's forced tokens and
-// sampler words (each may be NULL).
-struct GatherRows {
-  SlotState st;
-  int rows;
-  int* live;
-  const int* host_live;
-  const int* host_forced;
-  const unsigned* host_uniform;
-  int *token, *pos, *slot, *step, *forced;
-  unsigned* uniform;
-  float *inv_temp, *top_p;
-  long long* sample_id;
-};
-void launch_gather_decode_rows(const GatherRows& a, hipStream_t s);
 
 // Copies of 4-byte words from host memory mapped for the device, all in one launch.
 struct HostCopies {

@@ -4,6 +4,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "kernels.h"
 #include "tile_grid.h"
 
 // Kernels of a decode step take what their first loads need as leading scalar arguments, at most 14 dwords, and the rest
@@ -122,6 +123,7 @@ void launch_pack_weight(const void* src, void* dst, int N, int K, int tile_offse
 
 // x[r] (+= sum of `splits` partial planes) ; h[r] = bf16(x[r] * gain * rsqrt(mean(x[r]^2) + eps)).
 //   tokens != NULL : x[r] is first loaded from the bf16 embedding row tokens[r]
+//   gather.rows    : the same for a decode step, whose rows are gathered on the way
 //   rows_index != NULL : source row of x is rows_index[r], x is not written back (final norm)
 struct RowNormArgs {
   float* x;
@@ -134,6 +136,7 @@ struct RowNormArgs {
   float* ssq_out;           // when set: h = x * gain without the rsqrt factor, ssq_out[r] = sum x[r]^2
   bool h_frag = false;      // h in fragment order
   const int* tokens;
+  GatherRows gather{};
   const uint16_t* embed;
   const int* rows_index;
   int rows, hidden;

@@ -28,7 +28,7 @@ __global__ __launch_bounds__(ROW_T) void row_norm_kernel(float* x_rows, const fl
   const long long src_row = a.rows_index ? a.rows_index[r] : r;
   float4 x[V];
   if (a.tokens) {
-    const uint2* e = (const uint2*)(a.embed + (long long)a.tokens[r] * a.hidden);
+    const uint2* e = (const uint2*)(a.embed + (long long)(a.gather.rows ? gather_row(a.gather, r, t == 0) : a.tokens[r]) * a.hidden);
 #pragma unroll
     for (int v = 0; v < V; ++v) {
       const int c = t + ROW_T * v;

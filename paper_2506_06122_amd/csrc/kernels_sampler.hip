@@ -550,17 +550,18 @@ __device__ inline void select_token(const SampleRows& a, int r, const float* row
     const unsigned tau_key = st.prefix;
     unsigned long long s_n = S, of_segment;
     unsigned k_ties = 0;
-    __syncthreads();
+    const bool few = n_seg <= WAVE;  // then the first wavefront, which draws, holds all segments and needs no other
+    if (nucleus || !few) __syncthreads();
     if (nucleus) {
       const unsigned long long tau = key_weight(tau_key);
       k_ties = tau ? (unsigned)((st.theta - st.above + tau - 1) / tau) : 0u;  // theta > above: tau's bin was needed to reach it
       s_n = st.above + k_ties * tau;
       const unsigned mine = tid < n_seg ? sh.ties[tid] : 0u;
       unsigned long long all;
-      const unsigned before = (unsigned)block_scan_u64(mine, sh, all) - mine;
+      const unsigned before = (few ? (unsigned)wave_scan_u64(mine) : (unsigned)block_scan_u64(mine, sh, all)) - mine;
       const unsigned in = before < k_ties ? min(mine, k_ties - before) : 0u;
       of_segment = tid < n_seg ? sh.hist[tid] + in * tau : 0ull;
-      sh.ties[tid] = in;  // ids at tau that are in, per segment
+      if (!few || wave == 0) sh.ties[tid] = in;  // ids at tau that are in, per segment
     } else {
       of_segment = tid < n_seg ? sh.vals[tid] : 0ull;
     }
@@ -569,8 +570,14 @@ __device__ inline void select_token(const SampleRows& a, int r, const float* row
     const unsigned long long R = (s_n >> 32) * x + (((s_n & 0xffffffffull) * x) >> 32);
     int seg;
     unsigned long long before;
-    find_segment(sh, of_segment, R, seg, before);
+    if (!few) find_segment(sh, of_segment, R, seg, before);
     if (wave == 0) {
+      if (few) {
+        const unsigned long long inc = wave_scan_u64(of_segment);
+        const unsigned long long hit = __ballot(inc > R && inc - of_segment <= R);
+        seg = hit ? __ffsll((long long)hit) - 1 : 0;
+        before = hit ? read_lane_u64(inc - of_segment, seg) : 0ull;
+      }
       const int i0 = seg * 256 + lane * 4;
       const Logit4 z = logits4(request4<true>(row, i0, vocab), i0, vocab);
       const Key4 q = keys4(z, i0, vocab, inv_t, m);
@@ -930,7 +937,22 @@ __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab)
   select_token(a, r, row, vocab, inv_t, m, S, st, nucleus, a.uniforms ? a.uniforms + r : nullptr, sh);
 }
 
-// Large vocabularies with scratch at hand: the sweeps of a row on several workgroups (about 512 in all) and two launches,
+// Parts of a row: as many as give every CU one workgroup, of a nucleus at most one to a wavefront of the last part.  A part waits
+// for the slowest, and a CU that holds two while others hold one is the slowest.  Only where a part's share gets long - more than 5
+// tiles, 9 of a nucleus, whose phases end in more waits - two workgroups to every CU, that fill each other's gaps.
+// us a call, static, one / two to a CU:    top_p 0.9                                  top_p 1
+//   32001 ids                       42 rows 25.9 / 31.7, 128 rows 32.3 / 36.4    42 rows 11.1 / 13.2, 128 rows 13.7 / 14.7
+//   151936 ids                      16 rows 28.8 / 36.8, 50 rows 41.3 / 42.9     16 rows 12.0 / 13.5, 64 rows 24.0 / 22.7
+//                                   96 rows 67.2 / 59.1                          40 rows 17.3 / 16.5, 96 rows 37.1 / 31.9
+// (64 rows x 151936, top_p 0.9: 47.2 / 48.1, but 65.6 / 62.8 with the host's wait behind each call; 8 rows, 31 / 16 parts: 28.2 / 27.0.)
+static int sample_parts(int rows, int n_tiles, bool nucleus) {
+  const int most = std::min(n_tiles, nucleus ? SAMP_T / WAVE : kSampleParts - 1);
+  const int one = std::min(most, 256 / rows);
+  if (one >= 2 && n_tiles <= one * (nucleus ? 9 : 5)) return one;
+  return std::max(2, std::min(most, 512 / rows));
+}
+
+// Large vocabularies with scratch at hand: the sweeps of a row on several workgroups and two launches,
 // the maximum and the rest; else everything in one workgroup per row.
 // 64 rows x 151936 ids, top_p 0.9: 9.0 us for the maximum, 41.4 for the rest, of which some 11 are histogram 0, 10 the sweep that
 // lists, 10 the draw and 3 each time the parts meet; 65 us per call of rollout_sample.  In six launches (9.5 + 14.2 + 15.3 +
@@ -941,7 +963,7 @@ static void launch_sample_rows(const SampleRows& r, int rows, int vocab, hipStre
   const int n_tiles = (vocab + 4095) >> 12;
   int parts = 0;
   if (r.part_max && r.seg_sums && (r.nucleus || !r.any_nucleus) && n_tiles >= 8 && vocab <= 256 * kSampleSegments)
-    parts = std::max(2, std::min({n_tiles, kSampleParts - 1, 512 / rows}));
+    parts = sample_parts(rows, n_tiles, r.any_nucleus);
   if (parts < 2) {
     sample_kernel<<<rows, SAMP_T, 0, s>>>(r, vocab);
     return;

@@ -528,6 +528,11 @@ __device__ inline bool nucleus_is_flat(const NucleusState& st, int parts) {
   return (float)st.here > __uint_as_float((st.prefix << 19) & 0x7f800000u) * ((float)parts * room * room);
 }
 
+// Do the bin's ids fit one part's places, wherever they lie?  An id weighs at least the power of two below the bin.
+__device__ inline bool nucleus_fits(const NucleusState& st, int parts) {
+  return (float)st.here <= __uint_as_float((st.prefix << 19) & 0x7f800000u) * (float)nucleus_listed(parts);
+}
+
 // What the draw from a row starts with: weights, and with a nucleus its end (st) and, in sh.hist and sh.ties, per segment
 // the weight above tau and the ids at tau; without one the segments' weights in sh.vals.  word: the row's random word.
 // A chain of round trips and barriers: in a draw the logarithm of the sum is another wavefront's, and the token's logit comes
@@ -814,17 +819,19 @@ __global__ __launch_bounds__(SAMP_T, 8) void sample_rest_kernel(SampleRows a, in
     };
     shares = meet(words, 0, parts, shares, a.patience, last, sh);
     if (!shares) return;
-    bool flat = false;
+    bool flat = false, fits = false;
     {
       const unsigned long long h0 = nucleus_bin_from_top<true>(scratch, 0);
       each_share(
           [&] {
             nucleus_descend(h0, 0, top_p, st, sh);
             flat = nucleus_is_flat(st, parts);
+            fits = nucleus_fits(st, parts);
           },
           [&](int part, const RowTiles<4>& tiles) { list_share(a, r, tiles, part, parts, flat, inv_t, m, st, scratch, sh, ls); });
     }
-    shares = meet(words, 1, parts, shares, a.patience, last, sh);
+    // only the last part goes on where all ids are listed, and the others need not wait to hear that
+    shares = meet(words, 1, parts, shares, !flat && fits ? -1 : a.patience, last, sh);
     if (!shares) return;
     // all that is needed as a rule, requested at once: the first 64 ids of this wavefront's part come before their number
     const unsigned long long h1 = nucleus_bin_from_top<true>(scratch + kNucleusBins0, 1);

@@ -120,6 +120,26 @@ def test_whole_vocabulary_matches_oracle(vocab):
         assert int(toks[r]) == sampler.draw(w, sampler.nucleus(w, 1.0), int(x[r])), f"row {r}"
 
 
+@pytest.mark.parametrize("rows,vocab", [(9, 16384), (9, 16385), (42, 28676), (128, 28676), (129, 28676), (171, 28676), (51, 147457)])
+@pytest.mark.parametrize("top_p", [0.9, 1.0])
+def test_lines_between_the_ways_to_draw(rows, vocab, top_p):
+    """64 and 65 segments (one wavefront draws, or the workgroup); one and two workgroups to a CU, two to four parts to a row."""
+    import torch
+    import paper_2506_06122_amd as R
+    hard = hard_rows(vocab, seed=vocab)
+    z = torch.from_numpy(hard).cuda()[torch.arange(rows, device="cuda") % len(hard)].contiguous()
+    x = workloads.uniform_words(rows, seed=6)
+    x[::5] = 2 ** 32 - 1
+    toks, _, sums = R.rollout_sample(z, 0.8, top_p, x)
+    inv_t = sampler.inv_temperature(0.8)
+    weights = [sampler.fixexp_weights(h, inv_t) for h in hard]
+    members = [sampler.nucleus(w, top_p) for w in weights]
+    for r in range(rows):
+        w = weights[r % len(hard)]
+        assert int(sums[r]) == int(np.sum(w, dtype=np.uint64)), f"row {r}"
+        assert int(toks[r]) == sampler.draw(w, members[r % len(hard)], int(x[r])), f"row {r}"
+
+
 @pytest.mark.parametrize("vocab", [28673, 32001, 65536 + 3, 151936, 262144])
 @pytest.mark.parametrize("top_p", [0.5, 0.9, 1.0])
 def test_shares_left_to_the_last(vocab, top_p):

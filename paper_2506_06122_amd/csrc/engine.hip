@@ -308,8 +308,8 @@ void engine_init(rollout_ctx& c, const rollout_weights& w) {
     c.attn_tickets.alloc((size_t)r.max_live_samples * m.n_kv_heads * kTicketStride);
     HIP_TRY(hipMemsetAsync(c.attn_tickets.p, 0, c.attn_tickets.n * sizeof(unsigned), c.stream));
     c.ssq.alloc((size_t)(d / 16 + 1) * 256);
-    c.join_parts.alloc(kJoinTiles * kJoinParts * 256);
-    c.join_tickets.alloc(kJoinTiles * kTicketStride);
+    c.join_parts.alloc((size_t)kJoinTiles * kJoinParts * 256);
+    c.join_tickets.alloc((size_t)kJoinTiles * kTicketStride);
     HIP_TRY(hipMemsetAsync(c.join_tickets.p, 0, c.join_tickets.n * sizeof(unsigned), c.stream));
     {
       const size_t parts = lse_parts_max(m.vocab);

@@ -5,6 +5,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "stream_plan.h"
 #include "tile_grid.h"
 
 // Kernels of a decode step take what their first loads need as leading scalar arguments, at most 14 dwords, and the rest
@@ -44,11 +45,8 @@ __host__ __device__ inline long long plane_offset(int m, int k, int K) {
   return 2 * (long long)m * K + ((k >> 5) << 6) + (k & 31);
 }
 
-// Scratch of the K splits that meet in their launch (join_splits): at most kJoinTiles joined tiles, each of at most
-// kJoinParts KiB, and as many tickets.
 constexpr int kTicketStride = 32;  // a ticket has its 128-byte line to itself
 constexpr int kDeviceScope = 16;   // cache policy of a buffer access at the scope of the device: sc1
-constexpr size_t kJoinTiles = 512, kJoinParts = 16;
 
 struct GemmArgs {
   const void* a;     // activations as bf16 hi and lo parts: interleaved rows (plane_offset), or with `frag` two

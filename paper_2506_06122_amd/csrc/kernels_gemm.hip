@@ -678,32 +678,6 @@ __global__ __launch_bounds__(WM* WN* KG * 64, wide_wavefronts(WM, WN, MT, NT, KG
 }
 
 // ------------------------------------------------------------------------------------------
-// The stream kernel's shapes, with the epilogues each is planned with.
-//     MT NT KU NW KEEP
-#define STREAM_SHAPES(X)                                                                                     \
-  X(0, 1, 2, 2, 8, false, EPI_F32, EPI_SWIGLU_BF16)  /* up to 16 rows, wide outputs */                       \
-  X(1, 1, 4, 1, 8, false, EPI_F32, EPI_F32)          /* the same from 9 rows on, without SwiGLU */           \
-  X(2, 1, 1, 3, 16, false, EPI_F32, EPI_RESID)       /* narrow outputs in one piece */                       \
-  X(3, 1, 2, 3, 8, false, EPI_F32, EPI_RESID)        /* narrow outputs in K splits: planes, or joined */     \
-  X(4, 1, 4, 2, 8, false, EPI_RESID, EPI_RESID)      /* the same, deep and wider */                          \
-  X(5, 2, 2, 2, 4, false, EPI_F32, EPI_SWIGLU_BF16)  /* up to 32 rows, wide outputs */                       \
-  X(6, 2, 4, 1, 4, false, EPI_F32, EPI_F32)          /* the logits */                                        \
-  X(7, 1, 1, 3, 16, true, EPI_F32, EPI_RESID)        /* narrow outputs in one piece, a row block per 16 rows */ \
-  X(8, 2, 2, 2, 8, false, EPI_F32, EPI_RESID)        /* narrow outputs in K splits */
-struct StreamShape {
-  int mt, nt;
-  const char* name[3];  // by epilogue: F32, SWIGLU, RESID
-};
-static const StreamShape kStreamShapes[] = {
-#define X(id, mt, nt, ku, nw, keep, ...)                                                                         \
-  {mt, nt, {"gemm_stream_kernel<" #mt "," #nt "," #ku "," #nw "," #keep ",0>",                                    \
-            "gemm_stream_kernel<" #mt "," #nt "," #ku "," #nw "," #keep ",1>",                                    \
-            "gemm_stream_kernel<" #mt "," #nt "," #ku "," #nw "," #keep ",2>"}},
-    STREAM_SHAPES(X)
-#undef X
-};
-
-
 static GemmPlan gemm_plan_tiled(int M, int N, int K, int epi, int max_splits) {
   static thread_local TilePlans plans;
   const TileChoice pick = plans(TileAsk{M, N, K, epi == EPI_F32 ? max_splits : 1, epi == EPI_LSE ? kLseMinTile : 0});
@@ -771,52 +745,25 @@ static int launch_tile(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s) {
   return a.grid.nz;
 }
 
-// Wide outputs (SwiGLU, the logits): no split, workgroups enough without.  Two column tiles to a workgroup; the logits
-// four as soon as the activations weigh as much as the weights (a fragment of up to 8 rows is half as many lines):
-// 151936 x 1536, 6 rows 68.6 / 72.4 us with two / four, 16 rows 82.8 / 77.7, 32 rows 112 / 95.
-//
-// Narrow outputs are bound by what one CU can fetch, about 65 GB/s: (64 MT + 32 NT) K bytes per workgroup, and as many
+// Narrow outputs are bound by what one CU can fetch, 65 to 90 GB/s: (64 MT + 32 NT) K bytes per workgroup, and as many
 // workgroups as there are column blocks.  So the K range is cut until the CUs are full: where the splits' planes are
 // summed by the next launch anyway (max_splits > 1: attention sums those of q, k, v), or joined in the launch
-// (EPI_RESID), which costs about 2 us (3 with four column tiles).  us with weights from HBM, 6 / 16 / 32 rows, in one
-// piece and in splits:
-//   1536 x 8960    13.3 / 16.8 / 16.3  ->   9.3 / 10.0 / 11.7  (two column tiles, 5 splits)
-//   1536 x 1536     5.1 /  5.8 /  6.0  ->   5.6 /  6.1 /  6.7  (4 splits): left in one piece
-//   2048 x 1536     5.2 /  5.7 /  5.9  ->   4.2 /  4.3 /  5.3  (4 planes)
-//   3584 x 18944   27.4 / 35.0 (4 / 12 rows) -> 26.3 / 27.5 with four column tiles and 4 splits, 25.5 / 29.0 with two and 2
-//   3584 x 3584     8.0 /  9.6 (4 / 12 rows) ->  8.6 /  9.3: left in one piece
-//   4608 x 3584    10.1 / 11.8 (4 / 12 rows, 16 wavefronts) -> 9.8 / 10.6 (3 planes)
+// (EPI_RESID), which costs about 1.5 us.  One workgroup more than 256 is another round: that is what the
+// plan weighs (stream_plan.h).  us with weights from HBM, 6 / 16 / 32 rows, in one piece and in splits:
+//   1536 x 8960    12.7 / 16.4 / 15.6  ->   8.7 /  9.4 / 11.0  (two column tiles, 5 splits)
+//   1536 x 1536     4.6 /  5.2 /  5.2  ->   5.1 /  5.3 /  6.0  (4 splits): left in one piece
+//   2048 x 1536     4.6 /  5.2 /  5.1  ->   3.8 /  3.9 /  4.7  (4 planes)
+//   6144 x 2048     6.8 /  7.5 /  9.1  ->   8.0 /  8.6 / 10.4  (2 planes, 384 workgroups): left in one piece
+//   3584 x 18944   26.9 / 34.4 (4 / 12 rows) -> 24.9 / 28.2 with two column tiles and 2 splits, 25.9 / 27.0 with four and 4
+//   3584 x 3584     7.5 /  9.1 (4 / 12 rows) ->  8.1 /  8.8 (2 splits)
+//   4096 x 4096     8.4 /  9.9 (4 / 12 rows) ->  9.6 / 10.0 (2 splits): left in one piece
+//   4608 x 3584     9.2 / 11.0 (4 / 12 rows) ->  9.1 /  9.9 (3 planes)
 GemmPlan gemm_plan_stream(int M, int N, int K, int epi, int max_splits) {
+  const StreamChoice pick = epi == EPI_SWIGLU_BF16 ? StreamChoice{M > 16 ? 5 : 0, 1} : stream_choose(M, N, K, epi == EPI_RESID, max_splits);
   GemmPlan pl{};
-  const int n_tiles = N >> 4, k_tiles = K >> 5, mt = M > 16 ? 2 : 1;
   pl.kind = 0;
-  pl.splits = 1;
-  if (epi == EPI_SWIGLU_BF16) {
-    pl.shape = mt == 2 ? 5 : 0;
-  } else if (epi == EPI_F32 && n_tiles >= 1024) {
-    pl.shape = mt == 2 ? 6 : M > 8 ? 1 : 0;
-  } else if (epi == EPI_F32) {
-    const int blocks = ceil_div(n_tiles, 2);
-    pl.splits = std::max(1, std::min({ceil_div(384, blocks), max_splits, 4, k_tiles / 8}));
-    pl.shape = pl.splits > 1 ? (mt == 2 ? 8 : 3) : mt == 2 ? 7 : 2;
-  } else {
-    // us of one CU's fetches with nt column tiles per workgroup and z splits
-    auto fetch = [&](int nt, int z, int rows64) {
-      const double us = (double)K / z * (rows64 * 64 + 32 * nt) / 65e3;
-      return us * std::max(1.0, (double)ceil_div(n_tiles, nt) * z / 256) + (z > 1 ? 1.0 + 0.5 * nt : 0.0);
-    };
-    auto splits = [&](int nt) { return std::max(1, std::min({256 / ceil_div(n_tiles, nt), nt == 2 ? 5 : 4, k_tiles / 8})); };
-    const int z2 = splits(2), z4 = splits(4);
-    const double one = fetch(1, 1, 1), two = fetch(2, z2, mt), four = fetch(4, z4, mt);
-    pl.shape = mt == 2 ? 7 : 2;
-    if (z2 > 1 && two < one && (mt == 2 || two <= four)) {
-      pl.shape = mt == 2 ? 8 : 3;
-      pl.splits = z2;
-    } else if (z4 > 1 && four < one && mt == 1) {
-      pl.shape = 4;
-      pl.splits = z4;
-    }
-  }
+  pl.shape = pick.shape;
+  pl.splits = pick.splits;
   pl.nt = kStreamShapes[pl.shape].nt;
   pl.name = kStreamShapes[pl.shape].name[epi];
   return pl;
@@ -833,10 +780,10 @@ static int launch_stream(GemmArgs a, int epi, const GemmPlan& pl, hipStream_t s)
   const long long lo_off = ((const uint16_t*)a.a_lo - (const uint16_t*)a.a) >> 3;  // 16-byte pieces
   a.k_tiles_per_split = ceil_div(k_tiles, pl.splits);
   const dim3 grid(ceil_div(n_tiles, t.nt), ceil_div(k_tiles, a.k_tiles_per_split), ceil_div(a.M, 16 * t.mt));
-  if (epi == EPI_RESID && grid.y > 1 && (!a.join || (size_t)grid.x * grid.z * t.mt > kJoinTiles || grid.y * t.nt > kJoinParts))
+  if (epi == EPI_RESID && grid.y > 1 && (!a.join || (int)(grid.x * grid.z) * t.mt > kJoinTiles || (int)grid.y * t.nt > kJoinParts))
     throw HipError(hipErrorInvalidValue, "joined projection", __FILE__, __LINE__);
   switch (pl.shape) {
-#define X(id, mt, nt, ku, nw, keep, e0, e1)                                                        \
+#define X(id, mt, nt, ku, nw, keep, e0, e1, ...)                                                      \
   case id:                                                                                         \
     if (epi == e0) gemm_stream_kernel<mt, nt, ku, nw, keep, e0><<<grid, nw * 64, 0, s>>>(STREAM_ARGS);        \
     else if (epi == e1) gemm_stream_kernel<mt, nt, ku, nw, keep, e1><<<grid, nw * 64, 0, s>>>(STREAM_ARGS);   \

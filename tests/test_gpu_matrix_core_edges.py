@@ -172,6 +172,54 @@ def test_streamed_splits_join(rows, hidden, ffn):
     assert all(np.array_equal(a, b) for a, b in zip(*runs))
 
 
+def stream_kernels(eng):
+    """template arguments of the streamed projections' kernels that ran"""
+    return {k["name"][len("gemm_stream_kernel<"):-1] for k in eng.rollout_kernel_stats() if k["name"].startswith("gemm_stream_kernel<")}
+
+
+@pytest.mark.parametrize("rows,hidden,ffn,kernel", [(1, 5152, 4896, "1,4,2,8,false,2"), (9, 5152, 4896, "1,4,2,8,false,2"),
+                                                    (16, 5120, 5024, "1,4,2,8,false,2"), (16, 3104, 8032, "1,2,3,8,false,2"),
+                                                    (4, 4096, 4096, "1,1,3,16,false,2"), (32, 1056, 6016, "2,2,2,8,false,2")])
+def test_streamed_residual_shapes(rows, hidden, ffn, kernel):
+    """O and down projections on either side of the lines between one piece, splits with two column tiles and splits with four, the
+    last of 322 column tiles not a whole block, 153 k-tiles in three splits."""
+    shape = dataclasses.replace(workloads.SMALL_BF16, n_layers=2, hidden=hidden, ffn_dim=ffn)
+    w = scaled_weights(shape, seed=1, scale=0.5 if hidden > 4000 else 0.7)
+    model = oracle_model(shape, w)
+    toks, offs = workloads.make_prompts(1, 20, 20, shape.vocab, seed=4)
+    forced = np.random.default_rng(6).integers(0, shape.vocab, (rows, 3)).astype(np.int32)
+    eng = make_engine(shape, w, max_live_samples=40, flags=4)
+    worst, worst_lp = teacher_forced_compare(eng, model, toks, offs, rows, forced, 3)
+    ran = stream_kernels(eng)
+    eng.close()
+    print(f"{rows} rows, hidden {hidden}, ffn {ffn}: max |dlogits| = {worst:.3e}, {sorted(ran)}")
+    assert worst <= TOL and worst_lp <= TOL
+    assert kernel in ran
+
+
+@pytest.mark.parametrize("rows,hidden,vocab,kernel", [
+    (8, 512, 16 * 1025, "1,2,2,8,false,0"), (9, 512, 16 * 1025, "1,4,1,8,false,0"), (16, 512, 16 * 1027, "1,4,1,8,false,0"),
+    (16, 2048, 16 * 1025, "1,2,2,8,false,0"), (17, 512, 16 * 1025, "2,4,1,4,false,0"), (31, 512, 16 * 1026, "2,4,1,4,false,0"),
+    (32, 512, 16 * 1027, "2,4,1,4,false,0"), (8, 512, 16 * 501, "1,2,2,8,false,0"), (16, 512, 16 * 1023, "1,2,2,8,false,0"),
+    (17, 512, 16 * 501, "2,2,2,4,false,0"), (32, 512, 16 * 1023, "2,2,2,4,false,0"), (8, 1536, 16 * 191, "1,1,3,16,false,0"),
+    (17, 512, 16 * 65, "1,1,3,16,true,0")])
+def test_streamed_logits(rows, hidden, vocab, kernel):
+    """The logits of decode steps in every shape they are planned with, vocabularies that leave one, two or three of a workgroup's
+    column tiles over: all logits against the oracle."""
+    shape = dataclasses.replace(workloads.SMALL_BF16, n_layers=1, hidden=hidden, ffn_dim=544, vocab=vocab)
+    w = scaled_weights(shape, seed=1, scale=0.7 if hidden > 1024 else 1.0)
+    model = oracle_model(shape, w)
+    toks, offs = workloads.make_prompts(1, 20, 20, shape.vocab, seed=4)
+    forced = np.random.default_rng(6).integers(0, shape.vocab, (rows, 3)).astype(np.int32)
+    eng = make_engine(shape, w, max_live_samples=40, flags=4)
+    worst, worst_lp = teacher_forced_compare(eng, model, toks, offs, rows, forced, 3)
+    ran = stream_kernels(eng)
+    eng.close()
+    print(f"{rows} rows, hidden {hidden}, vocab {vocab}: max |dlogits| = {worst:.3e}, {sorted(ran)}")
+    assert worst <= TOL and worst_lp <= TOL
+    assert kernel in ran
+
+
 @pytest.mark.parametrize("rows", [7, 20, 43, 127, 129])
 def test_attention_splits_fill_the_chip_once(rows):
     """Row counts that do not divide the 256 CUs, with contexts long enough to be cut: 16, 6, 2 and 1 splits per

@@ -1,5 +1,5 @@
-"""The tile launch's mapping of workgroups to blocks (csrc/tile_grid.h) and the choice of tile shapes (csrc/tile_plan.h),
-plain integers and floats, on the CPU."""
+"""The tile launch's mapping of workgroups to blocks (csrc/tile_grid.h), the choice of tile shapes (csrc/tile_plan.h) and of the
+streamed projections' shapes (csrc/stream_plan.h), plain integers and floats, on the CPU."""
 import os
 import shutil
 import subprocess
@@ -28,3 +28,7 @@ def test_every_block_is_visited_once(tmp_path):
 
 def test_a_plan_is_evaluated_once(tmp_path):
     assert run_driver("tile_plan_driver", tmp_path).count("plans") == 4
+
+
+def test_streamed_plans_are_near_the_best_measured(tmp_path):
+    assert int(run_driver("stream_plan_driver", tmp_path).split()[0]) > 100000

@@ -15,13 +15,12 @@
 // significant bits, so as a float it is exact and its bits order like its value: 6 bits of
 // exponent and 23 of mantissa.  Histogram 0 bins by exponent and 4 mantissa bits (656 bins), the next
 // two by the following 10 and the last 9 bits among the ids of the bin found before; a bin is
-// found from the top by a prefix sum.  What bounds it: the arithmetic of the weights, 60 instructions per id and
-// sweep, so the sweeps of a row run on several workgroups, and the sweep that fills
+// found from the top by a prefix sum.  The sweeps of a row run on several workgroups, and the sweep that fills
 // histogram 1 is the last one as a rule: it leaves, per segment of 256 ids, the weight of the bins above the one found,
 // and lists the ids of that bin (some 500 of 151936 where logits spread like N(0, 2.5)); the draw finds the
 // rest from the list.  Rows so flat that the list would overflow (nucleus_is_flat) take full sweeps instead:
 // histogram 1, histogram 2, then per segment the weight above tau and the number of ids at tau.  64 rows x 151936 ids,
-// top_p 0.9: see launch_sample.
+// top_p 0.9: see launch_sample_rows.
 #include <algorithm>
 
 #include "kernels.h"
@@ -277,7 +276,9 @@ struct RowShares {
 
 // This thread's four logits of a part's share of a row, round by round.  The first AHEAD rounds are requested where the object
 // is made, so that they are under way while a sweep finds out what it needs to know of the sweeps before (those
-// sweeps have vocabularies of several tiles).
+// sweeps have vocabularies of several tiles).  One round ahead in the sweeps of a nucleus, each round the next: with four, the
+// 64 registers that two workgroups to a CU leave to a thread overflowed into memory in every round (64 rows x 151936 48.1 -> 39.6 us
+// a call, 96 x 65536 42.6 -> 33.6, 170 x 32001 38.3 -> 31.7); four in the sweeps without one, which have the registers.
 template <int AHEAD>
 struct RowTiles {
   const float* row;
@@ -300,14 +301,29 @@ struct RowTiles {
   // others': 1024 ids, top_p 1 / 0.9 6.0 -> 5.4, 13.3 -> 11.9 us a call.)
   template <typename F>
   __device__ inline void each(F&& f) const {
+    if constexpr (AHEAD == 1) {  // every round's logits are requested ahead of the round before
+      auto round = [&](int q, const Logit4& z) {
+        const int i0 = first_id(q);
+        if ((i0 & ~255) < vocab) f(i0, logits4(z, i0, vocab));  // (uniform: a wavefront's 256 ids are one segment)
+      };
+      Logit4 next = ahead[0];
+      for (int q = 0; q < in.rounds; ++q) {
+        const Logit4 z = next;
+        next = request4<false>(row, first_id(q + 1), vocab);
+        __builtin_amdgcn_sched_barrier(0);
+        round(q, z);
+      }
+      round(in.rounds, next);
+    } else {
 #pragma unroll
-    for (int q = 0; q < AHEAD; ++q) {
-      const int i0 = first_id(q);
-      if ((i0 & ~255) < vocab) f(i0, logits4(ahead[q], i0, vocab));  // (uniform: a wavefront's 256 ids are one segment)
-    }
-    for (int q = AHEAD; q <= in.rounds; ++q) {
-      const int i0 = first_id(q);
-      if ((i0 & ~255) < vocab) f(i0, logits4(request4<AHEAD == 0>(row, i0, vocab), i0, vocab));
+      for (int q = 0; q < AHEAD; ++q) {
+        const int i0 = first_id(q);
+        if ((i0 & ~255) < vocab) f(i0, logits4(ahead[q], i0, vocab));
+      }
+      for (int q = AHEAD; q <= in.rounds; ++q) {
+        const int i0 = first_id(q);
+        if ((i0 & ~255) < vocab) f(i0, logits4(request4<AHEAD == 0>(row, i0, vocab), i0, vocab));
+      }
     }
   }
 };
@@ -682,13 +698,13 @@ __device__ inline unsigned long long meet(unsigned* words, int phase, int parts,
 // One part's share of the sweep that lists: histogram 1, the segments' weights above the bin that histogram 0
 // names, and the list of its ids; of flat rows histogram 1 alone, and the part says that its list overflowed.
 // One id in eight or so can be at or above the bin: a wavefront queues those in LDS and computes their
-// weights 64 at a time.  64 rows x 151936 ids: see launch_sample.
+// weights 64 at a time.  64 rows x 151936 ids: see launch_sample_rows.
 struct ListShared {
   uint2 queue[SAMP_T / WAVE][256 + WAVE];  // (logit, id)
   uint2 list[2048];                        // (key, id)
   unsigned listed;
 };
-__device__ inline void list_share(const SampleRows& a, int r, const RowTiles<4>& tiles, int part, int parts, bool flat, float inv_t,
+__device__ inline void list_share(const SampleRows& a, int r, const RowTiles<1>& tiles, int part, int parts, bool flat, float inv_t,
                                   float m, const NucleusState& st, unsigned long long* scratch, SampShared& sh, ListShared& ls) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, vocab = tiles.vocab;
   const unsigned room = (unsigned)nucleus_listed(parts);
@@ -758,9 +774,9 @@ __device__ inline void list_share(const SampleRows& a, int r, const RowTiles<4>&
 // parts meet.  Without a nucleus one sum per 256-id segment, and the last part draws.  With one: histogram 0; the sweep that lists;
 // then, unless a part found more ids than it could list, the last part draws, else histogram 2, the
 // segments, and the last part draws.  (In flat rows every part says so: nucleus_is_flat.)
-// What bounds it: the arithmetic of the weights, some 35 instructions per id and sweep.  A part's first tiles are requested before
+// What a phase takes: see launch_sample_rows.  A part's first tiles are requested before
 // it knows what it needs to know of the phase before.  As launches of their own the phases cost 2 us each to start, two of
-// them for nothing in ordinary rows, and their last workgroups' time: see launch_sample.
+// them for nothing in ordinary rows, and their last workgroups' time: see launch_sample_rows.
 // NUCLEUS: some rows may have one.
 template <bool NUCLEUS>
 __global__ __launch_bounds__(SAMP_T, 8) void sample_rest_kernel(SampleRows a, int vocab, RowShares in) {
@@ -799,7 +815,7 @@ __global__ __launch_bounds__(SAMP_T, 8) void sample_rest_kernel(SampleRows a, in
     __shared__ ListShared ls;
     unsigned long long* scratch = a.nucleus + (long long)r * kNucleusScratch;
     {
-      const RowTiles<4> tiles(row, vocab, blockIdx.x, in);
+      const RowTiles<1> tiles(row, vocab, blockIdx.x, in);
       m = wave_max(part_max);
       nucleus_histogram(tiles, inv_t, m, 0, 0u, sh);
       if (tid < kNucleusBins0 && sh.hist[tid]) atomicAdd(scratch + tid, sh.hist[tid]);
@@ -811,7 +827,7 @@ __global__ __launch_bounds__(SAMP_T, 8) void sample_rest_kernel(SampleRows a, in
       bool first = true;
       for (unsigned long long rest = shares; rest; rest &= rest - 1) {
         part = __ffsll((long long)rest) - 1;
-        const RowTiles<4> tiles(row, vocab, part, in);
+        const RowTiles<1> tiles(row, vocab, part, in);
         if (first) before();
         first = false;
         f(part, tiles);
@@ -828,12 +844,12 @@ __global__ __launch_bounds__(SAMP_T, 8) void sample_rest_kernel(SampleRows a, in
             flat = nucleus_is_flat(st, parts);
             fits = nucleus_fits(st, parts);
           },
-          [&](int part, const RowTiles<4>& tiles) { list_share(a, r, tiles, part, parts, flat, inv_t, m, st, scratch, sh, ls); });
+          [&](int part, const RowTiles<1>& tiles) { list_share(a, r, tiles, part, parts, flat, inv_t, m, st, scratch, sh, ls); });
     }
     // only the last part goes on where all ids are listed, and the others need not wait to hear that
     shares = meet(words, 1, parts, shares, !flat && fits ? -1 : a.patience, last, sh);
     if (!shares) return;
-    // all that is needed as a rule, requested at once: the first 64 ids of this wavefront's part come before their number
+    // all that is needed as a rule, requested at once: this wavefront's first 64 ids come before their number
     const unsigned long long h1 = nucleus_bin_from_top<true>(scratch + kNucleusBins0, 1);
     const bool overflow = nucleus_overflow(scratch, parts);
     if (!overflow && !last) return;
@@ -842,22 +858,22 @@ __global__ __launch_bounds__(SAMP_T, 8) void sample_rest_kernel(SampleRows a, in
       const unsigned long long* list = scratch + kNucleusList;
       const int room = nucleus_listed(parts);
       const unsigned long long sum = load_device(seg_sums + min(tid, n_seg - 1));
-      const int n_part = wave < parts ? (int)load_device(counts + wave) : 0;
-      static_assert(kNucleusListed / kSampleParts >= WAVE, "a part has room for 64 ids");
-      const unsigned long long first = load_device(list + min(wave, parts - 1) * room + lane);
+      // 16 wavefronts share the lists of up to 16 parts, 8, 4, 2 or one to a part
+      const int share = parts > 8 ? 0 : parts > 4 ? 1 : parts > 2 ? 2 : 3, step = WAVE << share;
+      const int q = min(wave >> share, parts - 1), i0 = (wave & ((1 << share) - 1)) * WAVE + lane;
+      const int n_part = wave >> share < parts ? (int)load_device(counts + q) : 0;
+      static_assert(kNucleusListed >= SAMP_T, "a part has room for 64 ids of each of its wavefronts");
+      const unsigned long long first = load_device(list + q * room + i0);
       sh.hist[tid] = tid < n_seg ? sum : 0ull;
       sh.vals[tid] = 0ull;
       sh.ties[tid] = 0u;
       nucleus_descend(h1, 1, top_p, st, sh);
-      auto each_listed = [&](auto&& f) {  // a wavefront takes the parts wave, wave + 16, ...
-        if (lane < n_part) f((unsigned)first, (unsigned)(first >> 32));
-        auto from = [&](int q, int i) {
+      auto each_listed = [&](auto&& f) {
+        if (i0 < n_part) f((unsigned)first, (unsigned)(first >> 32));
+        for (int i = i0 + step; i < n_part; i += step) {
           const unsigned long long u = load_device(list + q * room + i);
           f((unsigned)u, (unsigned)(u >> 32));
-        };
-        for (int i = WAVE + lane; i < n_part; i += WAVE) from(wave, i);
-        for (int q = wave + SAMP_T / WAVE; q < parts; q += SAMP_T / WAVE)
-          for (int i = lane, n = (int)load_device(counts + q); i < n; i += WAVE) from(q, i);
+        }
       };
       each_listed([&](unsigned key, unsigned) {
         if (nucleus_prefix(key, 2) == st.prefix) atomicAdd(&sh.vals[nucleus_bin(key, 2)], key_weight(key));
@@ -874,7 +890,7 @@ __global__ __launch_bounds__(SAMP_T, 8) void sample_rest_kernel(SampleRows a, in
     // the ids did not fit
     {
       each_share([&] { nucleus_descend(h1, 1, top_p, st, sh); },
-                 [&](int, const RowTiles<4>& tiles) {
+                 [&](int, const RowTiles<1>& tiles) {
                    nucleus_histogram(tiles, inv_t, m, 2, st.prefix, sh);
                    if (tid < nucleus_bins(2) && sh.hist[tid]) atomicAdd(scratch + kNucleusBins0 + 1024 + tid, sh.hist[tid]);
                    __syncthreads();
@@ -886,7 +902,7 @@ __global__ __launch_bounds__(SAMP_T, 8) void sample_rest_kernel(SampleRows a, in
     {
       const unsigned long long h2 = nucleus_bin_from_top<true>(scratch + kNucleusBins0 + 1024, 2);
       each_share([&] { nucleus_descend(h2, 2, top_p, st, sh); },
-                 [&](int, const RowTiles<4>& tiles) {
+                 [&](int, const RowTiles<1>& tiles) {
                    nucleus_segments(tiles, inv_t, m, st.prefix, [&](int seg, unsigned long long above, unsigned n) {
                      store_device(seg_sums + seg, above);
                      store_device(ties + seg, n);
@@ -946,26 +962,29 @@ __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab)
 
 // Parts of a row: as many as give every CU one workgroup, of a nucleus at most one to a wavefront of the last part.  A part waits
 // for the slowest, and a CU that holds two while others hold one is the slowest.  Only where a part's share gets long - more than 5
-// tiles, 9 of a nucleus, whose phases end in more waits - two workgroups to every CU, that fill each other's gaps.
-// us a call, static, one / two to a CU:    top_p 0.9                                  top_p 1
-//   32001 ids                       42 rows 25.9 / 31.7, 128 rows 32.3 / 36.4    42 rows 11.1 / 13.2, 128 rows 13.7 / 14.7
-//   151936 ids                      16 rows 28.8 / 36.8, 50 rows 41.3 / 42.9     16 rows 12.0 / 13.5, 64 rows 24.0 / 22.7
-//                                   96 rows 67.2 / 59.1                          40 rows 17.3 / 16.5, 96 rows 37.1 / 31.9
-// (64 rows x 151936, top_p 0.9: 47.2 / 48.1, but 65.6 / 62.8 with the host's wait behind each call; 8 rows, 31 / 16 parts: 28.2 / 27.0.)
+// tiles, 7 of a nucleus, whose phases end in more waits - two workgroups to every CU, that fill each other's gaps.
+// us a call, back to back on a stream, one / two to a CU:
+//                   top_p 0.9                                                top_p 1
+//   32001 ids       42 rows 23.0 / 26.6, 128 rows 27.9 / 30.0                42 rows 11.5 / 13.5, 128 rows 14.2 / 15.2
+//   65536 ids       64 rows 27.8 / 30.0, 80 rows 30.1 / 31.2, 88 rows 36.7 / 32.7    50 rows 13.1 / 14.5, 80 rows 16.2 / 16.0
+//   151936 ids      42 rows 32.6 / 33.4, 50 rows 35.1 / 34.7, 64 rows 40.0 / 39.6    16 rows 12.4 / 13.8, 42 rows 18.1 / 16.9,
+//                   88 rows 58.1 / 51.0                                              64 rows 24.7 / 23.1, 88 rows 39.5 / 31.8
 static int sample_parts(int rows, int n_tiles, bool nucleus) {
   const int most = std::min(n_tiles, nucleus ? SAMP_T / WAVE : kSampleParts - 1);
   const int one = std::min(most, 256 / rows);
-  if (one >= 2 && n_tiles <= one * (nucleus ? 9 : 5)) return one;
+  if (one >= 2 && n_tiles <= one * (nucleus ? 7 : 5)) return one;
   return std::max(2, std::min(most, 512 / rows));
 }
 
 // Large vocabularies with scratch at hand: the sweeps of a row on several workgroups and two launches,
 // the maximum and the rest; else everything in one workgroup per row.
-// 64 rows x 151936 ids, top_p 0.9: 9.0 us for the maximum, 41.4 for the rest, of which some 11 are histogram 0, 10 the sweep that
-// lists, 10 the draw and 3 each time the parts meet; 65 us per call of rollout_sample.  In six launches (9.5 + 14.2 + 15.3 +
-// 2.9 + 2.7 + 13.7, where two found nothing to do) 69 us; one row 53 -> 45, 16 rows x 32001 56 -> 44, 64 flat rows
-// (N(0, 0.2)) 100 -> 87, 64 rows without a nucleus 44.5 -> 41; one workgroup per row that searched tau bit by bit 1809 us.
-// The sweeps' arithmetic takes the time: 39 MB of logits pass in 8 us.
+// 64 rows x 151936 ids, top_p 0.9, in us (clock readings of the parts, averages): the maximum 8.0, a launch of its own; then 8.7 for
+// histogram 0 (all weights: 35 instructions an id), 2.1 to meet, 7.2 for the sweep that lists (one id in eight is weighed), 1.0 to report
+// and 8 for the draw, a chain of round trips and barriers (1.2 to fetch, 0.8 + 1.3 to find tau, 4.6 from there to the token); 6.6 go
+// by because a part waits for its row's slowest.  Launches 8.0 + 35.3, 39.6 a call back to back.  No one thing bounds it: 39 MB of logits
+// are read three times, at 6 us each from memory.
+// In six launches (9.5 + 14.2 + 15.3 + 2.9 + 2.7 + 13.7, where two found nothing to do) 50.9; one row 27.2 -> 23.2, 64 flat rows
+// (N(0, 0.2)) 80.9 -> 59.5, 64 rows without a nucleus 25.5 -> 23.1; one workgroup per row that searched tau bit by bit 1809.
 static void launch_sample_rows(const SampleRows& r, int rows, int vocab, hipStream_t s) {
   const int n_tiles = (vocab + 4095) >> 12;
   int parts = 0;

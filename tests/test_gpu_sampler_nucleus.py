@@ -74,7 +74,7 @@ def test_wavefronts_without_ids(vocab, top_p):
 @pytest.mark.parametrize("rows,vocab", [(1, 151936), (40, 65536 + 3), (300, 28676)])
 def test_rows_from_flat_to_spread(rows, vocab):
     """The bin that ends the nucleus holds from all ids down to a few: on either side of what a workgroup can list,
-    with 38, 12 and 2 workgroups to a row (the scratch of a call holds 512 rows, so 300 are one batch)."""
+    with 16, 6 and 2 workgroups to a row (the scratch of a call holds 512 rows, so 300 are one batch)."""
     import torch
     import paper_2506_06122_amd as R
     for scale in np.geomspace(0.01, 4.0, 9):
@@ -87,11 +87,11 @@ def test_rows_from_flat_to_spread(rows, vocab):
             assert int(toks[r]) == sampler.draw(w, sampler.nucleus(w, 0.9), int(x[r])), f"scale {scale} row {r}"
 
 
-@pytest.mark.parametrize("rows,vocab", [(64, 151936), (64, 32001), (256, 32001)])
+@pytest.mark.parametrize("rows,vocab", [(64, 151936), (64, 32001), (256, 32001), (30, 262144)])
 @pytest.mark.parametrize("top_p", [0.5, 0.9, 0.99])
 def test_flat_rows_lines(rows, vocab, top_p):
-    """Rows on either side of the line between the list and full sweeps (8 workgroups to a row with five tiles or one, 2 with
-    four), flat and spread ones in one call."""
+    """Rows on either side of the line between the list and full sweeps (8 workgroups to a row with five tiles each, 4 with two, 2 with
+    four, 16 with four), flat and spread ones in one call; 2, 4, 8 or one of the last workgroup's wavefronts take a part's list."""
     import torch
     import paper_2506_06122_amd as R
     scales = np.array([0.03, 0.1, 0.2, 0.35, 0.5, 0.6, 0.7, 0.8, 1.0, 1.5], np.float32)
@@ -120,10 +120,12 @@ def test_whole_vocabulary_matches_oracle(vocab):
         assert int(toks[r]) == sampler.draw(w, sampler.nucleus(w, 1.0), int(x[r])), f"row {r}"
 
 
-@pytest.mark.parametrize("rows,vocab", [(9, 16384), (9, 16385), (42, 28676), (128, 28676), (129, 28676), (171, 28676), (51, 147457)])
+@pytest.mark.parametrize("rows,vocab", [(9, 16384), (9, 16385), (42, 28676), (128, 28676), (129, 28676), (171, 28676), (51, 147457),
+                                        (64, 20 * 4096), (64, 20 * 4096 + 1), (64, 28 * 4096), (64, 28 * 4096 + 1), (4, 262144)])
 @pytest.mark.parametrize("top_p", [0.9, 1.0])
 def test_lines_between_the_ways_to_draw(rows, vocab, top_p):
-    """64 and 65 segments (one wavefront draws, or the workgroup); one and two workgroups to a CU, two to four parts to a row."""
+    """64 and 65 segments (one wavefront draws, or the workgroup); 2 to 16 parts to a row, and 63 without a nucleus; the longest shares
+    with one workgroup to a CU and the shortest with two (of 64 rows 20 tiles without a nucleus, 28 with one: 4 parts, then 8)."""
     import torch
     import paper_2506_06122_amd as R
     hard = hard_rows(vocab, seed=vocab)

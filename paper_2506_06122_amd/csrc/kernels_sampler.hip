@@ -613,6 +613,7 @@ __device__ inline void select_token(const SampleRows& a, int r, const float* row
           if (lane >= o) rank += up;
         }
         rank -= at_tau;  // ids at tau before this lane's
+        if (few) wave_lds_fence();  // another lane's word (the other way has a barrier between)
         const unsigned in = sh.ties[seg];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {

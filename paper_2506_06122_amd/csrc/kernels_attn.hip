@@ -776,6 +776,9 @@ __global__ __launch_bounds__(256) void attn_merge_fused_kernel(AttnArgs a) {
                     a.geom.page_tokens, a.split_tokens, a
 void launch_attention_decode_fused(const AttnArgs& a, hipStream_t s) {
   if (!a.rows) return;
+  // the kernel takes no prompt's shared part (it would attend to it twice, or leave it out) and joins at most 16 splits, by ticket
+  if (a.row_t0 || a.slot0 || a.n_slots || a.n_groups || a.n_splits > 16 || (a.n_splits > 1 && !a.tickets))
+    throw HipError(hipErrorInvalidValue, "plain decode attention", __FILE__, __LINE__);
   const dim3 grid(a.n_splits, a.geom.n_kv_heads, a.rows);
   const bool extra = a.extra.bias || a.extra.q_gain;
   if (a.wide) {
@@ -797,6 +800,8 @@ static void launch_grouped(const AttnArgs& a, unsigned grid, hipStream_t s) {
 }
 void launch_attention_decode_grouped(const AttnArgs& a, hipStream_t s) {
   if (!a.rows) return;
+  // slots are joined by launch_attention_merge: a ticket's holder would join them before the shared parts are there
+  if (a.tickets) throw HipError(hipErrorInvalidValue, "grouped decode attention", __FILE__, __LINE__);
   const int n_kv = a.geom.n_kv_heads, G = a.n_q_heads / n_kv;
   const unsigned grid = (unsigned)(a.n_groups * n_kv * a.n_splits_a + a.rows * n_kv * a.n_splits);
   if (GROUP_MEMBERS * G <= 16) launch_grouped<1>(a, grid, s);

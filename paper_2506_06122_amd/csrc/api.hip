@@ -657,10 +657,8 @@ static void decode_impl(rollout_ctx& c, const int32_t* forced_tokens, const uint
   sr.row_pos = c.row_pos.p;
   sr.pos_step = 1;
   sr.slots = c.st;
-  c.timer.begin("sample_kernel", 4.0 * B * m.vocab, 0, c.stream);
   set_sampler_scratch(c, sr, B, any_nucleus && !forced_tokens);
-  launch_sample(sr, B, m.vocab, c.stream);
-  c.timer.end(c.stream);
+  launch_sample(sr, B, m.vocab, c.stream, &c.timer);
   // prompts that end in this step: response position 0 of their samples
   std::vector<PendingPrompt*> fin;
   if (n_fin) {

@@ -160,7 +160,9 @@ constexpr int kNucleusCounts = kNucleusHist + kSampleSegments / 2;  // behind 10
 constexpr int kNucleusList = kNucleusCounts + kSampleParts / 2;  // the listed ids, shared out among the parts
 constexpr int kNucleusListed = 8192;
 constexpr int kNucleusScratch = kNucleusList + kNucleusListed;   // 64-bit words
-void launch_sample(SampleRows r, int rows, int vocab, hipStream_t s);
+struct KernelTimer;
+// timer: brackets every launch under its kernel's name, or NULL
+void launch_sample(SampleRows r, int rows, int vocab, hipStream_t s, KernelTimer* timer = nullptr);
 void launch_philox_words(unsigned long long seed, const long long* ids, const unsigned* steps, unsigned* out,
                          int n, hipStream_t s);
 // out[r] = log softmax(logits[r] * inv_temp)[target[r]]; target < 0 writes 0

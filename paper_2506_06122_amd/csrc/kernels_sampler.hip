@@ -23,6 +23,7 @@
 // top_p 0.9: see launch_sample_rows.
 #include <algorithm>
 
+#include "kernel_timer.h"
 #include "kernels.h"
 
 #pragma clang fp contract(off)
@@ -986,23 +987,28 @@ static int sample_parts(int rows, int n_tiles, bool nucleus) {
 // are read three times, at 6 us each from memory.
 // In six launches (9.5 + 14.2 + 15.3 + 2.9 + 2.7 + 13.7, where two found nothing to do) 50.9; one row 27.2 -> 23.2, 64 flat rows
 // (N(0, 0.2)) 80.9 -> 59.5, 64 rows without a nucleus 25.5 -> 23.1; one workgroup per row that searched tau bit by bit 1809.
-static void launch_sample_rows(const SampleRows& r, int rows, int vocab, hipStream_t s) {
+static void launch_sample_rows(const SampleRows& r, int rows, int vocab, hipStream_t s, KernelTimer* timer) {
+  auto timed = [&](const char* name, auto&& launch) {  // each reads all logits
+    if (timer) timer->begin(name, 4.0 * rows * vocab, 0, s);
+    launch();
+    if (timer) timer->end(s);
+  };
   const int n_tiles = (vocab + 4095) >> 12;
   int parts = 0;
   if (r.part_max && r.seg_sums && (r.nucleus || !r.any_nucleus) && n_tiles >= 8 && vocab <= 256 * kSampleSegments)
     parts = sample_parts(rows, n_tiles, r.any_nucleus);
   if (parts < 2) {
-    sample_kernel<<<rows, SAMP_T, 0, s>>>(r, vocab);
+    timed("sample_kernel", [&] { sample_kernel<<<rows, SAMP_T, 0, s>>>(r, vocab); });
     return;
   }
   const dim3 grid(parts, rows);
   const RowShares in(vocab, parts);
-  sample_max_kernel<<<grid, SAMP_T, 0, s>>>(r, vocab, in);
-  if (r.any_nucleus) sample_rest_kernel<true><<<grid, SAMP_T, 0, s>>>(r, vocab, in);
-  else sample_rest_kernel<false><<<grid, SAMP_T, 0, s>>>(r, vocab, in);
+  timed("sample_max_kernel", [&] { sample_max_kernel<<<grid, SAMP_T, 0, s>>>(r, vocab, in); });
+  if (r.any_nucleus) timed("sample_rest_kernel<true>", [&] { sample_rest_kernel<true><<<grid, SAMP_T, 0, s>>>(r, vocab, in); });
+  else timed("sample_rest_kernel<false>", [&] { sample_rest_kernel<false><<<grid, SAMP_T, 0, s>>>(r, vocab, in); });
 }
 
-void launch_sample(SampleRows r, int rows, int vocab, hipStream_t s) {
+void launch_sample(SampleRows r, int rows, int vocab, hipStream_t s, KernelTimer* timer) {
   if (!r.any_nucleus) r.nucleus = nullptr;
   // the nucleus scratch holds nucleus_rows rows: more of them go batch by batch
   const int batch = r.any_nucleus && r.nucleus ? r.nucleus_rows : rows;
@@ -1023,7 +1029,7 @@ void launch_sample(SampleRows r, int rows, int vocab, hipStream_t s) {
       if (b.host_tokens) b.host_tokens += r0, b.host_logprobs += r0;
       if (b.row_slot) b.row_slot += r0, b.row_pos += r0;
     }
-    launch_sample_rows(b, std::min(batch, rows - r0), vocab, s);
+    launch_sample_rows(b, std::min(batch, rows - r0), vocab, s, timer);
   }
 }
 

@@ -163,3 +163,21 @@ def test_shares_left_to_the_last(vocab, top_p):
         for call in (binding.rollout_debug_sample_impatient, R.rollout_sample):
             got = call(z, 0.8, top_p, x)
             assert all(np.array_equal(a, b, equal_nan=True) for a, b in zip(got, (toks, lps, sums)))
+
+
+@pytest.mark.parametrize("vocab,top_p,kernels", [(4096, 0.9, {"sample_kernel"}), (32768, 1.0, {"sample_max_kernel", "sample_rest_kernel<false>"}),
+                                                 (32768, 0.9, {"sample_max_kernel", "sample_rest_kernel<true>"})])
+def test_launches_are_timed_under_their_names(vocab, top_p, kernels):
+    """A decode step's sampler in the timing records: one bracket to a launch, each with its logits."""
+    import dataclasses
+    from gpu_util import make_engine, scaled_weights
+    shape = dataclasses.replace(workloads.SMALL_BF16, n_layers=1, ffn_dim=544, vocab=vocab)
+    eng = make_engine(shape, scaled_weights(shape, seed=1), flags=4)
+    toks, offs = workloads.make_prompts(1, 20, 20, shape.vocab, seed=4)
+    eng.rollout_prefill(toks, offs, 3, np.full(3, 6, np.int32), top_p=top_p)
+    for _ in range(4):
+        eng.rollout_decode_step()
+    got = {k["name"]: k for k in eng.rollout_kernel_stats() if k["name"].startswith("sample_")}
+    eng.close()
+    assert set(got) == kernels
+    assert all(k["launches"] == 4 and k["bytes"] == 4 * 4.0 * 3 * vocab and k["ms"] > 0 for k in got.values())

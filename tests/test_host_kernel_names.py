@@ -25,6 +25,19 @@ def test_every_projection_and_attention_kernel_is_timed_under_its_own_name():
     assert not kernels - literals, sorted(kernels - literals)
 
 
+def test_every_sampler_kernel_is_timed_under_its_own_name():
+    nm = shutil.which("nm")
+    if not nm:
+        pytest.skip("no nm")
+    path = binding.load_library()._name
+    stubs = subprocess.run([nm, "-C", path], capture_output=True, text=True, check=True).stdout
+    kernels = {m.group(1).replace(" ", "") for m in re.finditer(r"__device_stub__(sample_\w+(?:<[^>]*>)?)\(", stubs)}
+    assert len(kernels) == 4, kernels
+    with open(path, "rb") as fh:
+        strings = set(fh.read().split(b"\0"))
+    assert all(k.encode() in strings for k in kernels), kernels
+
+
 def test_decode_attention_refuses_what_its_kernel_leaves_out(tmp_path):
     if not os.path.exists(build.HIPCC):
         pytest.skip("no hipcc")

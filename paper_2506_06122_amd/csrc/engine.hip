@@ -868,9 +868,9 @@ static void forward_rows_decode(rollout_ctx& c, int R, const GatherRows* gather)
     at.tickets = c.attn_tickets.p;
     at.part_o = c.attn_part_o.p;
     at.part_ml = c.attn_part_ml.p;
-    // every cached key and value once (a shared prompt once for all its samples), q in, out
+    // every cached key and value once (a shared prompt once for all its samples), the planes of q, k, v in, out
     c.timer.begin(decode_attention_name(at),
-                  c.kv_unique_tokens_this_call * (double)m.n_kv_heads * 128 * 2 * 2 + (double)R * (4.0 * c.qkv_dim + 4.0 * c.q_dim),
+                  c.kv_unique_tokens_this_call * (double)m.n_kv_heads * 128 * 2 * 2 + (double)R * (4.0 * z * c.qkv_dim + 4.0 * c.q_dim),
                   c.attn_flops_this_call, s);
     launch_attention_decode_fused(at, s);
     c.timer.end(s);

@@ -220,6 +220,24 @@ def test_streamed_logits(rows, hidden, vocab, kernel):
     assert kernel in ran
 
 
+def test_timing_records_count_the_planes_that_attention_reads():
+    """A streamed step of 3 rows whose QKV projection (1536 x 1024) leaves four planes: the attention's record counts them, as it does
+    on the tile path."""
+    shape = dataclasses.replace(workloads.SMALL_BF16, n_layers=1, hidden=1024, ffn_dim=544)
+    eng = make_engine(shape, scaled_weights(shape, seed=1), flags=4)
+    toks, offs = workloads.make_prompts(1, 20, 20, shape.vocab, seed=4)
+    eng.rollout_prefill(toks, offs, 3, np.full(3, 4, np.int32), forced_first=np.array([1, 2, 3], np.int32))
+    eng.rollout_decode_step(forced_tokens=np.array([4, 5, 6], np.int32))
+    (attn,) = [k for k in eng.rollout_kernel_stats() if k["name"].startswith("attn_decode_fused_kernel")]
+    ran = stream_kernels(eng)
+    eng.close()
+    assert "1,2,3,8,false,0" in ran
+    cached = 3 * (20 + 1)                             # 20 prompt positions fill no page of 32: nothing is shared
+    q, qkv = 8 * 128, (8 + 2 * 2) * 128
+    assert attn["launches"] == 1
+    assert attn["bytes"] == cached * 2 * 128 * 2 * 2 + 3 * (4.0 * 4 * qkv + 4.0 * q)
+
+
 @pytest.mark.parametrize("rows", [7, 20, 43, 127, 129])
 def test_attention_splits_fill_the_chip_once(rows):
     """Row counts that do not divide the 256 CUs, with contexts long enough to be cut: 16, 6, 2 and 1 splits per

@@ -489,8 +489,7 @@ __device__ inline unsigned* meeting_words(const SampleRows& a, int r) {
   return (unsigned*)a.part_max + (long long)r * kSampleHead + kSampleParts;
 }
 
-// First launch, `parts` workgroups per row: maximum of the scaled logits over tiles
-// blockIdx.x, blockIdx.x + parts, ...
+// First launch, `parts` workgroups per row: maximum of the scaled logits over a part's share (RowShares)
 __global__ __launch_bounds__(SAMP_T, 8) void sample_max_kernel(SampleRows a, int vocab, RowShares in) {
   const int parts = in.parts;
   __shared__ SampShared sh;
@@ -971,6 +970,7 @@ __global__ __launch_bounds__(SAMP_T) void sample_kernel(SampleRows a, int vocab)
 //   65536 ids       64 rows 27.8 / 30.0, 80 rows 30.1 / 31.2, 88 rows 36.7 / 32.7    50 rows 13.1 / 14.5, 80 rows 16.2 / 16.0
 //   151936 ids      42 rows 32.6 / 33.4, 50 rows 35.1 / 34.7, 64 rows 40.0 / 39.6    16 rows 12.4 / 13.8, 42 rows 18.1 / 16.9,
 //                   88 rows 58.1 / 51.0                                              64 rows 24.7 / 23.1, 88 rows 39.5 / 31.8
+// (the draw of a nucleus counts on that: a wavefront to a part's list)
 static int sample_parts(int rows, int n_tiles, bool nucleus) {
   const int most = std::min(n_tiles, nucleus ? SAMP_T / WAVE : kSampleParts - 1);
   const int one = std::min(most, 256 / rows);

@@ -489,8 +489,8 @@ static void embed_and_norm(rollout_ctx& c, int R, const GatherRows* gather) {
   c.timer.end(c.stream);
 }
 
-// The second launch of a decode attention with shared prompts: joins the slots of every (row, KV head).  Timed under its own name; bytes = the slots read (output
-// fragments, maxima and sums) and the rows written as two bf16 planes.
+// The second launch of a decode attention with shared prompts: joins the slots of every (row, KV head).  Timed under its
+// own name; bytes = the slots read (output fragments, maxima and sums) and the rows written as two bf16 planes.
 static void merge_attention_slots(rollout_ctx& c, const AttnArgs& at, int rows) {
   const int slots = at.n_slots ? at.n_slots : at.n_splits;
   c.timer.begin("attn_merge_fused_kernel",
@@ -765,8 +765,7 @@ static void forward_rows_tiled(rollout_ctx& c, int R, const SeqBatch* seqs, cons
 }
 
 // ------------------------------------------------------------------------------------------
-// Matrix-core path, one decode step with at most stream_rows live samples: five launches per layer
-// (six when attention is split over the cached positions).
+// Matrix-core path, one decode step with at most stream_rows live samples: five launches per layer.
 //   QKV projection -> fused attention (rotary, KV-page write, paged attention) -> O projection
 //   with the residual add -> gate/up projection with SwiGLU -> down projection with the
 //   residual add.

@@ -211,7 +211,7 @@ struct AttnArgs {
   float* part_o;                   // [rows][n_kv_heads][n_slots][16][128]
   float* part_ml;                  // [rows][n_kv_heads][n_slots][2][16]
   unsigned* tickets = nullptr;     // decode, plain: one per (row, KV head), kTicketStride apart, 0 between launches
-  int n_slots = 0;                 // partial results per (row, KV head); the launcher sets n_splits when 0
+  int n_slots = 0;                 // shared prompts: partial results per (row, KV head); 0: n_splits
   // decode with shared prompts (launch_attention_decode_grouped): the samples of one prompt
   // attend to the prompt's shared pages together - each key and value fragment is read once
   // for all of them - and every row attends alone only to what follows its row_t0.
@@ -221,7 +221,7 @@ struct AttnArgs {
   const int* grp_len = nullptr;    // [n_groups] shared positions (a multiple of 32)
   const int* grp_slot = nullptr;   // [n_groups] page-table row of one member
   int n_groups = 0, n_splits_a = 0, split_tokens_a = 0;  // shared part: splits of split_tokens_a (multiple of 128)
-  // decode (rotary + KV write + attention in one launch, split merge in a second)
+  // decode (rotary, KV write and attention in one launch)
   const float* qkv_raw;            // fp32 [planes][rows][(n_q_heads + 2 n_kv_heads) * 128], projections before
                                    // rotary, as split-K planes that the kernel sums in ascending order
   int qkv_planes;                  // >= 1

@@ -91,8 +91,8 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // depend on who came last - and goes on with the epilogue; the others are done.
 //   What makes the parts visible, since each XCD has its own L2: they are stored and loaded at the scope of the device (sc1:
 //   through to the memory side, and past the L2), and the ticket is drawn only when the stores have been acknowledged.
-//   No fence is needed, whose write-back of a whole L2 is what makes a join expensive: 96 column tiles x 8960, 6
-//   rows, two halves 7.8 us as two planes, 8.8 joined, where a second launch takes 4.
+//   No fence is needed, whose write-back of a whole L2 is what makes a join expensive: 96 column tiles x 8960, 8
+//   rows, two splits 10.6 us as planes, 11.9 joined, four 7.6 and 9.1, where a second launch takes 4.
 //   The last one sets the ticket back to 0 for the next launch.
 // One wavefront's N quads per lane; `tile`: its index among the launch's joined tiles.  True in the last wavefront of
 // the `splits`, whose t then holds the sum.
